@@ -286,8 +286,10 @@ blest_status blest_build(const blest_csr* csr, const blest_opts* opts_in, blest_
   const bool wide = o.sigma != 8 || o.wide_slices || n > (int64_t(1) << 24);
   blest::Bvss b;
   blest::Panels pn;
+  std::vector<int32_t> rows;
   try {
     blest::build_bvss(n, rp, col, o.sigma, o.tau, wide, &b);
+    rows = blest::long_rows(n, o.directed ? rpt.data() : rp, blest::kMsLightDeg);
   } catch (...) {
     delete g;
     return fail(BLEST_ERR_OOM, "host allocation during BVSS build");
@@ -460,6 +462,19 @@ blest_status blest_build(const blest_csr* csr, const blest_opts* opts_in, blest_
     d.rp_in = d.rp;
     d.col_in = d.col;
     d.degmask_in = d.degmask;
+  }
+  {
+    // the rows that the multi-source gather step gives a wave or a workgroup each
+    d.ms_nrows = static_cast<int>(rows.size());
+    const int32_t* rpi = o.directed ? rpt.data() : rp;
+    for (const int32_t u : rows) {
+      const int32_t deg = rpi[u + 1] - rpi[u];
+      d.ms_nwide += deg > blest::kMsWideDeg;
+      d.ms_nlong += deg > blest::kMsLongDeg;
+    }
+    d.ms_nwide = std::min(d.ms_nwide, blest::kMsWideSlots * d.num_cu);  // one multi-source workgroup per compute unit
+    TRY(dalloc_t(g, &d.ms_rows, rows.size()));
+    if (!rows.empty()) TRY(hipMemcpy(d.ms_rows, rows.data(), sizeof(int32_t) * rows.size(), hipMemcpyHostToDevice));
   }
   TRY(hipDeviceSynchronize());
 #undef TRY

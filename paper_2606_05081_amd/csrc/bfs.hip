@@ -155,7 +155,7 @@ __device__ __forceinline__ int choose_engine_inl(const BfsArgs& a, const LevelVi
     case BLEST_POLICY_LEARNED:
       if (s_mlp != nullptr) {
         if (threadIdx.x < 64) {
-          int c = mlp_choose_wave(s_mlp, feat);
+          int c = mlp_choose_wave(to_lds(s_mlp), feat);
           if (threadIdx.x == 0) s_choice = c;
         }
         __syncthreads();

@@ -25,12 +25,39 @@
 
 namespace blest {
 
+// Pointers to device (global) memory. Kernel argument structs hold them, so
+// that device code reads and writes through them with global instructions: a
+// generic pointer loaded from memory would make every access a flat one,
+// which also counts against the LDS/scalar wait counter (so an LDS wait also
+// waits for every load in flight). lptr<T> points into LDS, cptr<T> into the
+// constant address space: memory no kernel writes while it runs, whose
+// wave-uniform loads become scalar loads (waited on with the LDS/scalar
+// counter instead of the vector-load counter).
+// (The host pass of the single-source compile only parses device code; there
+// the qualifiers are dropped, since x86 has no generic address space that
+// contains them.)
+#if defined(__HIP_DEVICE_COMPILE__)
+template <class T>
+using gptr = __attribute__((address_space(1))) T*;
+template <class T>
+using lptr = __attribute__((address_space(3))) T*;
+template <class T>
+using cptr = __attribute__((address_space(4))) T*;
+#else
+template <class T>
+using gptr = T*;
+template <class T>
+using lptr = T*;
+template <class T>
+using cptr = T*;
+#endif
+
 // Entries past the last chunk base of the panel copy, so that a wave may read
 // the bases of a whole batch of consecutive chunks with scalar loads.
 constexpr int kPanelBasePad = 8;
 
 
-constexpr int kStatFields = 12;     // accumulated by Stage 2, one 256-byte line each
+constexpr int kStatFields = 11;     // accumulated by Stage 2, one 256-byte line each
 constexpr int kStatSlots = 3;       // rotating per-level slots
 constexpr int kPad = 32;            // 32 x 8 bytes = 256 bytes
 constexpr int kMaxSwitchFeatures = 12;
@@ -47,7 +74,6 @@ enum StatField : int {
   F_CUMV = 8,      // vertices visited through this level
   F_CUME = 9,      // sum of degrees of those vertices
   F_WORK = 10,     // adjacency entries (slices or CSR edges) read by the engine that left this level
-  F_LIVE = 11,     // multi-source: one 64-bit word per batch word, bit c set iff traversal c gained a vertex
 };
 
 // Push-engine work split: vertices of degree <= kLightMax are walked by one
@@ -55,10 +81,21 @@ enum StatField : int {
 constexpr int kLightMax = 32;
 constexpr int kHeavyChunk = 256;
 
+// Multi-source gather step: rows of in-degree up to kMsLightDeg are scanned by
+// a lane group each, longer ones (the list ms_rows) several to a wave, those
+// above kMsLongDeg by a wave each and above kMsWideDeg in pieces by the waves of
+// a workgroup, which holds the partial results of kMsWideSlots such rows.
+constexpr int kMsLightDeg = 32;
+constexpr int kMsLongDeg = 256;
+constexpr int kMsWideDeg = 4096;
+constexpr int kMsWideSlots = 64;
+constexpr int kMsStatWords = 16;  // words of a level's multi-source statistics
+
 // Device control block. Fields that many workgroups update sit on their own
 // 256-byte lines.
 struct alignas(256) Ctl {
   unsigned long long acc[kStatSlots][kStatFields][kPad];
+  unsigned long long ms_acc[kStatSlots][8][kMsStatWords];  // multi-source statistics, one line per XCD
   unsigned int bar_count[kPad * 2];      // top-level arrivals (one per XCD leader, or per block)
   unsigned int bar_gen[kPad * 2];        // top-level generation
   unsigned int xcd_count[8][kPad];       // per-XCD arrivals
@@ -72,7 +109,7 @@ struct alignas(256) Ctl {
   unsigned int single_gen[kPad];   // number of finished single-workgroup episodes
   int single_progress[kPad];       // last level a running single-workgroup episode finished
   int nlevels[kPad * 2]; // frontier levels of the last traversal
-  int ms_state[2][kPad];   // multi-source graph mode: {phase, batch, level} read by even/odd kernels
+  int ms_state[2][kPad];   // multi-source graph mode: {phase, batch, level, records, listed} read by even/odd kernels
   int ms_nrec[kPad];       // multi-source level records written by the last call
 };
 
@@ -196,6 +233,8 @@ struct DevGraph {
   size_t mark_bytes = 0;
   double tick_us = 0.01;      // device clock period in microseconds
   int eager = 0;              // single-source traversals use the eager scheme (Alg. 2)
+  int32_t* ms_rows = nullptr; // vertices of in-degree > kMsLightDeg, by descending in-degree (ties by id)
+  int ms_nrows = 0, ms_nwide = 0, ms_nlong = 0;  // their number; those above kMsWideDeg, kMsLongDeg
   int ms_ablation = 0;        // multi-source ablation flags (BLEST_MS_NO_*)
   int ms_mfma = 0;            // multi-source top-down check on MFMA (experiment)
   int grid_eager = 0;         // co-resident grid of the eager kernel

@@ -41,37 +41,56 @@ __device__ __forceinline__ unsigned long long dev_ticks() { return __builtin_amd
 
 __device__ __forceinline__ int lane_id() { return static_cast<int>(threadIdx.x & 63u); }
 
-// Pointers to device (global) memory. Pointers read from an argument struct
-// that lives on the stack reach a callee with no address space, and accesses
-// through them become flat instructions, which also count against the
-// LDS/scalar wait counter (so an LDS wait also waits for every load in
-// flight). Hot loops access device memory through gptr<T>, which makes the
-// compiler emit global loads, stores and atomics.
-// (The host pass of the single-source compile only parses device code; there
-// the qualifiers are dropped, since x86 has no generic address space that
-// contains them.)
-// cptr<T> points into the constant address space: memory no kernel writes
-// while it runs, whose wave-uniform loads become scalar loads (waited on with
-// the LDS/scalar counter instead of the vector-load counter).
-#if defined(__HIP_DEVICE_COMPILE__)
 template <class T>
-using gptr = __attribute__((address_space(1))) T*;
-template <class T>
-using lptr = __attribute__((address_space(3))) T*;
-template <class T>
-using cptr = __attribute__((address_space(4))) T*;
-#else
-template <class T>
-using gptr = T*;
-template <class T>
-using lptr = T*;
-template <class T>
-using cptr = T*;
-#endif
-template <class T>
-__device__ __forceinline__ gptr<T> to_global(T* p) {
+__host__ __device__ __forceinline__ gptr<T> to_global(T* p) {
   return (gptr<T>)p;
 }
+#if defined(__HIP_DEVICE_COMPILE__)
+template <class T>
+__host__ __device__ __forceinline__ gptr<T> to_global(gptr<T> p) {
+  return p;
+}
+#endif
+// A kernel's arguments, read where they lie: kernel code hands the kernarg
+// segment (constant memory) on to the functions it calls, and each of those
+// makes the reference wave-uniform, so an argument costs a scalar load that
+// stays in the scalar cache. A struct passed by reference is copied to the
+// stack instead, and a stack word read after a device-wide barrier (which
+// empties the L2) costs a round trip to memory: chains of them were most of
+// the 20 microseconds between two multi-source levels.
+#if defined(__HIP_DEVICE_COMPILE__)
+template <class A>
+using args_ref = const __attribute__((address_space(4))) A&;
+template <class A>
+__device__ __forceinline__ args_ref<A> kernel_args(const A&) {
+  return *(cptr<const A>)__builtin_amdgcn_kernarg_segment_ptr();
+}
+template <class A>
+__device__ __forceinline__ args_ref<A> uniform_args(const __attribute__((address_space(4))) A& a) {
+  const unsigned long long v = (unsigned long long)(&a);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
+  return *(cptr<const A>)((static_cast<unsigned long long>(hi) << 32) | lo);
+}
+#else
+template <class A>
+using args_ref = const A&;
+template <class A>
+__device__ __forceinline__ args_ref<A> kernel_args(const A& a) {
+  return a;
+}
+template <class A>
+__device__ __forceinline__ args_ref<A> uniform_args(const A& a) {
+  return a;
+}
+#endif
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ long long uniform(long long v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<unsigned long long>(v) >> 32));
+  return static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo);
+}
+
 // A pointer the caller knows to be the same in every lane, made wave-uniform
 // for the compiler (a pointer read through a function argument is not), so
 // that loads through it with uniform indices can be scalar loads.

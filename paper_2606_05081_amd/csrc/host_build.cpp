@@ -417,6 +417,27 @@ bool build_bvss(int64_t n, const int32_t* rp, const int32_t* col, int sigma, int
   return true;
 }
 
+std::vector<int32_t> long_rows(int64_t n, const int32_t* rp, int32_t min_degree) {
+  int32_t top = 0;
+  for (int64_t u = 0; u < n; ++u) top = std::max(top, rp[u + 1] - rp[u]);
+  if (top <= min_degree) return {};
+  // first[d] = vertices of degree above d, i.e. where degree d starts
+  std::vector<int64_t> first(static_cast<size_t>(top) + 2, 0);
+  for (int64_t u = 0; u < n; ++u) ++first[rp[u + 1] - rp[u]];
+  int64_t above = 0;
+  for (int32_t d = top; d > min_degree; --d) {
+    const int64_t c = first[d];
+    first[d] = above;
+    above += c;
+  }
+  std::vector<int32_t> rows(static_cast<size_t>(above));
+  for (int64_t u = 0; u < n; ++u) {
+    const int32_t d = rp[u + 1] - rp[u];
+    if (d > min_degree) rows[first[d]++] = static_cast<int32_t>(u);
+  }
+  return rows;
+}
+
 double update_divergence(const Bvss& b, int tau) {
   if (b.nvss == 0) return 0.0;
   const int theta = std::max(1, tau / 32);

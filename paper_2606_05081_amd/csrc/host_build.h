@@ -52,6 +52,10 @@ void permute_csr(int64_t n, const int32_t* rp, const int32_t* col, const std::ve
 
 bool build_bvss(int64_t n, const int32_t* rp, const int32_t* col, int sigma, int tau, bool wide, Bvss* out);
 
+// Vertices of degree above `min_degree`, by descending degree, ties by
+// ascending id (a counting sort, O(n + largest degree)).
+std::vector<int32_t> long_rows(int64_t n, const int32_t* rp, int32_t min_degree);
+
 // Update divergence (Section "Boosting Cache Locality"): a VSS of tau slices
 // is a (tau / theta) x theta matrix whose slice j sits in column j mod theta;
 // a column's divergence is the population standard deviation of the row ids

@@ -40,7 +40,7 @@ static __device__ __forceinline__ void mlp_to_lds(const MlpDev* mlp, float* s) {
 // Forward pass by one full wave; returns the argmax engine, or -1 when a
 // standardised input lies outside [-6, 6] or the softmax probability of the
 // argmax is below the model's confidence floor (caller falls back to Eq. 3).
-static __device__ int mlp_choose_wave(const float* s, const float (&feat)[kMaxSwitchFeatures]) {
+static __device__ __forceinline__ int mlp_choose_wave(lptr<const float> s, const float (&feat)[kMaxSwitchFeatures]) {
   float z[kMaxSwitchFeatures];
   bool ood = false;
 #pragma unroll

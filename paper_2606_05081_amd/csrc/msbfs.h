@@ -9,6 +9,8 @@
 
 namespace blest {
 
+constexpr int kMsPlanes = 15;  // bits of the largest int16 level
+
 // Device buffers of the multi-source traversal, sized for the widest batch
 // (kappa = 64 * wmax bits per vertex) on first use.
 struct MsDev {
@@ -16,15 +18,16 @@ struct MsDev {
   int wmax = 0;
   int64_t nhat = 0;
   int64_t nsets = 0;
-  unsigned long long* F = nullptr;   // frontier words, getVI-ordered, W per vertex
+  unsigned long long* F[2] = {nullptr, nullptr};  // frontier words of even and odd levels, getVI-ordered, W per vertex
+  uint32_t* fb[3] = {nullptr, nullptr, nullptr};  // front bits (one per vertex) of level l in fb[l % 3]
   unsigned long long* V = nullptr;   // visited words
   unsigned long long* N = nullptr;   // next words: visited bits plus this level's marks (atomic OR targets)
   unsigned long long* act = nullptr; // per slice set: sources active in it
-  // int16 level output: a batch's levels are first written by internal id
-  // (lstage[i * 64 W + c], the row of vertex i) and copied to the caller's
+  // int16 level output: a batch's levels are kept as kMsPlanes bit planes (W
+  // words per vertex each, getVI-ordered) and written to the caller's
   // source-major rows once the batch is done; perm: input id -> internal id
-  int16_t* lstage = nullptr;
-  int64_t lstage_elems = 0;
+  unsigned long long* planes = nullptr;
+  int64_t plane_words = 0;
   int32_t* perm = nullptr;
   uint8_t* dirty = nullptr;          // per slice set: marked in Stage 1
   uint4* queue[2] = {nullptr, nullptr};

@@ -15,20 +15,20 @@
 // loop computes. Words whose sources are inactive in s (activeSets) are
 // skipped; bits already visited are dropped; the rest is OR-ed into N with
 // one no-return 64-bit atomic per word, and the row's set is marked dirty.
-// Stage 1, bottom-up (E2): a lane owns a vertex with unvisited traversals and
-// ORs its neighbours' frontier words until every unvisited bit is covered;
-// it alone writes N[u], so no atomics. Only live traversals count (those
-// whose frontier is non-empty, from Stage 2's OR of all new words): a
-// traversal with an empty frontier can reach nothing more, and waiting for
-// its bit (a source in a small component, or one that has finished) would
-// turn every early exit into a full adjacency scan.
-// Stage 2 visits dirty slice sets only: new = N & ~V, V |= new, F = new,
+// Stage 2 then visits dirty slice sets only: new = N & ~V, V |= new, F = new,
 // activeSets[s] = OR of the set's new words, the set's VSSs are enqueued when
-// nonzero, int16 levels are written, and per-source counts of newly reached
+// nonzero, levels are written, and per-source counts of newly reached
 // vertices feed the closeness sums.
+// Bottom-up (E2) and dense top-down levels take the gather step instead (its
+// own section below): the rows of A one by one, Stage 2 included. Only live
+// traversals count there (those whose frontier is non-empty, from the OR of
+// all new words): a traversal with an empty frontier can reach nothing more,
+// and waiting for its bit (a source in a small component, or one that has
+// finished) would turn every early exit into a full adjacency scan.
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "device_common.h"
@@ -49,6 +49,18 @@ constexpr int ms_lds_words() {
   return (SIGMA == 8 ? SIGMA + 32 : SIGMA) * kWMax;
 }
 
+// Statistics of one level: words of a 128-byte line that each XCD's
+// workgroups accumulate into by themselves (kMsLive and above by OR, the
+// others by addition); readers combine the eight lines.
+enum MsStat : int {
+  MS_FRESH = 0,    // new (vertex, traversal) pairs
+  MS_QUEUE = 1,    // VSSs of the sets that gained a vertex
+  MS_QSLICES = 2,  // their slices
+  MS_CUMIN = 3,    // pairs visited before this level
+  kMsLive = 8,     // + w: OR of the level's new words w (live traversals)
+};
+static_assert(kMsLive + kWMax <= kMsStatWords, "statistics line");
+
 struct MsBatch {
   int32_t offset;  // first source index of the batch in the call's source list
   int32_t count;   // sources in the batch (<= 64 * W)
@@ -57,40 +69,43 @@ struct MsBatch {
 };
 
 struct MsArgs {
-  const int32_t* rp;
-  const int32_t* col;
-  const int32_t* rp_in;   // in-arcs (the bottom-up engine); rp/col for an undirected graph
-  const int32_t* col_in;
-  const uint32_t* slice_ptr;
-  const void* slices;
-  const int32_t* orig_id;
+  gptr<const int32_t> rp;
+  gptr<const int32_t> col;
+  gptr<const int32_t> rp_in;   // in-arcs (the gather step); rp/col for an undirected graph
+  gptr<const int32_t> col_in;
+  gptr<const int32_t> rows;    // vertices of in-degree > kMsLightDeg, by descending in-degree
+  int32_t nrows, nwide, nlong;  // their number; the first nwide have in-degree > kMsWideDeg, the first nlong > kMsLongDeg
+  gptr<const uint32_t> slice_ptr;
+  gptr<const void> slices;
+  gptr<const int32_t> orig_id;
   int64_t n, m, nsets;
   int32_t tau;
-  unsigned long long* F;
-  unsigned long long* V;
-  unsigned long long* N;
-  unsigned long long* act;
-  uint8_t* dirty;
-  uint4* queue[2];
-  const int32_t* srcs;
-  const MsBatch* batches;
+  gptr<unsigned long long> F[2];  // frontier words of even and odd levels (valid where the level's front bit is set)
+  gptr<unsigned long long> V;
+  gptr<unsigned long long> N;
+  gptr<unsigned long long> act;
+  gptr<uint32_t> fb[3];    // front bits of level l in fb[l % 3]: bit u set iff a traversal reached vertex u at level l
+  gptr<uint8_t> dirty;
+  gptr<uint4> queue[2];
+  gptr<const int32_t> srcs;
+  gptr<const MsBatch> batches;
   int32_t nbatches;
-  int16_t* levels16;  // k * n or NULL
-  int16_t* lstage;    // the batch's levels by internal id (n * 64 W), or NULL: Stage 2 writes levels16 directly
-  const int32_t* perm;  // input id -> internal id, or NULL when not relabelled
-  int64_t* sums;      // k or NULL
-  int64_t* reach;     // k or NULL
-  double* cc;         // k or NULL
-  int64_t* far;       // n (input ids) or NULL: per-target sums of Eq. 4, accumulated
-  long long* part;    // per block: kappa sums then kappa reach counts
-  Ctl* ctl;
+  gptr<int16_t> levels16;  // k * n or NULL
+  gptr<unsigned long long> planes;  // bit planes of the batch's levels, or NULL: levels16 is written directly
+  gptr<const int32_t> perm;  // input id -> internal id, or NULL when not relabelled
+  gptr<int64_t> sums;      // k or NULL
+  gptr<int64_t> reach;     // k or NULL
+  gptr<double> cc;         // k or NULL
+  gptr<int64_t> far;       // n (input ids) or NULL: per-target sums of Eq. 4, accumulated
+  gptr<long long> part;    // per block: kappa sums then kappa reach counts
+  gptr<Ctl> ctl;
   int32_t policy;
   float eta;
   uint64_t seed;
   int64_t nvss, nslices;  // BVSS totals (switch features)
-  const MlpDev* mlp;      // multi-source switch network (policy LEARNED), or NULL
+  gptr<const MlpDev> mlp;      // multi-source switch network (policy LEARNED), or NULL
   int32_t probe;          // 1: every level runs both engines from the same state and times each
-  MsLevelRec* log;        // one record per level of the call, or NULL
+  gptr<MsLevelRec> log;        // one record per level of the call, or NULL
   int32_t log_cap;
   unsigned long long timeout_ticks;
   int32_t ablation;       // BLEST_MS_NO_GETVI | BLEST_MS_NO_DIRTY (the paper's ablation steps), else 0
@@ -103,7 +118,7 @@ __device__ __forceinline__ long long get_vi(long long u, long long rho, int sigm
 // Ablation flags: ABL >= 0 is a compile-time value (the full method's kernel
 // uses 0, so the flags cost it nothing); ABL = -1 reads them from the arguments.
 template <int ABL>
-__device__ __forceinline__ int ms_abl(const MsArgs& a) {
+__device__ __forceinline__ int ms_abl(args_ref<MsArgs> a) {
   if constexpr (ABL >= 0)
     return ABL;
   else
@@ -112,7 +127,7 @@ __device__ __forceinline__ int ms_abl(const MsArgs& a) {
 
 // Word index of vertex u: getVI order, or u itself in the ablation without it.
 template <int ABL>
-__device__ __forceinline__ long long ms_vi(const MsArgs& a, long long u, long long rho, int sigma) {
+__device__ __forceinline__ long long ms_vi(args_ref<MsArgs> a, long long u, long long rho, int sigma) {
   return (ms_abl<ABL>(a) & BLEST_MS_NO_GETVI) ? u : get_vi(u, rho, sigma);
 }
 
@@ -129,15 +144,19 @@ __device__ __forceinline__ unsigned long long mix64_ms(unsigned long long z) {
   return z ^ (z >> 31);
 }
 
-// Sets count int16 values to -1: elementwise up to 16-byte alignment, then
-// 16-byte stores, then the tail.
+__device__ __forceinline__ unsigned long long readlane64(unsigned long long x, int l) {
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(x), l);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(x >> 32), l);
+  return (static_cast<unsigned long long>(hi) << 32) | lo;
+}
+
 // Switch inputs of a multi-source level, counted in (vertex, traversal) pairs
 // (base-2 logarithms): new pairs and queued slices (absolute), then shares:
 // new pairs / all pairs, VSSs / N_v, queued slices / all slices, unvisited
 // pairs / all pairs, the batch width, the ratio of the pairs rule
 // (log |Q| - log unvisited pairs), live traversals / batch width; three
 // reserved zeros.
-__device__ __forceinline__ void ms_features(float (&f)[kMaxSwitchFeatures], const MsArgs& a, long long fresh,
+__device__ __forceinline__ void ms_features(float (&f)[kMaxSwitchFeatures], args_ref<MsArgs> a, long long fresh,
                                             long long qlen, long long qslices, long long unv, int count,
                                             int live) {
   const float pairs = log2f(static_cast<float>(count) * static_cast<float>(a.n));
@@ -155,36 +174,72 @@ __device__ __forceinline__ void ms_features(float (&f)[kMaxSwitchFeatures], cons
   for (int k = 9; k < kMaxSwitchFeatures; ++k) f[k] = 0.0f;
 }
 
-// Live traversals of a stat slot (Stage 2 ORs the new words into F_LIVE;
-// words beyond the batch width stay zero). One 64-byte read, no dependent loads.
-__device__ __forceinline__ int ms_live_count(const Ctl* ctl, int slot) {
-  const unsigned long long* p = &ctl->acc[slot][F_LIVE][0];
-  int c = 0;
+// A level's statistics, spread over the lanes of the calling wave: lane t
+// holds word t % 16 (get() makes one wave-uniform).
+struct MsView {
+  unsigned long long raw;
+  __device__ __forceinline__ long long get(int t) const { return static_cast<long long>(readlane64(raw, t)); }
+  // live traversals: words beyond the batch width stay zero
+  __device__ __forceinline__ int live() const {
+    int c = 0;
 #pragma unroll
-  for (int w = 0; w < kWMax; ++w) c += __popcll(p[w]);
-  return c;
+    for (int w = 0; w < kWMax; ++w) c += __popcll(readlane64(raw, kMsLive + w));
+    return c;
+  }
+};
+
+__device__ __forceinline__ MsView ms_stats(gptr<Ctl> ctl, int slot) {
+  const gptr<const unsigned long long> p = &ctl->ms_acc[slot][0][0];
+  const int lane = lane_id();
+  const bool add = (lane % kMsStatWords) < kMsLive;
+  unsigned long long v = p[lane];
+  static_assert(8 * kMsStatWords == 128, "two words per lane");
+  const unsigned long long b = p[lane + 64];
+  v = add ? v + b : v | b;
+#pragma unroll
+  for (int d = kMsStatWords; d < 64; d <<= 1) {
+    const unsigned long long o = __shfl_xor(v, d, 64);
+    v = add ? v + o : v | o;
+  }
+  return MsView{v};
 }
 
-// Block 0 clears one stat slot: element 0 of every field and the F_LIVE words.
-__device__ __forceinline__ void ms_clear_slot(Ctl* ctl, int slot) {
-  for (int t = threadIdx.x; t < kStatFields + kWMax; t += blockDim.x) {
-    if (t < kStatFields)
-      ctl->acc[slot][t][0] = 0ULL;
-    else
-      ctl->acc[slot][F_LIVE][t - kStatFields] = 0ULL;
+// Workgroup 0 clears one statistics slot and its queue cursor.
+__device__ __forceinline__ void ms_clear_slot(gptr<Ctl> ctl, int slot) {
+  for (int t = threadIdx.x; t < 8 * kMsStatWords; t += blockDim.x) ctl->ms_acc[slot][0][t] = 0ULL;
+  if (threadIdx.x == 0) ctl->acc[slot][F_QUEUE][0] = 0ULL;
+}
+
+// Adds a workgroup's statistics (LDS, complete after the barrier inside) to
+// its XCD's line of the slot and zeroes them.
+__device__ __forceinline__ void ms_publish(gptr<Ctl> ctl, int slot, unsigned xcc, lptr<unsigned long long> s_stat) {
+  __syncthreads();
+  if (threadIdx.x < kMsStatWords) {
+    const unsigned long long v = s_stat[threadIdx.x];
+    const gptr<unsigned long long> p = &ctl->ms_acc[slot][xcc][threadIdx.x];
+    if (v) {
+      if (threadIdx.x < kMsLive)
+        add_u64(p, v);
+      else
+        __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_stat[threadIdx.x] = 0ULL;
+    }
   }
 }
 
-// Engine of a multi-source level (uniform across the grid: every input is).
-// Eq. 3 counted in (vertex, traversal) pairs: the bottom-up engine reads W
-// frontier words per scanned edge and rarely stops early while many
-// traversals are open, so it is chosen only once fewer than eta * |Q| pairs
-// remain unvisited. LEARNED: the switch network (output 0 = BVSS, 2 =
-// bottom-up; anything else, or low confidence, falls back to the pairs rule).
-// Contains __syncthreads() when s_mlp is set.
-__device__ int ms_choose(const MsArgs& a, const float (&feat)[kMaxSwitchFeatures], long long qlen, long long unv,
-                         int level, int bi, const float* s_mlp, int* fallback) {
-  __shared__ int s_choice;
+__device__ __forceinline__ void lds_add(lptr<unsigned long long> p, unsigned long long v) {
+  __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_or(lptr<unsigned long long> p, unsigned long long v) {
+  __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Engine of a multi-source level, computed by each wave on its own (every
+// input is uniform over the grid). Eq. 3 counted in (vertex, traversal) pairs.
+// LEARNED: the switch network (output 0 = BVSS, 2 = bottom-up; anything else,
+// or low confidence, falls back to the pairs rule).
+__device__ __forceinline__ int ms_choose(args_ref<MsArgs> a, const float (&feat)[kMaxSwitchFeatures], long long qlen, long long unv,
+                         int level, int bi, lptr<const float> s_mlp, bool learned, int* fallback) {
   *fallback = 0;
   const int rule = (static_cast<double>(unv) < static_cast<double>(a.eta) * static_cast<double>(qlen))
                        ? BLEST_ENGINE_BOTTOM_UP
@@ -200,14 +255,8 @@ __device__ int ms_choose(const MsArgs& a, const float (&feat)[kMaxSwitchFeatures
                  ? BLEST_ENGINE_BOTTOM_UP
                  : BLEST_ENGINE_BVSS;
     case BLEST_POLICY_LEARNED:
-      if (s_mlp != nullptr) {
-        if (threadIdx.x < 64) {
-          const int c = mlp_choose_wave(s_mlp, feat);
-          if (threadIdx.x == 0) s_choice = c;
-        }
-        __syncthreads();
-        const int c = s_choice;
-        __syncthreads();
+      if (learned) {
+        const int c = mlp_choose_wave(s_mlp, feat);
         if (c == BLEST_ENGINE_BVSS || c == BLEST_ENGINE_BOTTOM_UP) return c;
       }
       *fallback = 1;
@@ -217,22 +266,69 @@ __device__ int ms_choose(const MsArgs& a, const float (&feat)[kMaxSwitchFeatures
   }
 }
 
-__device__ void fill_minus_one(int16_t* p, long long count, long long gtid, long long nthreads) {
-  const long long mis = (16 - (reinterpret_cast<uintptr_t>(p) & 15)) & 15;
+// Sets count int16 values to -1: elementwise up to 16-byte alignment, then
+// 16-byte stores, then the tail.
+__device__ __forceinline__ void fill_minus_one(gptr<int16_t> p, long long count, long long gtid, long long nthreads) {
+  const long long mis = (16 - ((uintptr_t)p & 15)) & 15;
   const long long head = min(count, mis / 2);
   for (long long i = gtid; i < head; i += nthreads) p[i] = -1;
   const long long nvec = (count - head) / 8;
-  ulonglong2* v = reinterpret_cast<ulonglong2*>(p + head);
-  for (long long i = gtid; i < nvec; i += nthreads) v[i] = make_ulonglong2(~0ULL, ~0ULL);
+  const gptr<u64x2> v = (gptr<u64x2>)(p + head);
+  for (long long i = gtid; i < nvec; i += nthreads) v[i] = u64x2{~0ULL, ~0ULL};
   for (long long i = head + nvec * 8 + gtid; i < count; i += nthreads) p[i] = -1;
+}
+
+// Zeroes count 64-bit words (16-byte aligned) with 16-byte stores.
+__device__ __forceinline__ void zero_words(gptr<unsigned long long> p, long long count, long long gtid, long long nthreads) {
+  const gptr<u64x2> v = (gptr<u64x2>)p;
+  for (long long i = gtid; i < count / 2; i += nthreads) v[i] = u64x2{0ULL, 0ULL};
+  if (gtid == 0 && (count & 1)) p[count - 1] = 0ULL;
+}
+
+// Front bits of a slice set (bit b: vertex s * SIGMA + b).
+template <int SIGMA>
+__device__ __forceinline__ uint32_t set_bits(gptr<const uint32_t> fb, long long s) {
+  return ((gptr<const typename MaskOf<SIGMA>::T>)fb)[s];
+}
+
+// What a level reads and writes, the same for both forms of the step.
+struct MsStep {
+  gptr<const unsigned long long> F;  // frontier words of the level
+  gptr<unsigned long long> Fn;       // of the next level
+  gptr<const uint32_t> fb;           // front bits of the level
+  gptr<uint32_t> fbn;                // of the next level (all zero when the step starts)
+  int offset, count, W;              // the batch
+  int new_level, slot_out;
+};
+
+// Batch bi of the call's plan (bi wave-uniform: scalar loads; the plan is
+// written before the launch).
+__device__ __forceinline__ MsBatch ms_batch(args_ref<MsArgs> a, int bi) {
+  const cptr<const MsBatch> p = (cptr<const MsBatch>)a.batches + bi;
+  return MsBatch{p->offset, p->count, p->W, 0};
+}
+
+__device__ __forceinline__ MsStep ms_step(args_ref<MsArgs> a, int bi, int level) {
+  const MsBatch bt = ms_batch(a, bi);
+  return MsStep{a.F[level & 1],      a.F[(level & 1) ^ 1], a.fb[level % 3], a.fb[(level + 1) % 3], bt.offset,
+                bt.count,            bt.W,                 level + 1,       (level + 1) % kStatSlots};
 }
 
 // ---------------------------------------------------------------- Stage 1
 
 template <int SIGMA, class SliceT, int K, int ABL>
-__device__ void ms_engine_bvss_k(const MsArgs& a, const uint4* __restrict__ q, long long qlen, int W,
-                                 long long gwave, long long nwaves, unsigned long long* lds_f) {
-  const SliceT* __restrict__ sl = static_cast<const SliceT*>(a.slices);
+__device__ __attribute__((noinline)) void ms_engine_bvss_k(args_ref<MsArgs> a_, int bi, int level, long long qlen,
+                                 lptr<unsigned long long> lds_f) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  bi = uniform(bi);
+  level = uniform(level);
+  const MsStep sp = ms_step(a, bi, level);
+  qlen = uniform(qlen);
+  const gptr<const uint4> q = a.queue[level & 1];
+  const long long nw = blockDim.x / 64, nwaves = gridDim.x * nw;
+  const long long gwave = blockIdx.x * nw + wave_in_block();
+  const int W = sp.W;
+  const gptr<const SliceT> sl = (gptr<const SliceT>)a.slices;
   const long long rho = a.nsets;
   const int lane = lane_id();
   for (long long i = gwave; i < qlen; i += nwaves) {
@@ -240,10 +336,13 @@ __device__ void ms_engine_bvss_k(const MsArgs& a, const uint4* __restrict__ q, l
     const uint32_t start = d.x, cnt = d.y;
     const long long s = d.w;
     // Stage the frontier words of the set's sigma vertices (vertex s*SIGMA+b
-    // sits at b*rho + s in getVI order).
+    // sits at b*rho + s in getVI order); those without a front bit hold words
+    // of other levels.
+    const uint32_t bits = set_bits<SIGMA>(sp.fb, s);
     for (int j = lane; j < SIGMA * W; j += 64) {
       const int b = j / W, w = j % W;
-      lds_f[j] = a.F[ms_vi<ABL>(a, s * SIGMA + b, rho, SIGMA) * W + w];
+      const unsigned long long x = sp.F[ms_vi<ABL>(a, s * SIGMA + b, rho, SIGMA) * W + w];
+      lds_f[j] = ((bits >> b) & 1u) ? x : 0ULL;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -283,12 +382,6 @@ __device__ void ms_engine_bvss_k(const MsArgs& a, const uint4* __restrict__ q, l
   }
 }
 
-__device__ __forceinline__ unsigned long long readlane64(unsigned long long x, int l) {
-  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(x), l);
-  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(x >> 32), l);
-  return (static_cast<unsigned long long>(hi) << 32) | lo;
-}
-
 // The sigma = 8 form of the engine above, shaped for memory latency. Per VSS
 // the slices, the set's frontier words and its activity words are loaded
 // together. The frontier words are staged in LDS and expanded into two
@@ -307,17 +400,23 @@ __device__ __forceinline__ unsigned long long readlane64(unsigned long long x, i
 // (Not inlined: it gets its own register allocation instead of adding to the
 // persistent kernel's; its pointers are converted to the global address space.)
 template <class SliceT, int K, int ABL>
-__device__ __attribute__((noinline)) void ms_engine_bvss8(const MsArgs& a, const uint4* q_in, long long qlen, int W,
-                                                          long long gwave, long long nwaves,
-                                                          unsigned long long* lds_in) {
+__device__ __attribute__((noinline)) void ms_engine_bvss8(args_ref<MsArgs> a_, int bi, int level,
+                                                          long long qlen, lptr<unsigned long long> lds) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  bi = uniform(bi);
+  level = uniform(level);
+  const MsStep sp = ms_step(a, bi, level);
+  qlen = uniform(qlen);
+  const gptr<const uint4> q = a.queue[level & 1];
+  const long long nw = blockDim.x / 64, nwaves = gridDim.x * nw;
+  const long long gwave = blockIdx.x * nw + wave_in_block();
   constexpr int SIGMA = 8;
-  const gptr<const SliceT> sl = to_global(static_cast<const SliceT*>(a.slices));
-  const gptr<const uint4> q = to_global(q_in);
-  const gptr<const unsigned long long> F = to_global(static_cast<const unsigned long long*>(a.F));
-  const gptr<const unsigned long long> act = to_global(static_cast<const unsigned long long*>(a.act));
-  const gptr<unsigned long long> N = to_global(a.N);
-  const gptr<uint8_t> dirty = to_global(a.dirty);
-  const lptr<unsigned long long> lds = to_lds(lds_in);
+  const int W = sp.W;
+  const gptr<const SliceT> sl = (gptr<const SliceT>)a.slices;
+  const gptr<const unsigned long long> F = sp.F;
+  const gptr<const unsigned long long> act = a.act;
+  const gptr<unsigned long long> N = a.N;
+  const gptr<uint8_t> dirty = a.dirty;
   const long long rho = a.nsets;
   const int lane = lane_id();
   const lptr<unsigned long long> tab = lds + SIGMA * W;
@@ -332,9 +431,10 @@ __device__ __attribute__((noinline)) void ms_engine_bvss8(const MsArgs& a, const
       sv[k] = (j < cnt) ? sl[start + j] : SliceT(0);
     }
     unsigned long long fw = 0ULL, aw = 0ULL;
+    const uint32_t bits = set_bits<SIGMA>(sp.fb, s);  // vertices without a front bit hold words of other levels
     if (lane < SIGMA * W) fw = F[ms_vi<ABL>(a, s * SIGMA + lane / W, rho, SIGMA) * W + lane % W];
     if (lane < W) aw = act[s * W + lane];
-    if (lane < SIGMA * W) lds[lane] = fw;
+    if (lane < SIGMA * W) lds[lane] = ((bits >> (lane / W)) & 1u) ? fw : 0ULL;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -418,10 +518,19 @@ __device__ __attribute__((noinline)) void ms_engine_bvss8(const MsArgs& a, const
 typedef int ms_v4i __attribute__((ext_vector_type(4)));
 
 template <class SliceT, int ABL>
-__device__ void ms_engine_mfma(const MsArgs& a, const uint4* __restrict__ q, long long qlen, int W, long long gwave,
-                               long long nwaves, unsigned long long* lds_f) {
+__device__ __attribute__((noinline)) void ms_engine_mfma(args_ref<MsArgs> a_, int bi, int level, long long qlen,
+                                 lptr<unsigned long long> lds_f) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  bi = uniform(bi);
+  level = uniform(level);
+  const MsStep sp = ms_step(a, bi, level);
+  qlen = uniform(qlen);
+  const gptr<const uint4> q = a.queue[level & 1];
+  const long long nw = blockDim.x / 64, nwaves = gridDim.x * nw;
+  const long long gwave = blockIdx.x * nw + wave_in_block();
   constexpr int SIGMA = 8;
-  const SliceT* __restrict__ sl = static_cast<const SliceT*>(a.slices);
+  const int W = sp.W;
+  const gptr<const SliceT> sl = (gptr<const SliceT>)a.slices;
   const long long rho = a.nsets;
   const int lane = lane_id();
   const int c16 = lane & 15;
@@ -430,9 +539,11 @@ __device__ void ms_engine_mfma(const MsArgs& a, const uint4* __restrict__ q, lon
     const uint4 d = q[i];
     const uint32_t start = d.x, cnt = d.y;
     const long long s = d.w;
+    const uint32_t bits = set_bits<SIGMA>(sp.fb, s);
     for (int j = lane; j < SIGMA * W; j += 64) {
       const int b = j / W, w = j % W;
-      lds_f[j] = a.F[ms_vi<ABL>(a, s * SIGMA + b, rho, SIGMA) * W + w];
+      const unsigned long long x = sp.F[ms_vi<ABL>(a, s * SIGMA + b, rho, SIGMA) * W + w];
+      lds_f[j] = ((bits >> b) & 1u) ? x : 0ULL;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -489,345 +600,1219 @@ __device__ void ms_engine_mfma(const MsArgs& a, const uint4* __restrict__ q, lon
 }
 
 template <int SIGMA, class SliceT, bool MF, int ABL>
-__device__ void ms_engine_bvss(const MsArgs& a, const uint4* q, long long qlen, int W, long long gwave,
-                               long long nwaves, unsigned long long* lds_f) {
+__device__ __forceinline__ void ms_engine_bvss(args_ref<MsArgs> a, int bi, int level, long long qlen,
+                               lptr<unsigned long long> lds_f) {
   if constexpr (MF && SIGMA == 8) {
-    ms_engine_mfma<SliceT, ABL>(a, q, qlen, W, gwave, nwaves, lds_f);
+    ms_engine_mfma<SliceT, ABL>(a, bi, level, qlen, lds_f);
     return;
   }
   if constexpr (SIGMA == 8) {
     switch (a.tau) {
       case 64:
-        ms_engine_bvss8<SliceT, 1, ABL>(a, q, qlen, W, gwave, nwaves, lds_f);
+        ms_engine_bvss8<SliceT, 1, ABL>(a, bi, level, qlen, lds_f);
         break;
       case 128:
-        ms_engine_bvss8<SliceT, 2, ABL>(a, q, qlen, W, gwave, nwaves, lds_f);
+        ms_engine_bvss8<SliceT, 2, ABL>(a, bi, level, qlen, lds_f);
         break;
       case 192:
-        ms_engine_bvss8<SliceT, 3, ABL>(a, q, qlen, W, gwave, nwaves, lds_f);
+        ms_engine_bvss8<SliceT, 3, ABL>(a, bi, level, qlen, lds_f);
         break;
       default:
-        ms_engine_bvss8<SliceT, 4, ABL>(a, q, qlen, W, gwave, nwaves, lds_f);
+        ms_engine_bvss8<SliceT, 4, ABL>(a, bi, level, qlen, lds_f);
         break;
     }
     return;
   }
   switch (a.tau) {
     case 64:
-      ms_engine_bvss_k<SIGMA, SliceT, 1, ABL>(a, q, qlen, W, gwave, nwaves, lds_f);
+      ms_engine_bvss_k<SIGMA, SliceT, 1, ABL>(a, bi, level, qlen, lds_f);
       break;
     case 128:
-      ms_engine_bvss_k<SIGMA, SliceT, 2, ABL>(a, q, qlen, W, gwave, nwaves, lds_f);
+      ms_engine_bvss_k<SIGMA, SliceT, 2, ABL>(a, bi, level, qlen, lds_f);
       break;
     case 192:
-      ms_engine_bvss_k<SIGMA, SliceT, 3, ABL>(a, q, qlen, W, gwave, nwaves, lds_f);
+      ms_engine_bvss_k<SIGMA, SliceT, 3, ABL>(a, bi, level, qlen, lds_f);
       break;
     default:
-      ms_engine_bvss_k<SIGMA, SliceT, 4, ABL>(a, q, qlen, W, gwave, nwaves, lds_f);
+      ms_engine_bvss_k<SIGMA, SliceT, 4, ABL>(a, bi, level, qlen, lds_f);
       break;
   }
 }
 
-template <int SIGMA, int ABL>
-__device__ void ms_engine_pull(const MsArgs& a, int W, int count, const unsigned long long* live, long long gtid,
-                               long long nthreads) {
-  const long long rho = a.nsets;
-  unsigned long long bm[kWMax];
+// ------------------------------------------------------- gather step
+//
+// The dense form of a level: every vertex with an open (unvisited, live)
+// traversal ORs the frontier words of its in-neighbours, row by row of A
+// (Eq. 1 read literally; Alg. 4's bottom-up scan for kappa traversals), and
+// stops once every open traversal is covered. The row is owned by the lanes
+// that scan it, so nothing is marked with atomics, and Stage 2 is done in the
+// same pass (FUSED): visited, next-frontier and level words are written once,
+// with one device-wide barrier per level instead of two.
+//
+// What bounds it is the gathers of W-word frontier rows, one per arc to a
+// frontier vertex (an arc to any other vertex costs one bit of fb, which a
+// scale-18 graph holds in 32 KB), and before their rate the three dependent
+// loads to one (column, front bit, frontier row). A row of W words is read by
+// W / 2 lanes of 16 bytes each (kRowLanes), so a wave reads kRowsPerWave
+// neighbours per load. Four kinds of task, so that every wave has many arcs
+// in flight and none is much longer than the rest: kRowsPerWave consecutive
+// vertices of in-degree <= kMsLightDeg, a lane group each; two (four) longer
+// rows of about the same degree (a list kept with the graph, by descending
+// degree), 64 columns of each at a time; one row above kMsLongDeg, 128 (256)
+// of its columns at a time; a piece of a row above kMsWideDeg. The tasks of a
+// kind are dealt to the workgroups in turn; inside a workgroup each wave
+// takes the next one from a counter in LDS (dealt to the waves in turn, the
+// slowest wave of a workgroup finished 1.4 times later than its first). The
+// row-owner replaces a lane-per-vertex scan whose hub rows (60,000 arcs by
+// one lane) took 20 to 66 ms at scale 20.
+constexpr int kMsWidePieces = 16;  // tasks a wide row is cut into
+template <int W>
+constexpr int kRowLanes = W <= 2 ? 1 : W / 2;
+template <int W>
+constexpr int kRowsPerWave = 64 / kRowLanes<W>;
+
+// Words 2 sub, 2 sub + 1 of a row (W = 1: its only word and 0).
+template <int W>
+__device__ __forceinline__ u64x2 load_pair(gptr<const unsigned long long> base, long long vi, int sub) {
+  if constexpr (W == 1)
+    return u64x2{base[vi], 0ULL};
+  else
+    return *(gptr<const u64x2>)(base + vi * W + 2 * sub);
+}
+template <int W>
+__device__ __forceinline__ void store_pair(gptr<unsigned long long> base, long long vi, int sub, u64x2 x) {
+  if constexpr (W == 1)
+    base[vi] = x.x;
+  else
+    *(gptr<u64x2>)(base + vi * W + 2 * sub) = x;
+}
+
+// Lane J of the caller's group of G lanes (a quad permutation).
+template <int G, int J>
+__device__ __forceinline__ int group_bcast(int v) {
+  if constexpr (G == 1)
+    return v;
+  else if constexpr (G == 2)
+    return __builtin_amdgcn_mov_dpp(v, J | (J << 2) | ((2 + J) << 4) | ((2 + J) << 6), 0xf, 0xf, true);
+  else
+    return __builtin_amdgcn_mov_dpp(v, J * 0x55, 0xf, 0xf, true);
+}
+
+// OR of v over the lanes l, l + L, l + 2 L, ... of the wave (L = 1, 2 or 4),
+// in every one of them: rotations within 16 lanes, then swaps of 16- and
+// 32-lane halves, all of them register moves (no LDS).
+template <int L>
+__device__ __forceinline__ uint32_t or_slots32(uint32_t v) {
+  if constexpr (L <= 1) v |= __builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x121, 0xf, 0xf, true);
+  if constexpr (L <= 2) v |= __builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x122, 0xf, 0xf, true);
+  v |= __builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x124, 0xf, 0xf, true);
+  v |= __builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x128, 0xf, 0xf, true);
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = a[0] | a[1];
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return b[0] | b[1];
+}
+template <int W>
+__device__ __forceinline__ u64x2 or_slots(u64x2 x) {
+  constexpr int L = kRowLanes<W>;
+  auto one = [](unsigned long long q) {
+    return (static_cast<unsigned long long>(or_slots32<L>(static_cast<uint32_t>(q >> 32))) << 32) |
+           or_slots32<L>(static_cast<uint32_t>(q));
+  };
+  x.x = one(x.x);
+  if (W > 1) x.y = one(x.y);
+  return x;
+}
+
+// Per-traversal counts of a wave's new bits, bit-sliced: lane l adds its word
+// pairs into six carry-save planes (63 additions), flush() adds the planes of
+// all lanes holding the same pair and the totals go to LDS counters. About
+// one vector instruction per row, where a ballot per traversal took 70.
+template <int W>
+struct MsCounter {
+  static constexpr int P = 6;
+  u64x2 c[P];
+  int added;
+  __device__ __forceinline__ void clear() {
 #pragma unroll
-  for (int w = 0; w < kWMax; ++w) bm[w] = (w < W) ? (batch_mask(count, w) & live[w]) : 0ULL;
-  for (long long u = gtid; u < a.n; u += nthreads) {
-    const int p0 = a.rp_in[u], p1 = a.rp_in[u + 1];
-    if (p0 == p1) continue;
-    const long long vi = ms_vi<ABL>(a, u, rho, SIGMA);
-    unsigned long long vis[kWMax], unv[kWMax], acc[kWMax];
-    bool open = false;
+    for (int i = 0; i < P; ++i) c[i] = u64x2{0ULL, 0ULL};
+    added = 0;
+  }
+  __device__ __forceinline__ void flush(lptr<int> cnt) {
+    constexpr int L = kRowLanes<W>, R = kRowsPerWave<W>;
+    constexpr int T = P + (R == 64 ? 6 : R == 32 ? 5 : 4);
+    u64x2 s[T];
 #pragma unroll
-    for (int w = 0; w < kWMax; ++w) {
-      vis[w] = (w < W) ? a.V[vi * W + w] : ~0ULL;
-      unv[w] = ~vis[w] & bm[w];
-      acc[w] = 0ULL;
-      open |= unv[w] != 0ULL;
+    for (int i = 0; i < T; ++i) s[i] = i < P ? c[i < P ? i : 0] : u64x2{0ULL, 0ULL};
+#pragma unroll
+    for (int k = 0; k < T - P; ++k) {
+      const int d = L << k;
+      u64x2 carry = {0ULL, 0ULL};
+#pragma unroll
+      for (int i = 0; i < P + k; ++i) {
+        const u64x2 x = s[i];
+        const u64x2 o = {__shfl_xor(x.x, d, 64), __shfl_xor(x.y, d, 64)};
+        const u64x2 t = x ^ o;
+        s[i] = t ^ carry;
+        carry = (x & o) | (t & carry);
+      }
+      s[P + k] = carry;
     }
-    if (!open) continue;
-    // Four in-neighbours at a time: their column indices and frontier words
-    // are loaded before any is tested (the test may end the scan, so one at a
-    // time every load waited for the previous one); up to three loads past
-    // the covering neighbour are wasted.
-    for (int p = p0; p < p1; p += 4) {
-      long long iv[4];
+    constexpr int PER = W == 1 ? 1 : 128 / R;  // counters each lane extracts
+    const int lane = lane_id(), sub = lane % L, r = lane / L;
+#pragma unroll 1
+    for (int i = 0; i < PER; ++i) {
+      const int t = r * PER + i;
+      int v = 0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) iv[j] = p + j < p1 ? ms_vi<ABL>(a, a.col_in[p + j], rho, SIGMA) : -1;
-      bool covered = true;
+      for (int j = 0; j < T; ++j)
+        v |= static_cast<int>(((t < 64 ? s[j].x : s[j].y) >> (t & 63)) & 1ULL) << j;
+      if (v)
+        __hip_atomic_fetch_add(cnt + 128 * sub + t, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    clear();
+  }
+  __device__ __forceinline__ void add(u64x2 x) {
 #pragma unroll
-      for (int w = 0; w < kWMax; ++w) {
-        if (w < W && unv[w]) {
-          unsigned long long f[4];
+    for (int i = 0; i < P; ++i) {
+      const u64x2 t = c[i] & x;
+      c[i] ^= x;
+      x = t;
+    }
+    ++added;
+  }
+  __device__ __forceinline__ bool full() const { return added == (1 << P) - 1; }
+};
+
+// LDS of one gather step.
+struct MsGatherLds {
+  lptr<int> row;                  // 256 ints of the wave: compacted neighbours
+  lptr<unsigned long long> wide;  // kWMax words per wide row of the workgroup: the OR of its pieces
+  lptr<int> done;                 // finished pieces per wide row
+  lptr<int> cnt;                  // 64 * kWMax per-traversal counts
+  lptr<unsigned long long> stat;  // kMsStatWords statistics
+  lptr<int> next;                 // the workgroup's next task
+};
+
+// FUSED: also Stage 2 of the level; otherwise the marks go to N and the dirty
+// flags for ms_finalize. COUNT: per-traversal counts of the new pairs.
+template <int SIGMA, int W, int BLOCK, bool FUSED, bool COUNT, int ABL>
+__device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi, int level,
+                                                    unsigned long long raw_stats, MsGatherLds lds) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  bi = uniform(bi);
+  level = uniform(level);
+  const MsStep sp = ms_step(a, bi, level);
+  constexpr int L = kRowLanes<W>, R = kRowsPerWave<W>;
+  const int lane = lane_id();
+  const int sub = lane % L, r = lane / L;
+  const long long rho = a.nsets, n = a.n;
+  const long long plane = rho * SIGMA * W;  // words of one level plane
+  const gptr<const int32_t> rp = a.rp_in, col = a.col_in, rows = a.rows;
+  const gptr<const unsigned long long> F = sp.F;
+  const gptr<const uint32_t> fb = sp.fb;
+  const gptr<unsigned long long> Fn = sp.Fn, V = a.V, N = a.N;
+  const gptr<uint32_t> fbn = sp.fbn;
+  const gptr<const uint32_t> slp = a.slice_ptr;
+  const gptr<unsigned long long> planes = a.planes;
+  const uint32_t tau = static_cast<uint32_t>(a.tau);
+  const int new_level = sp.new_level;
+  const bool direct = FUSED && a.levels16 != nullptr && a.planes == nullptr;
+  const bool overflow = FUSED && a.levels16 != nullptr && new_level > 32767;
+  // open traversals of this lane's word pair: in the batch and live
+  const int w0 = W == 1 ? 0 : 2 * sub;
+  u64x2 bm;
+  bm.x = batch_mask(sp.count, w0) & __shfl(raw_stats, kMsLive + w0, 64);
+  bm.y = W == 1 ? 0ULL : batch_mask(sp.count, w0 + 1) & __shfl(raw_stats, kMsLive + w0 + 1, 64);
+
+  uint32_t fresh = 0, nq = 0, nqs = 0;
+  u64x2 live = {0ULL, 0ULL};
+  MsCounter<W> counter;
+  if (COUNT) counter.clear();
+  // The set whose front bits this lane last ORed into: whether it was the
+  // first to do so is read off the returned word one row later, when the
+  // atomic has long returned.
+  bool pend = false;
+  uint32_t pend_old = 0, pend_mask = 0;
+  int pend_s = 0;
+  auto resolve = [&]() {
+    if (pend && !(pend_old & pend_mask)) {
+      const uint32_t ns = slp[pend_s + 1] - slp[pend_s];
+      nqs += ns;
+      nq += (ns + tau - 1) / tau;
+    }
+    pend = false;
+  };
+  auto front = [&](int u, uint32_t bits) {  // bits of vertices u, u + 1, ... of one set
+    const int s = u / SIGMA;
+    pend_s = s;
+    pend_mask = (SIGMA == 32 ? ~0u : ((1u << (SIGMA & 31)) - 1u)) << (static_cast<unsigned>(s * SIGMA) & 31u);
+    pend_old = __hip_atomic_fetch_or(fbn + (u >> 5), bits << (u & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    pend = true;
+  };
+  // Writes a finished row: `on` lanes (whole groups) hold the row's visited
+  // words v and new words x.
+  auto commit = [&](bool on, int u, long long vi, u64x2 v, u64x2 x) {
+    if (!on) return;
+    const u64x2 vx = v | x;
+    if constexpr (!FUSED) {
+      store_pair<W>(N, vi, sub, vx);  // N = visited words plus this level's marks
+      if (sub == 0) a.dirty[u / SIGMA] = 1;
+      return;
+    }
+    store_pair<W>(V, vi, sub, vx);
+    store_pair<W>(N, vi, sub, vx);
+    store_pair<W>(Fn, vi, sub, x);
+    const uint32_t pc = static_cast<uint32_t>(__popcll(x.x) + __popcll(x.y));
+    fresh += pc;
+    live |= x;
+    if (overflow) {
+      __hip_atomic_store(&a.ctl->error[0], static_cast<int>(BLEST_ERR_OVERFLOW), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    } else if (planes) {
+      if (pc)
+        for (int nl = new_level; nl; nl &= nl - 1) {
+          const gptr<unsigned long long> pl = planes + static_cast<long long>(__builtin_ctz(nl)) * plane;
+          store_pair<W>(pl, vi, sub, load_pair<W>(pl, vi, sub) | x);
+        }
+    } else if (direct) {
+      const long long o = a.orig_id ? a.orig_id[u] : u;
 #pragma unroll
-          for (int j = 0; j < 4; ++j) f[j] = iv[j] >= 0 ? a.F[iv[j] * W + w] : 0ULL;
-          acc[w] |= f[0] | f[1] | f[2] | f[3];
-          covered &= (acc[w] & unv[w]) == unv[w];
+      for (int k = 0; k < (W == 1 ? 1 : 2); ++k) {
+        unsigned long long t = k ? x.y : x.x;
+        const gptr<int16_t> out = a.levels16 + (static_cast<long long>(sp.offset) + 64 * (w0 + k)) * n + o;
+        while (t) {
+          const int c = __builtin_ctzll(t);
+          t &= t - 1;
+          out[c * n] = static_cast<int16_t>(new_level);
         }
       }
-      if (covered) break;
     }
-    bool any = false;
+    if (a.far) {
+      uint32_t s = pc;
+      if (L >= 2) s += __shfl_xor(s, 1, 64);
+      if (L >= 4) s += __shfl_xor(s, 2, 64);
+      if (sub == 0) a.far[a.orig_id ? a.orig_id[u] : u] += static_cast<int64_t>(new_level) * s;
+    }
+  };
+  auto slots = [&](u64x2 x) { return or_slots<W>(x); };  // OR over the lanes that hold the same word pair
+  auto is_open = [](u64x2 x) { return (x.x | x.y) != 0ULL; };
+
+  // Scanning rows by the whole wave, 64 columns of each of M pieces per step
+  // (piece m: columns P[m] .. E[m]). The front bits of a step's columns are
+  // tested together, the frontier ones compacted through LDS so that every
+  // lane group has a neighbour to read, and their frontier rows ORed into
+  // acc[m] (this lane's part). load_cols() and load_words() take the columns
+  // and front words of the first step; scan() also takes those of the next
+  // one, `stride` columns on, while the frontier rows are in flight.
+  constexpr int M = W == 8 ? 2 : 4;
+  constexpr int MP = W == 4 ? 2 : M;  // pieces whose frontier rows are in flight together
+  struct Cols {
+    int c[M];
+    uint32_t w[M];
+  };
+  auto load_cols = [&](const int (&P)[M], const int (&E)[M], int ahead, int (&c)[M]) {
 #pragma unroll
-    for (int w = 0; w < kWMax; ++w) {
-      const unsigned long long x = acc[w] & unv[w];
-      if (w < W && x) {
-        a.N[vi * W + w] = vis[w] | x;  // N = visited words plus this level's marks
-        any = true;
+    for (int m = 0; m < M; ++m) {
+      const int i = P[m] + ahead + lane;
+      c[m] = i < E[m] ? col[i] : -1;
+    }
+  };
+  auto load_words = [&](Cols& k) {
+#pragma unroll
+    for (int m = 0; m < M; ++m) k.w[m] = k.c[m] >= 0 ? fb[k.c[m] >> 5] : 0u;
+  };
+  auto scan = [&](const int (&P)[M], const int (&E)[M], int stride, Cols& k, u64x2 (&acc)[M]) {
+    Cols nx;
+    load_cols(P, E, stride, nx.c);
+    int na[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const bool hit = (k.w[m] >> (k.c[m] & 31)) & 1u;
+      if constexpr (L == 1) {
+        if (!hit) k.c[m] = -1;
+      } else {
+        const unsigned long long b = __ballot(hit);
+        na[m] = __popcll(b);
+        if (hit)
+          lds.row[64 * m + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u))] = k.c[m];
       }
     }
-    if (any) a.dirty[u / SIGMA] = 1;
+    if constexpr (L > 1) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+#pragma unroll
+    for (int pass = 0; pass < M / MP; ++pass) {
+      u64x2 f[MP][L];
+#pragma unroll
+      for (int kk = 0; kk < MP; ++kk)
+#pragma unroll
+        for (int q = 0; q < L; ++q) {
+          const int m = pass * MP + kk;
+          int cv = -1;
+          if constexpr (L == 1)
+            cv = k.c[m];
+          else if (q * R + r < na[m])
+            cv = lds.row[64 * m + q * R + r];
+          f[kk][q] = cv >= 0 ? load_pair<W>(F, ms_vi<ABL>(a, cv, rho, SIGMA), sub) : u64x2{0ULL, 0ULL};
+        }
+      if (pass == M / MP - 1) load_words(nx);
+#pragma unroll
+      for (int kk = 0; kk < MP; ++kk)
+#pragma unroll
+        for (int q = 0; q < L; ++q) acc[pass * MP + kk] |= f[kk][q];
+    }
+    if constexpr (L > 1) __builtin_amdgcn_wave_barrier();
+    k = nx;
+  };
+  auto group = [&](bool b) {  // any lane of the caller's group
+    const unsigned long long t = __ballot(b);
+    return L == 1 ? b : ((t >> (r * L)) & ((1ULL << L) - 1ULL)) != 0ULL;
+  };
+
+  // The workgroup's tasks: its share of the wide rows (kMsWidePieces pieces
+  // each), of the long rows, of the groups of M medium rows and of the chunks
+  // of R vertices.
+  const int grid = static_cast<int>(gridDim.x), me = static_cast<int>(blockIdx.x);
+  auto share = [&](long long total) { return total > me ? static_cast<int>((total - 1 - me) / grid + 1) : 0; };
+  const int twide = share(a.nwide) * kMsWidePieces;
+  const int tlong = twide + share(a.nlong - a.nwide);
+  const int tmed = tlong + share((a.nrows - a.nlong + M - 1) / M);
+  const int tall = tmed + share((n + R - 1) / R);
+  // Round k's chunks are dealt in another order of the workgroups each time,
+  // so that positions which recur at a fixed stride in the vertex order (a
+  // relabelling that puts each window's long rows first) go round them: dealt
+  // always in the same order, the slowest workgroup took 3.5 times as long as
+  // the fastest one on scale-20 R-MAT.
+  const int rounds = static_cast<int>((n + R - 1) / R) / grid;  // full ones; the last, partial round keeps its order
+  const int p2 = 1 << (31 - __builtin_clz(static_cast<unsigned>(grid)));  // largest power of two up to grid
+  auto take = [&]() {
+    int t = 0;
+    if (lane == 0) t = __hip_atomic_fetch_add(lds.next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return uniform(t);
+  };
+  // What a task reads first: this lane group's vertex (-1: none), its columns
+  // and its visited words. The next task's are loaded before the current one
+  // is worked on.
+  struct Head {
+    int u, p0, p1;
+  };
+  auto head = [&](int t) {
+    Head h{-1, 0, 0};
+    if (t < tmed) {
+      const long long i = t < twide   ? me + static_cast<long long>(t / kMsWidePieces) * grid
+                          : t < tlong ? a.nwide + me + static_cast<long long>(t - twide) * grid
+                                      : a.nlong + (me + static_cast<long long>(t - tlong) * grid) * M + r;
+      if (r < M && i < a.nrows) h.u = rows[i];
+    } else if (t < tall) {
+      const int k = t - tmed;
+      const int b = k < rounds && me < p2 ? me ^ ((37 * k) & (p2 - 1)) : me;
+      const long long u = (static_cast<long long>(k) * grid + b) * R + r;
+      if (u < n) h.u = static_cast<int>(u);
+    }
+    if (h.u >= 0) {
+      h.p0 = rp[h.u];
+      h.p1 = rp[h.u + 1];
+    }
+    return h;
+  };
+  auto visited = [&](int u) {
+    return u >= 0 ? load_pair<W>(V, ms_vi<ABL>(a, u, rho, SIGMA), sub) : u64x2{~0ULL, ~0ULL};
+  };
+  for (int i = threadIdx.x; i < kMsWideSlots * kWMax; i += BLOCK) lds.wide[i] = 0ULL;
+  if (threadIdx.x < kMsWideSlots) lds.done[threadIdx.x] = 0;
+  if (threadIdx.x == 0) *lds.next = 0;
+  __syncthreads();
+  int t = take();
+  Head cur = head(t);
+  u64x2 v = visited(cur.u);
+  while (t < tall) {
+    const int tn = take();
+    const Head nxt = head(tn);
+    const u64x2 op = ~v & bm;
+    u64x2 x = {0ULL, 0ULL};
+    if (t < tlong) {
+      // One row, or a piece of a wide one, 64 M columns per step; every slot
+      // holds the row, slot 0 writes it. The pieces of a wide row meet in
+      // LDS; the wave that adds the last one goes on with the whole row.
+      const bool open = __ballot(is_open(op)) != 0ULL;
+      int p = __builtin_amdgcn_readlane(cur.p0, 0), pe = __builtin_amdgcn_readlane(cur.p1, 0);
+      const int slot = t / kMsWidePieces;
+      if (t < twide) {
+        const int len = ((pe - p + kMsWidePieces - 1) / kMsWidePieces + 63) & ~63;
+        p += (t % kMsWidePieces) * len;
+        pe = min(pe, p + len);
+      }
+      if (open) {
+        int P[M], E[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+          P[m] = p + 64 * m;
+          E[m] = pe;
+        }
+        Cols k;
+        load_cols(P, E, 0, k.c);
+        load_words(k);
+        while (P[0] < pe) {
+          u64x2 acc[M];
+#pragma unroll
+          for (int m = 0; m < M; ++m) acc[m] = u64x2{0ULL, 0ULL};
+          scan(P, E, 64 * M, k, acc);
+#pragma unroll
+          for (int m = 0; m < M; ++m) {
+            x |= acc[m];
+            P[m] += 64 * M;
+          }
+          x = slots(x);
+          if (!__ballot(is_open(op & ~x))) break;
+        }
+      }
+      if (t < twide) {
+        if (r == 0) {
+          if (x.x) lds_or(lds.wide + slot * kWMax + w0, x.x);
+          if (W > 1 && x.y) lds_or(lds.wide + slot * kWMax + w0 + 1, x.y);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        int d = 0;
+        if (lane == 0) d = __hip_atomic_fetch_add(lds.done + slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        x = u64x2{0ULL, 0ULL};
+        if (uniform(d) == kMsWidePieces - 1) {
+          x.x = lds.wide[slot * kWMax + w0];
+          if (W > 1) x.y = lds.wide[slot * kWMax + (W > 1 ? w0 + 1 : 0)];
+        }
+      }
+      x = r == 0 ? x & op : u64x2{0ULL, 0ULL};
+    } else if (t < tmed) {
+      // M rows (neighbours in the list, so of about the same degree), 64
+      // columns of each per step; slot m writes row m
+      const bool open = group(is_open(op));
+      int P[M], E[M];
+      u64x2 acc[M];
+      bool more = false;
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        P[m] = __builtin_amdgcn_readlane(cur.p0, m * L);
+        E[m] = __builtin_amdgcn_readlane(open ? cur.p1 : cur.p0, m * L);
+        acc[m] = u64x2{0ULL, 0ULL};
+        more |= P[m] < E[m];
+      }
+      if (more) {
+        Cols k;
+        load_cols(P, E, 0, k.c);
+        load_words(k);
+        while (more) {
+          scan(P, E, 64, k, acc);
+          more = false;
+#pragma unroll
+          for (int m = 0; m < M; ++m) {
+            P[m] += 64;
+            acc[m] = slots(acc[m]);
+            if (P[m] < E[m] && !__ballot(r == m && is_open(op & ~acc[m]))) E[m] = P[m];  // covered
+            more |= P[m] < E[m];
+          }
+        }
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+          if (r == m) x = acc[m] & op;
+      }
+    } else {
+      // R consecutive vertices, a lane group each, 8 columns (4 where a lane
+      // is a whole group) of each per step. Columns are loaded two steps
+      // ahead and their front bits one, so a step waits for one round of
+      // frontier rows.
+      constexpr int G = L == 1 ? 4 : 8 / L, STEP = G * L;
+      int p = cur.p0;
+      const int p1 = cur.p1 - cur.p0 > kMsLightDeg ? cur.p0 : cur.p1;  // longer rows are in the lists above
+      bool run = group(is_open(op)) && p < p1;
+      if (__ballot(run)) {
+        auto columns = [&](int q, int (&c)[G]) {
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const int i = q + g * L + sub;
+            c[g] = run && i < p1 ? col[i] : -1;
+          }
+        };
+        auto words = [&](const int (&c)[G], uint32_t (&w)[G]) {
+#pragma unroll
+          for (int g = 0; g < G; ++g) w[g] = c[g] >= 0 ? fb[c[g] >> 5] : 0u;
+        };
+        int c0[G], c1[G];
+        uint32_t fw[G];
+        columns(p, c0);
+        columns(p + STEP, c1);
+        words(c0, fw);
+        for (;;) {
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+            if (!run || !((fw[g] >> (c0[g] & 31)) & 1u)) c0[g] = -1;
+          u64x2 f[G][L];
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const int cv[4] = {group_bcast<L, 0>(c0[g]), group_bcast<L, (L > 1 ? 1 : 0)>(c0[g]),
+                               group_bcast<L, (L > 2 ? 2 : 0)>(c0[g]), group_bcast<L, (L > 2 ? 3 : 0)>(c0[g])};
+#pragma unroll
+            for (int q = 0; q < L; ++q)
+              f[g][q] = cv[q] >= 0 ? load_pair<W>(F, ms_vi<ABL>(a, cv[q], rho, SIGMA), sub) : u64x2{0ULL, 0ULL};
+          }
+          words(c1, fw);
+#pragma unroll
+          for (int g = 0; g < G; ++g) c0[g] = c1[g];
+          columns(p + 2 * STEP, c1);
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int q = 0; q < L; ++q) x |= f[g][q];
+          p += STEP;
+          const bool left = group(is_open(op & ~x));
+          run = run && left && p < p1;
+          if (!__ballot(run)) break;
+        }
+        x &= op;
+      }
+    }
+    const bool any = group(is_open(x));
+    const int u = cur.u;
+    const u64x2 vu = v;
+    const bool chunk = t >= tmed;
+    t = tn;
+    cur = nxt;
+    v = visited(nxt.u);
+    if (__ballot(any)) {
+      commit(any, u, any ? ms_vi<ABL>(a, u, rho, SIGMA) : 0, vu, x);
+      if (FUSED) {
+        resolve();
+        if (chunk) {
+          // front bits of the wave's vertices, a set (or the part of it) per lane
+          const unsigned long long b64 = __ballot(any);
+          const unsigned long long bits = __ballot(lane < R && ((b64 >> (lane * L)) & 1ULL));
+          constexpr int S = SIGMA < R ? SIGMA : R;
+          const int u0 = __builtin_amdgcn_readlane(u, 0);
+          if (lane < R / S) {
+            const uint32_t b = static_cast<uint32_t>((bits >> (lane * S)) & ((1ULL << S) - 1ULL));
+            if (b) front(u0 + lane * S, b);
+          }
+        } else if (any && sub == 0) {
+          front(u, 1u);
+        }
+        if (COUNT) counter.add(x);
+      }
+    }
+    if (COUNT && (counter.full() || (t >= tall && counter.added))) counter.flush(lds.cnt);
+  }
+  if constexpr (FUSED) {
+    resolve();
+    const unsigned long long sf = wave_sum(static_cast<unsigned long long>(fresh));
+    if (sf) {  // uniform in the wave
+      const unsigned long long sq = wave_sum(static_cast<unsigned long long>(nq)), ss = wave_sum(static_cast<unsigned long long>(nqs));
+      live = slots(live);
+      if (lane == 0) {
+        lds_add(lds.stat + MS_FRESH, sf);
+        const bool track = !(ms_abl<ABL>(a) & BLEST_MS_NO_DIRTY);
+        if (sq && track) lds_add(lds.stat + MS_QUEUE, sq);
+        if (ss && track) lds_add(lds.stat + MS_QSLICES, ss);
+      }
+      if (r == 0) {
+        if (live.x) lds_or(lds.stat + kMsLive + w0, live.x);
+        if (W > 1 && live.y) lds_or(lds.stat + kMsLive + w0 + 1, live.y);
+      }
+    }
+  }
+}
+
+template <int SIGMA, int BLOCK, bool FUSED, int ABL>
+__device__ __forceinline__ void ms_gather_any(args_ref<MsArgs> a, int bi, int level, int W, const MsView& st,
+                                              const MsGatherLds& lds, bool count) {
+  auto go = [&](auto width) {
+    constexpr int WW = decltype(width)::value;
+    if (FUSED && count)
+      ms_gather<SIGMA, WW, BLOCK, FUSED, FUSED, ABL>(a, bi, level, st.raw, lds);
+    else
+      ms_gather<SIGMA, WW, BLOCK, FUSED, false, ABL>(a, bi, level, st.raw, lds);
+  };
+  switch (W) {
+    case 1:
+      return go(std::integral_constant<int, 1>{});
+    case 2:
+      return go(std::integral_constant<int, 2>{});
+    case 4:
+      return go(std::integral_constant<int, 4>{});
+    default:
+      return go(std::integral_constant<int, 8>{});
   }
 }
 
 // ---------------------------------------------------------------- Stage 2
 
-struct MsExpandRec {
-  unsigned long long out;
-  uint32_t n, s0, ns, s;
-};
-// Copies a finished batch's staged levels to the caller's rows:
-// levels16[(offset + c) * n + v] = level of input vertex v in traversal c, -1
-// if the traversal did not reach it. Thread t handles input ids v = t, t +
-// nthreads, ...: for each traversal the wave's 64 stores are consecutive, and
-// each lane reads its vertex's staging row 16 bytes at a time. Visited bits
-// come from V (getVI order), so unreached pairs need no staged value.
-template <int SIGMA, int ABL>
-__device__ __attribute__((noinline)) void ms_copy_levels(const MsArgs& a, const MsBatch& bt, long long gtid,
-                                                         long long nthreads) {
+// Copies a finished batch's levels to the caller's rows: levels16[(offset +
+// c) * n + v] = level of input vertex v in traversal c, -1 if the traversal
+// did not reach it. The levels were kept as bit planes: plane j holds bit j
+// of every (vertex, traversal) level, in the layout of the visited words
+// (a vertex's row of W words per plane), so a level's writes are whole rows
+// and a vertex costs W * 8 bytes per plane instead of 128 W of int16.
+// Thread t handles input ids v = t, t + nthreads, ...: a lane reads its
+// vertex's rows of Q words per plane at once (a word at a time, the rows of
+// the workgroup's lanes would leave the L1 between words), and a pair of
+// lanes exchanges values so that each stores both vertices of one traversal:
+// one 4-byte store per lane covers 128 bytes of two traversals' rows.
+// P: planes read (those past np are zero).
+typedef uint32_t u32_half_aligned __attribute__((aligned(2)));
+
+template <int SIGMA, int ABL, int P, int Q>
+__device__ __attribute__((noinline)) void ms_copy_planes(args_ref<MsArgs> a_, int bi, int np) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  bi = uniform(bi);
+  np = uniform(np);
+  const MsBatch bt = ms_batch(a, bi);
+  const long long nthreads = static_cast<long long>(gridDim.x) * blockDim.x;
+  const int lane = lane_id();
   const int W = bt.W;
-  const long long K = 64LL * W;
-  const long long n = a.n;
-  const long long rho = a.nsets;
+  const long long n = a.n, rho = a.nsets;
+  const long long plane = rho * SIGMA * W;
   const int count = bt.count;
-  int16_t* out = a.levels16 + static_cast<long long>(bt.offset) * n;
-  for (long long v = gtid; v < n; v += nthreads) {
-    const long long i = a.perm ? a.perm[v] : v;
-    const long long vi = ms_vi<ABL>(a, i, rho, SIGMA);
-    const uint4* row = reinterpret_cast<const uint4*>(a.lstage + i * K);
-    for (int w = 0; w < W && 64 * w < count; ++w) {
-      const unsigned long long vis = a.V[vi * W + w];
-      for (int j = 0; j < 8 && 64 * w + 8 * j < count; ++j) {
-        const uint32_t bits = static_cast<uint32_t>(vis >> (8 * j)) & 0xffu;
-        uint4 q = make_uint4(0u, 0u, 0u, 0u);
-        if (bits) q = row[8 * w + j];
-        const uint32_t h[4] = {q.x, q.y, q.z, q.w};
+  const gptr<const unsigned long long> V = a.V, planes = a.planes;
+  const gptr<int16_t> out = a.levels16 + static_cast<long long>(bt.offset) * n;
+  const gptr<const int32_t> perm = a.perm;
+  // whole waves: the lanes of a pair both take part in every exchange
+  for (long long base = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x - lane; base < n;
+       base += nthreads) {
+    const long long v = base + lane;
+    const bool in = v < n;
+    const long long i = in ? (perm ? perm[v] : v) : 0;
+    const long long vi = ms_vi<ABL>(a, i, rho, SIGMA) * W;
+    const bool odd = lane & 1;
+    const bool pair = (v | 1) < n;  // both vertices of the pair exist
+    for (int q0 = 0; q0 < W && 64 * q0 < count; q0 += Q) {
+      unsigned long long nv[Q], pl[P][Q];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int c = 64 * w + 8 * j + e;
-          if (c >= count) break;
-          const int16_t lv = static_cast<int16_t>((h[e / 2] >> (16 * (e % 2))) & 0xffffu);
-          out[static_cast<long long>(c) * n + v] = ((bits >> e) & 1u) ? lv : static_cast<int16_t>(-1);
+      for (int k = 0; k < Q; ++k) nv[k] = q0 + k < W ? ~V[vi + q0 + k] : 0ULL;
+#pragma unroll
+      for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int k = 0; k < Q; ++k) pl[j][k] = j < np && q0 + k < W ? planes[j * plane + vi + q0 + k] : 0ULL;
+#pragma unroll
+      for (int k = 0; k < Q; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int c0 = 64 * (q0 + k) + 32 * h;
+          if (c0 >= count) continue;
+          const uint32_t u = static_cast<uint32_t>(nv[k] >> (32 * h));
+          uint32_t p[P];
+#pragma unroll
+          for (int j = 0; j < P; ++j) p[j] = static_cast<uint32_t>(pl[j][k] >> (32 * h));
+          gptr<int16_t> o = out + static_cast<long long>(c0 + (odd && pair ? 1 : 0)) * n + (pair ? base + (lane & ~1) : v);
+          const int cn = min(32, count - c0);
+          auto emit2 = [&](int c) {
+            // both traversals' levels of this vertex, 0xffff where not reached
+            uint32_t lv = ((u >> c) & 1u ? 0xffffu : 0u) | ((u >> (c + 1)) & 1u ? 0xffff0000u : 0u);
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+              const uint32_t t = p[j] >> c;
+              lv |= ((t & 1u) | ((t & 2u) << 15)) << j;
+            }
+            const uint32_t ot = static_cast<uint32_t>(
+                __builtin_amdgcn_mov_dpp(static_cast<int>(lv), 0xb1, 0xf, 0xf, true));  // the pair's other lane
+            if (pair) {
+              const uint32_t w = odd ? (lv & 0xffff0000u) | (ot >> 16) : (lv & 0xffffu) | (ot << 16);
+              if (c + (odd ? 1 : 0) < cn) *(gptr<u32_half_aligned>)o = w;
+            } else if (in) {
+              o[0] = static_cast<int16_t>(lv & 0xffffu);
+              if (c + 1 < cn) o[n] = static_cast<int16_t>(lv >> 16);
+            }
+            o += 2 * n;
+          };
+          if (cn == 32) {
+#pragma unroll
+            for (int c = 0; c < 32; c += 2) emit2(c);
+          } else {
+#pragma unroll 1
+            for (int c = 0; c < cn; c += 2) emit2(c);
+          }
         }
-      }
     }
   }
 }
 
+// last: the batch's deepest level.
+template <int SIGMA, int ABL>
+__device__ __forceinline__ void ms_copy_levels(args_ref<MsArgs> a, int bi, int last) {
+  const int np = last > 0 ? 32 - __builtin_clz(static_cast<unsigned>(last)) : 0;
+  if (np <= 4)
+    ms_copy_planes<SIGMA, ABL, 4, 8>(a, bi, np);
+  else if (np <= 8)
+    ms_copy_planes<SIGMA, ABL, 8, 4>(a, bi, np);
+  else
+    ms_copy_planes<SIGMA, ABL, kMsPlanes, 2>(a, bi, np);
+}
+
+struct MsExpandRec {
+  unsigned long long out;
+  uint32_t n, s0, ns, s;
+};
 constexpr int kMsExpandMin = 8;
 constexpr int kMsMaxExpand = 128;
 
+// LDS of ms_append.
+template <int BLOCK>
+struct MsAppendLds {
+  int scan[BLOCK / 64];
+  unsigned long long base;
+  MsExpandRec rec[kMsMaxExpand];
+  int nrec;
+};
+
+// Appends the nq VSSs of each calling thread's slice set s (slices s0 .. s0 +
+// ns) to the queue; cursor is its length. Called by the whole workgroup;
+// L.nrec must be zero before (visible to all) and is zero after.
+template <int BLOCK>
+__device__ __forceinline__ void ms_append(gptr<uint4> queue, gptr<unsigned long long> cursor, uint32_t tau, int nq, uint32_t s0,
+                                          uint32_t ns, long long s, MsAppendLds<BLOCK>& L) {
+  int v1[1] = {nq}, ex1[1], tot1[1];
+  block_exclusive_scan<BLOCK, 1>(v1, ex1, tot1, L.scan);
+  if (threadIdx.x == 0) L.base = tot1[0] ? fetch_add_u64(cursor, tot1[0]) : 0ULL;
+  __syncthreads();
+  const long long oq = static_cast<long long>(L.base) + ex1[0];
+  if (nq > kMsExpandMin) {
+    const int r = atomicAdd(&L.nrec, 1);
+    if (r < kMsMaxExpand) {
+      L.rec[r] = MsExpandRec{static_cast<unsigned long long>(oq), static_cast<uint32_t>(nq), s0, ns,
+                             static_cast<uint32_t>(s)};
+      nq = 0;
+    }
+  }
+  for (int k2 = 0; k2 < nq; ++k2) {
+    const uint32_t off = static_cast<uint32_t>(k2) * tau;
+    queue[oq + k2] = make_uint4(s0 + off, min(tau, ns - off), 0u, static_cast<uint32_t>(s));
+  }
+  __syncthreads();
+  const int nr = min(L.nrec, kMsMaxExpand);
+  for (int r = 0; r < nr; ++r) {
+    const MsExpandRec e = L.rec[r];
+    for (uint32_t i = threadIdx.x; i < e.n; i += BLOCK) {
+      const uint32_t off = i * tau;
+      queue[e.out + i] = make_uint4(e.s0 + off, min(tau, e.ns - off), 0u, e.s);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) L.nrec = 0;
+  __syncthreads();
+}
+
+// The queue and the activity words of a level whose frontier a gather step
+// (or the seeding) wrote, for a level that the queue form takes.
 template <int SIGMA, int BLOCK, int ABL>
-__device__ void ms_finalize(const MsArgs& a, const MsBatch& bt, int new_level, int slot_out, int sel_out,
-                            long long cum_in, int* lds_cnt, bool count_sources) {
-  __shared__ int lds32[BLOCK / 64];
-  __shared__ long long lds64[3 * (BLOCK / 64)];
-  __shared__ unsigned long long qbase;
-  __shared__ MsExpandRec rec[kMsMaxExpand];
-  __shared__ int nrec;
-  __shared__ unsigned long long lds_live[kWMax];  // OR of this block's new words
-  if (threadIdx.x == 0) nrec = 0;
-  if (threadIdx.x < kWMax) lds_live[threadIdx.x] = 0ULL;
-  const int W = bt.W;
-  const long long rho = a.nsets;
+__device__ __attribute__((noinline)) void ms_emit(args_ref<MsArgs> a_, int W, int level) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  W = uniform(W);
+  level = uniform(level);
+  __shared__ MsAppendLds<BLOCK> L;
+  if (threadIdx.x == 0) L.nrec = 0;
+  const bool track = !(ms_abl<ABL>(a) & BLEST_MS_NO_DIRTY);
+  const gptr<const unsigned long long> F = a.F[level & 1];
+  const gptr<const uint32_t> fb = a.fb[level % 3];
   const uint32_t tau = static_cast<uint32_t>(a.tau);
-  unsigned long long* acc = &a.ctl->acc[slot_out][0][0];
-  uint4* __restrict__ queue = a.queue[sel_out];
+  const long long rho = a.nsets;
+  for (long long base = static_cast<long long>(blockIdx.x) * BLOCK; base < rho;
+       base += static_cast<long long>(gridDim.x) * BLOCK) {
+    const long long s = base + threadIdx.x;
+    const uint32_t bits = s < rho ? set_bits<SIGMA>(fb, s) : 0u;
+    const bool mine = s < rho && (bits || !track);
+    if (!__syncthreads_or(mine)) continue;
+    uint32_t s0 = 0, ns = 0;
+    int nq = 0;
+    if (mine) {
+      for (int w = 0; w < W; ++w) {
+        unsigned long long x = 0ULL;
+        for (uint32_t t = bits; t; t &= t - 1)
+          x |= F[ms_vi<ABL>(a, s * SIGMA + __builtin_ctz(t), rho, SIGMA) * W + w];
+        a.act[s * W + w] = track ? x : ~0ULL;
+      }
+      s0 = a.slice_ptr[s];
+      ns = a.slice_ptr[s + 1] - s0;
+      nq = static_cast<int>((ns + tau - 1) / tau);
+    }
+    ms_append<BLOCK>(a.queue[level & 1], &a.ctl->acc[level % kStatSlots][F_QUEUE][0], tau, nq, s0, ns, s, L);
+  }
+}
+
+// Stage 2 of a queue level: every dirty slice set.
+template <int SIGMA, int BLOCK, int ABL>
+__device__ __attribute__((noinline)) void ms_finalize(args_ref<MsArgs> a_, int bi, int level, lptr<int> lds_cnt,
+                                                      lptr<unsigned long long> s_stat, bool count_sources) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  bi = uniform(bi);
+  level = uniform(level);
+  const MsStep sp = ms_step(a, bi, level);
+  __shared__ MsAppendLds<BLOCK> L;
+  if (threadIdx.x == 0) L.nrec = 0;
+  const int W = sp.W, new_level = sp.new_level;
+  const long long rho = a.nsets;
+  const long long plane = rho * SIGMA * W;
+  const uint32_t tau = static_cast<uint32_t>(a.tau);
   const int lane = lane_id();
-  long long st[3] = {0, 0, 0};  // new pairs, queued slices, (unused)
+  constexpr int VG = 8;  // vertices of a set handled together (their words stay in registers)
+  unsigned long long fresh = 0, qs = 0, nqs = 0;
   const bool overflow = a.levels16 != nullptr && new_level > 32767;
+  // Without dynamic slice-set tracking (an ablation step) every set is
+  // finalised at every level, all its words count as active and all its
+  // VSSs are queued.
+  const bool track = !(ms_abl<ABL>(a) & BLEST_MS_NO_DIRTY);
   for (long long base = static_cast<long long>(blockIdx.x) * BLOCK; base < a.nsets;
        base += static_cast<long long>(gridDim.x) * BLOCK) {
     const long long s = base + threadIdx.x;
-    // Without dynamic slice-set tracking (an ablation step) every set is
-    // finalised at every level, all its words count as active and all its
-    // VSSs are queued.
-    const bool track = !(ms_abl<ABL>(a) & BLEST_MS_NO_DIRTY);
     const bool mine = s < a.nsets && (!track || a.dirty[s]);
+    if (!__syncthreads_or(mine)) continue;
     int nq = 0;
-    uint32_t s0 = 0, ns = 0;
-    if (__syncthreads_or(mine)) {
-      if (mine) a.dirty[s] = 0;
-      const bool wave_any = __ballot(mine) != 0ULL;
-      unsigned long long A_any = 0ULL;
-      int far_cnt[SIGMA];  // per vertex of the set: traversals that reached it at this level
-#pragma unroll
-      for (int b = 0; b < SIGMA; ++b) far_cnt[b] = 0;
-      if (wave_any) {
-        for (int w = 0; w < W; ++w) {
-          unsigned long long dw[SIGMA];
-          unsigned long long Aw = 0ULL;
+    uint32_t s0 = 0, ns = 0, fbits = 0;
+    if (mine) a.dirty[s] = 0;
+    if (__ballot(mine)) {
+      for (int w = 0; w < W; ++w) {
+        unsigned long long Aw = 0ULL;
+        int cnt_c = 0;  // lane c: new vertices of traversal w*64+c in this wave
+#pragma unroll 1
+        for (int b0 = 0; b0 < SIGMA; b0 += VG) {
           // N holds the visited words plus this level's marks (Alg. 5's
-          // V_next); the new bits are its difference from V. All the set's
-          // N and V words for word w are loaded before any store (the stores
-          // below would otherwise order each vertex's loads after the
-          // previous vertex's stores).
-          long long idx[SIGMA];
-          unsigned long long nx[SIGMA], old[SIGMA];
+          // V_next); the new bits are its difference from V. All words of
+          // the group are loaded before any store (the stores would
+          // otherwise order each vertex's loads after the previous vertex's).
+          unsigned long long dw[VG], nx[VG];
+          long long idx[VG];
 #pragma unroll
-          for (int b = 0; b < SIGMA; ++b) {
-            idx[b] = ms_vi<ABL>(a, s * SIGMA + b, rho, SIGMA) * W + w;
+          for (int b = 0; b < VG; ++b) {
+            idx[b] = ms_vi<ABL>(a, s * SIGMA + b0 + b, rho, SIGMA) * W + w;
             nx[b] = mine ? a.N[idx[b]] : 0ULL;
-            old[b] = mine ? a.V[idx[b]] : 0ULL;
+            dw[b] = mine ? a.V[idx[b]] : 0ULL;
           }
 #pragma unroll
-          for (int b = 0; b < SIGMA; ++b) {
-            dw[b] = 0ULL;
+          for (int b = 0; b < VG; ++b) {
+            const unsigned long long dd = nx[b] & ~dw[b];
             if (mine) {
-              const unsigned long long dd = nx[b] & ~old[b];
               if (dd) a.V[idx[b]] = nx[b];
-              a.F[idx[b]] = dd;
-              dw[b] = dd;
-              Aw |= dd;
-              far_cnt[b] += __popcll(dd);
+              sp.Fn[idx[b]] = dd;
             }
+            dw[b] = dd;
+            Aw |= dd;
+            fbits |= dd ? 1u << (b0 + b) : 0u;
+            fresh += __popcll(dd);
           }
-          if (mine) a.act[s * W + w] = track ? Aw : ~0ULL;
-          A_any |= Aw;
-          if (Aw & ~lds_live[w])
-            __hip_atomic_fetch_or(&lds_live[w], Aw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          // int16 levels. Staged: each new (vertex, traversal) pair goes to
-          // the vertex's staging row. The wave writes them together: for each
-          // of its lanes' sets with new bits (lane l holds set s - lane + l),
-          // lane c stores traversal 64 w + c of each of the set's vertices,
-          // so one store covers 128 contiguous bytes of a row. Direct (no
-          // staging buffer): for each traversal c with new vertices in this
-          // set, the set's vertices in c's output row (scattered when
-          // relabelled).
-          if (a.lstage && !overflow) {
-            const long long K = 64LL * W;
-            unsigned long long todo = __ballot(Aw != 0ULL);
-            while (todo) {
-              const int l = __builtin_ctzll(todo);
-              todo &= todo - 1;
-              int16_t* rows = a.lstage + (s - lane + l) * SIGMA * K + 64 * w + lane;
+          if (Aw && overflow) {
+            __hip_atomic_store(&a.ctl->error[0], static_cast<int>(BLEST_ERR_OVERFLOW), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+          } else if (a.planes && new_level > 0) {
+            for (int nl = new_level; nl; nl &= nl - 1) {
+              const gptr<unsigned long long> pl = a.planes + static_cast<long long>(__builtin_ctz(nl)) * plane;
+              unsigned long long pv[VG];
 #pragma unroll
-              for (int b = 0; b < SIGMA; ++b) {
-                const unsigned long long d = readlane64(dw[b], l);
-                if ((d >> lane) & 1ULL) rows[b * K] = static_cast<int16_t>(new_level);
-              }
+              for (int b = 0; b < VG; ++b) pv[b] = dw[b] ? pl[idx[b]] : 0ULL;
+#pragma unroll
+              for (int b = 0; b < VG; ++b)
+                if (dw[b]) pl[idx[b]] = pv[b] | dw[b];
             }
-          } else if (a.levels16 && Aw && !overflow) {
-            unsigned long long t = Aw;
-            while (t) {
-              const int c = __builtin_ctzll(t);
-              t &= t - 1;
-              const long long row = static_cast<long long>(bt.offset) + w * 64 + c;
-              int16_t* out = a.levels16 + row * a.n;
+          } else if (a.levels16) {
+            // direct: for each traversal c with new vertices in this set, the
+            // set's vertices in c's output row (scattered when relabelled)
+            unsigned long long any = 0ULL;
 #pragma unroll
-              for (int b = 0; b < SIGMA; ++b)
+            for (int b = 0; b < VG; ++b) any |= dw[b];
+            while (any) {
+              const int c = __builtin_ctzll(any);
+              any &= any - 1;
+              const gptr<int16_t> out = a.levels16 + (static_cast<long long>(sp.offset) + w * 64 + c) * a.n;
+#pragma unroll
+              for (int b = 0; b < VG; ++b)
                 if ((dw[b] >> c) & 1ULL) {
-                  const long long u = s * SIGMA + b;
+                  const long long u = s * SIGMA + b0 + b;
                   out[a.orig_id ? a.orig_id[u] : u] = static_cast<int16_t>(new_level);
                 }
             }
           }
-          if (Aw && overflow) __hip_atomic_store(&a.ctl->error[0], static_cast<int>(BLEST_ERR_OVERFLOW),
-                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (a.far && mine && new_level > 0) {
+            // Eq. 4: far[u] += level * (traversals reaching u at this level);
+            // the thread owns set s, so no other thread updates these vertices
+#pragma unroll
+            for (int b = 0; b < VG; ++b)
+              if (dw[b]) {
+                const long long u = s * SIGMA + b0 + b;
+                a.far[a.orig_id ? a.orig_id[u] : u] += static_cast<int64_t>(new_level) * __popcll(dw[b]);
+              }
+          }
           // Per-source counts of new vertices: lane c accumulates traversal
           // w*64+c by a ballot over the wave's lanes (vertical popcount).
-          int cnt_c = 0;  // lane c: new vertices of traversal w*64+c in this wave
+          if (count_sources) {
 #pragma unroll
-          for (int b = 0; b < SIGMA; ++b) {
-            st[0] += __popcll(dw[b]);
-            if (count_sources && __ballot(dw[b] != 0ULL)) {
-              for (int c = 0; c < 64; ++c) {
-                const int pc = __popcll(__ballot((dw[b] >> c) & 1ULL));
-                if (lane == c) cnt_c += pc;
-              }
-            }
+            for (int b = 0; b < VG; ++b)
+              if (__ballot(dw[b] != 0ULL))
+                for (int c = 0; c < 64; ++c) {
+                  const int pc = __popcll(__ballot((dw[b] >> c) & 1ULL));
+                  if (lane == c) cnt_c += pc;
+                }
           }
-          if (cnt_c) atomicAdd(&lds_cnt[w * 64 + lane], cnt_c);
         }
+        if (mine) a.act[s * W + w] = track ? Aw : ~0ULL;
+        if (Aw & ~s_stat[kMsLive + w]) lds_or(s_stat + kMsLive + w, Aw);
+        if (cnt_c) __hip_atomic_fetch_add(lds_cnt + w * 64 + lane, cnt_c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
-      if (a.far && mine && A_any && new_level > 0) {
-        // Eq. 4: far[u] += level * (traversals reaching u at this level); the
-        // thread owns set s, so no other thread updates these vertices
-#pragma unroll
-        for (int b = 0; b < SIGMA; ++b)
-          if (far_cnt[b]) {
-            const long long u = s * SIGMA + b;
-            a.far[a.orig_id ? a.orig_id[u] : u] += static_cast<int64_t>(new_level) * far_cnt[b];
-          }
-      }
-      if (mine && (A_any || !track)) {
-        s0 = a.slice_ptr[s];
-        ns = a.slice_ptr[s + 1] - s0;
-        nq = static_cast<int>((ns + tau - 1) / tau);
-        st[1] += ns;
-      }
-      // enqueue the VSSs of every set that gained a vertex in some traversal
-      int v1[1] = {nq}, ex1[1], tot1[1];
-      block_exclusive_scan<BLOCK, 1>(v1, ex1, tot1, lds32);
-      if (threadIdx.x == 0) qbase = tot1[0] ? fetch_add_u64(acc + F_QUEUE * kPad, tot1[0]) : 0ULL;
-      __syncthreads();
-      long long oq = static_cast<long long>(qbase) + ex1[0];
-      if (nq > kMsExpandMin) {
-        const int r = atomicAdd(&nrec, 1);
-        if (r < kMsMaxExpand) {
-          rec[r] = MsExpandRec{static_cast<unsigned long long>(oq), static_cast<uint32_t>(nq), s0, ns,
-                               static_cast<uint32_t>(s)};
-          nq = 0;
-        }
-      }
-      for (int k2 = 0; k2 < nq; ++k2) {
-        const uint32_t off = static_cast<uint32_t>(k2) * tau;
-        queue[oq + k2] = make_uint4(s0 + off, min(tau, ns - off), 0u, static_cast<uint32_t>(s));
-      }
-      __syncthreads();
-      const int nr = min(nrec, kMsMaxExpand);
-      for (int r = 0; r < nr; ++r) {
-        const MsExpandRec e = rec[r];
-        for (uint32_t i = threadIdx.x; i < e.n; i += BLOCK) {
-          const uint32_t off = i * tau;
-          queue[e.out + i] = make_uint4(e.s0 + off, min(tau, e.ns - off), 0u, e.s);
-        }
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) nrec = 0;
-      __syncthreads();
     }
+    if (mine && fbits) ((gptr<typename MaskOf<SIGMA>::T>)sp.fbn)[s] = static_cast<typename MaskOf<SIGMA>::T>(fbits);
+    if (mine && (fbits || !track)) {
+      s0 = a.slice_ptr[s];
+      ns = a.slice_ptr[s + 1] - s0;
+      nq = static_cast<int>((ns + tau - 1) / tau);
+      qs += ns;
+      nqs += static_cast<unsigned long long>(nq);
+    }
+    // enqueue the VSSs of every set that gained a vertex in some traversal
+    ms_append<BLOCK>(a.queue[new_level & 1], &a.ctl->acc[sp.slot_out][F_QUEUE][0], tau, nq, s0, ns, s, L);
   }
-  block_sum64<BLOCK, 3>(st, lds64);
+  const unsigned long long sf = wave_sum(fresh), sq = wave_sum(nqs), ss = wave_sum(qs);
+  if (lane == 0) {
+    if (sf) lds_add(s_stat + MS_FRESH, sf);
+    if (sq) lds_add(s_stat + MS_QUEUE, sq);
+    if (ss) lds_add(s_stat + MS_QSLICES, ss);
+  }
+}
+
+// ------------------------------------------------------------- batches
+
+// LDS every multi-source kernel needs.
+template <int SIGMA, int BLOCK>
+struct MsLds {
+  unsigned long long f[(BLOCK / 64) * ms_lds_words<SIGMA>()];  // the queue engine's tables; the gather's compaction
+  unsigned long long wide[kMsWideSlots * kWMax];
+  int done[kMsWideSlots];
+  unsigned long long stat[kMsStatWords];
+  int cnt[64 * kWMax];
+  int next;
+};
+
+template <int SIGMA, int BLOCK>
+__device__ __forceinline__ void ms_lds_init(MsLds<SIGMA, BLOCK>& s) {
+  for (int c = threadIdx.x; c < 64 * kWMax; c += BLOCK) s.cnt[c] = 0;
+  if (threadIdx.x < kMsStatWords) s.stat[threadIdx.x] = 0ULL;
   __syncthreads();
-  if (threadIdx.x < W) {
-    const unsigned long long v = lds_live[threadIdx.x];
-    if (v) __hip_atomic_fetch_or(acc + F_LIVE * kPad + threadIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  if (threadIdx.x == 0) {
-    if (st[0]) {
-      add_u64(acc + F_FRONTIER * kPad, st[0]);
-      add_u64(acc + F_CUMV * kPad, st[0]);
-    }
-    if (st[1]) add_u64(acc + F_QSLICES * kPad, st[1]);
-    if (blockIdx.x == 0 && cum_in) add_u64(acc + F_CUMV * kPad, cum_in);
-  }
+}
+
+template <int SIGMA, int BLOCK>
+__device__ __forceinline__ MsGatherLds ms_gather_lds(MsLds<SIGMA, BLOCK>& s) {
+  static_assert(ms_lds_words<SIGMA>() * 2 >= 256, "the gather compacts up to 256 columns per wave");
+  return MsGatherLds{to_lds(reinterpret_cast<int*>(s.f + wave_in_block() * ms_lds_words<SIGMA>())), to_lds(s.wide),
+                     to_lds(s.done), to_lds(s.cnt), to_lds(s.stat), to_lds(&s.next)};
+}
+
+// Clears what a batch starts from: visited and next words, the front bits,
+// the first level plane, its sources' rows of the level-0 frontier words (the
+// other rows are read only where a front bit is set), its level rows when
+// they are written directly, the partial sums and the statistics.
+template <int SIGMA, int ABL>
+__device__ __attribute__((noinline)) void ms_batch_clear(args_ref<MsArgs> a_, int bi, bool count_sources) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  const MsBatch bt = ms_batch(a, uniform(bi));
+  const long long nthreads = static_cast<long long>(gridDim.x) * blockDim.x;
+  const long long gtid = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int W = bt.W;
+  const long long nhat = a.nsets * SIGMA;
+  zero_words(a.V, nhat * W, gtid, nthreads);
+  zero_words(a.N, nhat * W, gtid, nthreads);
+  if (a.planes) zero_words(a.planes, nhat * W, gtid, nthreads);
+  for (int b = 0; b < 3; ++b)
+    for (long long i = gtid; i < (nhat + 31) / 32; i += nthreads) a.fb[b][i] = 0u;
+  for (long long i = gtid; i < static_cast<long long>(bt.count) * W; i += nthreads)
+    a.F[0][ms_vi<ABL>(a, a.srcs[bt.offset + i / W], a.nsets, SIGMA) * W + i % W] = 0ULL;
+  if (a.levels16 && !a.planes)
+    fill_minus_one(a.levels16 + static_cast<long long>(bt.offset) * a.n, static_cast<long long>(bt.count) * a.n, gtid,
+                   nthreads);
   if (count_sources) {
-    __syncthreads();
-    // block-private partial sums across levels: sum += level * count, reach += count
-    long long* part = a.part + static_cast<long long>(blockIdx.x) * (2 * 64 * kWMax);
-    for (int c = threadIdx.x; c < 64 * W; c += BLOCK) {
-      const int x = lds_cnt[c];
-      if (x) {
-        part[c] += static_cast<long long>(new_level) * x;
-        part[64 * kWMax + c] += x;
-        lds_cnt[c] = 0;
-      }
+    const gptr<long long> part = a.part + static_cast<long long>(blockIdx.x) * (2 * 64 * kWMax);
+    for (int c = threadIdx.x; c < 2 * 64 * kWMax; c += blockDim.x) part[c] = 0;
+  }
+  if (blockIdx.x == 0)
+    for (int t = 0; t < kStatSlots; ++t) ms_clear_slot(a.ctl, t);
+}
+
+// Level 0: every source in its own traversal's bit, and its statistics.
+template <int SIGMA, int ABL>
+__device__ __attribute__((noinline)) void ms_batch_seed(args_ref<MsArgs> a_, int bi, unsigned xcc) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  const MsBatch bt = ms_batch(a, uniform(bi));
+  const long long nthreads = static_cast<long long>(gridDim.x) * blockDim.x;
+  const long long gtid = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+  using M = typename MaskOf<SIGMA>::T;
+  const bool track = !(ms_abl<ABL>(a) & BLEST_MS_NO_DIRTY);
+  const uint32_t tau = static_cast<uint32_t>(a.tau);
+  const gptr<unsigned long long> st = &a.ctl->ms_acc[0][xcc][0];
+  for (long long c = gtid; c < bt.count; c += nthreads) {
+    const long long u = a.srcs[bt.offset + c];
+    const long long i = ms_vi<ABL>(a, u, a.nsets, SIGMA) * bt.W + c / 64;
+    const unsigned long long bit = 1ULL << (c % 64);
+    __hip_atomic_fetch_or(a.V + i, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_or(a.N + i, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_or(a.F[0] + i, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (a.planes == nullptr && a.levels16) a.levels16[(bt.offset + c) * a.n + (a.orig_id ? a.orig_id[u] : u)] = 0;
+    const uint32_t old = __hip_atomic_fetch_or(a.fb[0] + (u >> 5), 1u << (u & 31), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+    const long long s = u / SIGMA;
+    if (track && !static_cast<M>(old >> ((s * SIGMA) & 31))) {  // the set's first source
+      const uint32_t ns = a.slice_ptr[s + 1] - a.slice_ptr[s];
+      add_u64(st + MS_QUEUE, (ns + tau - 1) / tau);
+      add_u64(st + MS_QSLICES, ns);
     }
-    __syncthreads();
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    add_u64(st + MS_FRESH, static_cast<unsigned long long>(bt.count));
+    if (!track) {
+      add_u64(st + MS_QUEUE, static_cast<unsigned long long>(a.nvss));
+      add_u64(st + MS_QSLICES, static_cast<unsigned long long>(a.nslices));
+    }
+    for (int w = 0; w < bt.W; ++w)
+      __hip_atomic_fetch_or(st + kMsLive + w, batch_mask(bt.count, w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// Housekeeping of the step that builds level new_level: the statistics slot
+// and the front bits that the step after it accumulates into, and the level
+// plane whose first writer is that step.
+template <int SIGMA>
+__device__ __attribute__((noinline)) void ms_prepare_next(args_ref<MsArgs> a_, int W, int new_level) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  W = uniform(W);
+  new_level = uniform(new_level);
+  const long long nthreads = static_cast<long long>(gridDim.x) * blockDim.x;
+  const long long gtid = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const long long nhat = a.nsets * SIGMA;
+  if (blockIdx.x == 0) ms_clear_slot(a.ctl, (new_level + 1) % kStatSlots);
+  const gptr<uint32_t> fbz = a.fb[(new_level + 1) % 3];
+  for (long long i = gtid; i < (nhat + 31) / 32; i += nthreads) fbz[i] = 0u;
+  const unsigned nx = static_cast<unsigned>(new_level) + 1u;
+  if (a.planes && !(nx & (nx - 1u)) && nx < (1u << kMsPlanes)) {
+    const long long words = nhat * W;
+    zero_words(a.planes + static_cast<long long>(__builtin_ctz(nx)) * words, words, gtid, nthreads);
+  }
+}
+
+// Adds a level's per-traversal counts to the workgroup's partial sums: sum +=
+// level * count, reach += count.
+__device__ __forceinline__ void ms_flush_counts(args_ref<MsArgs> a, lptr<int> cnt, int W, int new_level) {
+  __syncthreads();
+  const gptr<long long> part = a.part + static_cast<long long>(blockIdx.x) * (2 * 64 * kWMax);
+  for (int c = threadIdx.x; c < 64 * W; c += blockDim.x) {
+    const int x = cnt[c];
+    if (x) {
+      part[c] += static_cast<long long>(new_level) * x;
+      part[64 * kWMax + c] += x;
+      cnt[c] = 0;
+    }
+  }
+}
+
+// Sums the workgroups' partials of a batch, one wave per source (a lane per
+// workgroup, so a source costs one round of loads instead of a chain of one
+// per workgroup). Each source reaches itself at level 0.
+__device__ __attribute__((noinline)) void ms_reduce_batch(args_ref<MsArgs> a_, int bi) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  const MsBatch bt = ms_batch(a, uniform(bi));
+  const long long nw = blockDim.x / 64, nwaves = gridDim.x * nw;
+  const long long gwave = blockIdx.x * nw + wave_in_block();
+  const gptr<const long long> part = a.part;
+  const int lane = lane_id();
+  for (long long c = gwave; c < bt.count; c += nwaves) {
+    long long su = 0, re = 0;
+    for (unsigned b = lane; b < gridDim.x; b += 64) {
+      su += part[b * (2LL * 64 * kWMax) + c];
+      re += part[b * (2LL * 64 * kWMax) + 64 * kWMax + c];
+    }
+    su = wave_sum(su);
+    re = wave_sum(re) + 1;
+    if (lane == 0) {
+      const long long row = bt.offset + c;
+      if (a.sums) a.sums[row] = su;
+      if (a.reach) a.reach[row] = re;
+      if (a.cc) a.cc[row] = su ? static_cast<double>(re - 1) / static_cast<double>(su) : 0.0;
+    }
+  }
+}
+
+// A level whose queue holds fewer than 1 / kMsDenseDenom of the graph's arcs
+// as slices takes the queue form of a BVSS step, any other the gather step,
+// which reads at most the arcs of the vertices still open.
+constexpr long long kMsDenseDenom = 128;
+
+// What a level does, from its statistics alone (the same in every wave).
+struct MsChoice {
+  bool dense;    // a BVSS step takes the gather form
+  int engine, fallback;
+  __device__ __forceinline__ bool gather() const { return dense || engine == BLEST_ENGINE_BOTTOM_UP; }
+};
+
+// Writes the level's record: workgroup 0, one lane of its first wave.
+__device__ __forceinline__ void ms_log(args_ref<MsArgs> a, int nrec, int bi, int level, int width, const MsChoice& ch,
+                                       long long fresh, long long qlen, long long qslices, long long unv, int live,
+                                       const float (&feat)[kMaxSwitchFeatures]) {
+  if (!a.log || nrec >= a.log_cap || lane_id() != 0) return;
+  const gptr<MsLevelRec> rec = a.log + nrec;
+  rec->batch = bi;
+  rec->level = level;
+  rec->engine = a.probe ? -1 : ch.engine;
+  rec->fallback = ch.fallback;
+  rec->width = width;
+  rec->live = live;
+  rec->fresh = fresh;
+  rec->queue = qlen;
+  rec->qslices = qslices;
+  rec->unvisited = unv;
+  rec->t_engine[0] = rec->t_engine[1] = 0ULL;
+  for (int k = 0; k < kMaxSwitchFeatures; ++k) rec->feat[k] = feat[k];
+}
+
+// Decides level `level` and logs it. The engine of a dense level changes
+// nothing but its record (both engines take the gather form), so there only
+// workgroup 0's first wave, which writes the record, evaluates it.
+template <int ABL, bool MF>
+__device__ __attribute__((noinline)) int ms_decide_level(args_ref<MsArgs> a_, unsigned long long raw_stats, int bi,
+                                                         int level, int nrec, lptr<const float> s_mlp,
+                                                         bool learned) {
+  args_ref<MsArgs> a = uniform_args(a_);
+  bi = uniform(bi);
+  level = uniform(level);
+  nrec = uniform(nrec);
+  const MsView st{raw_stats};
+  const MsBatch bt = ms_batch(a, bi);
+  const long long fresh = st.get(MS_FRESH), qlen = st.get(MS_QUEUE), qslices = st.get(MS_QSLICES);
+  const long long unv = static_cast<long long>(bt.count) * a.n - st.get(MS_CUMIN) - fresh;
+  MsChoice ch{!MF && ms_abl<ABL>(a) == 0 && qslices * kMsDenseDenom >= a.m, BLEST_ENGINE_BVSS, 0};
+  const bool writer = blockIdx.x == 0 && wave_in_block() == 0;
+  if (!ch.dense || writer) {
+    float feat[kMaxSwitchFeatures];
+    const int live = st.live();
+    ms_features(feat, a, fresh, qlen, qslices, unv, bt.count, live);
+    ch.engine = ms_choose(a, feat, qlen, unv, level, bi, s_mlp, learned, &ch.fallback);
+    if (writer) ms_log(a, nrec, bi, level, bt.count, ch, fresh, qlen, qslices, unv, live, feat);
+  }
+  return (ch.dense ? 1 : 0) | (ch.engine << 1);
+}
+
+template <int ABL, bool MF>
+__device__ __forceinline__ MsChoice ms_decide(args_ref<MsArgs> a, const MsView& st, int bi, int level, int nrec,
+                                              lptr<const float> s_mlp, bool learned) {
+  const int c = uniform(ms_decide_level<ABL, MF>(a, st.raw, bi, level, nrec, s_mlp, learned));
+  return MsChoice{(c & 1) != 0, c >> 1, 0};
+}
+
+// Thread 0 of workgroup 0 adds what no workgroup counts: the pairs visited
+// before the new level and, without slice-set tracking, the totals of the
+// queue (every set counts) when the step was not a queue level.
+template <int ABL>
+__device__ __forceinline__ void ms_level_end(args_ref<MsArgs> a, const MsView& st, bool finalized, lptr<unsigned long long> s_stat) {
+  if (blockIdx.x != 0 || wave_in_block() != 0) return;
+  const long long cum = st.get(MS_CUMIN) + st.get(MS_FRESH);
+  if (threadIdx.x == 0) {
+    lds_add(s_stat + MS_CUMIN, static_cast<unsigned long long>(cum));
+    if ((ms_abl<ABL>(a) & BLEST_MS_NO_DIRTY) && !finalized) {
+      lds_add(s_stat + MS_QUEUE, static_cast<unsigned long long>(a.nvss));
+      lds_add(s_stat + MS_QSLICES, static_cast<unsigned long long>(a.nslices));
+    }
   }
 }
 
@@ -837,129 +1822,81 @@ __device__ void ms_finalize(const MsArgs& a, const MsBatch& bt, int new_level, i
 // cores; 10 + f: the bitwise check with ablation flags f (each a kernel of its
 // own, so no variant's branches or registers weigh on another).
 template <int SIGMA, class SliceT, int BLOCK, int MODE = 0>
-__global__ void __launch_bounds__(BLOCK) k_ms_persistent(MsArgs a) {
+__global__ void __launch_bounds__(BLOCK) k_ms_persistent(MsArgs args) {
+  args_ref<MsArgs> a = kernel_args(args);
   constexpr bool MF = MODE == 1;
   constexpr int ABL = MODE >= 10 ? MODE - 10 : 0;
+  constexpr int GABL = MODE >= 10 ? -1 : 0;  // the gather's: one body for all ablation kernels
   extern __shared__ float s_mlp[];
-  __shared__ unsigned long long lds_f[(BLOCK / 64) * ms_lds_words<SIGMA>()];
-  __shared__ int lds_cnt[64 * kWMax];
+  __shared__ MsLds<SIGMA, BLOCK> lds;
   const bool learned = a.policy == BLEST_POLICY_LEARNED && a.mlp != nullptr && a.mlp->valid;
-  if (learned) mlp_to_lds(a.mlp, s_mlp);
-  const long long nthreads = static_cast<long long>(gridDim.x) * BLOCK;
-  const long long gtid = static_cast<long long>(blockIdx.x) * BLOCK + threadIdx.x;
+  if (learned) mlp_to_lds((const MlpDev*)a.mlp, s_mlp);
   const int wave = wave_in_block();
-  const long long gwave = static_cast<long long>(blockIdx.x) * (BLOCK / 64) + wave;
-  const long long nwaves = static_cast<long long>(gridDim.x) * (BLOCK / 64);
-  unsigned long long* my_f = lds_f + wave * ms_lds_words<SIGMA>();
-  const long long rho = a.nsets;
-  const long long nhat = a.nsets * SIGMA;
+  const lptr<unsigned long long> my_f = to_lds(lds.f) + wave * ms_lds_words<SIGMA>();
+  const MsGatherLds glds = ms_gather_lds(lds);
   const bool count_sources = a.sums != nullptr || a.reach != nullptr || a.cc != nullptr;
-  for (int c = threadIdx.x; c < 64 * kWMax; c += BLOCK) lds_cnt[c] = 0;
+  ms_lds_init(lds);
   BarrierCtx bc;
-  if (!barrier_register(a.ctl, &bc, a.timeout_ticks)) return;
+  if (!barrier_register((Ctl*)a.ctl, &bc, a.timeout_ticks)) return;
   int total_levels = 0;
   int nrec = 0;  // level records written so far (the same count in every workgroup)
   for (int bi = 0; bi < a.nbatches; ++bi) {
-    const MsBatch bt = a.batches[bi];
-    const int W = bt.W;
-    // clear the batch's state and its level rows
-    for (long long i = gtid; i < nhat * W; i += nthreads) {
-      a.F[i] = 0ULL;
-      a.V[i] = 0ULL;
-      a.N[i] = 0ULL;
-    }
-    if (a.levels16 && !a.lstage) fill_minus_one(a.levels16 + static_cast<long long>(bt.offset) * a.n,
-                                                static_cast<long long>(bt.count) * a.n, gtid, nthreads);
-    if (count_sources) {
-      long long* part = a.part + static_cast<long long>(blockIdx.x) * (2 * 64 * kWMax);
-      for (int c = threadIdx.x; c < 2 * 64 * kWMax; c += BLOCK) part[c] = 0;
-    }
-    if (blockIdx.x == 0)
-      for (int t = 0; t < kStatSlots; ++t) ms_clear_slot(a.ctl, t);
-    if (!grid_barrier(a.ctl, bc)) return;
-    // seed: mark each source in its own traversal's bit
-    for (long long c = gtid; c < bt.count; c += nthreads) {
-      const long long u = a.srcs[bt.offset + c];
-      const long long vi = ms_vi<ABL>(a, u, rho, SIGMA);
-      __hip_atomic_fetch_or(&a.N[vi * W + c / 64], 1ULL << (c % 64), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      a.dirty[u / SIGMA] = 1;
-    }
-    if (!grid_barrier(a.ctl, bc)) return;
-    ms_finalize<SIGMA, BLOCK, ABL>(a, bt, 0, 0, 0, 0, lds_cnt, count_sources);
-    if (!grid_barrier(a.ctl, bc)) return;
-    const long long pairs_total = static_cast<long long>(bt.count) * a.n;
-    for (int level = 0;; ++level) {
-      const int slot = level % kStatSlots;
-      const unsigned long long* accr = &a.ctl->acc[slot][0][0];
-      const long long fresh = static_cast<long long>(accr[F_FRONTIER * kPad]);
-      if (fresh == 0) break;
-      const long long qlen = static_cast<long long>(accr[F_QUEUE * kPad]);
-      const long long qslices = static_cast<long long>(accr[F_QSLICES * kPad]);
-      const long long cumv = static_cast<long long>(accr[F_CUMV * kPad]);
-      const int live = ms_live_count(a.ctl, slot);
-      const unsigned long long* live_w = accr + F_LIVE * kPad;
-      float feat[kMaxSwitchFeatures];
-      ms_features(feat, a, fresh, qlen, qslices, pairs_total - cumv, bt.count, live);
-      int fallback = 0;
-      const int engine = ms_choose(a, feat, qlen, pairs_total - cumv, level, bi, learned ? s_mlp : nullptr, &fallback);
-      if (blockIdx.x == 0) ms_clear_slot(a.ctl, (level + 1) % kStatSlots);
-      MsLevelRec* rec = (a.log && nrec < a.log_cap) ? a.log + nrec : nullptr;
-      if (blockIdx.x == 0 && threadIdx.x == 0 && rec) {
-        rec->batch = bi;
-        rec->level = level;
-        rec->engine = a.probe ? -1 : engine;
-        rec->fallback = fallback;
-        rec->width = bt.count;
-        rec->live = live;
-        rec->fresh = fresh;
-        rec->queue = qlen;
-        rec->qslices = qslices;
-        rec->unvisited = pairs_total - cumv;
-        rec->t_engine[0] = rec->t_engine[1] = 0ULL;
-        for (int k = 0; k < kMaxSwitchFeatures; ++k) rec->feat[k] = feat[k];
-      }
+    const MsBatch bt = ms_batch(a, bi);
+    ms_batch_clear<SIGMA, ABL>(a, bi, count_sources);
+    if (!grid_barrier((Ctl*)a.ctl, bc)) return;
+    ms_batch_seed<SIGMA, ABL>(a, bi, bc.xcc);
+    if (!grid_barrier((Ctl*)a.ctl, bc)) return;
+    bool listed = false;  // the level's queue and activity words exist
+    int level = 0;
+    for (;; ++level) {
+      const MsView st = ms_stats(a.ctl, level % kStatSlots);
+      if (st.get(MS_FRESH) == 0) break;
+      const MsChoice ch =
+          ms_decide<ABL, MF>(a, st, bi, level, nrec, to_lds((const float*)s_mlp), learned);
+      const gptr<MsLevelRec> rec = (a.log && nrec < a.log_cap) ? a.log + nrec : nullptr;
       ++nrec;
+      ms_prepare_next<SIGMA>(a, bt.W, level + 1);
+      const bool gather = ch.gather();
+      const bool queued = !ch.dense && (a.probe || !gather);  // the queue form runs
+      if (queued && !listed) {
+        ms_emit<SIGMA, BLOCK, ABL>(a, bt.W, level);
+        if (!grid_barrier((Ctl*)a.ctl, bc)) return;
+      }
+      const long long qlen = st.get(MS_QUEUE);
       if (a.probe) {
-        // both engines from the same state: their marks are the same set
+        // both engines from the same state, each in the form it takes at this
+        // level: their marks are the same set. At a dense level both take the
+        // gather step, so one run times both.
         const unsigned long long t0 = dev_ticks();
-        ms_engine_bvss<SIGMA, SliceT, MF, ABL>(a, a.queue[level & 1], qlen, W, gwave, nwaves, my_f);
-        if (!grid_barrier(a.ctl, bc)) return;
+        if (queued) {
+          ms_engine_bvss<SIGMA, SliceT, MF, ABL>(a, bi, level, qlen, my_f);
+          if (!grid_barrier((Ctl*)a.ctl, bc)) return;
+        }
         const unsigned long long t1 = dev_ticks();
-        ms_engine_pull<SIGMA, ABL>(a, W, bt.count, live_w, gtid, nthreads);
-        if (!grid_barrier(a.ctl, bc)) return;
+        ms_gather_any<SIGMA, BLOCK, false, GABL>(a, bi, level, bt.W, st, glds, false);
+        if (!grid_barrier((Ctl*)a.ctl, bc)) return;
         if (blockIdx.x == 0 && threadIdx.x == 0 && rec) {
-          rec->t_engine[0] = t1 - t0;
-          rec->t_engine[1] = dev_ticks() - t1;
+          const unsigned long long t2 = dev_ticks();
+          rec->t_engine[0] = (queued ? t1 : t2) - t0;
+          rec->t_engine[1] = t2 - t1;
         }
+      } else if (gather) {
+        ms_gather_any<SIGMA, BLOCK, true, GABL>(a, bi, level, bt.W, st, glds, count_sources);
       } else {
-        if (engine == BLEST_ENGINE_BVSS)
-          ms_engine_bvss<SIGMA, SliceT, MF, ABL>(a, a.queue[level & 1], qlen, W, gwave, nwaves, my_f);
-        else
-          ms_engine_pull<SIGMA, ABL>(a, W, bt.count, live_w, gtid, nthreads);
-        if (!grid_barrier(a.ctl, bc)) return;
+        ms_engine_bvss<SIGMA, SliceT, MF, ABL>(a, bi, level, qlen, my_f);
+        if (!grid_barrier((Ctl*)a.ctl, bc)) return;
       }
-      ms_finalize<SIGMA, BLOCK, ABL>(a, bt, level + 1, (level + 1) % kStatSlots, (level & 1) ^ 1, cumv, lds_cnt,
-                                count_sources);
-      if (!grid_barrier(a.ctl, bc)) return;
-      total_levels = max(total_levels, level + 1);
+      listed = a.probe || !gather;
+      if (listed) ms_finalize<SIGMA, BLOCK, ABL>(a, bi, level, glds.cnt, glds.stat, count_sources);
+      if (count_sources) ms_flush_counts(a, glds.cnt, bt.W, level + 1);
+      ms_level_end<ABL>(a, st, listed, glds.stat);
+      ms_publish(a.ctl, (level + 1) % kStatSlots, bc.xcc, glds.stat);
+      if (!grid_barrier((Ctl*)a.ctl, bc)) return;
     }
-    if (a.lstage && a.ctl->error[0] == 0) ms_copy_levels<SIGMA, ABL>(a, bt, gtid, nthreads);
-    if (count_sources) {
-      // reduce the block partials of this batch
-      for (long long c = gtid; c < bt.count; c += nthreads) {
-        long long su = 0, re = 0;
-        for (unsigned blk = 0; blk < gridDim.x; ++blk) {
-          const long long* part = a.part + static_cast<long long>(blk) * (2 * 64 * kWMax);
-          su += part[c];
-          re += part[64 * kWMax + c];
-        }
-        const long long row = bt.offset + c;
-        if (a.sums) a.sums[row] = su;
-        if (a.reach) a.reach[row] = re;
-        if (a.cc) a.cc[row] = su ? static_cast<double>(re - 1) / static_cast<double>(su) : 0.0;
-      }
-    }
-    if (!grid_barrier(a.ctl, bc)) return;
+    total_levels = max(total_levels, level);
+    if (a.planes && a.ctl->error[0] == 0) ms_copy_levels<SIGMA, ABL>(a, bi, level - 1);
+    if (count_sources) ms_reduce_batch(a, bi);
+    if (!grid_barrier((Ctl*)a.ctl, bc)) return;
   }
   if (blockIdx.x == 0) {
     if (threadIdx.x < 8) a.ctl->xcd_blocks[threadIdx.x][0] = 0u;
@@ -973,143 +1910,94 @@ __global__ void __launch_bounds__(BLOCK) k_ms_persistent(MsArgs a) {
 //
 // The same traversal as k_ms_persistent, cut into one kernel per grid-wide
 // phase so that a fixed sequence of launches can be captured in a hipGraph
-// and replayed: the kernel's work is chosen by a state {phase, batch, level}
-// in the control block. Kernel i of a graph reads state slot i % 2 and
-// workgroup 0 writes the next state to the other slot (the next kernel starts
-// only after every workgroup of this one has finished, so no workgroup reads a
-// slot while it is being written). After the last batch the phase is
-// MS_DONE and the remaining kernels of a replay do nothing.
-enum MsPhase : int { MS_INIT = 0, MS_SEED = 1, MS_FIN0 = 2, MS_ENGINE = 3, MS_FIN = 4, MS_END = 5, MS_DONE = 6 };
+// and replayed: the kernel's work is chosen by a state {phase, batch, level,
+// records, listed} in the control block. Kernel i of a graph reads state slot
+// i % 2 and workgroup 0 writes the next state to the other slot (the next
+// kernel starts only after every workgroup of this one has finished, so no
+// workgroup reads a slot while it is being written). After the last batch the
+// phase is MS_DONE and the remaining kernels of a replay do nothing.
+enum MsPhase : int { MS_INIT = 0, MS_SEED = 1, MS_LEVEL = 2, MS_FIN = 3, MS_END = 4, MS_DONE = 5 };
 constexpr int kMsGraphKernels = 32;  // kernels per graph (even)
 static_assert(sizeof(MsDev::gnode) / sizeof(hipGraphNode_t) == kMsGraphKernels, "one node handle per kernel");
 
 template <int SIGMA, class SliceT, int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_ms_phase(MsArgs a, int parity) {
+__global__ void __launch_bounds__(BLOCK) k_ms_phase(MsArgs args, int parity) {
+  args_ref<MsArgs> a = kernel_args(args);
   constexpr int ABL = -1;
   extern __shared__ float s_mlp[];
-  __shared__ unsigned long long lds_f[(BLOCK / 64) * ms_lds_words<SIGMA>()];
-  __shared__ int lds_cnt[64 * kWMax];
+  __shared__ MsLds<SIGMA, BLOCK> lds;
   const int phase = a.ctl->ms_state[parity][0];
-  const int bi = a.ctl->ms_state[parity][1];
-  const int level = a.ctl->ms_state[parity][2];
+  const int bi = uniform(a.ctl->ms_state[parity][1]);
+  const int level = uniform(a.ctl->ms_state[parity][2]);
   const int nrec = a.ctl->ms_state[parity][3];
-  int next[4] = {MS_DONE, bi, level, nrec};
+  const int listed = a.ctl->ms_state[parity][4];
+  int next[5] = {MS_DONE, bi, level, nrec, 0};
   if (phase != MS_DONE) {
-    const long long nthreads = static_cast<long long>(gridDim.x) * BLOCK;
-    const long long gtid = static_cast<long long>(blockIdx.x) * BLOCK + threadIdx.x;
     const int wave = wave_in_block();
-    const long long gwave = static_cast<long long>(blockIdx.x) * (BLOCK / 64) + wave;
-    const long long nwaves = static_cast<long long>(gridDim.x) * (BLOCK / 64);
-    unsigned long long* my_f = lds_f + wave * ms_lds_words<SIGMA>();
-    const long long rho = a.nsets;
-    const long long nhat = a.nsets * SIGMA;
+    const lptr<unsigned long long> my_f = to_lds(lds.f) + wave * ms_lds_words<SIGMA>();
+    const MsGatherLds glds = ms_gather_lds(lds);
+    const unsigned xcc = xcc_id();
     const bool count_sources = a.sums != nullptr || a.reach != nullptr || a.cc != nullptr;
-    for (int q = threadIdx.x; q < 64 * kWMax; q += BLOCK) lds_cnt[q] = 0;
-    __syncthreads();
-    const MsBatch bt = a.batches[bi];
-    const int W = bt.W;
+    ms_lds_init(lds);
+    const MsBatch bt = ms_batch(a, bi);
     switch (phase) {
       case MS_INIT:
-        for (long long i = gtid; i < nhat * W; i += nthreads) {
-          a.F[i] = 0ULL;
-          a.V[i] = 0ULL;
-          a.N[i] = 0ULL;
-        }
-        if (a.levels16 && !a.lstage) fill_minus_one(a.levels16 + static_cast<long long>(bt.offset) * a.n,
-                                                    static_cast<long long>(bt.count) * a.n, gtid, nthreads);
-        if (count_sources) {
-          long long* part = a.part + static_cast<long long>(blockIdx.x) * (2 * 64 * kWMax);
-          for (int q = threadIdx.x; q < 2 * 64 * kWMax; q += BLOCK) part[q] = 0;
-        }
-        if (blockIdx.x == 0)
-          for (int t = 0; t < kStatSlots; ++t) ms_clear_slot(a.ctl, t);
+        ms_batch_clear<SIGMA, ABL>(a, bi, count_sources);
         next[0] = MS_SEED;
         break;
       case MS_SEED:
-        for (long long q = gtid; q < bt.count; q += nthreads) {
-          const long long u = a.srcs[bt.offset + q];
-          const long long vi = ms_vi<ABL>(a, u, rho, SIGMA);
-          __hip_atomic_fetch_or(&a.N[vi * W + q / 64], 1ULL << (q % 64), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          a.dirty[u / SIGMA] = 1;
-        }
-        next[0] = MS_FIN0;
-        break;
-      case MS_FIN0:
-        ms_finalize<SIGMA, BLOCK, ABL>(a, bt, 0, 0, 0, 0, lds_cnt, count_sources);
-        next[0] = MS_ENGINE;
+        ms_batch_seed<SIGMA, ABL>(a, bi, xcc);
+        next[0] = MS_LEVEL;
         next[2] = 0;
         break;
-      case MS_ENGINE: {
-        const unsigned long long* accr = &a.ctl->acc[level % kStatSlots][0][0];
-        const long long fresh = static_cast<long long>(accr[F_FRONTIER * kPad]);
-        if (fresh == 0) {
+      case MS_LEVEL: {
+        const MsView st = ms_stats(a.ctl, level % kStatSlots);
+        if (st.get(MS_FRESH) == 0) {
           next[0] = MS_END;
           break;
         }
-        const long long qlen = static_cast<long long>(accr[F_QUEUE * kPad]);
-        const long long qslices = static_cast<long long>(accr[F_QSLICES * kPad]);
-        const long long cumv = static_cast<long long>(accr[F_CUMV * kPad]);
-        const long long unv = static_cast<long long>(bt.count) * a.n - cumv;
         const bool learned = a.policy == BLEST_POLICY_LEARNED && a.mlp != nullptr && a.mlp->valid;
         if (learned) {
-          mlp_to_lds(a.mlp, s_mlp);
+          mlp_to_lds((const MlpDev*)a.mlp, s_mlp);
           __syncthreads();
         }
-        const int live = ms_live_count(a.ctl, level % kStatSlots);
-        float feat[kMaxSwitchFeatures];
-        ms_features(feat, a, fresh, qlen, qslices, unv, bt.count, live);
-        int fallback = 0;
-        const int engine = ms_choose(a, feat, qlen, unv, level, bi, learned ? s_mlp : nullptr, &fallback);
-        if (blockIdx.x == 0) {
-          ms_clear_slot(a.ctl, (level + 1) % kStatSlots);
-          if (threadIdx.x == 0 && a.log && nrec < a.log_cap) {
-            MsLevelRec* rec = a.log + nrec;
-            rec->batch = bi;
-            rec->level = level;
-            rec->engine = engine;
-            rec->fallback = fallback;
-            rec->width = bt.count;
-            rec->live = live;
-            rec->fresh = fresh;
-            rec->queue = qlen;
-            rec->qslices = qslices;
-            rec->unvisited = unv;
-            rec->t_engine[0] = rec->t_engine[1] = 0ULL;
-            for (int k = 0; k < kMaxSwitchFeatures; ++k) rec->feat[k] = feat[k];
-          }
+        const MsChoice ch = ms_decide<ABL, false>(a, st, bi, level, nrec, to_lds((const float*)s_mlp), learned);
+        const bool gather = ch.gather();
+        if (!gather && !listed) {
+          ms_emit<SIGMA, BLOCK, ABL>(a, bt.W, level);
+          next[0] = MS_LEVEL;
+          next[4] = 1;
+          break;
         }
         next[3] = nrec + 1;
-        if (engine == BLEST_ENGINE_BVSS)
-          ms_engine_bvss<SIGMA, SliceT, false, ABL>(a, a.queue[level & 1], qlen, W, gwave, nwaves, my_f);
-        else
-          ms_engine_pull<SIGMA, ABL>(a, W, bt.count, accr + F_LIVE * kPad, gtid, nthreads);
-        next[0] = MS_FIN;
+        ms_prepare_next<SIGMA>(a, bt.W, level + 1);
+        if (gather) {
+          ms_gather_any<SIGMA, BLOCK, true, ABL>(a, bi, level, bt.W, st, glds, count_sources);
+          if (count_sources) ms_flush_counts(a, glds.cnt, bt.W, level + 1);
+          ms_level_end<ABL>(a, st, false, glds.stat);
+          ms_publish(a.ctl, (level + 1) % kStatSlots, xcc, glds.stat);
+          next[0] = MS_LEVEL;
+          next[2] = level + 1;
+        } else {
+          ms_engine_bvss<SIGMA, SliceT, false, ABL>(a, bi, level, st.get(MS_QUEUE), my_f);
+          next[0] = MS_FIN;
+        }
         break;
       }
       case MS_FIN: {
-        const long long cumv = static_cast<long long>(a.ctl->acc[level % kStatSlots][F_CUMV][0]);
-        ms_finalize<SIGMA, BLOCK, ABL>(a, bt, level + 1, (level + 1) % kStatSlots, (level & 1) ^ 1, cumv, lds_cnt,
-                                  count_sources);
-        next[0] = MS_ENGINE;
+        const MsView st = ms_stats(a.ctl, level % kStatSlots);
+        ms_finalize<SIGMA, BLOCK, ABL>(a, bi, level, glds.cnt, glds.stat, count_sources);
+        if (count_sources) ms_flush_counts(a, glds.cnt, bt.W, level + 1);
+        ms_level_end<ABL>(a, st, true, glds.stat);
+        ms_publish(a.ctl, (level + 1) % kStatSlots, xcc, glds.stat);
+        next[0] = MS_LEVEL;
         next[2] = level + 1;
+        next[4] = 1;
         break;
       }
       default:  // MS_END
-        if (a.lstage && a.ctl->error[0] == 0) ms_copy_levels<SIGMA, ABL>(a, bt, gtid, nthreads);
-        if (count_sources) {
-          for (long long q = gtid; q < bt.count; q += nthreads) {
-            long long su = 0, re = 0;
-            for (unsigned blk = 0; blk < gridDim.x; ++blk) {
-              const long long* part = a.part + static_cast<long long>(blk) * (2 * 64 * kWMax);
-              su += part[q];
-              re += part[64 * kWMax + q];
-            }
-            const long long row = bt.offset + q;
-            if (a.sums) a.sums[row] = su;
-            if (a.reach) a.reach[row] = re;
-            if (a.cc) a.cc[row] = su ? static_cast<double>(re - 1) / static_cast<double>(su) : 0.0;
-          }
-        }
+        if (a.planes && a.ctl->error[0] == 0) ms_copy_levels<SIGMA, ABL>(a, bi, level - 1);
+        if (count_sources) ms_reduce_batch(a, bi);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
           if (level > a.ctl->nlevels[0]) a.ctl->nlevels[0] = level;
           a.ctl->ms_nrec[0] = nrec;
@@ -1121,45 +2009,32 @@ __global__ void __launch_bounds__(BLOCK) k_ms_phase(MsArgs a, int parity) {
     }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0)
-    for (int i = 0; i < 4; ++i) a.ctl->ms_state[parity ^ 1][i] = next[i];
+    for (int i = 0; i < 5; ++i) a.ctl->ms_state[parity ^ 1][i] = next[i];
 }
 
 __global__ void k_ms_start(Ctl* ctl) {
   if (threadIdx.x == 0) {
-    ctl->ms_state[0][0] = MS_INIT;
-    ctl->ms_state[0][1] = 0;
-    ctl->ms_state[0][2] = 0;
-    ctl->ms_state[0][3] = 0;
+    for (int i = 0; i < 5; ++i) ctl->ms_state[0][i] = 0;  // MS_INIT, batch 0
     ctl->nlevels[0] = 0;
     ctl->ms_nrec[0] = 0;
   }
 }
 
+// One workgroup of 16 waves per compute unit: the gather step is bound by the
+// latency of its loads, so it wants as many waves as 128 registers allow, and
+// the device-wide barrier wants few workgroups.
+constexpr int kMsBlock = 1024;
+
 template <int SIGMA, class SliceT>
 const void* ms_phase_fn() {
-  return reinterpret_cast<const void*>(&k_ms_phase<SIGMA, SliceT, 512>);
-}
-
-template <int SIGMA, class SliceT, int BLOCK>
-const void* ms_fn() {
-  return reinterpret_cast<const void*>(&k_ms_persistent<SIGMA, SliceT, BLOCK>);
+  return reinterpret_cast<const void*>(&k_ms_phase<SIGMA, SliceT, kMsBlock>);
 }
 
 template <int SIGMA, class SliceT>
-const void* ms_fn_block(int block) {
-  switch (block) {
-    case 256:
-      return ms_fn<SIGMA, SliceT, 256>();
-    case 1024:
-      return ms_fn<SIGMA, SliceT, 1024>();
-    default:
-      return ms_fn<SIGMA, SliceT, 512>();
-  }
+const void* ms_fn() {
+  return reinterpret_cast<const void*>(&k_ms_persistent<SIGMA, SliceT, kMsBlock>);
 }
 
-// The multi-source kernel keeps sigma words per slice set live in Stage 2;
-// 512-thread blocks leave it enough registers to avoid spilling at sigma 8.
-constexpr int kMsBlock = 512;
 constexpr int kMsLogCap = 1 << 16;  // level records per call
 
 const void* ms_kernel(const DevGraph& g) {
@@ -1177,10 +2052,10 @@ const void* ms_kernel(const DevGraph& g) {
            : g.ms_ablation == 2 ? reinterpret_cast<const void*>(&k_ms_persistent<8, uint32_t, kMsBlock, 12>)
                                 : reinterpret_cast<const void*>(&k_ms_persistent<8, uint32_t, kMsBlock, 13>);
   }
-  if (g.sigma == 8 && !g.wide) return ms_fn_block<8, uint32_t>(kMsBlock);
-  if (g.sigma == 8) return ms_fn_block<8, uint64_t>(kMsBlock);
-  if (g.sigma == 16) return ms_fn_block<16, uint64_t>(kMsBlock);
-  return ms_fn_block<32, uint64_t>(kMsBlock);
+  if (g.sigma == 8 && !g.wide) return ms_fn<8, uint32_t>();
+  if (g.sigma == 8) return ms_fn<8, uint64_t>();
+  if (g.sigma == 16) return ms_fn<16, uint64_t>();
+  return ms_fn<32, uint64_t>();
 }
 
 void ms_graph_destroy(MsDev* ms) {
@@ -1198,7 +2073,10 @@ hipError_t ensure(const DevGraph& g, MsDev* ms, int wmax, int32_t k, int nbatche
     ms_release(ms);
     const size_t words = static_cast<size_t>(nhat) * wmax;
     hipError_t e;
-    if ((e = hipMalloc(&ms->F, words * 8)) != hipSuccess) return e;
+    for (auto& f : ms->F)
+      if ((e = hipMalloc(&f, words * 8)) != hipSuccess) return e;
+    for (auto& b : ms->fb)
+      if ((e = hipMalloc(&b, static_cast<size_t>(nhat / 8) + 16)) != hipSuccess) return e;
     if ((e = hipMalloc(&ms->V, words * 8)) != hipSuccess) return e;
     if ((e = hipMalloc(&ms->N, words * 8)) != hipSuccess) return e;
     if ((e = hipMalloc(&ms->act, static_cast<size_t>(g.nsets) * wmax * 8)) != hipSuccess) return e;
@@ -1233,8 +2111,7 @@ hipError_t ensure(const DevGraph& g, MsDev* ms, int wmax, int32_t k, int nbatche
                                                                  kLdsMlpFloats * sizeof(float));
     if (e != hipSuccess) return e;
     if (nb < 1) return hipErrorInvalidConfiguration;
-    nb = std::min(nb, 2);
-    ms->grid = nb * g.num_cu;
+    ms->grid = g.num_cu;
     ms->block = kMsBlock;
   }
   if (!ms->log) {
@@ -1258,42 +2135,47 @@ MsArgs ms_args(const DevGraph& g, const MsDev* ms, const int32_t* srcs_dev, cons
                int policy, float eta, uint64_t seed, int16_t* levels16, int64_t* sums, int64_t* reach, double* cc,
                int64_t* far, int probe) {
   MsArgs a{};
-  a.rp = g.rp;
-  a.col = g.col;
-  a.rp_in = g.rp_in;
-  a.col_in = g.col_in;
-  a.slice_ptr = g.slice_ptr;
-  a.slices = g.slices;
-  a.orig_id = g.orig_id;
+  a.rp = to_global(g.rp);
+  a.col = to_global(g.col);
+  a.rp_in = to_global(g.rp_in);
+  a.col_in = to_global(g.col_in);
+  a.slice_ptr = to_global(g.slice_ptr);
+  a.slices = to_global(g.slices);
+  a.orig_id = to_global(g.orig_id);
   a.n = g.n;
   a.m = g.m;
   a.nsets = g.nsets;
   a.tau = g.tau;
-  a.F = ms->F;
-  a.V = ms->V;
-  a.N = ms->N;
-  a.act = ms->act;
-  a.dirty = ms->dirty;
-  a.queue[0] = ms->queue[0];
-  a.queue[1] = ms->queue[1];
-  a.srcs = srcs_dev;
-  a.batches = batches_dev;
+  a.rows = to_global(g.ms_rows);
+  a.nrows = g.ms_nrows;
+  a.nwide = g.ms_nwide;
+  a.nlong = g.ms_nlong;
+  for (int i = 0; i < 2; ++i) a.F[i] = to_global(ms->F[i]);
+  for (int i = 0; i < 3; ++i) a.fb[i] = to_global(ms->fb[i]);
+  a.V = to_global(ms->V);
+  a.N = to_global(ms->N);
+  a.act = to_global(ms->act);
+  a.dirty = to_global(ms->dirty);
+  a.queue[0] = to_global(ms->queue[0]);
+  a.queue[1] = to_global(ms->queue[1]);
+  a.srcs = to_global(srcs_dev);
+  a.batches = to_global(batches_dev);
   a.nbatches = nplan;
-  a.levels16 = levels16;
-  a.lstage = levels16 ? ms->lstage : nullptr;
-  a.perm = ms->perm;
-  a.sums = sums;
-  a.reach = reach;
-  a.cc = cc;
-  a.far = far;
+  a.levels16 = to_global(levels16);
+  a.planes = to_global(levels16 ? ms->planes : nullptr);
+  a.perm = to_global(ms->perm);
+  a.sums = to_global(sums);
+  a.reach = to_global(reach);
+  a.cc = to_global(cc);
+  a.far = to_global(far);
   a.nvss = g.nvss;
   a.nslices = g.nslices;
-  a.mlp = g.ms_mlp;
+  a.mlp = to_global(g.ms_mlp);
   a.probe = probe;
-  a.log = ms->log;
+  a.log = to_global(ms->log);
   a.log_cap = ms->log_cap;
-  a.part = ms->part;
-  a.ctl = g.ctl;
+  a.part = to_global(ms->part);
+  a.ctl = to_global(g.ctl);
   a.policy = policy;
   a.eta = eta;
   a.seed = seed;
@@ -1310,18 +2192,18 @@ __global__ void k_ms_perm(const int32_t* __restrict__ orig_id, int64_t n, int32_
     perm[orig_id[i]] = static_cast<int32_t>(i);
 }
 
-// Staging rows for the int16 level output of batches up to 64 * wmax wide,
-// and (for a relabelled graph) the input -> internal id map they are read
-// back through.
+// Level planes for the int16 output of batches up to 64 * wmax wide (a level
+// has kMsPlanes bits), and (for a relabelled graph) the input -> internal id
+// map they are read back through.
 hipError_t ensure_levels(const DevGraph& g, MsDev* ms, int wmax, hipStream_t st) {
-  const int64_t need = g.n * 64 * static_cast<int64_t>(wmax);
+  const int64_t need = static_cast<int64_t>(kMsPlanes) * g.nsets * g.sigma * wmax;
   hipError_t e;
-  if (ms->lstage_elems < need) {
-    if (ms->lstage) (void)hipFree(ms->lstage);
-    ms->lstage = nullptr;
-    ms->lstage_elems = 0;
-    if ((e = hipMalloc(&ms->lstage, sizeof(int16_t) * static_cast<size_t>(need))) != hipSuccess) return e;
-    ms->lstage_elems = need;
+  if (ms->plane_words < need) {
+    if (ms->planes) (void)hipFree(ms->planes);
+    ms->planes = nullptr;
+    ms->plane_words = 0;
+    if ((e = hipMalloc(&ms->planes, 8 * static_cast<size_t>(need))) != hipSuccess) return e;
+    ms->plane_words = need;
   }
   if (g.orig_id && !ms->perm) {
     if ((e = hipMalloc(&ms->perm, sizeof(int32_t) * static_cast<size_t>(std::max<int64_t>(g.n, 1)))) != hipSuccess)
@@ -1430,8 +2312,8 @@ hipError_t ms_run(const DevGraph& g, MsDev* ms, const int32_t* srcs, int32_t k, 
   if ((e = hipStreamWaitEvent(gs, ms->gev[0], 0)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_ms_start, dim3(1), dim3(64), 0, gs, g.ctl);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  // every batch has at most 3 + 2 * 32768 + 1 phases (levels are int16)
-  const long long max_replays = static_cast<long long>(nplan) * (2LL * 32768 + 4) / kMsGraphKernels + 2;
+  // every batch has at most 3 + 3 * 32768 phases (levels are int16)
+  const long long max_replays = static_cast<long long>(nplan) * (3LL * 32768 + 4) / kMsGraphKernels + 2;
   for (long long r = 0; e == hipSuccess; ++r) {
     if (r >= max_replays) {
       e = hipErrorLaunchTimeOut;
@@ -1447,19 +2329,22 @@ hipError_t ms_run(const DevGraph& g, MsDev* ms, const int32_t* srcs, int32_t k, 
 }
 
 void ms_release(MsDev* ms) {
-  for (void* p : {static_cast<void*>(ms->F), static_cast<void*>(ms->V), static_cast<void*>(ms->N),
-                  static_cast<void*>(ms->act), static_cast<void*>(ms->dirty), static_cast<void*>(ms->queue[0]),
-                  static_cast<void*>(ms->queue[1])})
+  for (void* p : {static_cast<void*>(ms->F[0]), static_cast<void*>(ms->F[1]), static_cast<void*>(ms->fb[0]),
+                  static_cast<void*>(ms->fb[1]), static_cast<void*>(ms->fb[2]), static_cast<void*>(ms->V),
+                  static_cast<void*>(ms->N), static_cast<void*>(ms->act), static_cast<void*>(ms->dirty),
+                  static_cast<void*>(ms->queue[0]), static_cast<void*>(ms->queue[1])})
     if (p) (void)hipFree(p);
-  ms->F = ms->V = ms->N = ms->act = nullptr;
+  for (auto& f : ms->F) f = nullptr;
+  for (auto& b : ms->fb) b = nullptr;
+  ms->V = ms->N = ms->act = nullptr;
   ms->dirty = nullptr;
   ms->queue[0] = ms->queue[1] = nullptr;
   ms->wmax = 0;
   ms->nhat = 0;
-  if (ms->lstage) (void)hipFree(ms->lstage);
+  if (ms->planes) (void)hipFree(ms->planes);
   if (ms->perm) (void)hipFree(ms->perm);
-  ms->lstage = nullptr;
-  ms->lstage_elems = 0;
+  ms->planes = nullptr;
+  ms->plane_words = 0;
   ms->perm = nullptr;
 }
 
@@ -1529,7 +2414,7 @@ hipError_t noalloc_scratch(int device, int32_t** out) {
 }  // namespace
 
 bool ms_ready(const DevGraph& g, const MsDev* ms, int W) {
-  return ms->wmax >= W && ms->nhat == g.nsets * g.sigma && ms->F && ms->V && ms->N && ms->act && ms->dirty &&
+  return ms->wmax >= W && ms->nhat == g.nsets * g.sigma && ms->F[0] && ms->F[1] && ms->fb[0] && ms->fb[1] && ms->fb[2] && ms->V && ms->N && ms->act && ms->dirty &&
          ms->queue[0] && ms->queue[1] && ms->grid > 0 && ms->log && ms->part && ms->part_blocks >= ms->grid;
 }
 
@@ -1562,9 +2447,9 @@ hipError_t ms_run_noalloc(const DevGraph& g, MsDev* ms, const int32_t* srcs, con
   if ((e = hipMemcpyAsync(dplan, plan, sizeof(MsBatch) * nplan, hipMemcpyHostToDevice, st)) != hipSuccess) return e;
   if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
   MsArgs a = ms_args(g, ms, dsrcs, dplan, nplan, policy, eta, seed, levels16, nullptr, nullptr, nullptr, nullptr, 0);
-  // no staging buffer here (the entry point allocates nothing): Stage 2
-  // writes the caller's rows directly
-  a.lstage = nullptr;
+  // no level planes here (the entry point allocates nothing): the caller's
+  // rows are written directly
+  a.planes = nullptr;
   const unsigned shmem = policy == BLEST_POLICY_LEARNED ? kLdsMlpFloats * sizeof(float) : 0u;
   void* args[] = {static_cast<void*>(&a)};
   return hipLaunchCooperativeKernel(ms_kernel(g), dim3(ms->grid), dim3(ms->block), args, shmem, st);
