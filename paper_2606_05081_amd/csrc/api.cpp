@@ -126,7 +126,7 @@ blest_status bfs_common(blest_graph* g, int32_t src, int32_t* levels_dev, void* 
   hipStream_t st = static_cast<hipStream_t>(stream);
   CK(hipSetDevice(g->d.device));
   blest::BfsArgs a = blest::bfs_args(g->d);
-  a.levels = levels_dev;
+  a.levels = blest::to_global(levels_dev);
   a.src = g->perm.empty() ? src : g->perm[src];
   a.policy = g->opts.policy;
   a.eta = g->opts.eta;

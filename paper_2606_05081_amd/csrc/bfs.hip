@@ -28,8 +28,8 @@ namespace blest {
 
 // Frontier buffer of a level parity (level l reads buffer l & 1; its Stage 2
 // writes the other one, so an engine never reads words being rewritten).
-__device__ __forceinline__ void* front_buf(const BfsArgs& a, int sel) {
-  return static_cast<char*>(a.front) + (sel ? a.fstride : 0LL);
+__device__ __forceinline__ gptr<void> front_buf(args_ref<BfsArgs> a, int sel) {
+  return (gptr<char>)a.front + (sel ? a.fstride : 0LL);
 }
 
 // Per-workgroup Stage 2 partial counters: frontier, queued slices, frontier
@@ -56,54 +56,57 @@ __device__ __forceinline__ void load_set_rp(gptr<const int32_t> rp, long long s,
 
 // ------------------------------------------------------------- decisions
 
+// (every count is at most n, m or the number of slices, all below 2^31; ten
+// 32-bit words are passed to a function in registers)
 struct LevelView {
-  long long frontier, queue, qslices, fedges, deg32, deg1024, light, heavy, cumv, cume;
+  uint32_t frontier, queue, qslices, fedges, deg32, deg1024, light, heavy, cumv, cume;
 };
 
-__device__ __forceinline__ LevelView read_level(const Ctl* ctl, int slot) {
-  const gptr<const unsigned long long> acc = to_global(&ctl->acc[slot][0][0]);
+__device__ __forceinline__ uint32_t u32_uniform(unsigned long long v) {
+  return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+}
+
+__device__ __forceinline__ LevelView read_level(gptr<const Ctl> ctl, int slot) {
+  const gptr<const unsigned long long> acc = &ctl->acc[slot][0][0];
   LevelView v;
-  v.frontier = static_cast<long long>(acc[F_FRONTIER * kPad]);
-  v.queue = static_cast<long long>(acc[F_QUEUE * kPad]);
-  v.qslices = static_cast<long long>(acc[F_QSLICES * kPad]);
-  v.fedges = static_cast<long long>(acc[F_FEDGES * kPad]);
-  v.deg32 = static_cast<long long>(acc[F_DEG32 * kPad]);
-  v.deg1024 = static_cast<long long>(acc[F_DEG1024 * kPad]);
-  v.light = static_cast<long long>(acc[F_LIGHT * kPad]);
-  v.heavy = static_cast<long long>(acc[F_HEAVY * kPad]);
-  v.cumv = static_cast<long long>(acc[F_CUMV * kPad]);
-  v.cume = static_cast<long long>(acc[F_CUME * kPad]);
+  v.frontier = u32_uniform(acc[F_FRONTIER * kPad]);
+  v.queue = u32_uniform(acc[F_QUEUE * kPad]);
+  v.qslices = u32_uniform(acc[F_QSLICES * kPad]);
+  v.fedges = u32_uniform(acc[F_FEDGES * kPad]);
+  v.deg32 = u32_uniform(acc[F_DEG32 * kPad]);
+  v.deg1024 = u32_uniform(acc[F_DEG1024 * kPad]);
+  v.light = u32_uniform(acc[F_LIGHT * kPad]);
+  v.heavy = u32_uniform(acc[F_HEAVY * kPad]);
+  v.cumv = u32_uniform(acc[F_CUMV * kPad]);
+  v.cume = u32_uniform(acc[F_CUME * kPad]);
   return v;
 }
 
 // Same, with agent-scope loads (used inside a single-workgroup episode, where
 // the counters were just updated by device atomics without a barrier).
-__device__ __forceinline__ LevelView read_level_atomic(const Ctl* ctl, int slot) {
-  const gptr<const unsigned long long> acc = to_global(&ctl->acc[slot][0][0]);
+__device__ __forceinline__ LevelView read_level_atomic(gptr<const Ctl> ctl, int slot) {
+  const gptr<const unsigned long long> acc = &ctl->acc[slot][0][0];
   LevelView v;
-  v.frontier = static_cast<long long>(ld_relaxed_u64(acc + F_FRONTIER * kPad));
-  v.queue = static_cast<long long>(ld_relaxed_u64(acc + F_QUEUE * kPad));
-  v.qslices = static_cast<long long>(ld_relaxed_u64(acc + F_QSLICES * kPad));
-  v.fedges = static_cast<long long>(ld_relaxed_u64(acc + F_FEDGES * kPad));
-  v.deg32 = static_cast<long long>(ld_relaxed_u64(acc + F_DEG32 * kPad));
-  v.deg1024 = static_cast<long long>(ld_relaxed_u64(acc + F_DEG1024 * kPad));
-  v.light = static_cast<long long>(ld_relaxed_u64(acc + F_LIGHT * kPad));
-  v.heavy = static_cast<long long>(ld_relaxed_u64(acc + F_HEAVY * kPad));
-  v.cumv = static_cast<long long>(ld_relaxed_u64(acc + F_CUMV * kPad));
-  v.cume = static_cast<long long>(ld_relaxed_u64(acc + F_CUME * kPad));
+  v.frontier = u32_uniform(ld_relaxed_u64(acc + F_FRONTIER * kPad));
+  v.queue = u32_uniform(ld_relaxed_u64(acc + F_QUEUE * kPad));
+  v.qslices = u32_uniform(ld_relaxed_u64(acc + F_QSLICES * kPad));
+  v.fedges = u32_uniform(ld_relaxed_u64(acc + F_FEDGES * kPad));
+  v.deg32 = u32_uniform(ld_relaxed_u64(acc + F_DEG32 * kPad));
+  v.deg1024 = u32_uniform(ld_relaxed_u64(acc + F_DEG1024 * kPad));
+  v.light = u32_uniform(ld_relaxed_u64(acc + F_LIGHT * kPad));
+  v.heavy = u32_uniform(ld_relaxed_u64(acc + F_HEAVY * kPad));
+  v.cumv = u32_uniform(ld_relaxed_u64(acc + F_CUMV * kPad));
+  v.cume = u32_uniform(ld_relaxed_u64(acc + F_CUME * kPad));
   return v;
 }
 
 // The 12 switch features of a level (network inputs before standardising).
-__device__ __forceinline__ void level_features(float (&f)[kMaxSwitchFeatures], const LevelView& v, const BfsArgs& a,
-                                               int level, long long prev_frontier) {
-  (void)level;
+__device__ __forceinline__ void level_features(float (&f)[kMaxSwitchFeatures], const LevelView& v, args_ref<BfsArgs> a) {
   const long long unv = a.n - v.cumv, unv_e = a.m - v.cume;
   const float lf = log2f(1.0f + static_cast<float>(v.frontier));
   const float lqs = log2f(1.0f + static_cast<float>(v.qslices));
   const float ln = log2f(static_cast<float>(a.n));
   const float lm = log2f(1.0f + static_cast<float>(a.m));
-  (void)lm;
   f[0] = lf;
   f[1] = lqs;
   f[2] = lf - ln;
@@ -117,7 +120,6 @@ __device__ __forceinline__ void level_features(float (&f)[kMaxSwitchFeatures], c
   // Reserved (zero). The frontier degree histogram and the growth ratio were
   // inputs once; on R-MAT + grid training data they let the network learn
   // family shortcuts that failed on Erdos-Renyi graphs.
-  (void)prev_frontier;
   f[9] = 0.0f;
   f[10] = 0.0f;
   f[11] = 0.0f;
@@ -136,11 +138,11 @@ __device__ __forceinline__ unsigned long long mix64(unsigned long long z) {
   return z ^ (z >> 31);
 }
 
-// Uniform engine choice for the step out of `level`. Contains __syncthreads().
-__device__ __forceinline__ int choose_engine_inl(const BfsArgs& a, const LevelView& v,
-                                                 const float (&feat)[kMaxSwitchFeatures], int level,
-                                                 const float* s_mlp, int* fallback) {
-  __shared__ int s_choice;
+// Engine choice for the step out of `level`, evaluated by each wave on its
+// own (every input is uniform over the grid).
+__device__ __forceinline__ int choose_engine(args_ref<BfsArgs> a, const LevelView& v,
+                                             const float (&feat)[kMaxSwitchFeatures], int level, lptr<const float> s_mlp,
+                                             bool learned, int* fallback) {
   const long long unvisited = a.n - v.cumv;
   *fallback = 0;
   switch (a.policy) {
@@ -153,14 +155,8 @@ __device__ __forceinline__ int choose_engine_inl(const BfsArgs& a, const LevelVi
     case BLEST_POLICY_RANDOM:
       return static_cast<int>(mix64(a.seed + 0x9E3779B97F4A7C15ULL * static_cast<unsigned long long>(level + 1)) % 3ULL);
     case BLEST_POLICY_LEARNED:
-      if (s_mlp != nullptr) {
-        if (threadIdx.x < 64) {
-          int c = mlp_choose_wave(to_lds(s_mlp), feat);
-          if (threadIdx.x == 0) s_choice = c;
-        }
-        __syncthreads();
-        int c = s_choice;
-        __syncthreads();
+      if (learned) {
+        const int c = mlp_choose_wave(s_mlp, feat);
         if (c >= 0) return c;
       }
       *fallback = 1;
@@ -170,11 +166,44 @@ __device__ __forceinline__ int choose_engine_inl(const BfsArgs& a, const LevelVi
   }
 }
 
-// The same as an out-of-line call (the lazy kernel, where inlining it would
-// only add to the register pressure).
-__device__ int choose_engine(const BfsArgs& a, const LevelView& v, const float (&feat)[kMaxSwitchFeatures],
-                             int level, const float* s_mlp, int* fallback) {
-  return choose_engine_inl(a, v, feat, level, s_mlp, fallback);
+__device__ __forceinline__ bool use_panel(args_ref<BfsArgs> a, const LevelView& v);
+
+// Chooses the engine of the step out of `level` and (workgroup 0, one lane)
+// writes the level's record, all but its times. EAGER: a push choice runs the
+// BVSS engine, and never over the panel copy. A function of its own, so that
+// its features and network stay out of the kernel's registers.
+template <bool EAGER>
+__device__ __attribute__((noinline)) int decide_level(args_ref<BfsArgs> a_, LevelView v, int level,
+                                                      lptr<const float> s_mlp, bool learned) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  level = uniform(level);
+  float feat[kMaxSwitchFeatures];
+  level_features(feat, v, a);
+  int fallback = 0;
+  int engine = choose_engine(a, v, feat, level, s_mlp, learned, &fallback);
+  if (EAGER && engine == BLEST_ENGINE_PUSH) engine = BLEST_ENGINE_BVSS;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && level < a.log_cap) {
+    const gptr<LevelRec> r = a.log + level;
+    r->frontier = v.frontier;
+    r->queue = v.queue;
+    r->qslices = v.qslices;
+    r->fedges = v.fedges;
+    r->unvisited = a.n - v.cumv;
+    r->unvisited_edges = a.m - v.cume;
+    r->deg32 = v.deg32;
+    r->deg1024 = v.deg1024;
+    r->engine = a.probe ? -1 : engine;
+    r->fallback = fallback;
+    r->panel = !EAGER && engine == BLEST_ENGINE_BVSS && use_panel(a, v);
+    r->t_mid = 0;
+    r->t_end = 0;
+    r->t_count = 0;
+    r->t_engine[0] = r->t_engine[1] = r->t_engine[2] = 0;
+    r->work = 0;
+#pragma unroll
+    for (int k = 0; k < kMaxSwitchFeatures; ++k) r->feat[k] = feat[k];
+  }
+  return uniform(engine);
 }
 
 // ------------------------------------------------------------ Stage 1
@@ -186,7 +215,7 @@ constexpr long long kSingleMaxMarks = 4096;    // keeps the hash set at most hal
 // hs[kSingleHash].
 constexpr int kSingleLds = kSingleHash + 1 + kSingleMaxMarks;
 
-__device__ __forceinline__ void record_set(lptr<int> hs, long long s, Ctl* ctl) {
+__device__ __forceinline__ void record_set(lptr<int> hs, long long s, gptr<Ctl> ctl) {
   uint32_t h = (static_cast<uint32_t>(s) * 2654435761u) >> (32 - 13);
   for (int probe = 0; probe < kSingleHash; ++probe) {
     int old = -1;
@@ -210,15 +239,20 @@ __device__ __forceinline__ void record_set(lptr<int> hs, long long s, Ctl* ctl) 
 // testing any, so each lane keeps G * K independent loads in flight
 // (K = tau / 64 slices per lane per VSS).
 template <int SIGMA, class SliceT, int K, bool REC>
-__device__ long long engine_bvss_k(const BfsArgs& a, const uint4* __restrict__ q, long long qlen, long long gwave,
-                                   long long nwaves, lptr<int> hs) {
+__device__ __attribute__((noinline)) long long engine_bvss_k(args_ref<BfsArgs> a_, int sel, long long qlen,
+                                                             long long gwave, long long nwaves, lptr<int> hs) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  sel = uniform(sel);
+  qlen = uniform(qlen);
+  gwave = uniform(gwave);
+  nwaves = uniform(nwaves);
   long long work = 0;
   using M = typename MaskOf<SIGMA>::T;
   constexpr int G = 4;
-  const gptr<const uint4> qg = to_global(q);
-  gptr<const SliceT> __restrict__ sl = to_global(static_cast<const SliceT*>(a.slices));
-  gptr<const M> __restrict__ vis = to_global(static_cast<const M*>(a.vis));
-  gptr<uint8_t> __restrict__ mark = to_global(a.mark);
+  const gptr<const uint4> qg = a.queue[sel];
+  gptr<const SliceT> __restrict__ sl = (gptr<const SliceT>)a.slices;
+  gptr<const M> __restrict__ vis = (gptr<const M>)a.vis;
+  gptr<uint8_t> __restrict__ mark = a.mark;
   const uint32_t lane = static_cast<uint32_t>(lane_id());
   const bool pre = a.prefilter != 0;
   for (long long base = gwave * G; base < qlen; base += nwaves * G) {
@@ -276,17 +310,17 @@ __device__ long long engine_bvss_k(const BfsArgs& a, const uint4* __restrict__ q
 }
 
 template <int SIGMA, class SliceT, bool REC>
-__device__ long long engine_bvss(const BfsArgs& a, const uint4* __restrict__ q, long long qlen, long long gwave,
-                                 long long nwaves, lptr<int> hs) {
+__device__ __forceinline__ long long engine_bvss(args_ref<BfsArgs> a, int sel, long long qlen, long long gwave,
+                                                 long long nwaves, lptr<int> hs) {
   switch (a.tau) {
     case 64:
-      return engine_bvss_k<SIGMA, SliceT, 1, REC>(a, q, qlen, gwave, nwaves, hs);
+      return engine_bvss_k<SIGMA, SliceT, 1, REC>(a, sel, qlen, gwave, nwaves, hs);
     case 128:
-      return engine_bvss_k<SIGMA, SliceT, 2, REC>(a, q, qlen, gwave, nwaves, hs);
+      return engine_bvss_k<SIGMA, SliceT, 2, REC>(a, sel, qlen, gwave, nwaves, hs);
     case 192:
-      return engine_bvss_k<SIGMA, SliceT, 3, REC>(a, q, qlen, gwave, nwaves, hs);
+      return engine_bvss_k<SIGMA, SliceT, 3, REC>(a, sel, qlen, gwave, nwaves, hs);
     default:
-      return engine_bvss_k<SIGMA, SliceT, 4, REC>(a, q, qlen, gwave, nwaves, hs);
+      return engine_bvss_k<SIGMA, SliceT, 4, REC>(a, sel, qlen, gwave, nwaves, hs);
   }
 }
 
@@ -316,7 +350,7 @@ constexpr int kPanelMaxBytes = 1 << 15;  // LDS byte map of one panel (rb <= 15)
 static_assert(kSingleHash * 4 >= kPanelMaxBytes, "the panel byte map lives in the hash-set slots");
 constexpr long long kPanelDenom = 8;  // dense: queued slices >= panel slots / 8
 
-__device__ __forceinline__ bool use_panel(const BfsArgs& a, const LevelView& v) {
+__device__ __forceinline__ bool use_panel(args_ref<BfsArgs> a, const LevelView& v) {
   if (a.npanels <= 0) return false;
   if (a.panel_mode == 2) return true;
   return v.qslices > kSingleMaxMarks && kPanelDenom * v.qslices >= a.panel_slots;
@@ -408,12 +442,12 @@ __device__ __forceinline__ void panel_test_batch(const PanelBatch& B, uint32_t d
 // vertices are x: level writes and the counters of finalize_count. The 33
 // row pointers and 5 slice pointers of the group are loaded at once (rp and
 // slice_ptr are padded on the device so these loads stay in bounds).
-__device__ __forceinline__ void panel_count_group(const BfsArgs& a, long long g, uint32_t x, int new_level,
+__device__ __forceinline__ void panel_count_group(args_ref<BfsArgs> a, long long g, uint32_t x, int new_level,
                                                   long long (&st)[kParts]) {
-  const gptr<const int32_t> rp = to_global(a.rp);
-  const gptr<const uint32_t> sp = to_global(a.slice_ptr);
-  const gptr<int32_t> levels = to_global(a.levels);
-  const gptr<const int32_t> orig_id = to_global(a.orig_id);
+  const gptr<const int32_t> rp = a.rp;
+  const gptr<const uint32_t> sp = a.slice_ptr;
+  const gptr<int32_t> levels = a.levels;
+  const gptr<const int32_t> orig_id = a.orig_id;
   const uint32_t tau = static_cast<uint32_t>(a.tau);
   const gptr<const int4> r4 = (gptr<const int4>)(rp + 32 * g);
   int r[33];
@@ -454,8 +488,11 @@ __device__ __forceinline__ void panel_count_group(const BfsArgs& a, long long g,
 }
 
 template <int BLOCK>
-__device__ __attribute__((noinline)) long long engine_panel(const BfsArgs& a, lptr<uint32_t> pm, int sel,
+__device__ __attribute__((noinline)) long long engine_panel(args_ref<BfsArgs> a_, lptr<uint32_t> pm, int sel,
                                                             int new_level) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  sel = uniform(sel);
+  new_level = uniform(new_level);
   constexpr int U = kPanelUnroll;
   constexpr uint32_t NW = BLOCK / 64;
   constexpr uint32_t STEP = NW * U;
@@ -467,13 +504,13 @@ __device__ __attribute__((noinline)) long long engine_panel(const BfsArgs& a, lp
   const uint32_t dmask = (1u << (24 - rb)) - 1u;
   const int rshift = 32 - rb;
   PanelPtrs pp;
-  pp.words = to_global(reinterpret_cast<const uint4*>(a.pwords));
-  pp.front8 = to_global(static_cast<const uint2*>(front_buf(a, sel)));
-  pp.base = to_const_uniform(static_cast<const uint32_t*>(a.pbase));
-  const gptr<const uint32_t> pptr = to_global(static_cast<const uint32_t*>(a.pptr));
-  const gptr<uint32_t> vis32 = to_global(static_cast<uint32_t*>(a.vis));
-  const gptr<uint32_t> next32 = to_global(static_cast<uint32_t*>(front_buf(a, sel ^ 1)));
-  const gptr<uint4> mark16 = to_global(reinterpret_cast<uint4*>(a.mark));
+  pp.words = (gptr<const uint4>)a.pwords;
+  pp.front8 = (gptr<const uint2>)front_buf(a, sel);
+  pp.base = (cptr<const uint32_t>)a.pbase;
+  const gptr<const uint32_t> pptr = (gptr<const uint32_t>)a.pptr;
+  const gptr<uint32_t> vis32 = (gptr<uint32_t>)a.vis;
+  const gptr<uint32_t> next32 = (gptr<uint32_t>)front_buf(a, sel ^ 1);
+  const gptr<uint4> mark16 = (gptr<uint4>)a.mark;
   const bool fused = new_level >= 0;
   // fused: the workgroup's Stage 2 counters, summed per panel (kept out of
   // registers during the chunk loop)
@@ -577,7 +614,7 @@ __device__ __attribute__((noinline)) long long engine_panel(const BfsArgs& a, lp
     // every workgroup stores its partials (zero if it owns no panel)
     __syncthreads();
     if (threadIdx.x < kParts)
-      to_global(a.part)[static_cast<long long>(blockIdx.x) * kParts + threadIdx.x] =
+      a.part[static_cast<long long>(blockIdx.x) * kParts + threadIdx.x] =
           static_cast<long long>(s_part[threadIdx.x]);
   }
   return lane == 0 ? work : 0;
@@ -585,16 +622,23 @@ __device__ __attribute__((noinline)) long long engine_panel(const BfsArgs& a, lp
 
 // E1: push over the CSR rows of the frontier vertices.
 template <int SIGMA, bool REC>
-__device__ __attribute__((noinline)) long long engine_push(const BfsArgs& a, int sel, long long nlight, long long nheavy, long long gtid,
-                                 long long nthreads, long long gwave, long long nwaves, lptr<int> hs) {
+__device__ __attribute__((noinline)) long long engine_push(args_ref<BfsArgs> a_, int sel, long long nlight,
+                                                           long long nheavy, long long gwave, long long nwaves,
+                                                           lptr<int> hs) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  sel = uniform(sel);
+  nlight = uniform(nlight);
+  nheavy = uniform(nheavy);
+  gwave = uniform(gwave);
+  nwaves = uniform(nwaves);
   long long work = 0;
   using M = typename MaskOf<SIGMA>::T;
-  gptr<const M> __restrict__ vis = to_global(static_cast<const M*>(a.vis));
-  gptr<const int32_t> __restrict__ rp = to_global(a.rp);
-  gptr<const int32_t> __restrict__ col = to_global(a.col);
-  gptr<uint8_t> __restrict__ mark = to_global(a.mark);
+  gptr<const M> __restrict__ vis = (gptr<const M>)a.vis;
+  gptr<const int32_t> __restrict__ rp = a.rp;
+  gptr<const int32_t> __restrict__ col = a.col;
+  gptr<uint8_t> __restrict__ mark = a.mark;
   const int lane = lane_id();
-  gptr<const unsigned long long> __restrict__ heavy = to_global(a.fheavy[sel]);
+  gptr<const unsigned long long> __restrict__ heavy = a.fheavy[sel];
   for (long long i = gwave; i < nheavy; i += nwaves) {
     const unsigned long long e = heavy[i];
     const int u = static_cast<int>(e >> 32);
@@ -613,9 +657,7 @@ __device__ __attribute__((noinline)) long long engine_push(const BfsArgs& a, int
   // their rows, 64 edges at a time; each lane finds the vertex owning its edge
   // by a binary search over the wave's prefix sums of the degrees, so every
   // lane has an edge (not a vertex's serial chain of loads) in flight.
-  gptr<const int32_t> __restrict__ light = to_global(a.flight[sel]);
-  (void)gtid;
-  (void)nthreads;
+  gptr<const int32_t> __restrict__ light = a.flight[sel];
   for (long long base = gwave * 64; base < nlight; base += nwaves * 64) {
     const long long i = base + lane;
     int p0 = 0, d = 0;
@@ -655,22 +697,25 @@ __device__ __attribute__((noinline)) long long engine_push(const BfsArgs& a, int
 constexpr int kPullLight = 32;
 
 template <int SIGMA>
-__device__ __attribute__((noinline)) long long engine_pull(const BfsArgs& a, int sel, long long gtid,
-                                                           long long nthreads) {
+__device__ __attribute__((noinline)) long long engine_pull(args_ref<BfsArgs> a_, int sel, long long gw,
+                                                           long long nw) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  sel = uniform(sel);
+  gw = uniform(gw);
+  nw = uniform(nw);
   long long work = 0;
   using M = typename MaskOf<SIGMA>::T;
-  gptr<const M> __restrict__ vis = to_global(static_cast<const M*>(a.vis));
-  gptr<const M> __restrict__ front = to_global(static_cast<const M*>(front_buf(a, sel)));
-  gptr<const M> __restrict__ degm = to_global(static_cast<const M*>(a.degmask_in));
-  gptr<const int32_t> __restrict__ rp = to_global(a.rp_in);
-  gptr<const int32_t> __restrict__ col = to_global(a.col_in);
-  gptr<uint8_t> __restrict__ mark = to_global(a.mark);
+  gptr<const M> __restrict__ vis = (gptr<const M>)a.vis;
+  gptr<const M> __restrict__ front = (gptr<const M>)front_buf(a, sel);
+  gptr<const M> __restrict__ degm = (gptr<const M>)a.degmask_in;
+  gptr<const int32_t> __restrict__ rp = a.rp_in;
+  gptr<const int32_t> __restrict__ col = a.col_in;
+  gptr<uint8_t> __restrict__ mark = a.mark;
   const long long nv = a.nsets * SIGMA;
   const int lane = lane_id();
   // 64-vertex chunks: round k gives the waves chunks k*nw .. k*nw + nw - 1,
   // rotated by k, so chunks with heavy rows that recur with a fixed stride
   // (a relabelling that puts each window's hubs first) spread over all waves
-  const long long nw = nthreads / 64, gw = (gtid - lane) / 64;
   const long long nchunks = (nv + 63) / 64;
   for (long long k = 0; k * nw < nchunks; ++k) {
     const long long chunk = k * nw + (gw + k) % nw;
@@ -733,27 +778,26 @@ __device__ __attribute__((noinline)) long long engine_pull(const BfsArgs& a, int
 
 // Runs one engine and adds the adjacency entries it read to the level's
 // F_WORK counter (one atomic per block).
-// hs != nullptr: single-workgroup level, marked slice sets are recorded in hs
-// (only the BVSS and push engines run there). pm: LDS scratch for the
-// panel-blocked BVSS step (nullptr: that step is not available).
+// SINGLE: single-workgroup level, marked slice sets are recorded in hs (only
+// the BVSS and push engines run there). pm: LDS scratch for the panel-blocked
+// BVSS step, which only grid levels take. (Neither pointer is tested: LDS
+// offset 0 is a valid address that compares equal to a null pointer.)
 // fuse_level >= 0: a panel step also does Stage 2 for that new level.
-template <int SIGMA, class SliceT, int BLOCK>
-__device__ __forceinline__ void run_engine(const BfsArgs& a, int engine, int sel, int slot, const LevelView& v,
-                                           long long gtid, long long nthreads, long long gwave, long long nwaves,
-                                           lptr<int> hs, lptr<uint32_t> pm, int fuse_level = -1) {
+template <int SIGMA, class SliceT, int BLOCK, bool SINGLE>
+__device__ __forceinline__ void run_engine(args_ref<BfsArgs> a, int engine, int sel, int slot, const LevelView& v,
+                                           long long gwave, long long nwaves, lptr<int> hs, lptr<uint32_t> pm,
+                                           int fuse_level = -1) {
   __shared__ long long lds_work[BLOCK / 64];
   long long work[1];
   constexpr bool kPanelFmt = SIGMA == 8 && sizeof(SliceT) == 4;
-  if (kPanelFmt && engine == BLEST_ENGINE_BVSS && !hs && pm && use_panel(a, v))
+  if (kPanelFmt && engine == BLEST_ENGINE_BVSS && !SINGLE && use_panel(a, v))
     work[0] = engine_panel<BLOCK>(a, pm, sel, fuse_level);
   else if (engine == BLEST_ENGINE_BVSS)
-    work[0] = hs ? engine_bvss<SIGMA, SliceT, true>(a, a.queue[sel], v.queue, gwave, nwaves, hs)
-                 : engine_bvss<SIGMA, SliceT, false>(a, a.queue[sel], v.queue, gwave, nwaves, nullptr);
+    work[0] = engine_bvss<SIGMA, SliceT, SINGLE>(a, sel, v.queue, gwave, nwaves, hs);
   else if (engine == BLEST_ENGINE_PUSH)
-    work[0] = hs ? engine_push<SIGMA, true>(a, sel, v.light, v.heavy, gtid, nthreads, gwave, nwaves, hs)
-                 : engine_push<SIGMA, false>(a, sel, v.light, v.heavy, gtid, nthreads, gwave, nwaves, nullptr);
+    work[0] = engine_push<SIGMA, SINGLE>(a, sel, v.light, v.heavy, gwave, nwaves, hs);
   else
-    work[0] = engine_pull<SIGMA>(a, sel, gtid, nthreads);
+    work[0] = engine_pull<SIGMA>(a, sel, gwave, nwaves);
   if (a.count_work || a.probe) {
     block_sum64<BLOCK, 1>(work, lds_work);
     if (threadIdx.x == 0 && work[0]) add_u64(&a.ctl->acc[slot][F_WORK][0], static_cast<unsigned long long>(work[0]));
@@ -790,25 +834,25 @@ enum FinMode : int { FIN_ATOMIC = 0, FIN_LOCAL = 1, FIN_COUNT = 2, FIN_EMIT = 3 
 constexpr int kFinSpt = 4;
 
 template <int SIGMA, int BLOCK, int MODE, class SetAt>
-__device__ void finalize_windows(const BfsArgs& a, int new_level, gptr<unsigned long long> acc, int sel_out,
+__device__ __forceinline__ void finalize_windows(args_ref<BfsArgs> a, int new_level, gptr<unsigned long long> acc, int sel_out,
                                  long long win0, long long nwin, long long wstep, SetAt set_at, long long (&st)[8],
-                                 unsigned long long* local, bool want_push = true, bool want_queue = true) {
+                                 lptr<unsigned long long> local, bool want_push = true, bool want_queue = true) {
   using M = typename MaskOf<SIGMA>::T;
   constexpr int SPT = kFinSpt;
   constexpr bool UPDATE = MODE != FIN_EMIT;
   __shared__ int lds32[3 * (BLOCK / 64)];
   __shared__ unsigned long long bases[3];
-  gptr<M> __restrict__ vis = to_global(static_cast<M*>(a.vis));
-  gptr<M> __restrict__ front = to_global(static_cast<M*>(front_buf(a, sel_out)));
-  gptr<uint8_t> __restrict__ mark = to_global(a.mark);
-  gptr<const int32_t> __restrict__ rp = to_global(a.rp);
-  gptr<const uint32_t> __restrict__ sp = to_global(a.slice_ptr);
+  gptr<M> __restrict__ vis = (gptr<M>)a.vis;
+  gptr<M> __restrict__ front = (gptr<M>)front_buf(a, sel_out);
+  gptr<uint8_t> __restrict__ mark = a.mark;
+  gptr<const int32_t> __restrict__ rp = a.rp;
+  gptr<const uint32_t> __restrict__ sp = a.slice_ptr;
   const uint32_t tau = static_cast<uint32_t>(a.tau);
-  gptr<int32_t> __restrict__ light = to_global(a.flight[sel_out]);
-  gptr<unsigned long long> __restrict__ heavy = to_global(a.fheavy[sel_out]);
-  gptr<uint4> __restrict__ queue = to_global(a.queue[sel_out]);
-  gptr<int32_t> __restrict__ levels = to_global(a.levels);
-  const gptr<const int32_t> __restrict__ orig_id = to_global(a.orig_id);
+  gptr<int32_t> __restrict__ light = a.flight[sel_out];
+  gptr<unsigned long long> __restrict__ heavy = a.fheavy[sel_out];
+  gptr<uint4> __restrict__ queue = a.queue[sel_out];
+  gptr<int32_t> __restrict__ levels = a.levels;
+  const gptr<const int32_t> __restrict__ orig_id = a.orig_id;
   const int lane = lane_id();
   const bool need_rp = UPDATE || want_push;
   const bool need_sp = UPDATE || want_queue;
@@ -1054,7 +1098,7 @@ __device__ void finalize_windows(const BfsArgs& a, int new_level, gptr<unsigned 
 // Adds a block's Stage 2 statistics to the level slot (block 0 also carries
 // the cumulative counts of the previous level).
 template <int BLOCK>
-__device__ void finalize_stats(gptr<unsigned long long> acc, const long long (&st8)[8], long long cumv_in,
+__device__ __forceinline__ void finalize_stats(gptr<unsigned long long> acc, const long long (&st8)[8], long long cumv_in,
                                long long cume_in) {
   __shared__ long long lds64[5 * (BLOCK / 64)];
   long long st[5] = {st8[0], st8[1], st8[2], st8[3], st8[4]};
@@ -1080,10 +1124,10 @@ __device__ void finalize_stats(gptr<unsigned long long> acc, const long long (&s
 
 // Stage 2 of the whole grid: every slice set, windows spread over the blocks.
 template <int SIGMA, int BLOCK>
-__device__ void finalize(const BfsArgs& a, int new_level, int slot_out, int sel_out, long long cumv_in,
+__device__ __forceinline__ void finalize(args_ref<BfsArgs> a, int new_level, int slot_out, int sel_out, long long cumv_in,
                          long long cume_in, unsigned nblocks) {
   constexpr long long WIN = static_cast<long long>(BLOCK) * kFinSpt;
-  const gptr<unsigned long long> acc = to_global(&a.ctl->acc[slot_out][0][0]);
+  const gptr<unsigned long long> acc = (&a.ctl->acc[slot_out][0][0]);
   long long st[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // frontier, queued slices, frontier edges, deg>=32, deg>=1024
   const long long nsets = a.nsets;
   const long long tid = threadIdx.x;
@@ -1113,13 +1157,18 @@ __device__ void finalize(const BfsArgs& a, int new_level, int slot_out, int sel_
 // reserved with one device atomic per window and list on the cursors of
 // slot `slot_out`); either way the level statistics go to the partials.
 template <int SIGMA, int BLOCK, int MODE>
-__device__ void finalize_count(const BfsArgs& a, int new_level, int slot_out, int sel_out) {
+__device__ __attribute__((noinline)) void finalize_count(args_ref<BfsArgs> a_, int new_level, int slot_out,
+                                                         int sel_out) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  new_level = uniform(new_level);
+  slot_out = uniform(slot_out);
+  sel_out = uniform(sel_out);
   constexpr long long WIN = static_cast<long long>(BLOCK) * kFinSpt;
   __shared__ long long lds64[kParts * (BLOCK / 64)];
   long long st[kParts] = {0, 0, 0, 0, 0, 0, 0, 0};
   const long long nsets = a.nsets;
   const long long tid = threadIdx.x;
-  finalize_windows<SIGMA, BLOCK, MODE>(a, new_level, to_global(&a.ctl->acc[slot_out][0][0]), sel_out, blockIdx.x,
+  finalize_windows<SIGMA, BLOCK, MODE>(a, new_level, (&a.ctl->acc[slot_out][0][0]), sel_out, blockIdx.x,
                                             (nsets + WIN - 1) / WIN, gridDim.x,
                                             [=](long long win, int k) -> long long {
                                               const long long s = win * WIN + k * BLOCK + tid;
@@ -1127,7 +1176,7 @@ __device__ void finalize_count(const BfsArgs& a, int new_level, int slot_out, in
                                             },
                                             st, nullptr);
   block_sum64<BLOCK, kParts>(st, lds64);
-  const gptr<long long> part = to_global(a.part);
+  const gptr<long long> part = a.part;
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int f = 0; f < kParts; ++f) part[static_cast<long long>(blockIdx.x) * kParts + f] = st[f];
@@ -1138,9 +1187,9 @@ __device__ void finalize_count(const BfsArgs& a, int new_level, int slot_out, in
 // finalize_count). before[] = light, heavy and queue entries of the
 // workgroups with a smaller index (this workgroup's list offsets).
 template <int BLOCK>
-__device__ void reduce_parts(const BfsArgs& a, long long (&tot)[kParts], long long (&before)[3]) {
+__device__ __forceinline__ void reduce_parts(args_ref<BfsArgs> a, long long (&tot)[kParts], long long (&before)[3]) {
   __shared__ long long s_tot[kParts], s_bef[3];
-  const gptr<const long long> part = to_global(static_cast<const long long*>(a.part));
+  const gptr<const long long> part = (gptr<const long long>)a.part;
   const int nb = static_cast<int>(gridDim.x);
   const int me = static_cast<int>(blockIdx.x);
   const int lane = lane_id(), w = wave_in_block();
@@ -1160,9 +1209,9 @@ __device__ void reduce_parts(const BfsArgs& a, long long (&tot)[kParts], long lo
   }
   __syncthreads();
 #pragma unroll
-  for (int f = 0; f < kParts; ++f) tot[f] = s_tot[f];
+  for (int f = 0; f < kParts; ++f) tot[f] = uniform(s_tot[f]);
 #pragma unroll
-  for (int f = 0; f < 3; ++f) before[f] = s_bef[f];
+  for (int f = 0; f < 3; ++f) before[f] = uniform(s_bef[f]);
   __syncthreads();
 }
 
@@ -1171,16 +1220,21 @@ __device__ void reduce_parts(const BfsArgs& a, long long (&tot)[kParts], long lo
 // partial counters, and hence its offsets, were computed over); otherwise
 // the window partition of finalize_count.
 template <int SIGMA, int BLOCK>
-__device__ void finalize_emit(const BfsArgs& a, int sel_out, const long long (&before)[3], bool want_push,
-                              bool want_queue, bool panel_part) {
+__device__ __attribute__((noinline)) void finalize_emit(args_ref<BfsArgs> a_, int sel_out, long long before_light,
+                                                        long long before_heavy, long long before_queue, bool want_push,
+                                                        bool want_queue, bool panel_part) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  sel_out = uniform(sel_out);
+  const long long before[3] = {before_light, before_heavy, before_queue};
   constexpr long long WIN = static_cast<long long>(BLOCK) * kFinSpt;
   __shared__ unsigned long long cursor[3];
-  if (threadIdx.x < 3) cursor[threadIdx.x] = static_cast<unsigned long long>(before[threadIdx.x]);
+  if (threadIdx.x == 0)
+    for (int f = 0; f < 3; ++f) cursor[f] = static_cast<unsigned long long>(before[f]);
   __syncthreads();
   long long st[kParts] = {0, 0, 0, 0, 0, 0, 0, 0};
   const long long nsets = a.nsets;
   const long long tid = threadIdx.x;
-  const gptr<unsigned long long> acc0 = to_global(&a.ctl->acc[0][0][0]);
+  const gptr<unsigned long long> acc0 = (&a.ctl->acc[0][0][0]);
   if (panel_part) {
     // panel p holds sets [p * sp, (p + 1) * sp); this workgroup owns panels
     // blockIdx.x, blockIdx.x + G, ...; window w is window w % wpp of its
@@ -1198,7 +1252,7 @@ __device__ void finalize_emit(const BfsArgs& a, int sel_out, const long long (&b
                                                const long long s = p * sp + (win % wpp) * WIN + k * BLOCK + tid;
                                                return s < end ? s : -1;
                                              },
-                                             st, cursor, want_push, want_queue);
+                                             st, to_lds(cursor), want_push, want_queue);
     return;
   }
   finalize_windows<SIGMA, BLOCK, FIN_EMIT>(a, 0, acc0, sel_out, blockIdx.x, (nsets + WIN - 1) / WIN, gridDim.x,
@@ -1206,7 +1260,7 @@ __device__ void finalize_emit(const BfsArgs& a, int sel_out, const long long (&b
                                              const long long s = win * WIN + k * BLOCK + tid;
                                              return s < nsets ? s : -1;
                                            },
-                                           st, cursor, want_push, want_queue);
+                                           st, to_lds(cursor), want_push, want_queue);
 }
 
 // ------------------------------------------------- single-workgroup levels
@@ -1218,7 +1272,7 @@ __device__ void finalize_emit(const BfsArgs& a, int sel_out, const long long (&b
 // other workgroups wait on a flag until workgroup 0 reaches a level that is
 // not small (or the end), then all continue together.
 
-__device__ __forceinline__ bool single_eligible(const BfsArgs& a, int engine, const LevelView& v) {
+__device__ __forceinline__ bool single_eligible(args_ref<BfsArgs> a, int engine, const LevelView& v) {
   if (!a.single_block || a.probe) return false;
   if (engine == BLEST_ENGINE_BVSS) return v.qslices <= kSingleMaxMarks && !(a.npanels > 0 && a.panel_mode == 2);
   if (engine == BLEST_ENGINE_PUSH) return v.fedges <= kSingleMaxMarks;
@@ -1229,12 +1283,17 @@ __device__ __forceinline__ bool single_eligible(const BfsArgs& a, int engine, co
 // list after the hash set); empties both. Output cursors are block-local and
 // the level's counters are stored at the end (the slot was zeroed before).
 template <int SIGMA, int BLOCK>
-__device__ void finalize_list(const BfsArgs& a, int new_level, int slot_out, int sel_out, long long cumv_in,
-                              long long cume_in, lptr<int> hs) {
+__device__ __attribute__((noinline)) void finalize_list(args_ref<BfsArgs> a_, int new_level, int slot_out,
+                                                        int sel_out, long long cumv_in, long long cume_in,
+                                                        lptr<int> hs) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  new_level = uniform(new_level);
+  slot_out = uniform(slot_out);
+  sel_out = uniform(sel_out);
   constexpr int WIN = BLOCK * kFinSpt;
   __shared__ unsigned long long local[3];
   __shared__ long long lds64[5 * (BLOCK / 64)];
-  const gptr<unsigned long long> acc = to_global(&a.ctl->acc[slot_out][0][0]);
+  const gptr<unsigned long long> acc = (&a.ctl->acc[slot_out][0][0]);
   if (threadIdx.x < 3) local[threadIdx.x] = 0ULL;
   __syncthreads();
   const int count = hs[kSingleHash];
@@ -1246,7 +1305,7 @@ __device__ void finalize_list(const BfsArgs& a, int new_level, int slot_out, int
                                          const long long i = win * WIN + k * BLOCK + tid;
                                          return i < count ? static_cast<long long>(list[i]) : -1;
                                        },
-                                       st8, local);
+                                       st8, to_lds(local));
   __syncthreads();
   for (int i = tid; i < kSingleHash + 1; i += BLOCK) hs[i] = (i == kSingleHash) ? 0 : -1;
   long long st[5] = {st8[0], st8[1], st8[2], st8[3], st8[4]};
@@ -1274,11 +1333,10 @@ template <int SIGMA>
 // seeded: the threads that clear the source's visited/frontier word and
 // level write the source's values instead (level 0), so no barrier is needed
 // between the clear and those writes.
-__device__ __forceinline__ void clear_state(const BfsArgs& a, long long gtid, long long nthreads, bool seeded = false) {
+__device__ __forceinline__ void clear_state(args_ref<BfsArgs> a, long long gtid, long long nthreads, bool seeded = false) {
   using M = typename MaskOf<SIGMA>::T;
-  M* vis = static_cast<M*>(a.vis);
-  M* front0 = static_cast<M*>(front_buf(a, 0));
-  M* front1 = static_cast<M*>(front_buf(a, 1));
+  const gptr<M> vis = (gptr<M>)a.vis;
+  const gptr<M> front0 = (gptr<M>)front_buf(a, 0), front1 = (gptr<M>)front_buf(a, 1);
   const long long src_set = seeded ? a.src / SIGMA : -1;
   const M src_bit = static_cast<M>(M(1) << (a.src % SIGMA));
   const long long src_in = seeded ? (a.orig_id ? a.orig_id[a.src] : a.src) : -1;
@@ -1296,7 +1354,7 @@ __device__ __forceinline__ void clear_state(const BfsArgs& a, long long gtid, lo
 // Level 0: frontier = {src}, queue = the VSSs of src's slice set. One block.
 template <int SIGMA>
 // lists_only: clear_state(seeded) already wrote the visited/frontier bit and level.
-__device__ __forceinline__ void seed_source(const BfsArgs& a, bool lists_only = false) {
+__device__ __forceinline__ void seed_source(args_ref<BfsArgs> a, bool lists_only = false) {
   using M = typename MaskOf<SIGMA>::T;
   const long long src = a.src;
   const long long s = src / SIGMA;
@@ -1312,12 +1370,12 @@ __device__ __forceinline__ void seed_source(const BfsArgs& a, bool lists_only = 
     a.fheavy[0][c] = (static_cast<unsigned long long>(src) << 32) | static_cast<unsigned long long>(c * kHeavyChunk);
   if (threadIdx.x == 0) {
     if (!lists_only) {
-      static_cast<M*>(a.vis)[s] = bit;
-      static_cast<M*>(front_buf(a, 0))[s] = bit;
+      ((gptr<M>)a.vis)[s] = bit;
+      ((gptr<M>)front_buf(a, 0))[s] = bit;
       a.levels[a.orig_id ? a.orig_id[src] : src] = 0;
     }
     if (nh == 0) a.flight[0][0] = static_cast<int32_t>(src);
-    unsigned long long* acc = &a.ctl->acc[0][0][0];
+    const gptr<unsigned long long> acc = &a.ctl->acc[0][0][0];
     acc[F_FRONTIER * kPad] = 1;
     acc[F_QUEUE * kPad] = nq;
     acc[F_QSLICES * kPad] = ns;
@@ -1331,29 +1389,9 @@ __device__ __forceinline__ void seed_source(const BfsArgs& a, bool lists_only = 
   }
 }
 
-__device__ __forceinline__ void log_level(const BfsArgs& a, int level, const LevelView& v, int engine, int fallback,
-                                          const float (&feat)[kMaxSwitchFeatures]) {
-  if (level >= a.log_cap) return;
-  LevelRec& r = a.log[level];
-  r.frontier = v.frontier;
-  r.queue = v.queue;
-  r.qslices = v.qslices;
-  r.fedges = v.fedges;
-  r.unvisited = a.n - v.cumv;
-  r.unvisited_edges = a.m - v.cume;
-  r.deg32 = v.deg32;
-  r.deg1024 = v.deg1024;
-  r.engine = engine;
-  r.fallback = fallback;
-  r.panel = engine == BLEST_ENGINE_BVSS && use_panel(a, v);
-  r.t_begin = dev_ticks();
-  r.t_mid = 0;
-  r.t_end = 0;
-  r.t_count = 0;
-  r.t_engine[0] = r.t_engine[1] = r.t_engine[2] = 0;
-  r.work = 0;
-#pragma unroll
-  for (int k = 0; k < kMaxSwitchFeatures; ++k) r.feat[k] = feat[k];
+// Stamps the start of a level's step (one lane of workgroup 0).
+__device__ __forceinline__ void log_begin(args_ref<BfsArgs> a, int level) {
+  if (level < a.log_cap) a.log[level].t_begin = dev_ticks();
 }
 
 // ------------------------------------------------------ persistent kernel
@@ -1365,21 +1403,55 @@ __device__ __forceinline__ void block_sync_mem() {
   __syncthreads();
 }
 
+// Waits until workgroup 0 has finished its episode (one thread per waiting
+// workgroup), bounded like a barrier; the bound restarts whenever the episode
+// finishes a level, so it measures a stall, not the length of a long run of
+// small levels. Returns the level it stopped at, or -1. The polls are a
+// microsecond apart: they go to the memory that workgroup 0 works in.
+__device__ __forceinline__ int wait_episode(args_ref<BfsArgs> a, unsigned episodes) {
+  const gptr<Ctl> ctl = a.ctl;
+  unsigned long long t0 = dev_ticks();
+  int seen = -1;
+  bool ok = true;
+  while (__hip_atomic_load(&ctl->single_gen[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < episodes) {
+    if (__hip_atomic_load(&ctl->error[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+      ok = false;
+      break;
+    }
+    const int prog = __hip_atomic_load(&ctl->single_progress[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (prog != seen) {
+      seen = prog;
+      t0 = dev_ticks();
+    }
+    if (dev_ticks() - t0 > a.timeout_ticks) {
+      __hip_atomic_store(&ctl->error[0], static_cast<int>(BLEST_ERR_TIMEOUT), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      ok = false;
+      break;
+    }
+    __builtin_amdgcn_s_sleep(16);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  return ok ? __hip_atomic_load(&ctl->single_level[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+}
+
 // Workgroup 0 runs consecutive small levels alone, starting at `level` with
 // its view, chosen engine and features. Returns the first level it did not
 // run (its slot holds that level's statistics).
 template <int SIGMA, class SliceT, int BLOCK>
-__device__ int single_episode(const BfsArgs& a, int level, int engine, int fallback, float (&feat)[kMaxSwitchFeatures],
-                              LevelView v, const float* s_mlp, lptr<int> hs) {
-  const long long gtid = threadIdx.x, nthreads = BLOCK;
+__device__ __attribute__((noinline)) int single_episode(args_ref<BfsArgs> a_, int level, int engine, LevelView v,
+                                                        lptr<const float> s_mlp, bool learned, lptr<int> hs) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  level = uniform(level);
+  engine = uniform(engine);
   const long long gwave = wave_in_block(), nwaves = BLOCK / 64;
   for (;;) {
     const int slot = level % kStatSlots, nslot = (level + 1) % kStatSlots;
-    if (threadIdx.x == 0) log_level(a, level, v, engine, fallback, feat);
+    if (threadIdx.x == 0) log_begin(a, level);
     if (threadIdx.x < kStatFields)
       __hip_atomic_store(&a.ctl->acc[nslot][threadIdx.x][0], 0ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     block_sync_mem();
-    run_engine<SIGMA, SliceT, BLOCK>(a, engine, level & 1, slot, v, gtid, nthreads, gwave, nwaves, hs, nullptr);
+    run_engine<SIGMA, SliceT, BLOCK, true>(a, engine, level & 1, slot, v, gwave, nwaves, hs, (lptr<uint32_t>)hs);
     block_sync_mem();
     if (threadIdx.x == 0 && level < a.log_cap) a.log[level].t_mid = dev_ticks();
     finalize_list<SIGMA, BLOCK>(a, level + 1, nslot, (level & 1) ^ 1, v.cumv, v.cume, hs);
@@ -1388,7 +1460,6 @@ __device__ int single_episode(const BfsArgs& a, int level, int engine, int fallb
       a.log[level].t_end = dev_ticks();
       a.log[level].work = static_cast<long long>(ld_relaxed_u64(&a.ctl->acc[slot][F_WORK][0]));
     }
-    const long long prev = v.frontier;
     ++level;
     // progress for the waiting workgroups: their time bound restarts with every level
     if (threadIdx.x == 0)
@@ -1396,14 +1467,14 @@ __device__ int single_episode(const BfsArgs& a, int level, int engine, int fallb
     v = read_level_atomic(a.ctl, level % kStatSlots);
     if (v.frontier == 0) return level;
     if (__hip_atomic_load(&a.ctl->error[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return level;
-    level_features(feat, v, a, level, prev);
-    engine = choose_engine(a, v, feat, level, s_mlp, &fallback);
+    engine = decide_level<false>(a, v, level, s_mlp, learned);
     if (!single_eligible(a, engine, v)) return level;
   }
 }
 
 template <int SIGMA, class SliceT, int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs a) {
+__global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs args) {
+  args_ref<BfsArgs> a = kernel_args(args);
   extern __shared__ float s_mlp[];
   __shared__ __attribute__((aligned(16))) int hs[kSingleLds];
   __shared__ int s_level;
@@ -1413,7 +1484,8 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs a) {
   const long long gwave = static_cast<long long>(blockIdx.x) * (BLOCK / 64) + wave_in_block();
   const long long nwaves = static_cast<long long>(nblocks) * (BLOCK / 64);
   const bool learned = a.policy == BLEST_POLICY_LEARNED && a.mlp != nullptr && a.mlp->valid;
-  if (learned) mlp_to_lds(a.mlp, s_mlp);
+  const lptr<const float> mlp = to_lds((const float*)s_mlp);
+  if (learned) mlp_to_lds((const MlpDev*)a.mlp, s_mlp);
   for (int i = threadIdx.x; i < kSingleHash + 1; i += BLOCK) hs[i] = (i == kSingleHash) ? 0 : -1;
   // state clear and level-0 seed before the registration barrier, which also
   // publishes them (one device-wide barrier at kernel start)
@@ -1424,29 +1496,23 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs a) {
     if (threadIdx.x == 0) a.ctl->single_gen[0] = 0u;
   }
   BarrierCtx bc;
-  if (!barrier_register(a.ctl, &bc, a.timeout_ticks)) return;
+  if (!barrier_register((Ctl*)a.ctl, &bc, a.timeout_ticks)) return;
   unsigned episodes = 0;
   int level = 0;
   constexpr bool kPanelFmt = SIGMA == 8 && sizeof(SliceT) == 4;
   LevelView v = read_level(a.ctl, 0);
   long long prev_frontier = 0;
-  bool decided = false;  // engine/feat/fallback already computed for `level`
-  int engine = 0, fallback = 0;
-  float feat[kMaxSwitchFeatures];
+  bool decided = false;  // engine already chosen for `level`
+  int engine = 0;
   for (;;) {
     const int slot = level % kStatSlots;
     if (v.frontier == 0) break;
-    if (!decided) {
-      level_features(feat, v, a, level, prev_frontier);
-      fallback = 0;
-      engine = choose_engine(a, v, feat, level, learned ? s_mlp : nullptr, &fallback);
-    }
+    if (!decided) engine = decide_level<false>(a, v, level, mlp, learned);
     decided = false;
     if (single_eligible(a, engine, v)) {
       ++episodes;
       if (blockIdx.x == 0) {
-        const int next = single_episode<SIGMA, SliceT, BLOCK>(a, level, engine, fallback, feat, v,
-                                                              learned ? s_mlp : nullptr, to_lds(hs));
+        const int next = uniform(single_episode<SIGMA, SliceT, BLOCK>(a, level, engine, v, mlp, learned, to_lds(hs)));
         block_sync_mem();
         if (threadIdx.x == 0) {
           __hip_atomic_store(&a.ctl->single_level[0], next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1457,43 +1523,18 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs a) {
           s_level = next;
         }
       } else if (threadIdx.x == 0) {
-        // wait for workgroup 0 to finish the episode, bounded like a barrier;
-        // the bound restarts whenever the episode finishes a level, so it
-        // measures a stall, not the length of a long run of small levels
-        unsigned long long t0 = dev_ticks();
-        int seen = -1;
-        bool ok = true;
-        while (__hip_atomic_load(&a.ctl->single_gen[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < episodes) {
-          if (__hip_atomic_load(&a.ctl->error[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-            ok = false;
-            break;
-          }
-          const int prog = __hip_atomic_load(&a.ctl->single_progress[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (prog != seen) {
-            seen = prog;
-            t0 = dev_ticks();
-          }
-          if (dev_ticks() - t0 > a.timeout_ticks) {
-            __hip_atomic_store(&a.ctl->error[0], static_cast<int>(BLEST_ERR_TIMEOUT), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            ok = false;
-            break;
-          }
-          __builtin_amdgcn_s_sleep(2);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        s_level = ok ? __hip_atomic_load(&a.ctl->single_level[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+        s_level = wait_episode(a, episodes);
       }
       __syncthreads();
       if (s_level < 0 || __hip_atomic_load(&a.ctl->error[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
         return;
-      level = s_level;
+      level = uniform(s_level);
       v = read_level(a.ctl, level % kStatSlots);
       prev_frontier = level > 0 ? read_level(a.ctl, (level + kStatSlots - 1) % kStatSlots).frontier : 0;
       continue;
     }
     if (blockIdx.x == 0) {
-      if (threadIdx.x == 0) log_level(a, level, v, a.probe ? -1 : engine, fallback, feat);
+      if (threadIdx.x == 0) log_begin(a, level);
       const int nslot = (level + 1) % kStatSlots;
       for (int t = threadIdx.x; t < kStatFields; t += BLOCK) a.ctl->acc[nslot][t][0] = 0ULL;
     }
@@ -1504,15 +1545,15 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs a) {
     if (a.probe) {
       for (int e = 0; e < 3; ++e) {
         const unsigned long long t0 = dev_ticks();
-        run_engine<SIGMA, SliceT, BLOCK>(a, e, sel, slot, v, gtid, nthreads, gwave, nwaves, nullptr,
+        run_engine<SIGMA, SliceT, BLOCK, false>(a, e, sel, slot, v, gwave, nwaves, to_lds(hs),
                                          to_lds(reinterpret_cast<uint32_t*>(hs)));
-        if (!grid_barrier(a.ctl, bc)) return;
+        if (!grid_barrier((Ctl*)a.ctl, bc)) return;
         if (blockIdx.x == 0 && threadIdx.x == 0 && level < a.log_cap) a.log[level].t_engine[e] = dev_ticks() - t0;
       }
     } else {
-      run_engine<SIGMA, SliceT, BLOCK>(a, engine, sel, slot, v, gtid, nthreads, gwave, nwaves, nullptr,
+      run_engine<SIGMA, SliceT, BLOCK, false>(a, engine, sel, slot, v, gwave, nwaves, to_lds(hs),
                                        to_lds(reinterpret_cast<uint32_t*>(hs)), fused ? level + 1 : -1);
-      if (!grid_barrier(a.ctl, bc)) return;
+      if (!grid_barrier((Ctl*)a.ctl, bc)) return;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0 && level < a.log_cap) a.log[level].t_mid = dev_ticks();
     // Stage 2. When the next level is likely dense (this step was BVSS over
@@ -1526,7 +1567,7 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs a) {
     // The level statistics come from the per-workgroup partials either way.
     const bool dense_next = (engine == BLEST_ENGINE_BOTTOM_UP && v.frontier >= prev_frontier) ||
                             (engine == BLEST_ENGINE_BVSS && kPanelFmt && use_panel(a, v)) ||
-                            v.fedges >= 8 * v.frontier;
+                            v.fedges >= 8LL * v.frontier;
     const bool two_phase = fused || (!a.probe && (a.count_first == 2 || (a.count_first == 1 && dense_next)));
     LevelView nv;
     bool emitted = false;
@@ -1537,24 +1578,24 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs a) {
           finalize_count<SIGMA, BLOCK, FIN_COUNT>(a, level + 1, (level + 1) % kStatSlots, sel ^ 1);
         else
           finalize_count<SIGMA, BLOCK, FIN_ATOMIC>(a, level + 1, (level + 1) % kStatSlots, sel ^ 1);
-        if (!grid_barrier(a.ctl, bc)) return;
+        if (!grid_barrier((Ctl*)a.ctl, bc)) return;
       }
       long long tot[kParts];
       reduce_parts<BLOCK>(a, tot, before);
-      nv.frontier = tot[0];
-      nv.qslices = tot[1];
-      nv.fedges = tot[2];
-      nv.deg32 = tot[3];
-      nv.deg1024 = tot[4];
-      nv.light = tot[5];
-      nv.heavy = tot[6];
-      nv.queue = tot[7];
-      nv.cumv = v.cumv + tot[0];
-      nv.cume = v.cume + tot[2];
+      nv.frontier = static_cast<uint32_t>(tot[0]);
+      nv.qslices = static_cast<uint32_t>(tot[1]);
+      nv.fedges = static_cast<uint32_t>(tot[2]);
+      nv.deg32 = static_cast<uint32_t>(tot[3]);
+      nv.deg1024 = static_cast<uint32_t>(tot[4]);
+      nv.light = static_cast<uint32_t>(tot[5]);
+      nv.heavy = static_cast<uint32_t>(tot[6]);
+      nv.queue = static_cast<uint32_t>(tot[7]);
+      nv.cumv = v.cumv + nv.frontier;
+      nv.cume = v.cume + nv.fedges;
       if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (level < a.log_cap) a.log[level].t_count = dev_ticks();
         // the level's counters, for a single-workgroup episode that may follow
-        unsigned long long* acc = &a.ctl->acc[(level + 1) % kStatSlots][0][0];
+        const gptr<unsigned long long> acc = &a.ctl->acc[(level + 1) % kStatSlots][0][0];
         const long long vals[10] = {nv.frontier, nv.queue, nv.qslices, nv.fedges, nv.deg32,
                                     nv.deg1024,  nv.light, nv.heavy,   nv.cumv,   nv.cume};
         for (int f = 0; f < 10; ++f)
@@ -1563,20 +1604,18 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs a) {
       }
     }
     if (nv.frontier > 0) {
-      level_features(feat, nv, a, level + 1, v.frontier);
-      fallback = 0;
-      engine = choose_engine(a, nv, feat, level + 1, learned ? s_mlp : nullptr, &fallback);
+      engine = decide_level<false>(a, nv, level + 1, mlp, learned);
       decided = true;
       if (two_phase) {
         const bool want_queue = engine == BLEST_ENGINE_BVSS && !(kPanelFmt && use_panel(a, nv));
         const bool want_push = engine == BLEST_ENGINE_PUSH;
         if (want_queue || want_push) {
-          finalize_emit<SIGMA, BLOCK>(a, sel ^ 1, before, want_push, want_queue, fused);
+          finalize_emit<SIGMA, BLOCK>(a, sel ^ 1, before[0], before[1], before[2], want_push, want_queue, fused);
           emitted = true;
         }
       }
     }
-    if (emitted && !grid_barrier(a.ctl, bc)) return;
+    if (emitted && !grid_barrier((Ctl*)a.ctl, bc)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0 && level < a.log_cap) {
       a.log[level].t_end = dev_ticks();
       a.log[level].work = static_cast<long long>(a.ctl->acc[slot][F_WORK][0]);
@@ -1617,21 +1656,21 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs a) {
 // of Eq. 3 and of the switch network) are summed by device atomics into the
 // rotating counter slot (l + 1) mod 3, which level l - 1 zeroed.
 
-__device__ __forceinline__ void* eager_front(const BfsArgs& a, int b) {
-  return static_cast<char*>(a.front) + static_cast<long long>(b) * a.fstride;
+__device__ __forceinline__ gptr<void> eager_front(args_ref<BfsArgs> a, int b) {
+  return (gptr<char>)a.front + static_cast<long long>(b) * a.fstride;
 }
 
 // Atomic OR of a sigma-bit word (8- and 16-bit words through the aligned
 // 32-bit word that holds them); returns the word's previous value.
 template <int SIGMA>
-__device__ __forceinline__ typename MaskOf<SIGMA>::T atomic_or_word(typename MaskOf<SIGMA>::T* p,
+__device__ __forceinline__ typename MaskOf<SIGMA>::T atomic_or_word(gptr<typename MaskOf<SIGMA>::T> p,
                                                                     typename MaskOf<SIGMA>::T bits) {
   using M = typename MaskOf<SIGMA>::T;
   if constexpr (SIGMA == 32) {
     return __hip_atomic_fetch_or(p, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else {
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(p);
-    uint32_t* w = reinterpret_cast<uint32_t*>(addr & ~uintptr_t(3));
+    const uintptr_t addr = (uintptr_t)p;
+    const gptr<uint32_t> w = (gptr<uint32_t>)(addr & ~uintptr_t(3));
     const uint32_t sh = static_cast<uint32_t>(addr & 3u) * 8u;
     const uint32_t old =
         __hip_atomic_fetch_or(w, static_cast<uint32_t>(bits) << sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1639,49 +1678,141 @@ __device__ __forceinline__ typename MaskOf<SIGMA>::T atomic_or_word(typename Mas
   }
 }
 
-// Per-lane counts of a level's new vertices, summed per wave at the end.
-struct EagerStats {
-  long long frontier = 0, qslices = 0, fedges = 0, deg32 = 0, deg1024 = 0, work = 0;
+constexpr int kEpList = 1024;       // vertices a frontier may have: a level of one workgroup costs 11 ns a vertex,
+                                    // one of the grid about 11 us (2048 x 2048 grid: 512 38.3 ms, 1024 36.4 ms)
+constexpr int kEpLog2Slots = 11, kEpSlots = 1 << kEpLog2Slots;  // table slots: at most half full
+constexpr uint32_t kEpEdges = 4096;  // a level's frontier edges (so the new vertices fit the list)
+
+struct EpisodeLds {
+  int tab[kEpSlots];      // slice set, -1 empty
+  uint32_t list[kEpEdges];
+  uint32_t sum[2][6];     // statistics of the new level, by level parity
+  int count[2];           // vertices found, by level parity
+  int queued;             // VSSs exported
+  // a grid level's new vertices (list, their number in found; bit 31: first of its set)
+  int found;
+  unsigned long long base;
 };
 
-__device__ __forceinline__ void eager_new_vertex(const BfsArgs& a, uint32_t u, int32_t deg, int new_level,
-                                                 EagerStats& st) {
+// Per-lane counts of a level's new vertices, summed per workgroup at the end
+// (each count is below 2^31, see LevelView).
+struct EagerStats {
+  uint32_t frontier = 0, qslices = 0, fedges = 0, deg32 = 0, deg1024 = 0, work = 0;
+};
+
+// A vertex reached at this level, by the lane that reached it first: into the
+// workgroup's list (its levels, statistics and queue entries follow at the end
+// of the step, for all of them together).
+__device__ __forceinline__ void eager_write(args_ref<BfsArgs> a, uint32_t u, int new_level, EagerStats& st) {
+  const int32_t deg = a.rp[u + 1] - a.rp[u];
   a.levels[a.orig_id ? a.orig_id[u] : static_cast<int32_t>(u)] = new_level;
   st.frontier += 1;
-  st.fedges += deg;
+  st.fedges += static_cast<uint32_t>(deg);
   st.deg32 += deg >= 32;
   st.deg1024 += deg >= 1024;
 }
 
-// Appends every VSS of slice set s to q; qcur is the F_QUEUE counter of the
-// next level's slot, which doubles as q's append cursor.
-__device__ __forceinline__ void eager_enqueue(const BfsArgs& a, uint32_t s, uint4* q, unsigned long long* qcur,
-                                              EagerStats& st) {
-  const uint32_t s0 = a.slice_ptr[s], ns = a.slice_ptr[s + 1] - s0;
+__device__ __forceinline__ void eager_found(args_ref<BfsArgs> a, uint32_t u, bool first, int level,
+                                            lptr<EpisodeLds> L, EagerStats& st);
+
+// The end of a step: the listed vertices' levels, statistics and, for the
+// first of each set, its VSSs, with one queue reservation and one set of
+// counter atomics per workgroup (one per new set and per wave, on the same
+// few addresses at the memory side, took most of a level of 1,700 vertices).
+template <int SIGMA, int BLOCK>
+__device__ __forceinline__ void eager_finish(args_ref<BfsArgs> a, int level, lptr<EpisodeLds> L, EagerStats st) {
+  __shared__ int lds32[BLOCK / 64];
+  const int nslot = (level + 1) % kStatSlots;
+  const gptr<uint4> q = a.queue[(level + 1) % 3];
+  const gptr<const uint32_t> slp = a.slice_ptr;
   const uint32_t tau = static_cast<uint32_t>(a.tau);
-  const uint32_t nv = (ns + tau - 1) / tau;
-  if (nv == 0) return;
-  const unsigned long long off = fetch_add_u64(qcur, nv);
-  for (uint32_t k = 0; k < nv; ++k) q[off + k] = make_uint4(s0 + k * tau, min(tau, ns - k * tau), 0u, s);
+  __syncthreads();
+  const int found = uniform(min(L->found, static_cast<int>(kEpEdges)));
+  for (int b = 0; b < found; b += BLOCK) {
+    const int i = b + static_cast<int>(threadIdx.x);
+    uint32_t s = 0, s0 = 0, ns = 0;
+    int nv[1] = {0}, ex[1], tot[1];
+    if (i < found) {
+      const uint32_t e = L->list[i], u = e & 0x7fffffffu;
+      s = u / SIGMA;
+      if (e >> 31) {
+        s0 = slp[s];
+        ns = slp[s + 1] - s0;
+      }
+      eager_write(a, u, level + 1, st);
+      nv[0] = static_cast<int>((ns + tau - 1) / tau);
+      st.qslices += ns;
+    }
+    block_exclusive_scan<BLOCK, 1>(nv, ex, tot, lds32);
+    if (threadIdx.x == 0) L->base = tot[0] ? fetch_add_u64(&a.ctl->acc[nslot][F_QUEUE][0], tot[0]) : 0ULL;
+    __syncthreads();
+    const unsigned long long o = L->base + ex[0];
+    for (int k = 0; k < nv[0]; ++k)
+      q[o + k] = make_uint4(s0 + k * tau, min(tau, ns - k * tau), 0u, s);
+    __syncthreads();
+  }
+  if (found) {
+    const uint32_t v[5] = {st.frontier, st.qslices, st.fedges, st.deg32, st.deg1024};
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      const uint32_t t = wave_sum(v[k]);
+      if (lane_id() == 0 && t)
+        __hip_atomic_fetch_add(&L->sum[0][k], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __syncthreads();
+    if (threadIdx.x < 5) {
+      constexpr int f[5] = {F_FRONTIER, F_QSLICES, F_FEDGES, F_DEG32, F_DEG1024};
+      const uint32_t t = L->sum[0][threadIdx.x];
+      if (t) add_u64(&a.ctl->acc[nslot][f[threadIdx.x]][0], t);
+      L->sum[0][threadIdx.x] = 0u;
+    }
+    if (threadIdx.x == 0) L->found = 0;
+  }
+  if (a.count_work || a.probe) {
+    const unsigned long long w = wave_sum(static_cast<unsigned long long>(st.work));
+    if (lane_id() == 0 && w) add_u64(&a.ctl->acc[level % kStatSlots][F_WORK][0], w);
+  }
+}
+
+__device__ __forceinline__ void eager_found(args_ref<BfsArgs> a, uint32_t u, bool first, int level,
+                                            lptr<EpisodeLds> L, EagerStats& st) {
+  const int i = __hip_atomic_fetch_add(&L->found, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  if (i < static_cast<int>(kEpEdges)) {
+    L->list[i] = u | (first ? 0x80000000u : 0u);
+    return;
+  }
+  // the list is full: this vertex on its own (its statistics still go with
+  // the workgroup's)
+  eager_write(a, u, level + 1, st);
+  if (!first) return;
+  const uint32_t s = u / static_cast<uint32_t>(a.sigma), tau = static_cast<uint32_t>(a.tau);
+  const uint32_t s0 = a.slice_ptr[s], ns = a.slice_ptr[s + 1] - s0, nv = (ns + tau - 1) / tau;
   st.qslices += ns;
+  if (nv == 0) return;
+  const unsigned long long o = fetch_add_u64(&a.ctl->acc[(level + 1) % kStatSlots][F_QUEUE][0], nv);
+  for (uint32_t k = 0; k < nv; ++k)
+    a.queue[(level + 1) % 3][o + k] = make_uint4(s0 + k * tau, min(tau, ns - k * tau), 0u, s);
 }
 
 // Top-down step of Alg. 2: a wave takes G queued VSSs at a time, reads their
 // sets' frontier words from F_l and all their slices, then handles the hits.
-template <int SIGMA, class SliceT, int K>
-__device__ void eager_td_k(const BfsArgs& a, int level, long long qlen, long long gwave, long long nwaves,
-                           EagerStats& st) {
+template <int SIGMA, class SliceT, int K, int BLOCK>
+__device__ __attribute__((noinline)) void eager_td_k(args_ref<BfsArgs> a_, int level, long long qlen, long long gwave,
+                                                     long long nwaves, lptr<EpisodeLds> L) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  level = uniform(level);
+  qlen = uniform(qlen);
+  gwave = uniform(gwave);
+  nwaves = uniform(nwaves);
+  EagerStats st;
   using M = typename MaskOf<SIGMA>::T;
   constexpr int G = 4;
   const int cb = level % 3, nb = (level + 1) % 3;
-  const gptr<const uint4> qg = to_global(static_cast<const uint4*>(a.queue[cb]));
-  uint4* qn = a.queue[nb];
-  unsigned long long* qcur = &a.ctl->acc[(level + 1) % kStatSlots][F_QUEUE][0];
-  gptr<const SliceT> __restrict__ sl = to_global(static_cast<const SliceT*>(a.slices));
-  gptr<const M> vis = to_global(static_cast<const M*>(a.vis));
-  gptr<const M> fc = to_global(static_cast<const M*>(eager_front(a, cb)));
-  M* fn = static_cast<M*>(eager_front(a, nb));
-  gptr<const int32_t> rp = to_global(a.rp);
+  const gptr<const uint4> qg = a.queue[cb];
+  gptr<const SliceT> __restrict__ sl = (gptr<const SliceT>)a.slices;
+  gptr<const M> vis = (gptr<const M>)a.vis;
+  gptr<const M> fc = (gptr<const M>)eager_front(a, cb);
+  const gptr<M> fn = (gptr<M>)eager_front(a, nb);
   const uint32_t lane = static_cast<uint32_t>(lane_id());
   for (long long base = gwave * G; base < qlen; base += nwaves * G) {
     uint4 dl = make_uint4(0u, 0u, 0u, 0u);
@@ -1691,12 +1822,10 @@ __device__ void eager_td_k(const BfsArgs& a, int level, long long qlen, long lon
       al_l = static_cast<uint32_t>(fc[dl.w]);
     }
     uint32_t s0[G], cn[G];
-    SliceT al[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       s0[g] = __builtin_amdgcn_readlane(dl.x, g);
       cn[g] = __builtin_amdgcn_readlane(dl.y, g);
-      al[g] = static_cast<SliceT>(static_cast<uint32_t>(__builtin_amdgcn_readlane(al_l, g)));
     }
     SliceT w[G][K];
 #pragma unroll
@@ -1707,6 +1836,10 @@ __device__ void eager_td_k(const BfsArgs& a, int level, long long qlen, long lon
         st.work += j < cn[g];
         w[g][k] = (j < cn[g]) ? sl[s0[g] + j] : SliceT(0);
       }
+    // (the frontier words are waited for only here, with the slices)
+    SliceT al[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) al[g] = static_cast<SliceT>(static_cast<uint32_t>(__builtin_amdgcn_readlane(al_l, g)));
     // visited | F_l of every hit row, all loads issued before any test
     M seen[G][K];
 #pragma unroll
@@ -1724,27 +1857,25 @@ __device__ void eager_td_k(const BfsArgs& a, int level, long long qlen, long lon
         const M bit = static_cast<M>(M(1) << (row % SIGMA));
         if (!(seen[g][k] & bit)) {
           const M old = atomic_or_word<SIGMA>(fn + row / SIGMA, bit);
-          if (!(old & bit)) {
-            eager_new_vertex(a, row, rp[row + 1] - rp[row], level + 1, st);
-            if (old == 0) eager_enqueue(a, row / SIGMA, qn, qcur, st);
-          }
+          if (!(old & bit)) eager_found(a, row, old == 0, level, L, st);
         }
       }
   }
+  eager_finish<SIGMA, BLOCK>(a, level, L, st);
 }
 
-template <int SIGMA, class SliceT>
-__device__ __forceinline__ void eager_td(const BfsArgs& a, int level, long long qlen, long long gwave,
-                                                   long long nwaves, EagerStats& st) {
+template <int SIGMA, class SliceT, int BLOCK>
+__device__ __forceinline__ void eager_td(args_ref<BfsArgs> a, int level, long long qlen, long long gwave,
+                                         long long nwaves, lptr<EpisodeLds> L) {
   switch (a.tau) {
     case 64:
-      return eager_td_k<SIGMA, SliceT, 1>(a, level, qlen, gwave, nwaves, st);
+      return eager_td_k<SIGMA, SliceT, 1, BLOCK>(a, level, qlen, gwave, nwaves, L);
     case 128:
-      return eager_td_k<SIGMA, SliceT, 2>(a, level, qlen, gwave, nwaves, st);
+      return eager_td_k<SIGMA, SliceT, 2, BLOCK>(a, level, qlen, gwave, nwaves, L);
     case 192:
-      return eager_td_k<SIGMA, SliceT, 3>(a, level, qlen, gwave, nwaves, st);
+      return eager_td_k<SIGMA, SliceT, 3, BLOCK>(a, level, qlen, gwave, nwaves, L);
     default:
-      return eager_td_k<SIGMA, SliceT, 4>(a, level, qlen, gwave, nwaves, st);
+      return eager_td_k<SIGMA, SliceT, 4, BLOCK>(a, level, qlen, gwave, nwaves, L);
   }
 }
 
@@ -1753,20 +1884,22 @@ __device__ __forceinline__ void eager_td(const BfsArgs& a, int level, long long 
 // kPullLight) for a neighbour in F_l. The wave owns all sigma vertices of each
 // of its sets, so it writes their F_{l+1} words with plain stores and
 // enqueues the sets that gained vertices.
-template <int SIGMA>
-__device__ __forceinline__ void eager_bu(const BfsArgs& a, int level, long long gwave, long long nwaves,
-                                                   EagerStats& st) {
+template <int SIGMA, int BLOCK>
+__device__ __attribute__((noinline)) void eager_bu(args_ref<BfsArgs> a_, int level, long long gwave, long long nwaves,
+                                                   lptr<EpisodeLds> L) {
+  args_ref<BfsArgs> a = uniform_args(a_);
+  level = uniform(level);
+  gwave = uniform(gwave);
+  nwaves = uniform(nwaves);
+  EagerStats st;
   using M = typename MaskOf<SIGMA>::T;
   const int cb = level % 3, nb = (level + 1) % 3;
-  gptr<const M> vis = to_global(static_cast<const M*>(a.vis));
-  gptr<const M> fc = to_global(static_cast<const M*>(eager_front(a, cb)));
-  gptr<const M> degm = to_global(static_cast<const M*>(a.degmask_in));
-  M* fn = static_cast<M*>(eager_front(a, nb));
-  uint4* qn = a.queue[nb];
-  unsigned long long* qcur = &a.ctl->acc[(level + 1) % kStatSlots][F_QUEUE][0];
-  gptr<const int32_t> rp = to_global(a.rp_in);
-  gptr<const int32_t> col = to_global(a.col_in);
-  gptr<const int32_t> rp_out = to_global(a.rp);
+  gptr<const M> vis = (gptr<const M>)a.vis;
+  gptr<const M> fc = (gptr<const M>)eager_front(a, cb);
+  gptr<const M> degm = (gptr<const M>)a.degmask_in;
+  const gptr<M> fn = (gptr<M>)eager_front(a, nb);
+  gptr<const int32_t> rp = a.rp_in;
+  gptr<const int32_t> col = a.col_in;
   const long long nv = a.nsets * SIGMA;
   const int lane = lane_id();
   const long long nchunks = (nv + 63) / 64;
@@ -1817,80 +1950,381 @@ __device__ __forceinline__ void eager_bu(const BfsArgs& a, int level, long long 
     }
     const unsigned long long got = __ballot(found);
     if (!got) continue;
-    // the statistics count out-arcs (the frontier's edges for the next step)
-    if (found) eager_new_vertex(a, static_cast<uint32_t>(u), rp_out[u + 1] - rp_out[u], level + 1, st);
     if (lane % SIGMA == 0) {
       const M bits = static_cast<M>(got >> lane);
-      if (bits) {
-        fn[u / SIGMA] = bits;
-        eager_enqueue(a, static_cast<uint32_t>(u / SIGMA), qn, qcur, st);
+      if (bits) fn[u / SIGMA] = bits;
+    }
+    if (found) {
+      const M below = static_cast<M>((got >> (lane & ~(SIGMA - 1))) & ((1ULL << (lane % SIGMA)) - 1ULL));
+      eager_found(a, static_cast<uint32_t>(u), below == 0, level, L, st);
+    }
+  }
+  eager_finish<SIGMA, BLOCK>(a, level, L, st);
+}
+
+// ---------------------------------------- eager levels of one workgroup
+//
+// A run of small levels on workgroup 0 alone, the frontier kept in registers
+// and LDS. What bounds such a level on the whole grid is not its work but its
+// chain of dependent loads from memory that no cache holds after a device-wide
+// barrier, plus the barrier itself. Here the chain stays in one compute unit
+// and its L2: a vertex's columns, their visited words, an atomic OR on those
+// not visited (performed in the L2: no other workgroup touches the visited
+// words meanwhile), the new vertices' row pointers. A level reads the rows of
+// its frontier vertices (the columns that the hits of the queued slices stand
+// for; a queued set of a grid graph has 18 slices for 1 to 3 frontier
+// vertices).
+// Measured on a 2048 x 2048 grid graph (2,492 levels of up to 3,312 vertices):
+// 59.2 ms when one workgroup ran levels of up to 256 queued slices through the
+// grid's own functions and arguments were read from the stack, 36.4 ms now;
+// 11 ns a frontier vertex here, about 11 us a level on the grid.
+// Phase A walks the rows and collects the new vertices in LDS, phase B loads
+// their row and slice pointers, writes levels and sums the statistics; a hash
+// table of the new vertices' slice sets tells the first vertex of a set.
+// Adds set s to the table; its slot if it was not there, else -1.
+__device__ __forceinline__ int ep_claim(lptr<int> tab, int s) {
+  uint32_t h = (static_cast<uint32_t>(s) * 2654435761u) >> (32 - kEpLog2Slots);
+  for (int probe = 0; probe < kEpSlots; ++probe, h = (h + 1) & (kEpSlots - 1)) {
+    int old = -1;
+    if (__hip_atomic_compare_exchange_strong(tab + h, &old, s, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP))
+      return static_cast<int>(h);
+    if (old == s) return -1;
+  }
+  return -1;
+}
+
+// Frontier vertex u into the grid scheme's words and queue (cursor in LDS);
+// the first of its set adds the set's VSSs and slices to st[0], st[1]. The
+// words are this workgroup's alone meanwhile, so the OR stays in its L2.
+template <int SIGMA>
+__device__ __forceinline__ void ep_export(gptr<typename MaskOf<SIGMA>::T> fo, gptr<uint4> qo,
+                                          gptr<const uint32_t> slp, int u, uint32_t tau, lptr<int> queued,
+                                          uint32_t* st) {
+  using M = typename MaskOf<SIGMA>::T;
+  const uint32_t s = static_cast<uint32_t>(u) / SIGMA;
+  const uint32_t old = __hip_atomic_fetch_or((gptr<uint32_t>)fo + (u >> 5), 1u << (u & 31), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+  if (static_cast<M>(old >> ((s * SIGMA) & 31))) return;
+  const uint32_t b0 = slp[s], ns = slp[s + 1] - b0, nv = (ns + tau - 1) / tau;
+  const int off = __hip_atomic_fetch_add(queued, static_cast<int>(nv), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  for (uint32_t k = 0; k < nv; ++k) qo[off + k] = make_uint4(b0 + k * tau, min(tau, ns - k * tau), 0u, s);
+  st[0] += nv;
+  st[1] += ns;
+}
+
+// Whether workgroup 0 may run the level alone (the same in every workgroup).
+__device__ __forceinline__ bool episode_eligible(args_ref<BfsArgs> a, const LevelView& v, int engine) {
+  return a.single_block && engine == BLEST_ENGINE_BVSS && v.frontier <= kEpList && v.fedges <= kEpEdges;
+}
+
+// Runs levels from `level` (view v, queue Q_level and words F_level of the
+// grid scheme; prev_queue VSSs of the level before) until one is not
+// eligible, its frontier is empty or has more than kEpList vertices, and
+// leaves the grid scheme's state for the level it returns, with no word of
+// the level before it left in the frontier buffers. Called by workgroup 0.
+typedef int i32x4_word_aligned __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int SIGMA, int BLOCK>
+__device__ __attribute__((noinline)) int eager_episode(args_ref<BfsArgs> a_, int level, LevelView v,
+                                                       uint32_t prev_queue, lptr<const float> s_mlp, bool learned,
+                                                       lptr<EpisodeLds> L) {
+  using M = typename MaskOf<SIGMA>::T;
+  args_ref<BfsArgs> a = uniform_args(a_);
+  level = uniform(level);
+  prev_queue = uniform(static_cast<int>(prev_queue));
+  constexpr int EPT = (kEpList + BLOCK - 1) / BLOCK;  // frontier vertices per thread
+  const int tid = static_cast<int>(threadIdx.x), lane = lane_id();
+  const gptr<const int32_t> rp = a.rp, col = a.col, orig_id = a.orig_id;
+  const gptr<const uint32_t> slp = a.slice_ptr;
+  const gptr<uint32_t> vis32 = (gptr<uint32_t>)a.vis;  // bit u % 32 of word u / 32, whatever sigma
+  const gptr<int32_t> levels = a.levels;
+  const uint32_t tau = static_cast<uint32_t>(a.tau);
+  const lptr<int> tab = &L->tab[0];
+
+  // take over the grid scheme's frontier: F_level into the list and the
+  // visited words, out of the frontier buffers
+  for (int i = tid; i < kEpSlots; i += BLOCK) tab[i] = -1;
+  if (tid < 2) L->count[tid] = 0;
+  if (tid < 12) L->sum[0][tid] = 0u;
+  __syncthreads();
+  {
+    const gptr<M> fc = (gptr<M>)eager_front(a, level % 3), fp = (gptr<M>)eager_front(a, (level + 2) % 3);
+    const gptr<const uint4> qc = a.queue[level % 3], qp = a.queue[(level + 2) % 3];
+    const gptr<M> vis = (gptr<M>)a.vis;
+    for (uint32_t i = tid; i < prev_queue; i += BLOCK) fp[qp[i].w] = 0;
+    for (uint32_t i = tid; i < v.queue; i += BLOCK) {
+      const uint32_t s = qc[i].w;
+      const M bits = fc[s];
+      if (bits && ep_claim(tab, static_cast<int>(s)) >= 0) {
+        vis[s] = static_cast<M>(vis[s] | bits);
+        for (uint32_t t = bits; t; t &= t - 1) {
+          const int k = __hip_atomic_fetch_add(&L->count[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          L->list[k] = s * SIGMA + __builtin_ctz(t);
+        }
       }
     }
+    block_sync_mem();
+    for (uint32_t i = tid; i < v.queue; i += BLOCK) fc[qc[i].w] = 0;
   }
+  int cnt = uniform(L->count[0]);
+  int eu[EPT], ep[EPT], ed[EPT], es[EPT];  // this thread's frontier vertices: id, first column, degree, table slot
+#pragma unroll
+  for (int g = 0; g < EPT; ++g) {
+    const int i = g * BLOCK + tid;
+    eu[g] = i < cnt ? static_cast<int>(L->list[i]) : -1;
+    ep[g] = ed[g] = 0;
+    es[g] = -1;
+    if (eu[g] >= 0) {
+      ep[g] = rp[eu[g]];
+      ed[g] = rp[eu[g] + 1] - ep[g];
+    }
+  }
+  for (int i = tid; i < kEpSlots; i += BLOCK) tab[i] = -1;
+  block_sync_mem();
+  if (tid == 0) L->count[0] = L->queued = 0;
+  __syncthreads();
+  bool big = false;
+  for (int done_levels = 0;; ++done_levels) {
+    const int par = done_levels & 1;
+    if (tid == 0) log_begin(a, level);
+    // phase A: the rows of the frontier, four columns per lane at a time
+    const lptr<int> count = &L->count[par];
+    auto visit = [&](const bool (&want)[4], const int (&c)[4]) {
+      uint32_t w[4];
+      bool on[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w[j] = want[j] ? vis32[c[j] >> 5] : ~0u;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        on[j] = !((w[j] >> (c[j] & 31)) & 1u);
+        if (on[j])
+          w[j] = __hip_atomic_fetch_or(vis32 + (c[j] >> 5), 1u << (c[j] & 31), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      unsigned long long b[4];
+      int total = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        on[j] = on[j] && !((w[j] >> (c[j] & 31)) & 1u);
+        b[j] = __ballot(on[j]);
+        total += __popcll(b[j]);
+      }
+      if (total == 0) return;
+      int k = 0;
+      if (lane == 0) k = __hip_atomic_fetch_add(count, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      k = uniform(k);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = k + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                              static_cast<uint32_t>(b[j] >> 32),
+                              __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b[j]), 0u)));
+        if (on[j]) L->list[i] = static_cast<uint32_t>(c[j]);  // at most kEpEdges of them
+        k += __popcll(b[j]);
+      }
+    };
+#pragma unroll
+    for (int g = 0; g < EPT; ++g) {
+      if (g * BLOCK >= cnt) break;
+      const int d = ed[g], p = ep[g];
+      // a table slot claimed for this level's frontier is free again
+      if (es[g] >= 0) tab[es[g]] = -1;
+      if (!__ballot(d > 8)) {
+        // short rows: a lane each (col is padded by 4 entries)
+#pragma unroll
+        for (int h = 0; h < 8; h += 4) {
+          if (!__ballot(d > h)) break;
+          i32x4_word_aligned q = {0, 0, 0, 0};
+          if (d > h) q = *(gptr<const i32x4_word_aligned>)(col + p + h);
+          const bool want[4] = {d > h, d > h + 1, d > h + 2, d > h + 3};
+          const int c[4] = {q.x, q.y, q.z, q.w};
+          visit(want, c);
+        }
+      } else {
+        // 256 columns of the wave's concatenated rows at a time; a lane finds
+        // the row of each of its four by a binary search over the degrees'
+        // prefix sums
+        const int incl = wave_inclusive_scan(d);
+        const int total = __shfl(incl, 63, 64);
+        for (int e0 = 0; e0 < total; e0 += 256) {
+          bool want[4];
+          int c[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int e = e0 + 64 * j + lane;
+            int lo = 0;
+#pragma unroll
+            for (int stp = 32; stp >= 1; stp >>= 1)
+              if (__shfl(incl, lo + stp - 1, 64) <= e) lo += stp;
+            const int owner = lo & 63;
+            const int at = __shfl(p - (incl - d), owner, 64) + e;
+            want[j] = e < total;
+            c[j] = want[j] ? col[at] : 0;
+          }
+          visit(want, c);
+        }
+      }
+    }
+    __syncthreads();
+    cnt = uniform(*count);
+    big = cnt > kEpList;
+    const lptr<uint32_t> sum = &L->sum[par][0];
+    if (tid < 6) L->sum[par ^ 1][tid] = 0u;
+    if (tid == 0) L->count[par ^ 1] = 0;
+    uint32_t st[5] = {0u, 0u, 0u, 0u, 0u};  // queued VSSs, slices, frontier edges, degree >= 32, >= 1024
+    const int new_level = level + 1;
+    if (big) {
+      // more vertices than this workgroup keeps: the grid goes on from here
+      const gptr<M> fo = (gptr<M>)eager_front(a, new_level % 3);
+      const gptr<uint4> qo = a.queue[new_level % 3];
+      for (int i = tid; i < cnt; i += BLOCK) {
+        const int u = static_cast<int>(L->list[i]);
+        const int d = rp[u + 1] - rp[u];
+        levels[orig_id ? orig_id[u] : u] = new_level;
+        st[2] += static_cast<uint32_t>(d);
+        st[3] += d >= 32;
+        st[4] += d >= 1024;
+        ep_export<SIGMA>(fo, qo, slp, u, tau, &L->queued, st);
+      }
+    } else {
+      // phase B: the new vertices
+      uint32_t s0[EPT], s1[EPT];
+      int oid[EPT];
+#pragma unroll
+      for (int g = 0; g < EPT; ++g) {
+        eu[g] = es[g] = -1;
+        ep[g] = ed[g] = 0;
+        s0[g] = s1[g] = 0u;
+        oid[g] = 0;
+        const int i = g * BLOCK + tid;
+        if (i < cnt) {
+          const int u = static_cast<int>(L->list[i]);
+          eu[g] = oid[g] = u;
+          ep[g] = rp[u];
+          ed[g] = rp[u + 1];
+          if (orig_id) oid[g] = orig_id[u];
+          es[g] = ep_claim(tab, u / SIGMA);
+          if (es[g] >= 0) {
+            s0[g] = slp[u / SIGMA];
+            s1[g] = slp[u / SIGMA + 1];
+          }
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < EPT; ++g) {
+        if (eu[g] < 0) continue;
+        levels[oid[g]] = new_level;
+        ed[g] -= ep[g];
+        const uint32_t ns = s1[g] - s0[g];
+        st[0] += (ns + tau - 1) / tau;
+        st[1] += ns;
+        st[2] += static_cast<uint32_t>(ed[g]);
+        st[3] += ed[g] >= 32;
+        st[4] += ed[g] >= 1024;
+      }
+    }
+    if (wave_in_block() * 64 < cnt) {
+#pragma unroll
+      for (int f = 0; f < 5; ++f) {
+        const uint32_t t = wave_sum(st[f]);
+        if (lane == 0 && t) __hip_atomic_fetch_add(sum + f, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    __syncthreads();
+    const uint32_t work = v.fedges;
+    v.frontier = static_cast<uint32_t>(cnt);
+    v.queue = uniform(static_cast<int>(sum[0]));
+    v.qslices = uniform(static_cast<int>(sum[1]));
+    v.fedges = uniform(static_cast<int>(sum[2]));
+    v.deg32 = uniform(static_cast<int>(sum[3]));
+    v.deg1024 = uniform(static_cast<int>(sum[4]));
+    v.light = v.heavy = 0u;
+    v.cumv += v.frontier;
+    v.cume += v.fedges;
+    if (tid == 0 && level < a.log_cap) {
+      const unsigned long long t = dev_ticks();
+      a.log[level].t_mid = t;
+      a.log[level].t_end = t;
+      if (a.count_work) a.log[level].work = work;
+    }
+    ++level;
+    // progress for the waiting workgroups: their time bound restarts with every level
+    if (tid == 0) __hip_atomic_store(&a.ctl->single_progress[0], level, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (v.frontier == 0 || big) break;
+    if ((level & 255) == 0 && __hip_atomic_load(&a.ctl->error[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+      break;
+    const int engine = decide_level<true>(a, v, level, s_mlp, learned);
+    if (!episode_eligible(a, v, engine)) break;
+  }
+  // hand over: F_level and Q_level in the grid scheme's buffers (all frontier
+  // words were zero), its statistics in the slot of its level
+  if (!big) {
+    const gptr<M> fo = (gptr<M>)eager_front(a, level % 3);
+    uint32_t st[2] = {0u, 0u};
+#pragma unroll
+    for (int g = 0; g < EPT; ++g)
+      if (eu[g] >= 0) ep_export<SIGMA>(fo, a.queue[level % 3], slp, eu[g], tau, &L->queued, st);
+  }
+  auto put = [&](int sl, int f, unsigned long long x) {
+    __hip_atomic_store(&a.ctl->acc[sl % kStatSlots][f][0], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if (tid < kStatFields) {
+    put(level + 1, tid, 0ULL);
+    put(level + 2, tid, 0ULL);
+  }
+  if (tid == 0) {
+    put(level, F_FRONTIER, v.frontier);
+    put(level, F_QUEUE, v.queue);
+    put(level, F_QSLICES, v.qslices);
+    put(level, F_FEDGES, v.fedges);
+    put(level, F_DEG32, v.deg32);
+    put(level, F_DEG1024, v.deg1024);
+    put(level, F_CUMV, v.cumv);
+    put(level, F_CUME, v.cume);
+    put(level, F_WORK, 0ULL);
+  }
+  return level;
 }
 
-// Adds the wave's counts to the next level's slot (one atomic per wave and field).
-__device__ __forceinline__ void eager_flush(const BfsArgs& a, const EagerStats& st, int nslot, int slot) {
-  long long v[6] = {st.frontier, st.qslices, st.fedges, st.deg32, st.deg1024, st.work};
-#pragma unroll
-  for (int k = 0; k < 6; ++k) v[k] = wave_sum(v[k]);
-  if (lane_id() == 0) {
-    constexpr int f[5] = {F_FRONTIER, F_QSLICES, F_FEDGES, F_DEG32, F_DEG1024};
-#pragma unroll
-    for (int k = 0; k < 5; ++k)
-      if (v[k]) add_u64(&a.ctl->acc[nslot][f[k]][0], static_cast<unsigned long long>(v[k]));
-    if (v[5] && (a.count_work || a.probe)) add_u64(&a.ctl->acc[slot][F_WORK][0], static_cast<unsigned long long>(v[5]));
-  }
-}
-
-// Levels whose queue holds at most this many slices run on workgroup 0 alone
-// (workgroup barriers instead of device-wide ones), consecutively, while the
-// other workgroups wait; a bottom-up level never does.
-constexpr long long kEagerSingleSlices = 256;
-
-// One level of the eager scheme by the calling workgroups (the whole grid,
-// or workgroup 0 alone): bookkeeping, the engine and its counters. The caller
-// synchronises afterwards (device-wide or workgroup barrier).
+// One level of the eager scheme by the whole grid: bookkeeping, the engine and its counters. The caller
+// synchronises afterwards.
 template <int SIGMA, class SliceT, int BLOCK>
-__device__ __forceinline__ void eager_level(const BfsArgs& a, int level, const LevelView& v, long long prev_queue,
-                                            int engine, int fallback, const float (&feat)[kMaxSwitchFeatures],
-                                            long long gtid, long long nthreads, long long gwave, long long nwaves) {
+__device__ __forceinline__ void eager_level(args_ref<BfsArgs> a, int level, const LevelView& v, uint32_t prev_queue,
+                                            int engine, long long gtid, long long nthreads, long long gwave,
+                                            long long nwaves, lptr<EpisodeLds> L) {
   using M = typename MaskOf<SIGMA>::T;
   if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) {
-      log_level(a, level, v, engine, fallback, feat);
-      if (level < a.log_cap) a.log[level].panel = 0;
-    }
+    if (threadIdx.x == 0) log_begin(a, level);
     // the slot level + 2 accumulates into during the next level
     const int zslot = (level + 2) % kStatSlots;
     for (int t = threadIdx.x; t < kStatFields; t += BLOCK)
       __hip_atomic_store(&a.ctl->acc[zslot][t][0], 0ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  EagerStats st;
-  if (engine == BLEST_ENGINE_BOTTOM_UP)
-    eager_bu<SIGMA>(a, level, gwave, nwaves, st);
-  else
-    eager_td<SIGMA, SliceT>(a, level, v.queue, gwave, nwaves, st);
   {
     // F_l into the visited words (walking Q_l); F_{l-1} cleared (walking Q_{l-1})
-    const gptr<const uint4> qc = to_global(static_cast<const uint4*>(a.queue[level % 3]));
-    const gptr<const uint4> qp = to_global(static_cast<const uint4*>(a.queue[(level + 2) % 3]));
-    gptr<M> vis = to_global(static_cast<M*>(a.vis));
-    const gptr<const M> fc = to_global(static_cast<const M*>(eager_front(a, level % 3)));
-    gptr<M> fp = to_global(static_cast<M*>(eager_front(a, (level + 2) % 3)));
+    const gptr<const uint4> qc = a.queue[level % 3];
+    const gptr<const uint4> qp = a.queue[(level + 2) % 3];
+    gptr<M> vis = (gptr<M>)a.vis;
+    const gptr<const M> fc = (gptr<const M>)eager_front(a, level % 3);
+    gptr<M> fp = (gptr<M>)eager_front(a, (level + 2) % 3);
     for (long long i = gtid; i < v.queue; i += nthreads) {
       const uint32_t s = qc[i].w;
       vis[s] = static_cast<M>(vis[s] | fc[s]);
     }
     for (long long i = gtid; i < prev_queue; i += nthreads) fp[qp[i].w] = 0;
   }
-  eager_flush(a, st, (level + 1) % kStatSlots, level % kStatSlots);
+  if (engine == BLEST_ENGINE_BOTTOM_UP)
+    eager_bu<SIGMA, BLOCK>(a, level, gwave, nwaves, L);
+  else
+    eager_td<SIGMA, SliceT, BLOCK>(a, level, v.queue, gwave, nwaves, L);
 }
 
 template <int SIGMA, class SliceT, int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_bfs_eager(BfsArgs a) {
+__global__ void __launch_bounds__(BLOCK) k_bfs_eager(BfsArgs args) {
+  args_ref<BfsArgs> a = kernel_args(args);
   extern __shared__ float s_mlp[];
   __shared__ int s_level;
+  __shared__ EpisodeLds s_ep;
   using M = typename MaskOf<SIGMA>::T;
   const unsigned nblocks = gridDim.x;
   const long long nthreads = static_cast<long long>(nblocks) * BLOCK;
@@ -1898,12 +2332,15 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_eager(BfsArgs a) {
   const long long gwave = static_cast<long long>(blockIdx.x) * (BLOCK / 64) + wave_in_block();
   const long long nwaves = static_cast<long long>(nblocks) * (BLOCK / 64);
   const bool learned = a.policy == BLEST_POLICY_LEARNED && a.mlp != nullptr && a.mlp->valid;
-  if (learned) mlp_to_lds(a.mlp, s_mlp);
+  const lptr<const float> mlp = to_lds((const float*)s_mlp);
+  if (threadIdx.x == 0) s_ep.found = 0;
+  if (threadIdx.x < 12) s_ep.sum[0][threadIdx.x] = 0u;
+  if (learned) mlp_to_lds((const MlpDev*)a.mlp, s_mlp);
   // levels, visited words and F_0, F_1 as in the lazy scheme, plus F_2; the
   // registration barrier publishes them with the level-0 counters and queue
   clear_state<SIGMA>(a, gtid, nthreads, true);
   {
-    M* f2 = static_cast<M*>(eager_front(a, 2));
+    const gptr<M> f2 = (gptr<M>)eager_front(a, 2);
     for (long long s = gtid; s < a.nsets; s += nthreads) f2[s] = 0;
   }
   if (blockIdx.x == 0) {
@@ -1912,111 +2349,45 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_eager(BfsArgs a) {
     if (threadIdx.x == 0) a.ctl->single_gen[0] = 0u;
   }
   BarrierCtx bc;
-  if (!barrier_register(a.ctl, &bc, a.timeout_ticks)) return;
+  if (!barrier_register((Ctl*)a.ctl, &bc, a.timeout_ticks)) return;
   int level = 0;
   unsigned episodes = 0;
-  bool in_episode = false;  // workgroup 0: running consecutive levels alone
   LevelView v = read_level(a.ctl, 0);
-  long long prev_frontier = 0, prev_queue = 0;
-  float feat[kMaxSwitchFeatures];
-  for (;;) {
-    const bool done = v.frontier == 0;
-    int engine = 0, fallback = 0;
-    bool single = false;
-    if (!done) {
-      level_features(feat, v, a, level, prev_frontier);
-      engine = choose_engine_inl(a, v, feat, level, learned ? s_mlp : nullptr, &fallback);
-      if (engine == BLEST_ENGINE_PUSH) engine = BLEST_ENGINE_BVSS;
-      single = a.single_block && engine != BLEST_ENGINE_BOTTOM_UP && v.qslices <= kEagerSingleSlices;
-    }
-    if (blockIdx.x == 0 && in_episode && (done || !single)) {
-      // end of an episode: hand the state to the waiting workgroups, with the
-      // cumulative counts they did not follow
-      block_sync_mem();
-      if (threadIdx.x == 0) {
-        unsigned long long* acc = &a.ctl->acc[level % kStatSlots][0][0];
-        __hip_atomic_store(acc + F_CUMV * kPad, static_cast<unsigned long long>(v.cumv), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(acc + F_CUME * kPad, static_cast<unsigned long long>(v.cume), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&a.ctl->single_level[0], level, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&a.ctl->single_gen[0], episodes, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      in_episode = false;
-    }
-    if (done) break;
-    if (single && blockIdx.x == 0) {
-      // a small level on workgroup 0 alone, workgroup barrier only
-      if (!in_episode) {
-        in_episode = true;
-        ++episodes;
-      }
-      eager_level<SIGMA, SliceT, BLOCK>(a, level, v, prev_queue, engine, fallback, feat, threadIdx.x, BLOCK,
-                                        wave_in_block(), BLOCK / 64);
-      block_sync_mem();
-      if (threadIdx.x == 0 && level < a.log_cap) {
-        const unsigned long long t = dev_ticks();
-        a.log[level].t_mid = t;
-        a.log[level].t_end = t;
-      }
-      LevelView nv = read_level_atomic(a.ctl, (level + 1) % kStatSlots);
-      nv.light = 0;
-      nv.heavy = 0;
-      nv.cumv = v.cumv + nv.frontier;
-      nv.cume = v.cume + nv.fedges;
-      prev_frontier = v.frontier;
-      prev_queue = v.queue;
-      v = nv;
-      ++level;
-      // progress for the waiting workgroups: their time bound restarts with every level
-      if (threadIdx.x == 0)
-        __hip_atomic_store(&a.ctl->single_progress[0], level, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (__hip_atomic_load(&a.ctl->error[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-      continue;
-    }
-    if (single) {
-      // wait for workgroup 0's episode, bounded like a barrier; the bound
-      // restarts at every level the episode finishes
+  uint32_t prev_queue = 0;
+  while (v.frontier != 0) {
+    const int engine = decide_level<true>(a, v, level, mlp, learned);
+    if (episode_eligible(a, v, engine)) {
+      // workgroup 0 runs levels alone; the others wait for the level it stops
+      // at. It leaves no word of the level before behind, so prev_queue is 0.
       ++episodes;
-      if (threadIdx.x == 0) {
-        unsigned long long t0 = dev_ticks();
-        int seen = -1;
-        bool ok = true;
-        while (__hip_atomic_load(&a.ctl->single_gen[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < episodes) {
-          if (__hip_atomic_load(&a.ctl->error[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-            ok = false;
-            break;
-          }
-          const int prog = __hip_atomic_load(&a.ctl->single_progress[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (prog != seen) {
-            seen = prog;
-            t0 = dev_ticks();
-          }
-          if (dev_ticks() - t0 > a.timeout_ticks) {
-            __hip_atomic_store(&a.ctl->error[0], static_cast<int>(BLEST_ERR_TIMEOUT), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            ok = false;
-            break;
-          }
-          __builtin_amdgcn_s_sleep(2);
+      if (blockIdx.x == 0) {
+        const int next = uniform(eager_episode<SIGMA, BLOCK>(a, level, v, prev_queue, mlp, learned, to_lds(&s_ep)));
+        block_sync_mem();
+        if (threadIdx.x == 0) {
+          __hip_atomic_store(&a.ctl->single_level[0], next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(&a.ctl->single_gen[0], episodes, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+          // counters were updated by device atomics during the episode; drop
+          // any cached copies before the plain loads of grid mode
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+          s_level = next;
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        s_level = ok ? __hip_atomic_load(&a.ctl->single_level[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+      } else if (threadIdx.x == 0) {
+        s_level = wait_episode(a, episodes);
       }
       __syncthreads();
       if (s_level < 0 || __hip_atomic_load(&a.ctl->error[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
         return;
-      level = s_level;
+      level = uniform(s_level);
+      if (threadIdx.x == 0) s_ep.found = 0;
+      if (threadIdx.x < 12) s_ep.sum[0][threadIdx.x] = 0u;
+      __syncthreads();  // s_level is read before the next episode writes it
       v = read_level(a.ctl, level % kStatSlots);
-      v.light = 0;
-      v.heavy = 0;
-      const LevelView pv = read_level(a.ctl, (level + kStatSlots - 1) % kStatSlots);
-      prev_frontier = pv.frontier;
-      prev_queue = pv.queue;
+      v.light = v.heavy = 0;
+      prev_queue = 0;
       continue;
     }
-    eager_level<SIGMA, SliceT, BLOCK>(a, level, v, prev_queue, engine, fallback, feat, gtid, nthreads, gwave, nwaves);
-    if (!grid_barrier(a.ctl, bc)) return;
+    eager_level<SIGMA, SliceT, BLOCK>(a, level, v, prev_queue, engine, gtid, nthreads, gwave, nwaves, to_lds(&s_ep));
+    if (!grid_barrier((Ctl*)a.ctl, bc)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0 && level < a.log_cap) {
       const unsigned long long t = dev_ticks();
       a.log[level].t_mid = t;
@@ -2028,7 +2399,6 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_eager(BfsArgs a) {
     nv.heavy = 0;
     nv.cumv = v.cumv + nv.frontier;
     nv.cume = v.cume + nv.fedges;
-    prev_frontier = v.frontier;
     prev_queue = v.queue;
     v = nv;
     ++level;
@@ -2043,26 +2413,26 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_eager(BfsArgs a) {
 // ------------------------------------------------------ per-stage kernels
 
 template <int SIGMA, int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_bfs_clear(BfsArgs a) {
+__global__ void __launch_bounds__(BLOCK) k_bfs_clear(BfsArgs args) {
+  args_ref<BfsArgs> a = kernel_args(args);
   const long long nthreads = static_cast<long long>(gridDim.x) * BLOCK;
   clear_state<SIGMA>(a, static_cast<long long>(blockIdx.x) * BLOCK + threadIdx.x, nthreads);
   if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->done[0] = 0;
 }
 
 template <int SIGMA, int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_bfs_seed(BfsArgs a) {
+__global__ void __launch_bounds__(BLOCK) k_bfs_seed(BfsArgs args) {
+  args_ref<BfsArgs> a = kernel_args(args);
   seed_source<SIGMA>(a);
 }
 
 template <int SIGMA, class SliceT, int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_bfs_stage1(BfsArgs a, int level, long long prev_slot_frontier_unused) {
+__global__ void __launch_bounds__(BLOCK) k_bfs_stage1(BfsArgs args, int level, long long prev_slot_frontier_unused) {
+  args_ref<BfsArgs> a = kernel_args(args);
   extern __shared__ float s_mlp[];
   if (a.ctl->done[0]) return;
-  const unsigned nblocks = gridDim.x;
-  const long long nthreads = static_cast<long long>(nblocks) * BLOCK;
-  const long long gtid = static_cast<long long>(blockIdx.x) * BLOCK + threadIdx.x;
   const long long gwave = static_cast<long long>(blockIdx.x) * (BLOCK / 64) + wave_in_block();
-  const long long nwaves = static_cast<long long>(nblocks) * (BLOCK / 64);
+  const long long nwaves = static_cast<long long>(gridDim.x) * (BLOCK / 64);
   const LevelView v = read_level(a.ctl, level % kStatSlots);
   if (v.frontier == 0) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -2071,28 +2441,25 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_stage1(BfsArgs a, int level, long
     }
     return;
   }
-  const long long prev = level > 0 ? read_level(a.ctl, (level + kStatSlots - 1) % kStatSlots).frontier : 0;
   const bool learned = a.policy == BLEST_POLICY_LEARNED && a.mlp != nullptr && a.mlp->valid;
   if (learned) {
-    mlp_to_lds(a.mlp, s_mlp);
+    mlp_to_lds((const MlpDev*)a.mlp, s_mlp);
     __syncthreads();
   }
-  float feat[kMaxSwitchFeatures];
-  level_features(feat, v, a, level, prev);
-  int fallback = 0;
-  const int engine = choose_engine(a, v, feat, level, learned ? s_mlp : nullptr, &fallback);
+  const int engine = decide_level<false>(a, v, level, to_lds((const float*)s_mlp), learned);
   if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) log_level(a, level, v, engine, fallback, feat);
+    if (threadIdx.x == 0) log_begin(a, level);
     const int nslot = (level + 1) % kStatSlots;
     for (int t = threadIdx.x; t < kStatFields; t += BLOCK) a.ctl->acc[nslot][t][0] = 0ULL;
   }
   __shared__ __attribute__((aligned(16))) uint32_t pm[kPanelMaxBytes / 4];
-  run_engine<SIGMA, SliceT, BLOCK>(a, engine, level & 1, level % kStatSlots, v, gtid, nthreads, gwave, nwaves, nullptr,
+  run_engine<SIGMA, SliceT, BLOCK, false>(a, engine, level & 1, level % kStatSlots, v, gwave, nwaves, (lptr<int>)to_lds(pm),
                                    to_lds(pm));
 }
 
 template <int SIGMA, int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_bfs_stage2(BfsArgs a, int level) {
+__global__ void __launch_bounds__(BLOCK) k_bfs_stage2(BfsArgs args, int level) {
+  args_ref<BfsArgs> a = kernel_args(args);
   if (a.ctl->done[0]) return;
   const LevelView v = read_level(a.ctl, level % kStatSlots);
   if (v.frontier == 0) return;
@@ -2212,45 +2579,52 @@ hipError_t bfs_grid_size_eager(const DevGraph& g, int blocks_per_cu, int* grid) 
   // (fewer arrivals per device-wide barrier) unless asked otherwise
   nb = blocks_per_cu > 0 ? std::min(nb, blocks_per_cu) : 1;
   *grid = nb * g.num_cu;
+  // A graph that few workgroups sweep gets few, for the same reason: a 4096-vertex
+  // R-MAT (56,314 slices) takes 149 us a call on 256 workgroups, 141 on 64, 139 on
+  // 32 and on 16; 65,536 vertices with 1.38 M slices take 190, 221 and 281 on 256,
+  // 64 and 32. 2048 slices a workgroup is one pass of its waves over the queue.
+  if (blocks_per_cu <= 0)
+    *grid = static_cast<int>(std::min<int64_t>(*grid, std::max<int64_t>(32, (g.nslices + 2047) / 2048)));
   return hipSuccess;
 }
 
 BfsArgs bfs_args(const DevGraph& g) {
   BfsArgs a{};
-  a.rp = g.rp;
-  a.col = g.col;
-  a.slice_ptr = g.slice_ptr;
-  a.slices = g.slices;
-  a.degmask = g.degmask;
-  a.rp_in = g.rp_in;
-  a.col_in = g.col_in;
-  a.degmask_in = g.degmask_in;
-  a.orig_id = g.orig_id;
+  a.rp = to_global(g.rp);
+  a.col = to_global(g.col);
+  a.slice_ptr = to_global(g.slice_ptr);
+  a.slices = to_global(g.slices);
+  a.degmask = to_global(g.degmask);
+  a.rp_in = to_global(g.rp_in);
+  a.col_in = to_global(g.col_in);
+  a.degmask_in = to_global(g.degmask_in);
+  a.orig_id = to_global(g.orig_id);
   a.n = g.n;
   a.m = g.m;
   a.nsets = g.nsets;
   a.tau = g.tau;
-  a.vis = g.vis;
-  a.front = g.front;
+  a.sigma = g.sigma;
+  a.vis = to_global(g.vis);
+  a.front = to_global(g.front);
   a.fstride = static_cast<long long>(g.fstride);
-  a.mark = g.mark;
-  a.queue[2] = g.queue[2];
+  a.mark = to_global(g.mark);
+  a.queue[2] = to_global(g.queue[2]);
   for (int i = 0; i < 2; ++i) {
-    a.queue[i] = g.queue[i];
-    a.flight[i] = g.flight[i];
-    a.fheavy[i] = g.fheavy[i];
+    a.queue[i] = to_global(g.queue[i]);
+    a.flight[i] = to_global(g.flight[i]);
+    a.fheavy[i] = to_global(g.fheavy[i]);
   }
-  a.ctl = g.ctl;
-  a.part = g.part;
-  a.log = g.log;
+  a.ctl = to_global(g.ctl);
+  a.part = to_global(g.part);
+  a.log = to_global(g.log);
   a.log_cap = g.log_cap;
-  a.mlp = g.mlp;
+  a.mlp = to_global(g.mlp);
   a.prefilter = g.prefilter;
   a.count_work = g.count_work;
   a.single_block = g.single_block;
-  a.pwords = g.pwords;
-  a.pbase = g.pbase;
-  a.pptr = g.pptr;
+  a.pwords = to_global(g.pwords);
+  a.pbase = to_global(g.pbase);
+  a.pptr = to_global(g.pptr);
   a.npanels = static_cast<int32_t>(g.npanels);
   a.panel_rb = g.panel_rb;
   a.panel_mode = g.panel_mode;

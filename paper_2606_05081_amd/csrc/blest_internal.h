@@ -52,6 +52,17 @@ template <class T>
 using cptr = T*;
 #endif
 
+template <class T>
+__host__ __device__ __forceinline__ gptr<T> to_global(T* p) {
+  return (gptr<T>)p;
+}
+#if defined(__HIP_DEVICE_COMPILE__)
+template <class T>
+__host__ __device__ __forceinline__ gptr<T> to_global(gptr<T> p) {
+  return p;
+}
+#endif
+
 // Entries past the last chunk base of the panel copy, so that a wave may read
 // the bases of a whole batch of consecutive chunks with scalar loads.
 constexpr int kPanelBasePad = 8;
@@ -146,34 +157,34 @@ struct MlpDev {
 
 // Kernel arguments of one single-source traversal (passed by value).
 struct BfsArgs {
-  const int32_t* rp;
-  const int32_t* col;
-  const int32_t* rp_in;     // in-arcs, read by the bottom-up engines (rp/col for an undirected graph)
-  const int32_t* col_in;
-  const void* degmask_in;   // vertices with an in-arc (degmask for an undirected graph)
-  const uint32_t* slice_ptr;
-  const void* slices;
-  const void* degmask;
-  const int32_t* orig_id;
+  gptr<const int32_t> rp;
+  gptr<const int32_t> col;
+  gptr<const int32_t> rp_in;     // in-arcs, read by the bottom-up engines (rp/col for an undirected graph)
+  gptr<const int32_t> col_in;
+  gptr<const void> degmask_in;   // vertices with an in-arc (degmask for an undirected graph)
+  gptr<const uint32_t> slice_ptr;
+  gptr<const void> slices;
+  gptr<const void> degmask;
+  gptr<const int32_t> orig_id;
   int64_t n, m, nsets;
   int64_t nvss, nslices;  // totals of the BVSS (switch features)
-  int32_t tau;
+  int32_t tau, sigma;
   // working state
-  void* vis;       // sigma-bit visited word per slice set (V_curr)
-  void* front;     // sigma-bit frontier words per slice set, three buffers fstride bytes apart: the lazy
+  gptr<void> vis;       // sigma-bit visited word per slice set (V_curr)
+  gptr<void> front;     // sigma-bit frontier words per slice set, three buffers fstride bytes apart: the lazy
                    // scheme uses the first two (by level parity), the eager scheme all three (level mod 3)
   long long fstride;  // bytes from the first frontier buffer to the second
-  uint8_t* mark;   // one byte per vertex: lazily marked in Stage 1 (V_next)
-  uint4* queue[3]; // VSS descriptors {first slice, count, frontier bits, set}; the eager
+  gptr<uint8_t> mark;   // one byte per vertex: lazily marked in Stage 1 (V_next)
+  gptr<uint4> queue[3]; // VSS descriptors {first slice, count, frontier bits, set}; the eager
                    // scheme rotates all three, the lazy scheme uses the first two
-  int32_t* flight[2];             // light frontier vertices
-  unsigned long long* fheavy[2];  // heavy frontier edge chunks: (vertex << 32) | first edge offset
-  Ctl* ctl;
-  long long* part;  // per-workgroup partial Stage 2 counters (grid size x 8)
-  LevelRec* log;
+  gptr<int32_t> flight[2];             // light frontier vertices
+  gptr<unsigned long long> fheavy[2];  // heavy frontier edge chunks: (vertex << 32) | first edge offset
+  gptr<Ctl> ctl;
+  gptr<long long> part;  // per-workgroup partial Stage 2 counters (grid size x 8)
+  gptr<LevelRec> log;
   int32_t log_cap;
-  const MlpDev* mlp;
-  int32_t* levels; // output, input ids
+  gptr<const MlpDev> mlp;
+  gptr<int32_t> levels; // output, input ids
   int32_t src;     // internal id
   int32_t policy;
   float eta;
@@ -183,9 +194,9 @@ struct BfsArgs {
   int32_t count_work;  // accumulate F_WORK (adjacency entries read per level)
   int32_t single_block;  // run small levels on workgroup 0 alone
   // panel-blocked BVSS copy (sigma = 8, 32-bit slices); npanels = 0 if absent
-  const uint32_t* pwords;  // nchunks * 64 slice words
-  const uint32_t* pbase;   // first set of each chunk (+ kPanelBasePad entries of padding)
-  const uint32_t* pptr;    // npanels + 1 chunk offsets
+  gptr<const uint32_t> pwords;  // nchunks * 64 slice words
+  gptr<const uint32_t> pbase;   // first set of each chunk (+ kPanelBasePad entries of padding)
+  gptr<const uint32_t> pptr;    // npanels + 1 chunk offsets
   int32_t npanels;
   int32_t panel_rb;        // log2 rows per panel
   int32_t panel_mode;      // 1: dense levels only, 2: every BVSS level

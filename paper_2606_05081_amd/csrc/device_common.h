@@ -41,16 +41,6 @@ __device__ __forceinline__ unsigned long long dev_ticks() { return __builtin_amd
 
 __device__ __forceinline__ int lane_id() { return static_cast<int>(threadIdx.x & 63u); }
 
-template <class T>
-__host__ __device__ __forceinline__ gptr<T> to_global(T* p) {
-  return (gptr<T>)p;
-}
-#if defined(__HIP_DEVICE_COMPILE__)
-template <class T>
-__host__ __device__ __forceinline__ gptr<T> to_global(gptr<T> p) {
-  return p;
-}
-#endif
 // A kernel's arguments, read where they lie: kernel code hands the kernarg
 // segment (constant memory) on to the functions it calls, and each of those
 // makes the reference wave-uniform, so an argument costs a scalar load that
