@@ -82,24 +82,6 @@ __device__ __forceinline__ LevelView read_level(gptr<const Ctl> ctl, int slot) {
   return v;
 }
 
-// Same, with agent-scope loads (used inside a single-workgroup episode, where
-// the counters were just updated by device atomics without a barrier).
-__device__ __forceinline__ LevelView read_level_atomic(gptr<const Ctl> ctl, int slot) {
-  const gptr<const unsigned long long> acc = &ctl->acc[slot][0][0];
-  LevelView v;
-  v.frontier = u32_uniform(ld_relaxed_u64(acc + F_FRONTIER * kPad));
-  v.queue = u32_uniform(ld_relaxed_u64(acc + F_QUEUE * kPad));
-  v.qslices = u32_uniform(ld_relaxed_u64(acc + F_QSLICES * kPad));
-  v.fedges = u32_uniform(ld_relaxed_u64(acc + F_FEDGES * kPad));
-  v.deg32 = u32_uniform(ld_relaxed_u64(acc + F_DEG32 * kPad));
-  v.deg1024 = u32_uniform(ld_relaxed_u64(acc + F_DEG1024 * kPad));
-  v.light = u32_uniform(ld_relaxed_u64(acc + F_LIGHT * kPad));
-  v.heavy = u32_uniform(ld_relaxed_u64(acc + F_HEAVY * kPad));
-  v.cumv = u32_uniform(ld_relaxed_u64(acc + F_CUMV * kPad));
-  v.cume = u32_uniform(ld_relaxed_u64(acc + F_CUME * kPad));
-  return v;
-}
-
 // The 12 switch features of a level (network inputs before standardising).
 __device__ __forceinline__ void level_features(float (&f)[kMaxSwitchFeatures], const LevelView& v, args_ref<BfsArgs> a) {
   const long long unv = a.n - v.cumv, unv_e = a.m - v.cume;
@@ -438,52 +420,50 @@ __device__ __forceinline__ void panel_test_batch(const PanelBatch& B, uint32_t d
   }
 }
 
-// Stage 2 for one 32-row group (four slice sets, sigma = 8) whose new
-// vertices are x: level writes and the counters of finalize_count. The 33
-// row pointers and 5 slice pointers of the group are loaded at once (rp and
-// slice_ptr are padded on the device so these loads stay in bounds).
-__device__ __forceinline__ void panel_count_group(args_ref<BfsArgs> a, long long g, uint32_t x, int new_level,
-                                                  long long (&st)[kParts]) {
+// Stage 2 of one panel (sigma = 8) by the workgroup that owns it: x words of
+// its W 32-row groups in pm[8 * j], levels and the counters of finalize_count.
+// A lane per vertex, as in finalize_windows: a thread that took its group's 32
+// vertices left three quarters of the workgroup idle (128 groups a panel at
+// 1 M vertices).
+template <int BLOCK>
+__device__ __forceinline__ void panel_count_rows(args_ref<BfsArgs> a, lptr<const uint32_t> pm, uint32_t row0,
+                                                 uint32_t W, int new_level, uint32_t (&st)[kParts]) {
+  constexpr int GB = 8;  // vertices per thread whose loads are issued together
   const gptr<const int32_t> rp = a.rp;
-  const gptr<const uint32_t> sp = a.slice_ptr;
   const gptr<int32_t> levels = a.levels;
   const gptr<const int32_t> orig_id = a.orig_id;
-  const uint32_t tau = static_cast<uint32_t>(a.tau);
-  const gptr<const int4> r4 = (gptr<const int4>)(rp + 32 * g);
-  int r[33];
+  for (uint32_t base = threadIdx.x; base < 32u * W; base += BLOCK * GB) {
+    bool on[GB];
+    int r0[GB], r1[GB], id[GB];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int4 q = r4[i];
-    r[4 * i + 0] = q.x;
-    r[4 * i + 1] = q.y;
-    r[4 * i + 2] = q.z;
-    r[4 * i + 3] = q.w;
-  }
-  r[32] = rp[32 * g + 32];
-  const uint4 s4 = *(gptr<const uint4>)(sp + 4 * g);
-  const uint32_t spt[5] = {s4.x, s4.y, s4.z, s4.w, sp[4 * g + 4]};
+    for (int j = 0; j < GB; ++j) {
+      const uint32_t v = base + j * BLOCK;
+      on[j] = v < 32u * W && ((pm[8 * (v >> 5)] >> (v & 31u)) & 1u);
+    }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t xb = (x >> (8 * k)) & 0xffu;
-    if (!xb) continue;
+    for (int j = 0; j < GB; ++j) {
+      const uint32_t u = row0 + base + j * BLOCK;
+      r0[j] = r1[j] = id[j] = 0;
+      if (on[j]) {
+        r0[j] = rp[u];
+        r1[j] = rp[u + 1];
+        id[j] = orig_id ? orig_id[u] : static_cast<int32_t>(u);
+      }
+    }
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      if (!((xb >> b) & 1u)) continue;
-      const long long u = 32 * g + 8 * k + b;
-      const int d = r[8 * k + b + 1] - r[8 * k + b];
+    for (int j = 0; j < GB; ++j) {
+      if (!on[j]) continue;
+      const int d = r1[j] - r0[j];
+      levels[id[j]] = new_level;
       st[0] += 1;
-      st[2] += d;
+      st[2] += static_cast<uint32_t>(d);
       st[3] += d >= 32;
       st[4] += d >= 1024;
       if (d > kLightMax)
         st[6] += (d + kHeavyChunk - 1) / kHeavyChunk;
       else
         st[5] += 1;
-      levels[orig_id ? orig_id[u] : u] = new_level;
     }
-    const uint32_t ns = spt[k + 1] - spt[k];
-    st[1] += ns;
-    st[7] += (ns + tau - 1) / tau;
   }
 }
 
@@ -514,8 +494,8 @@ __device__ __attribute__((noinline)) long long engine_panel(args_ref<BfsArgs> a_
   const bool fused = new_level >= 0;
   // fused: the workgroup's Stage 2 counters, summed per panel (kept out of
   // registers during the chunk loop)
-  __shared__ unsigned long long s_part[kParts];
-  if (threadIdx.x < kParts) s_part[threadIdx.x] = 0ULL;
+  __shared__ uint32_t s_part[kParts];
+  if (threadIdx.x < kParts) s_part[threadIdx.x] = 0u;
   const uint32_t lane = static_cast<uint32_t>(lane_id());
   const uint32_t wv = static_cast<uint32_t>(wave_in_block());
   long long work = 0;
@@ -571,7 +551,7 @@ __device__ __attribute__((noinline)) long long engine_panel(args_ref<BfsArgs> a_
     }
     __syncthreads();
     const size_t wb = static_cast<size_t>(p) * W;
-    long long st[kParts] = {0, 0, 0, 0, 0, 0, 0, 0};
+    uint32_t st[kParts] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
     for (uint32_t j = threadIdx.x; j < W; j += BLOCK) {
       const uint32_t m = gather8(pm64[4 * j]) | (gather8(pm64[4 * j + 1]) << 8) | (gather8(pm64[4 * j + 2]) << 16) |
                          (gather8(pm64[4 * j + 3]) << 24);
@@ -583,7 +563,20 @@ __device__ __attribute__((noinline)) long long engine_panel(args_ref<BfsArgs> a_
           if (x) vis32[wb + j] = old | x;
         }
         next32[wb + j] = x;
-        if (x) panel_count_group(a, static_cast<long long>(wb + j), x, new_level, st);
+        pm[8 * j] = x;  // (this thread's own marks, read above)
+        if (x) {
+          // the group's five slice pointers (slice_ptr is padded on the device)
+          const gptr<const uint32_t> sp = a.slice_ptr + 4 * (wb + j);
+          const uint32_t tau = static_cast<uint32_t>(a.tau);
+          const uint4 s4 = *(gptr<const uint4>)sp;
+          const uint32_t spt[5] = {s4.x, s4.y, s4.z, s4.w, sp[4]};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint32_t ns = (x >> (8 * k)) & 0xffu ? spt[k + 1] - spt[k] : 0u;
+            st[1] += ns;
+            st[7] += (ns + tau - 1) / tau;
+          }
+        }
         continue;
       }
       if (!m) continue;
@@ -599,12 +592,13 @@ __device__ __attribute__((noinline)) long long engine_panel(args_ref<BfsArgs> a_
       mark16[2 * (wb + j) + 1] = make_uint4(q[4], q[5], q[6], q[7]);
     }
     if (fused) {
+      __syncthreads();
+      panel_count_rows<BLOCK>(a, pm, static_cast<uint32_t>(p) << rb, W, new_level, st);
 #pragma unroll
       for (int f = 0; f < kParts; ++f) {
-        const long long t = wave_sum(st[f]);
+        const uint32_t t = wave_sum(st[f]);
         if (lane == 0 && t)
-          __hip_atomic_fetch_add(&s_part[f], static_cast<unsigned long long>(t), __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(&s_part[f], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
     __syncthreads();
@@ -614,8 +608,7 @@ __device__ __attribute__((noinline)) long long engine_panel(args_ref<BfsArgs> a_
     // every workgroup stores its partials (zero if it owns no panel)
     __syncthreads();
     if (threadIdx.x < kParts)
-      a.part[static_cast<long long>(blockIdx.x) * kParts + threadIdx.x] =
-          static_cast<long long>(s_part[threadIdx.x]);
+      a.part[static_cast<long long>(threadIdx.x) * gridDim.x + blockIdx.x] = s_part[threadIdx.x];
   }
   return lane == 0 ? work : 0;
 }
@@ -806,99 +799,113 @@ __device__ __forceinline__ void run_engine(args_ref<BfsArgs> a, int engine, int 
 
 // ------------------------------------------------------------ Stage 2
 
-
-
-
-// Stage 2 over windows of 2*BLOCK slice sets; set_at(win, k) gives the set
+// Stage 2 over windows of SPT * BLOCK slice sets; set_at(win, k) gives the set
 // handled by this thread in slot k of window win, or -1. MODE:
 //  FIN_ATOMIC  marks -> visited/frontier/levels, and the lists, with output
 //              space reserved per window by one device atomic per list;
 //  FIN_LOCAL   the same with the block-local cursors `local` (one workgroup
 //              alone: no atomics; the caller stores the totals);
 //  FIN_COUNT   marks -> visited/frontier/levels and counts only: every set's
-//              frontier word is rewritten (0 if it gained nothing) and the
-//              list sizes are added to st[5..7]; no list is written;
+//              frontier word is rewritten (0 if it gained nothing); no list is
+//              written;
 //  FIN_EMIT    no state change: the frontier words written by FIN_COUNT give
 //              the new vertices, and the lists asked for (want_push,
 //              want_queue) are written from the cursors `local`, which the
 //              caller presets to this block's offsets.
-// st[] accumulates frontier, queued slices, frontier edges, degree >= 32,
-// degree >= 1024 and (FIN_COUNT) light, heavy and queue entries. Queue
-// descriptors and heavy edge chunks are written wave-cooperatively: each lane
-// finds the run that owns its output index by a binary search over the wave's
-// prefix sums, so a hub set with thousands of VSSs costs a few wave steps.
+// The modes that update state add to st[] the level's frontier, queued slices,
+// frontier edges, degree >= 32, degree >= 1024, light, heavy and queue entries
+// (all below 2^31), whichever lists are written.
+//
+// A lane reads a set's marks and visited word, but the new vertices are
+// handled a lane each: lane i of group j takes bit i % sigma of the word that
+// lane j * 64 / sigma + i / sigma holds, so row pointers and input ids of 64
+// consecutive vertices are coalesced loads. (A lane that walked its set's
+// vertices itself issued 9 + 8 loads and 8 stores of its own per set, 64 cache
+// lines each, for 4 sets: 15 us of a 25 to 30 us level of a 1 M vertex graph,
+// 64 of whose 256 workgroups had a window.) What remains is a chain of four
+// round trips to memory: marks; visited words; slice and row pointers and
+// input ids; levels.
+// Queue descriptors and heavy edge chunks are written wave-cooperatively: each
+// lane finds the run that owns its output index by a binary search over the
+// wave's prefix sums, so a hub set with thousands of VSSs costs a few steps.
 enum FinMode : int { FIN_ATOMIC = 0, FIN_LOCAL = 1, FIN_COUNT = 2, FIN_EMIT = 3 };
 
-// Slice sets per thread in one window of the Stage 2 sweep (a window is
-// BLOCK * kFinSpt consecutive sets); their loads are issued together.
+// Slice sets per thread in one window: 1 where that already gives every
+// workgroup a window at most (then the windows spread over the most
+// workgroups), else 4, whose loads are issued together.
 constexpr int kFinSpt = 4;
+__device__ __forceinline__ bool fin_wide(args_ref<BfsArgs> a, int block) {
+  return a.nsets > 2LL * block * static_cast<long long>(gridDim.x);
+}
 
-template <int SIGMA, int BLOCK, int MODE, class SetAt>
-__device__ __forceinline__ void finalize_windows(args_ref<BfsArgs> a, int new_level, gptr<unsigned long long> acc, int sel_out,
-                                 long long win0, long long nwin, long long wstep, SetAt set_at, long long (&st)[8],
-                                 lptr<unsigned long long> local, bool want_push = true, bool want_queue = true) {
+// The output run that holds index i: the lane whose inclusive prefix sum is
+// the first above i.
+__device__ __forceinline__ int run_owner(int incl, int i) {
+  int lo = 0;
+#pragma unroll
+  for (int stp = 32; stp >= 1; stp >>= 1)
+    if (__shfl(incl, lo + stp - 1, 64) <= i) lo += stp;
+  return lo & 63;
+}
+
+// Whether a level may be explored by push (the vertex lists are needed).
+__device__ __forceinline__ bool push_possible(args_ref<BfsArgs> a) {
+  return a.probe || (a.policy != BLEST_POLICY_HEURISTIC && a.policy != BLEST_POLICY_BVSS &&
+                     a.policy != BLEST_POLICY_BOTTOM_UP);
+}
+
+template <int SIGMA, int BLOCK, int MODE, int SPT, class SetAt>
+__device__ __forceinline__ void finalize_windows(args_ref<BfsArgs> a, int new_level, gptr<unsigned long long> acc,
+                                                 int sel_out, int win0, int nwin, int wstep, SetAt set_at,
+                                                 uint32_t (&st)[kParts], lptr<uint32_t> local, bool want_push,
+                                                 bool want_queue) {
   using M = typename MaskOf<SIGMA>::T;
-  constexpr int SPT = kFinSpt;
   constexpr bool UPDATE = MODE != FIN_EMIT;
+  constexpr int GB = 8;  // groups of 64 vertices whose loads are issued together (a wave's 64 sets have SIGMA)
   __shared__ int lds32[3 * (BLOCK / 64)];
-  __shared__ unsigned long long bases[3];
+  __shared__ uint32_t bases[3];
   gptr<M> __restrict__ vis = (gptr<M>)a.vis;
   gptr<M> __restrict__ front = (gptr<M>)front_buf(a, sel_out);
   gptr<uint8_t> __restrict__ mark = a.mark;
   gptr<const int32_t> __restrict__ rp = a.rp;
   gptr<const uint32_t> __restrict__ sp = a.slice_ptr;
   const uint32_t tau = static_cast<uint32_t>(a.tau);
-  gptr<int32_t> __restrict__ light = a.flight[sel_out];
-  gptr<unsigned long long> __restrict__ heavy = a.fheavy[sel_out];
-  gptr<uint4> __restrict__ queue = a.queue[sel_out];
   gptr<int32_t> __restrict__ levels = a.levels;
   const gptr<const int32_t> __restrict__ orig_id = a.orig_id;
   const int lane = lane_id();
-  const bool need_rp = UPDATE || want_push;
+  const int vbit = lane % SIGMA, vset = lane / SIGMA;  // this lane's vertex in a group: bit, set of the group
   const bool need_sp = UPDATE || want_queue;
-  for (long long win = win0; win < nwin; win += wstep) {
-    // The SPT sets of a thread are finalised in phases, each issuing the
-    // loads of all SPT sets before any is used (marks; visited words; row and
-    // slice pointers; input ids), so a window costs four dependent memory
-    // round trips rather than four per set.
+  for (int win = win0; win < nwin; win += wstep) {
     M nw[SPT];
-    long long sset[SPT];
-    int nl[SPT], nh[SPT], nq[SPT];
-    M got[SPT];
+    int sset[SPT];
+    int nq[SPT];
 #pragma unroll
     for (int k = 0; k < SPT; ++k) {
-      const long long s = set_at(win, k);
+      const int s = set_at(win, k);
       sset[k] = s;
       nw[k] = 0;
-      nl[k] = nh[k] = nq[k] = 0;
-      got[k] = 0;
+      nq[k] = 0;
       if (s >= 0) {
         if constexpr (UPDATE)
-          got[k] = load_marks<SIGMA>(mark + s * SIGMA);
+          nw[k] = load_marks<SIGMA>(mark + static_cast<long long>(s) * SIGMA);
         else
-          got[k] = front[s];
+          nw[k] = front[s];
       }
     }
     if constexpr (UPDATE) {
       M old[SPT];
 #pragma unroll
-      for (int k = 0; k < SPT; ++k) old[k] = got[k] ? vis[sset[k]] : M(0);
+      for (int k = 0; k < SPT; ++k) old[k] = nw[k] ? vis[sset[k]] : M(0);
 #pragma unroll
       for (int k = 0; k < SPT; ++k) {
-        const long long s = sset[k];
+        const int s = sset[k];
         if (s < 0) continue;
-        const M x = static_cast<M>(got[k] & ~old[k]);
-        if (got[k]) clear_marks<SIGMA>(mark + s * SIGMA);
+        const M x = static_cast<M>(nw[k] & ~old[k]);
+        if (nw[k]) clear_marks<SIGMA>(mark + static_cast<long long>(s) * SIGMA);
         if (x) vis[s] = static_cast<M>(old[k] | x);
-        if (MODE == FIN_COUNT)
-          front[s] = x;
-        else if (x)
-          front[s] = x;
+        if (MODE == FIN_COUNT || x) front[s] = x;
         nw[k] = x;
       }
-    } else {
-#pragma unroll
-      for (int k = 0; k < SPT; ++k) nw[k] = got[k];
     }
     uint32_t p0[SPT], p1[SPT];
 #pragma unroll
@@ -909,74 +916,50 @@ __device__ __forceinline__ void finalize_windows(args_ref<BfsArgs> a, int new_le
         p1[k] = sp[sset[k] + 1];
       }
     }
-    if constexpr (SIGMA == 8) {
-      // eight vertices per set: every set's row pointers and input ids fit
-      // in registers at once
-      int r[SPT][SIGMA + 1];
-#pragma unroll
-      for (int k = 0; k < SPT; ++k)
-        if (nw[k] && need_rp) load_set_rp<SIGMA>(rp, sset[k], r[k]);
-      if constexpr (UPDATE) {
-        int32_t id[SPT][SIGMA];
-#pragma unroll
-        for (int k = 0; k < SPT; ++k)
-#pragma unroll
-          for (int b = 0; b < SIGMA; ++b) {
-            const long long u = sset[k] * SIGMA + b;
-            id[k][b] = ((nw[k] >> b) & 1u) ? (orig_id ? orig_id[u] : static_cast<int32_t>(u)) : 0;
-          }
-#pragma unroll
-        for (int k = 0; k < SPT; ++k)
-#pragma unroll
-          for (int b = 0; b < SIGMA; ++b)
-            if ((nw[k] >> b) & 1u) levels[id[k][b]] = new_level;
-      }
+    int nl = 0, nh = 0;
+    if (UPDATE || want_push) {
 #pragma unroll
       for (int k = 0; k < SPT; ++k) {
-        if (!nw[k] || !need_rp) continue;
+        if (!__ballot(nw[k] != 0)) continue;
+#pragma unroll 1
+        for (int j0 = 0; j0 < SIGMA; j0 += GB) {
+          bool on[GB];
+          int u[GB], r0[GB], r1[GB], id[GB];
 #pragma unroll
-        for (int b = 0; b < SIGMA; ++b) {
-          if (!((nw[k] >> b) & 1u)) continue;
-          const int d = r[k][b + 1] - r[k][b];
-          if constexpr (UPDATE) {
-            st[0] += 1;
-            st[2] += d;
-            st[3] += d >= 32;
-            st[4] += d >= 1024;
+          for (int j = 0; j < GB; ++j) {
+            const int owner = (j0 + j) * (64 / SIGMA) + vset;
+            on[j] = (static_cast<uint32_t>(__shfl(static_cast<int>(nw[k]), owner, 64)) >> vbit) & 1u;
+            u[j] = __shfl(sset[k], owner, 64) * SIGMA + vbit;
           }
-          if (d > kLightMax)
-            nh[k] += (d + kHeavyChunk - 1) / kHeavyChunk;
-          else
-            nl[k] += 1;
-        }
-      }
-    } else {
 #pragma unroll
-      for (int k = 0; k < SPT; ++k) {
-        const M x = nw[k];
-        if (!x || !need_rp) continue;
-        const long long s = sset[k];
-        int r[SIGMA + 1];
-        load_set_rp<SIGMA>(rp, s, r);
-#pragma unroll
-        for (int b = 0; b < SIGMA; ++b) {
-          if (!((x >> b) & 1u)) continue;
-          const long long u = s * SIGMA + b;
-          const int d = r[b + 1] - r[b];
-          if constexpr (UPDATE) {
-            st[0] += 1;
-            st[2] += d;
-            st[3] += d >= 32;
-            st[4] += d >= 1024;
-            levels[orig_id ? orig_id[u] : u] = new_level;
+          for (int j = 0; j < GB; ++j) {
+            r0[j] = r1[j] = id[j] = 0;
+            if (on[j]) {
+              r0[j] = rp[u[j]];
+              r1[j] = rp[u[j] + 1];
+              if constexpr (UPDATE) id[j] = orig_id ? orig_id[u[j]] : u[j];
+            }
           }
-          if (d > kLightMax)
-            nh[k] += (d + kHeavyChunk - 1) / kHeavyChunk;
-          else
-            nl[k] += 1;
+#pragma unroll
+          for (int j = 0; j < GB; ++j) {
+            if (!on[j]) continue;
+            const int d = r1[j] - r0[j];
+            if constexpr (UPDATE) {
+              levels[id[j]] = new_level;
+              st[0] += 1;
+              st[2] += static_cast<uint32_t>(d);
+              st[3] += d >= 32;
+              st[4] += d >= 1024;
+            }
+            if (d > kLightMax)
+              nh += (d + kHeavyChunk - 1) / kHeavyChunk;
+            else
+              nl += 1;
+          }
         }
       }
     }
+    int cnt[3] = {0, 0, 0};
 #pragma unroll
     for (int k = 0; k < SPT; ++k) {
       if (nw[k] && need_sp) {
@@ -984,160 +967,122 @@ __device__ __forceinline__ void finalize_windows(args_ref<BfsArgs> a, int new_le
         nq[k] = static_cast<int>((ns + tau - 1) / tau);
         if constexpr (UPDATE) st[1] += ns;
       }
-      if (MODE == FIN_EMIT && !want_push) nl[k] = nh[k] = 0;
+      cnt[2] += nq[k];
     }
     if constexpr (UPDATE) {
-#pragma unroll
-      for (int k = 0; k < SPT; ++k) {
-        st[5] += nl[k];
-        st[6] += nh[k];
-        st[7] += nq[k];
-      }
+      st[5] += static_cast<uint32_t>(nl);
+      st[6] += static_cast<uint32_t>(nh);
+      st[7] += static_cast<uint32_t>(cnt[2]);
     }
     if constexpr (MODE == FIN_COUNT) continue;
-    int cnt[3] = {0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < SPT; ++k) {
-      cnt[0] += nl[k];
-      cnt[1] += nh[k];
-      cnt[2] += nq[k];
+    if (want_push) {
+      cnt[0] = nl;
+      cnt[1] = nh;
     }
     if (!__syncthreads_or(cnt[0] | cnt[1] | cnt[2])) continue;
     int ex[3], tot[3];
     block_exclusive_scan<BLOCK, 3>(cnt, ex, tot, lds32);
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 3) {
+      const int f = threadIdx.x;
+      const uint32_t t = static_cast<uint32_t>(f == 0 ? tot[0] : f == 1 ? tot[1] : tot[2]);
       if (MODE != FIN_ATOMIC) {
-        for (int f = 0; f < 3; ++f) {
-          bases[f] = local[f];
-          local[f] += tot[f];
-        }
+        bases[f] = local[f];
+        local[f] += t;
       } else {
-        bases[0] = tot[0] ? fetch_add_u64(acc + F_LIGHT * kPad, tot[0]) : 0ULL;
-        bases[1] = tot[1] ? fetch_add_u64(acc + F_HEAVY * kPad, tot[1]) : 0ULL;
-        bases[2] = tot[2] ? fetch_add_u64(acc + F_QUEUE * kPad, tot[2]) : 0ULL;
+        bases[f] = t ? static_cast<uint32_t>(
+                           fetch_add_u64(acc + (f == 0 ? F_LIGHT : f == 1 ? F_HEAVY : F_QUEUE) * kPad, t))
+                     : 0u;
       }
     }
     __syncthreads();
-    // light vertices: the owning lane writes its (at most SIGMA) entries
-    long long ol = static_cast<long long>(bases[0]) + ex[0];
+    if (want_push) {
+      // light vertices and heavy edge chunks, group by group
+      gptr<int32_t> __restrict__ light = a.flight[sel_out];
+      gptr<unsigned long long> __restrict__ heavy = a.fheavy[sel_out];
+      uint32_t ol = bases[0] + ex[0], oh = bases[1] + ex[1];
 #pragma unroll
-    for (int k = 0; k < SPT; ++k) {
-      if (!nl[k]) continue;
-      int r[SIGMA + 1];
-      load_set_rp<SIGMA>(rp, sset[k], r);
+      for (int k = 0; k < SPT; ++k) {
+        if (!__ballot(nw[k] != 0)) continue;
+#pragma unroll 1
+        for (int j0 = 0; j0 < SIGMA; j0 += GB) {
+          int u[GB], d[GB];
 #pragma unroll
-      for (int b = 0; b < SIGMA; ++b)
-        if (((nw[k] >> b) & 1u) && r[b + 1] - r[b] <= kLightMax) light[ol++] = static_cast<int32_t>(sset[k] * SIGMA + b);
-    }
-    // queue descriptors and heavy chunks: wave-cooperative expansion
-    long long oq = static_cast<long long>(bases[2]) + ex[2];
-    long long oh = static_cast<long long>(bases[1]) + ex[1];
-#pragma unroll
-    for (int k = 0; k < SPT; ++k) {
-      const uint32_t s0 = nq[k] ? sp[sset[k]] : 0u;
-      const uint32_t ns = nq[k] ? sp[sset[k] + 1] - s0 : 0u;
-      {  // VSS descriptors of this lane's set k
-        const int incl = wave_inclusive_scan(nq[k]);
-        const int total = __shfl(incl, 63, 64);
-        for (int b0 = 0; b0 < total; b0 += 64) {
-          const int i = b0 + lane;
-          int lo = 0;
-#pragma unroll
-          for (int stp = 32; stp >= 1; stp >>= 1)
-            if (__shfl(incl, lo + stp - 1, 64) <= i) lo += stp;
-          const int owner = lo & 63;
-          const int start = __shfl(incl, owner, 64) - __shfl(nq[k], owner, 64);
-          const long long o = __shfl(oq, owner, 64);
-          const uint32_t os0 = __shfl(s0, owner, 64), ons = __shfl(ns, owner, 64);
-          const uint32_t obits = __shfl(static_cast<uint32_t>(nw[k]), owner, 64);
-          const long long os = __shfl(sset[k], owner, 64);
-          if (i < total) {
-            const uint32_t j = static_cast<uint32_t>(i - start), off = j * tau;
-            queue[o + j] = make_uint4(os0 + off, min(tau, ons - off), obits, static_cast<uint32_t>(os));
+          for (int j = 0; j < GB; ++j) {
+            const int owner = (j0 + j) * (64 / SIGMA) + vset;
+            const bool on = (static_cast<uint32_t>(__shfl(static_cast<int>(nw[k]), owner, 64)) >> vbit) & 1u;
+            u[j] = __shfl(sset[k], owner, 64) * SIGMA + vbit;
+            d[j] = on ? rp[u[j] + 1] - rp[u[j]] : -1;
           }
+#pragma unroll
+          for (int j = 0; j < GB; ++j) {
+            if (d[j] >= 0 && d[j] <= kLightMax) light[ol++] = u[j];
+            const int nch = d[j] > kLightMax ? (d[j] + kHeavyChunk - 1) / kHeavyChunk : 0;
+            if (!__ballot(nch != 0)) continue;
+            const int incl = wave_inclusive_scan(nch);
+            const int total = __builtin_amdgcn_readlane(incl, 63);
+            for (int b0 = 0; b0 < total; b0 += 64) {
+              const int i = b0 + lane, o = run_owner(incl, i);
+              const int c = i - (__shfl(incl, o, 64) - __shfl(nch, o, 64));
+              const uint32_t at = static_cast<uint32_t>(__shfl(static_cast<int>(oh), o, 64)) + c;
+              const uint32_t ou = static_cast<uint32_t>(__shfl(u[j], o, 64));
+              if (i < total)
+                heavy[at] = (static_cast<unsigned long long>(ou) << 32) |
+                            static_cast<unsigned long long>(c * kHeavyChunk);
+            }
+            oh += nch;
+          }
+        }
+      }
+    }
+    if (want_queue) {
+      gptr<uint4> __restrict__ queue = a.queue[sel_out];
+      uint32_t oq = bases[2] + ex[2];
+#pragma unroll
+      for (int k = 0; k < SPT; ++k) {
+        const int incl = wave_inclusive_scan(nq[k]);
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        for (int b0 = 0; b0 < total; b0 += 64) {
+          const int i = b0 + lane, o = run_owner(incl, i);
+          const uint32_t c = static_cast<uint32_t>(i - (__shfl(incl, o, 64) - __shfl(nq[k], o, 64)));
+          const uint32_t at = static_cast<uint32_t>(__shfl(static_cast<int>(oq), o, 64)) + c;
+          const uint32_t s0 = static_cast<uint32_t>(__shfl(static_cast<int>(p0[k]), o, 64)) + c * tau;
+          const uint32_t end = static_cast<uint32_t>(__shfl(static_cast<int>(p1[k]), o, 64));
+          const uint32_t bits = static_cast<uint32_t>(__shfl(static_cast<int>(nw[k]), o, 64));
+          const uint32_t s = static_cast<uint32_t>(__shfl(sset[k], o, 64));
+          if (i < total) queue[at] = make_uint4(s0, min(tau, end - s0), bits, s);
         }
         oq += nq[k];
       }
-      {  // heavy edge chunks of this lane's set k
-        const int incl = wave_inclusive_scan(nh[k]);
-        const int total = __shfl(incl, 63, 64);
-        for (int b0 = 0; b0 < total; b0 += 64) {
-          const int i = b0 + lane;
-          int lo = 0;
-#pragma unroll
-          for (int stp = 32; stp >= 1; stp >>= 1)
-            if (__shfl(incl, lo + stp - 1, 64) <= i) lo += stp;
-          const int owner = lo & 63;
-          const int start = __shfl(incl, owner, 64) - __shfl(nh[k], owner, 64);
-          const long long o = __shfl(oh, owner, 64);
-          const uint32_t obits = __shfl(static_cast<uint32_t>(nw[k]), owner, 64);
-          const long long os = __shfl(sset[k], owner, 64);
-          if (i < total) {
-            int j = i - start;
-            int r[SIGMA + 1];
-            load_set_rp<SIGMA>(rp, os, r);
-#pragma unroll
-            for (int b = 0; b < SIGMA; ++b) {
-              const int d = r[b + 1] - r[b];
-              if (!((obits >> b) & 1u) || d <= kLightMax || j < 0) continue;
-              const int nch = (d + kHeavyChunk - 1) / kHeavyChunk;
-              if (j < nch)
-                heavy[o + (i - start)] = (static_cast<unsigned long long>(os * SIGMA + b) << 32) |
-                                         static_cast<unsigned long long>(j * kHeavyChunk);
-              j -= nch;
-            }
-          }
-        }
-        oh += nh[k];
-      }
     }
     __syncthreads();
   }
 }
 
-// Adds a block's Stage 2 statistics to the level slot (block 0 also carries
-// the cumulative counts of the previous level).
-template <int BLOCK>
-__device__ __forceinline__ void finalize_stats(gptr<unsigned long long> acc, const long long (&st8)[8], long long cumv_in,
-                               long long cume_in) {
-  __shared__ long long lds64[5 * (BLOCK / 64)];
-  long long st[5] = {st8[0], st8[1], st8[2], st8[3], st8[4]};
-  block_sum64<BLOCK, 5>(st, lds64);
-  if (threadIdx.x == 0) {
-    if (st[0]) {
-      add_u64(acc + F_FRONTIER * kPad, st[0]);
-      add_u64(acc + F_CUMV * kPad, st[0]);
-    }
-    if (st[1]) add_u64(acc + F_QSLICES * kPad, st[1]);
-    if (st[2]) {
-      add_u64(acc + F_FEDGES * kPad, st[2]);
-      add_u64(acc + F_CUME * kPad, st[2]);
-    }
-    if (st[3]) add_u64(acc + F_DEG32 * kPad, st[3]);
-    if (st[4]) add_u64(acc + F_DEG1024 * kPad, st[4]);
-    if (blockIdx.x == 0) {
-      add_u64(acc + F_CUMV * kPad, cumv_in);
-      add_u64(acc + F_CUME * kPad, cume_in);
-    }
-  }
-}
-
-// Stage 2 of the whole grid: every slice set, windows spread over the blocks.
+// Stage 2 of the whole grid (per-stage launches): every slice set, windows
+// spread over the blocks, statistics added to the level's slot (block 0 also
+// carries the cumulative counts of the previous level).
 template <int SIGMA, int BLOCK>
 __device__ __forceinline__ void finalize(args_ref<BfsArgs> a, int new_level, int slot_out, int sel_out, long long cumv_in,
-                         long long cume_in, unsigned nblocks) {
-  constexpr long long WIN = static_cast<long long>(BLOCK) * kFinSpt;
+                                         long long cume_in) {
+  __shared__ uint32_t lds[kParts * (BLOCK / 64)];
   const gptr<unsigned long long> acc = (&a.ctl->acc[slot_out][0][0]);
-  long long st[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // frontier, queued slices, frontier edges, deg>=32, deg>=1024
-  const long long nsets = a.nsets;
-  const long long tid = threadIdx.x;
-  finalize_windows<SIGMA, BLOCK, FIN_ATOMIC>(a, new_level, acc, sel_out, blockIdx.x, (nsets + WIN - 1) / WIN, nblocks,
-                                        [=](long long win, int k) -> long long {
-                                          const long long s = win * WIN + k * BLOCK + tid;
-                                          return s < nsets ? s : -1;
-                                        },
-                                        st, nullptr);
-  finalize_stats<BLOCK>(acc, st, cumv_in, cume_in);
+  uint32_t st[kParts] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+  const int nsets = static_cast<int>(a.nsets), tid = threadIdx.x;
+  finalize_windows<SIGMA, BLOCK, FIN_ATOMIC, 1>(a, new_level, acc, sel_out, blockIdx.x, (nsets + BLOCK - 1) / BLOCK,
+                                                gridDim.x,
+                                                [=](int win, int) -> int {
+                                                  const int s = win * BLOCK + tid;
+                                                  return s < nsets ? s : -1;
+                                                },
+                                                st, nullptr, push_possible(a), true);
+  const uint32_t t = block_sum32<BLOCK, kParts>(st, to_lds(lds));
+  if (tid < 5) {
+    constexpr int f[5] = {F_FRONTIER, F_QSLICES, F_FEDGES, F_DEG32, F_DEG1024};
+    if (t) add_u64(acc + f[tid] * kPad, t);
+    const int cum = tid == 0 ? F_CUMV : F_CUME;
+    const long long in = blockIdx.x ? 0 : tid == 0 ? cumv_in : cume_in;
+    if ((tid == 0 || tid == 2) && (t || in)) add_u64(acc + cum * kPad, t + static_cast<unsigned long long>(in));
+  }
 }
 
 // ------------------------------------------------- two-phase grid Stage 2
@@ -1155,50 +1100,60 @@ __device__ __forceinline__ void finalize(args_ref<BfsArgs> a, int new_level, int
 
 // MODE = FIN_COUNT (counts only) or FIN_ATOMIC (lists too, output space
 // reserved with one device atomic per window and list on the cursors of
-// slot `slot_out`); either way the level statistics go to the partials.
-template <int SIGMA, int BLOCK, int MODE>
+// slot `slot_out`); either way the level statistics go to the partials
+// (field f of workgroup b at f * gridDim.x + b, so that a wave reads a field
+// of all workgroups with coalesced loads).
+template <int SIGMA, int BLOCK, int MODE, int SPT>
 __device__ __attribute__((noinline)) void finalize_count(args_ref<BfsArgs> a_, int new_level, int slot_out,
                                                          int sel_out) {
   args_ref<BfsArgs> a = uniform_args(a_);
   new_level = uniform(new_level);
   slot_out = uniform(slot_out);
   sel_out = uniform(sel_out);
-  constexpr long long WIN = static_cast<long long>(BLOCK) * kFinSpt;
-  __shared__ long long lds64[kParts * (BLOCK / 64)];
-  long long st[kParts] = {0, 0, 0, 0, 0, 0, 0, 0};
-  const long long nsets = a.nsets;
-  const long long tid = threadIdx.x;
-  finalize_windows<SIGMA, BLOCK, MODE>(a, new_level, (&a.ctl->acc[slot_out][0][0]), sel_out, blockIdx.x,
+  constexpr int WIN = BLOCK * SPT;
+  __shared__ uint32_t lds[kParts * (BLOCK / 64)];
+  uint32_t st[kParts] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+  const int nsets = static_cast<int>(a.nsets), tid = threadIdx.x;
+  finalize_windows<SIGMA, BLOCK, MODE, SPT>(a, new_level, (&a.ctl->acc[slot_out][0][0]), sel_out, blockIdx.x,
                                             (nsets + WIN - 1) / WIN, gridDim.x,
-                                            [=](long long win, int k) -> long long {
-                                              const long long s = win * WIN + k * BLOCK + tid;
+                                            [=](int win, int k) -> int {
+                                              const int s = win * WIN + k * BLOCK + tid;
                                               return s < nsets ? s : -1;
                                             },
-                                            st, nullptr);
-  block_sum64<BLOCK, kParts>(st, lds64);
-  const gptr<long long> part = a.part;
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int f = 0; f < kParts; ++f) part[static_cast<long long>(blockIdx.x) * kParts + f] = st[f];
-  }
+                                            st, nullptr, push_possible(a), true);
+  const uint32_t t = block_sum32<BLOCK, kParts>(st, to_lds(lds));
+  if (tid < kParts) a.part[static_cast<long long>(tid) * gridDim.x + blockIdx.x] = t;
+}
+
+// The view of the level after v from its counters (kParts fields).
+__device__ __forceinline__ LevelView next_view(const LevelView& v, const uint32_t (&t)[kParts]) {
+  return LevelView{t[0], t[7], t[1], t[2], t[3], t[4], t[5], t[6], v.cumv + t[0], v.cume + t[2]};
 }
 
 // Sums the partial counters of all workgroups (after the barrier that follows
 // finalize_count). before[] = light, heavy and queue entries of the
 // workgroups with a smaller index (this workgroup's list offsets).
 template <int BLOCK>
-__device__ __forceinline__ void reduce_parts(args_ref<BfsArgs> a, long long (&tot)[kParts], long long (&before)[3]) {
-  __shared__ long long s_tot[kParts], s_bef[3];
-  const gptr<const long long> part = (gptr<const long long>)a.part;
+__device__ __forceinline__ void reduce_parts(args_ref<BfsArgs> a, uint32_t (&tot)[kParts], uint32_t (&before)[3]) {
+  __shared__ uint32_t s_tot[kParts], s_bef[3];
+  const gptr<const uint32_t> part = a.part;
   const int nb = static_cast<int>(gridDim.x);
   const int me = static_cast<int>(blockIdx.x);
   const int lane = lane_id(), w = wave_in_block();
   for (int f = w; f < kParts; f += BLOCK / 64) {
-    long long t = 0, bs = 0;
-    for (int b = lane; b < nb; b += 64) {
-      const long long x = part[static_cast<long long>(b) * kParts + f];
-      t += x;
-      bs += b < me ? x : 0;
+    uint32_t t = 0, bs = 0;
+    for (int b0 = 0; b0 < nb; b0 += 256) {
+      uint32_t x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int b = b0 + j * 64 + lane;
+        x[j] = b < nb ? part[static_cast<long long>(f) * nb + b] : 0u;
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        t += x[j];
+        bs += b0 + j * 64 + lane < me ? x[j] : 0u;
+      }
     }
     t = wave_sum(t);
     bs = wave_sum(bs);
@@ -1209,58 +1164,48 @@ __device__ __forceinline__ void reduce_parts(args_ref<BfsArgs> a, long long (&to
   }
   __syncthreads();
 #pragma unroll
-  for (int f = 0; f < kParts; ++f) tot[f] = uniform(s_tot[f]);
+  for (int f = 0; f < kParts; ++f) tot[f] = static_cast<uint32_t>(uniform(static_cast<int>(s_tot[f])));
 #pragma unroll
-  for (int f = 0; f < 3; ++f) before[f] = uniform(s_bef[f]);
+  for (int f = 0; f < 3; ++f) before[f] = static_cast<uint32_t>(uniform(static_cast<int>(s_bef[f])));
   __syncthreads();
 }
 
-// panel_part: the counts came from the fused panel step, so each workgroup
-// emits the lists of the slice sets of its own panels (the partition its
-// partial counters, and hence its offsets, were computed over); otherwise
-// the window partition of finalize_count.
-template <int SIGMA, int BLOCK>
-__device__ __attribute__((noinline)) void finalize_emit(args_ref<BfsArgs> a_, int sel_out, long long before_light,
-                                                        long long before_heavy, long long before_queue, bool want_push,
+// The lists of the windows (or, panel_part, of the panels) whose counts this
+// workgroup stored, at its offsets. panel_part: the counts came from the fused
+// panel step, so each workgroup emits the lists of the slice sets of its own
+// panels (the partition its partial counters, and hence its offsets, were
+// computed over); otherwise the window partition of finalize_count.
+template <int SIGMA, int BLOCK, int SPT>
+__device__ __attribute__((noinline)) void finalize_emit(args_ref<BfsArgs> a_, int sel_out, uint32_t before_light,
+                                                        uint32_t before_heavy, uint32_t before_queue, bool want_push,
                                                         bool want_queue, bool panel_part) {
   args_ref<BfsArgs> a = uniform_args(a_);
   sel_out = uniform(sel_out);
-  const long long before[3] = {before_light, before_heavy, before_queue};
-  constexpr long long WIN = static_cast<long long>(BLOCK) * kFinSpt;
-  __shared__ unsigned long long cursor[3];
-  if (threadIdx.x == 0)
-    for (int f = 0; f < 3; ++f) cursor[f] = static_cast<unsigned long long>(before[f]);
+  constexpr int WIN = BLOCK * SPT;
+  __shared__ uint32_t cursor[3];
+  const int tid = threadIdx.x;
+  if (tid < 3) cursor[tid] = tid == 0 ? before_light : tid == 1 ? before_heavy : before_queue;
   __syncthreads();
-  long long st[kParts] = {0, 0, 0, 0, 0, 0, 0, 0};
-  const long long nsets = a.nsets;
-  const long long tid = threadIdx.x;
+  uint32_t st[kParts] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+  const int nsets = static_cast<int>(a.nsets);
   const gptr<unsigned long long> acc0 = (&a.ctl->acc[0][0][0]);
-  if (panel_part) {
-    // panel p holds sets [p * sp, (p + 1) * sp); this workgroup owns panels
-    // blockIdx.x, blockIdx.x + G, ...; window w is window w % wpp of its
-    // (w / wpp)-th panel
-    const long long sp = 1LL << (a.panel_rb - 3);
-    const long long wpp = (sp + WIN - 1) / WIN;
-    const long long mine = a.npanels > static_cast<int>(blockIdx.x)
-                               ? (a.npanels - 1 - static_cast<long long>(blockIdx.x)) / gridDim.x + 1
-                               : 0;
-    const long long b = blockIdx.x, G = gridDim.x;
-    finalize_windows<SIGMA, BLOCK, FIN_EMIT>(a, 0, acc0, sel_out, 0, mine * wpp, 1,
-                                             [=](long long win, int k) -> long long {
-                                               const long long p = b + (win / wpp) * G;
-                                               const long long end = min((p + 1) * sp, nsets);
-                                               const long long s = p * sp + (win % wpp) * WIN + k * BLOCK + tid;
-                                               return s < end ? s : -1;
-                                             },
-                                             st, to_lds(cursor), want_push, want_queue);
-    return;
-  }
-  finalize_windows<SIGMA, BLOCK, FIN_EMIT>(a, 0, acc0, sel_out, blockIdx.x, (nsets + WIN - 1) / WIN, gridDim.x,
-                                           [=](long long win, int k) -> long long {
-                                             const long long s = win * WIN + k * BLOCK + tid;
-                                             return s < nsets ? s : -1;
-                                           },
-                                           st, to_lds(cursor), want_push, want_queue);
+  // panel_part: panel p holds sets [p * sp, (p + 1) * sp); this workgroup owns
+  // panels blockIdx.x, blockIdx.x + G, ...; window w is window w % wpp of its
+  // (w / wpp)-th panel
+  const int sp = panel_part ? 1 << (a.panel_rb - 3) : nsets;
+  const int b = blockIdx.x, G = gridDim.x;
+  const int wpp = (sp + WIN - 1) / WIN;
+  const int mine = !panel_part ? 0 : a.npanels > b ? (a.npanels - 1 - b) / G + 1 : 0;
+  finalize_windows<SIGMA, BLOCK, FIN_EMIT, SPT>(a, 0, acc0, sel_out, panel_part ? 0 : b, panel_part ? mine * wpp : wpp,
+                                                panel_part ? 1 : G,
+                                                [=](int win, int k) -> int {
+                                                  const int p = panel_part ? b + (win / wpp) * G : 0;
+                                                  const int w = panel_part ? win % wpp : win;
+                                                  const int i = w * WIN + k * BLOCK + tid;  // in the panel
+                                                  const long long s = static_cast<long long>(p) * sp + i;
+                                                  return i < sp && s < nsets ? static_cast<int>(s) : -1;
+                                                },
+                                                st, to_lds(cursor), want_push, want_queue);
 }
 
 // ------------------------------------------------- single-workgroup levels
@@ -1280,50 +1225,42 @@ __device__ __forceinline__ bool single_eligible(args_ref<BfsArgs> a, int engine,
 }
 
 // Stage 2 of one workgroup over the sets recorded during Stage 1 (the LDS
-// list after the hash set); empties both. Output cursors are block-local and
-// the level's counters are stored at the end (the slot was zeroed before).
+// list after the hash set); empties both. Output cursors are block-local; the
+// level's counters go to tot (LDS) and to the level's slot.
 template <int SIGMA, int BLOCK>
 __device__ __attribute__((noinline)) void finalize_list(args_ref<BfsArgs> a_, int new_level, int slot_out,
-                                                        int sel_out, long long cumv_in, long long cume_in,
-                                                        lptr<int> hs) {
+                                                        int sel_out, uint32_t cumv_in, uint32_t cume_in,
+                                                        lptr<int> hs, lptr<uint32_t> tot) {
   args_ref<BfsArgs> a = uniform_args(a_);
   new_level = uniform(new_level);
   slot_out = uniform(slot_out);
   sel_out = uniform(sel_out);
-  constexpr int WIN = BLOCK * kFinSpt;
-  __shared__ unsigned long long local[3];
-  __shared__ long long lds64[5 * (BLOCK / 64)];
-  const gptr<unsigned long long> acc = (&a.ctl->acc[slot_out][0][0]);
-  if (threadIdx.x < 3) local[threadIdx.x] = 0ULL;
-  __syncthreads();
-  const int count = hs[kSingleHash];
-  const lptr<const int> list = hs + kSingleHash + 1;
-  long long st8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  __shared__ uint32_t local[3];
+  __shared__ uint32_t lds[kParts * (BLOCK / 64)];
   const int tid = threadIdx.x;
-  finalize_windows<SIGMA, BLOCK, FIN_LOCAL>(a, new_level, acc, sel_out, 0, (count + WIN - 1) / WIN, 1,
-                                       [=](long long win, int k) -> long long {
-                                         const long long i = win * WIN + k * BLOCK + tid;
-                                         return i < count ? static_cast<long long>(list[i]) : -1;
-                                       },
-                                       st8, to_lds(local));
+  const gptr<unsigned long long> acc = (&a.ctl->acc[slot_out][0][0]);
+  if (tid < 3) local[tid] = 0u;
   __syncthreads();
+  const int count = uniform(hs[kSingleHash]);
+  const lptr<const int> list = hs + kSingleHash + 1;
+  uint32_t st[kParts] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+  finalize_windows<SIGMA, BLOCK, FIN_LOCAL, 1>(a, new_level, acc, sel_out, 0, (count + BLOCK - 1) / BLOCK, 1,
+                                               [=](int win, int) -> int {
+                                                 const int i = win * BLOCK + tid;
+                                                 return i < count ? list[i] : -1;
+                                               },
+                                               st, to_lds(local), push_possible(a), true);
+  const uint32_t t = block_sum32<BLOCK, kParts>(st, to_lds(lds));
   for (int i = tid; i < kSingleHash + 1; i += BLOCK) hs[i] = (i == kSingleHash) ? 0 : -1;
-  long long st[5] = {st8[0], st8[1], st8[2], st8[3], st8[4]};
-  block_sum64<BLOCK, 5>(st, lds64);
-  if (threadIdx.x == 0) {
-    auto put = [&](int f, unsigned long long v) {
-      __hip_atomic_store(acc + f * kPad, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    put(F_LIGHT, local[0]);
-    put(F_HEAVY, local[1]);
-    put(F_QUEUE, local[2]);
-    put(F_FRONTIER, static_cast<unsigned long long>(st[0]));
-    put(F_QSLICES, static_cast<unsigned long long>(st[1]));
-    put(F_FEDGES, static_cast<unsigned long long>(st[2]));
-    put(F_DEG32, static_cast<unsigned long long>(st[3]));
-    put(F_DEG1024, static_cast<unsigned long long>(st[4]));
-    put(F_CUMV, static_cast<unsigned long long>(cumv_in + st[0]));
-    put(F_CUME, static_cast<unsigned long long>(cume_in + st[2]));
+  auto put = [&](int f, unsigned long long v) {
+    __hip_atomic_store(acc + f * kPad, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if (tid < kParts) {
+    constexpr int f[kParts] = {F_FRONTIER, F_QSLICES, F_FEDGES, F_DEG32, F_DEG1024, F_LIGHT, F_HEAVY, F_QUEUE};
+    tot[tid] = t;
+    put(f[tid], t);
+    if (tid == 0) put(F_CUMV, static_cast<unsigned long long>(cumv_in) + t);
+    if (tid == 2) put(F_CUME, static_cast<unsigned long long>(cume_in) + t);
   }
 }
 
@@ -1445,16 +1382,17 @@ __device__ __attribute__((noinline)) int single_episode(args_ref<BfsArgs> a_, in
   level = uniform(level);
   engine = uniform(engine);
   const long long gwave = wave_in_block(), nwaves = BLOCK / 64;
+  __shared__ uint32_t s_tot[kParts];
   for (;;) {
     const int slot = level % kStatSlots, nslot = (level + 1) % kStatSlots;
     if (threadIdx.x == 0) log_begin(a, level);
-    if (threadIdx.x < kStatFields)
-      __hip_atomic_store(&a.ctl->acc[nslot][threadIdx.x][0], 0ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    block_sync_mem();
+    // (the next level's work counter; its other fields are stored by Stage 2)
+    if (threadIdx.x == 0)
+      __hip_atomic_store(&a.ctl->acc[nslot][F_WORK][0], 0ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     run_engine<SIGMA, SliceT, BLOCK, true>(a, engine, level & 1, slot, v, gwave, nwaves, hs, (lptr<uint32_t>)hs);
     block_sync_mem();
     if (threadIdx.x == 0 && level < a.log_cap) a.log[level].t_mid = dev_ticks();
-    finalize_list<SIGMA, BLOCK>(a, level + 1, nslot, (level & 1) ^ 1, v.cumv, v.cume, hs);
+    finalize_list<SIGMA, BLOCK>(a, level + 1, nslot, (level & 1) ^ 1, v.cumv, v.cume, hs, to_lds(s_tot));
     block_sync_mem();
     if (threadIdx.x == 0 && level < a.log_cap) {
       a.log[level].t_end = dev_ticks();
@@ -1464,7 +1402,10 @@ __device__ __attribute__((noinline)) int single_episode(args_ref<BfsArgs> a_, in
     // progress for the waiting workgroups: their time bound restarts with every level
     if (threadIdx.x == 0)
       __hip_atomic_store(&a.ctl->single_progress[0], level, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    v = read_level_atomic(a.ctl, level % kStatSlots);
+    uint32_t tot[kParts];
+#pragma unroll
+    for (int f = 0; f < kParts; ++f) tot[f] = static_cast<uint32_t>(uniform(static_cast<int>(s_tot[f])));
+    v = next_view(v, tot);
     if (v.frontier == 0) return level;
     if (__hip_atomic_load(&a.ctl->error[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return level;
     engine = decide_level<false>(a, v, level, s_mlp, learned);
@@ -1571,27 +1512,24 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs args) {
     const bool two_phase = fused || (!a.probe && (a.count_first == 2 || (a.count_first == 1 && dense_next)));
     LevelView nv;
     bool emitted = false;
-    long long before[3] = {0, 0, 0};
+    uint32_t before[3] = {0u, 0u, 0u};
+    const bool wide = fin_wide(a, BLOCK);
     {
       if (!fused) {
-        if (two_phase)
-          finalize_count<SIGMA, BLOCK, FIN_COUNT>(a, level + 1, (level + 1) % kStatSlots, sel ^ 1);
+        const int ns = (level + 1) % kStatSlots;
+        if (two_phase && wide)
+          finalize_count<SIGMA, BLOCK, FIN_COUNT, kFinSpt>(a, level + 1, ns, sel ^ 1);
+        else if (two_phase)
+          finalize_count<SIGMA, BLOCK, FIN_COUNT, 1>(a, level + 1, ns, sel ^ 1);
+        else if (wide)
+          finalize_count<SIGMA, BLOCK, FIN_ATOMIC, kFinSpt>(a, level + 1, ns, sel ^ 1);
         else
-          finalize_count<SIGMA, BLOCK, FIN_ATOMIC>(a, level + 1, (level + 1) % kStatSlots, sel ^ 1);
+          finalize_count<SIGMA, BLOCK, FIN_ATOMIC, 1>(a, level + 1, ns, sel ^ 1);
         if (!grid_barrier((Ctl*)a.ctl, bc)) return;
       }
-      long long tot[kParts];
+      uint32_t tot[kParts];
       reduce_parts<BLOCK>(a, tot, before);
-      nv.frontier = static_cast<uint32_t>(tot[0]);
-      nv.qslices = static_cast<uint32_t>(tot[1]);
-      nv.fedges = static_cast<uint32_t>(tot[2]);
-      nv.deg32 = static_cast<uint32_t>(tot[3]);
-      nv.deg1024 = static_cast<uint32_t>(tot[4]);
-      nv.light = static_cast<uint32_t>(tot[5]);
-      nv.heavy = static_cast<uint32_t>(tot[6]);
-      nv.queue = static_cast<uint32_t>(tot[7]);
-      nv.cumv = v.cumv + nv.frontier;
-      nv.cume = v.cume + nv.fedges;
+      nv = next_view(v, tot);
       if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (level < a.log_cap) a.log[level].t_count = dev_ticks();
         // the level's counters, for a single-workgroup episode that may follow
@@ -1610,7 +1548,11 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs args) {
         const bool want_queue = engine == BLEST_ENGINE_BVSS && !(kPanelFmt && use_panel(a, nv));
         const bool want_push = engine == BLEST_ENGINE_PUSH;
         if (want_queue || want_push) {
-          finalize_emit<SIGMA, BLOCK>(a, sel ^ 1, before[0], before[1], before[2], want_push, want_queue, fused);
+          if (wide)
+            finalize_emit<SIGMA, BLOCK, kFinSpt>(a, sel ^ 1, before[0], before[1], before[2], want_push, want_queue,
+                                                 fused);
+          else
+            finalize_emit<SIGMA, BLOCK, 1>(a, sel ^ 1, before[0], before[1], before[2], want_push, want_queue, fused);
           emitted = true;
         }
       }
@@ -2464,7 +2406,7 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_stage2(BfsArgs args, int level) {
   const LevelView v = read_level(a.ctl, level % kStatSlots);
   if (v.frontier == 0) return;
   if (blockIdx.x == 0 && threadIdx.x == 0 && level < a.log_cap) a.log[level].t_mid = dev_ticks();
-  finalize<SIGMA, BLOCK>(a, level + 1, (level + 1) % kStatSlots, (level & 1) ^ 1, v.cumv, v.cume, gridDim.x);
+  finalize<SIGMA, BLOCK>(a, level + 1, (level + 1) % kStatSlots, (level & 1) ^ 1, v.cumv, v.cume);
   if (blockIdx.x == 0 && threadIdx.x == 0 && level < a.log_cap) {
     a.log[level].t_end = dev_ticks();
     a.log[level].work = static_cast<long long>(a.ctl->acc[level % kStatSlots][F_WORK][0]);

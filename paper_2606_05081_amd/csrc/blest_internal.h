@@ -180,7 +180,7 @@ struct BfsArgs {
   gptr<int32_t> flight[2];             // light frontier vertices
   gptr<unsigned long long> fheavy[2];  // heavy frontier edge chunks: (vertex << 32) | first edge offset
   gptr<Ctl> ctl;
-  gptr<long long> part;  // per-workgroup partial Stage 2 counters (grid size x 8)
+  gptr<uint32_t> part;  // per-workgroup partial Stage 2 counters (8 fields of grid size)
   gptr<LevelRec> log;
   int32_t log_cap;
   gptr<const MlpDev> mlp;
@@ -229,7 +229,7 @@ struct DevGraph {
   unsigned long long* fheavy[2] = {nullptr, nullptr};
   Ctl* ctl = nullptr;
   MlpDev* ms_mlp = nullptr;  // switch network of the multi-source kernels
-  long long* part = nullptr;
+  uint32_t* part = nullptr;
   LevelRec* log = nullptr;
   int log_cap = 0;
   MlpDev* mlp = nullptr;

@@ -2,6 +2,7 @@
 // reductions, the device-wide barrier, clocks and mask types.
 #pragma once
 
+#include <type_traits>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -104,22 +105,54 @@ __device__ __forceinline__ lptr<T> to_lds(T* p) {
 // Wave index inside the block, known uniform to the compiler.
 __device__ __forceinline__ int wave_in_block() { return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)); }
 
+// v of the lane that a DPP control selects, 0 where it selects none.
+template <int CTRL, int ROWS, class T>
+__device__ __forceinline__ T dpp_or_zero(T v) {
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "32- or 64-bit integers");
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xf, false);
+  if constexpr (sizeof(T) == 4) {
+    return static_cast<T>(lo);
+  } else {
+    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<unsigned long long>(v) >> 32), CTRL,
+                                               ROWS, 0xf, false);
+    return static_cast<T>((static_cast<unsigned long long>(static_cast<uint32_t>(hi)) << 32) |
+                          static_cast<uint32_t>(lo));
+  }
+}
+
+// Inclusive prefix sum over the wave (all 64 lanes active): four shifts inside
+// the rows of 16 lanes, then row ends broadcast to the rows after them. Six
+// register moves; through LDS permutes the same six steps wait for one another
+// for about 60 cycles each.
 template <class T>
-__device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+__device__ __forceinline__ T wave_inclusive_scan(T v) {
+  v += dpp_or_zero<0x111, 0xf>(v);  // row_shr:1
+  v += dpp_or_zero<0x112, 0xf>(v);  // row_shr:2
+  v += dpp_or_zero<0x114, 0xf>(v);  // row_shr:4
+  v += dpp_or_zero<0x118, 0xf>(v);  // row_shr:8
+  v += dpp_or_zero<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
   return v;
 }
 
+// Sum over the wave, in every lane. Whole numbers through the scan above;
+// floats keep the butterfly's order of additions.
 template <class T>
-__device__ __forceinline__ T wave_inclusive_scan(T v) {
-  const int lane = lane_id();
+__device__ __forceinline__ T wave_sum(T v) {
+  if constexpr (std::is_integral_v<T>) {
+    v = wave_inclusive_scan(v);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(v), 63);
+    if constexpr (sizeof(T) == 4) {
+      return static_cast<T>(lo);
+    } else {
+      const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<unsigned long long>(v) >> 32), 63);
+      return static_cast<T>((static_cast<unsigned long long>(hi) << 32) | lo);
+    }
+  } else {
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    T x = __shfl_up(v, d, 64);
-    if (lane >= d) v += x;
+    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+    return v;
   }
-  return v;
 }
 
 // Exclusive block scan of N int counters; tot[] receives the block totals.
@@ -147,6 +180,25 @@ __device__ __forceinline__ void block_exclusive_scan(const int (&v)[N], int (&ex
     tot[k] = all;
   }
   __syncthreads();
+}
+
+// Block sums of N <= BLOCK 32-bit counters: thread k < N returns the sum of
+// v[k] (other threads 0). lds: N * (BLOCK / 64) slots; one __syncthreads(), and
+// the caller must synchronise before the next use of lds.
+template <int BLOCK, int N>
+__device__ __forceinline__ uint32_t block_sum32(const uint32_t (&v)[N], lptr<uint32_t> lds) {
+  constexpr int W = BLOCK / 64;
+  const int lane = lane_id(), w = wave_in_block();
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const uint32_t s = wave_sum(v[k]);
+    if (lane == 0) lds[k * W + w] = s;
+  }
+  __syncthreads();
+  uint32_t t = 0;
+  if (static_cast<int>(threadIdx.x) < N)
+    for (int i = 0; i < W; ++i) t += lds[threadIdx.x * W + i];
+  return t;
 }
 
 // Block sum of N int64 values, result valid in thread 0. lds: N * (BLOCK/64) slots.
