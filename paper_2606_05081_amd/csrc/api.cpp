@@ -104,6 +104,12 @@ blest_status check_device(int want, int* dev, int* num_cu, double* tick_us) {
 
 blest_status wait_and_check(blest_graph* g, hipStream_t st) {
   CK(hipStreamSynchronize(st));
+  // a persistent launch that ended well has said so in pinned memory
+  const volatile int* status = g->d.host_flags + 4;
+  if (status[0] == 1) {
+    g->nlevels = status[1];
+    return BLEST_OK;
+  }
   int flags[2] = {0, 0};
   CK(hipMemcpy(&flags[0], &g->d.ctl->error[0], sizeof(int), hipMemcpyDeviceToHost));
   CK(hipMemcpy(&flags[1], &g->d.ctl->nlevels[0], sizeof(int), hipMemcpyDeviceToHost));
@@ -431,6 +437,12 @@ blest_status blest_build(const blest_csr* csr, const blest_opts* opts_in, blest_
     TRY(hipMemcpy(d.orig_id, orig.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice));
   }
   TRY(hipHostMalloc(reinterpret_cast<void**>(&d.host_flags), 64, hipHostMallocDefault));
+  std::memset(d.host_flags, 0, 64);
+  {
+    void* p = nullptr;
+    TRY(hipHostGetDevicePointer(&p, d.host_flags, 0));
+    d.hstat = reinterpret_cast<unsigned long long*>(static_cast<char*>(p) + 4 * sizeof(int));
+  }
   {
     std::vector<int32_t> rpp(rp_len + 4, static_cast<int32_t>(m));
     std::copy(rp, rp + n + 1, rpp.begin());

@@ -1434,7 +1434,10 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs args) {
   if (blockIdx.x == 0) {
     __syncthreads();  // block 0's counter clear before its seed counters
     seed_source<SIGMA>(a, true);
-    if (threadIdx.x == 0) a.ctl->single_gen[0] = 0u;
+    if (threadIdx.x == 0) {
+      a.ctl->single_gen[0] = 0u;
+      host_status_begin(a.hstat);
+    }
   }
   BarrierCtx bc;
   if (!barrier_register((Ctl*)a.ctl, &bc, a.timeout_ticks)) return;
@@ -1571,7 +1574,10 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs args) {
     // for the next launch.
     if (threadIdx.x < 8) a.ctl->xcd_blocks[threadIdx.x][0] = 0u;
     if (threadIdx.x == 8) a.ctl->xcd_active[0] = 0u;
-    if (threadIdx.x == 0) a.ctl->nlevels[0] = level;
+    if (threadIdx.x == 0) {
+      a.ctl->nlevels[0] = level;
+      host_status_end(a.hstat, a.ctl, level);
+    }
   }
 }
 
@@ -2288,7 +2294,10 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_eager(BfsArgs args) {
   if (blockIdx.x == 0) {
     __syncthreads();  // block 0's counter clear before its seed counters
     seed_source<SIGMA>(a, true);
-    if (threadIdx.x == 0) a.ctl->single_gen[0] = 0u;
+    if (threadIdx.x == 0) {
+      a.ctl->single_gen[0] = 0u;
+      host_status_begin(a.hstat);
+    }
   }
   BarrierCtx bc;
   if (!barrier_register((Ctl*)a.ctl, &bc, a.timeout_ticks)) return;
@@ -2348,7 +2357,10 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_eager(BfsArgs args) {
   if (blockIdx.x == 0) {
     if (threadIdx.x < 8) a.ctl->xcd_blocks[threadIdx.x][0] = 0u;
     if (threadIdx.x == 8) a.ctl->xcd_active[0] = 0u;
-    if (threadIdx.x == 0) a.ctl->nlevels[0] = level;
+    if (threadIdx.x == 0) {
+      a.ctl->nlevels[0] = level;
+      host_status_end(a.hstat, a.ctl, level);
+    }
   }
 }
 
@@ -2359,7 +2371,10 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_clear(BfsArgs args) {
   args_ref<BfsArgs> a = kernel_args(args);
   const long long nthreads = static_cast<long long>(gridDim.x) * BLOCK;
   clear_state<SIGMA>(a, static_cast<long long>(blockIdx.x) * BLOCK + threadIdx.x, nthreads);
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->done[0] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    a.ctl->done[0] = 0;
+    host_status_begin(a.hstat);  // (stays 0: the host reads the control block after per-stage launches)
+  }
 }
 
 template <int SIGMA, int BLOCK>
@@ -2558,6 +2573,7 @@ BfsArgs bfs_args(const DevGraph& g) {
   }
   a.ctl = to_global(g.ctl);
   a.part = to_global(g.part);
+  a.hstat = to_global(g.hstat);
   a.log = to_global(g.log);
   a.log_cap = g.log_cap;
   a.mlp = to_global(g.mlp);

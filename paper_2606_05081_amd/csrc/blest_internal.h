@@ -180,6 +180,7 @@ struct BfsArgs {
   gptr<int32_t> flight[2];             // light frontier vertices
   gptr<unsigned long long> fheavy[2];  // heavy frontier edge chunks: (vertex << 32) | first edge offset
   gptr<Ctl> ctl;
+  gptr<unsigned long long> hstat;  // pinned host word: how the launch went
   gptr<uint32_t> part;  // per-workgroup partial Stage 2 counters (8 fields of grid size)
   gptr<LevelRec> log;
   int32_t log_cap;
@@ -233,7 +234,9 @@ struct DevGraph {
   LevelRec* log = nullptr;
   int log_cap = 0;
   MlpDev* mlp = nullptr;
-  int* host_flags = nullptr;  // pinned: done flag readback of the per-stage mode
+  int* host_flags = nullptr;  // pinned: [0] done flag readback of the per-stage mode, [2..3] of the graph mode,
+                              // [4..5] status word of the persistent launches
+  unsigned long long* hstat = nullptr;  // device address of host_flags + 4
   int block = 512, grid = 0, num_cu = 0, persistent = 1, prefilter = 1, count_work = 0, single_block = 1;
   uint32_t* pwords = nullptr;
   uint32_t* pbase = nullptr;

@@ -68,6 +68,12 @@ struct MsBatch {
   int32_t pad;
 };
 
+// A call's source list and batch plan travel with the kernel arguments where
+// they are this small (512 is the widest batch); otherwise they are copied to
+// device memory first, two copies from pageable memory and a synchronisation,
+// about 30 us.
+constexpr int kMsInlineSrcs = 512, kMsInlineBatches = 8;
+
 struct MsArgs {
   gptr<const int32_t> rp;
   gptr<const int32_t> col;
@@ -109,7 +115,15 @@ struct MsArgs {
   int32_t log_cap;
   unsigned long long timeout_ticks;
   int32_t ablation;       // BLEST_MS_NO_GETVI | BLEST_MS_NO_DIRTY (the paper's ablation steps), else 0
+  gptr<unsigned long long> hstat;  // pinned host word: how the launch went
+  int32_t inlined;        // 1: the sources and the plan are these, not srcs and batches
+  MsBatch plan_in[kMsInlineBatches];
+  int32_t srcs_in[kMsInlineSrcs];
 };
+
+__device__ __forceinline__ gptr<const int32_t> ms_srcs(args_ref<MsArgs> a) {
+  return a.inlined ? (gptr<const int32_t>)(uintptr_t)&a.srcs_in[0] : a.srcs;
+}
 
 __device__ __forceinline__ long long get_vi(long long u, long long rho, int sigma) {
   return (u % sigma) * rho + u / sigma;
@@ -304,7 +318,8 @@ struct MsStep {
 // Batch bi of the call's plan (bi wave-uniform: scalar loads; the plan is
 // written before the launch).
 __device__ __forceinline__ MsBatch ms_batch(args_ref<MsArgs> a, int bi) {
-  const cptr<const MsBatch> p = (cptr<const MsBatch>)a.batches + bi;
+  const cptr<const MsBatch> p =
+      a.inlined ? (cptr<const MsBatch>)(uintptr_t)&a.plan_in[bi] : (cptr<const MsBatch>)a.batches + bi;
   return MsBatch{p->offset, p->count, p->W, 0};
 }
 
@@ -1620,7 +1635,7 @@ __device__ __attribute__((noinline)) void ms_batch_clear(args_ref<MsArgs> a_, in
   for (int b = 0; b < 3; ++b)
     for (long long i = gtid; i < (nhat + 31) / 32; i += nthreads) a.fb[b][i] = 0u;
   for (long long i = gtid; i < static_cast<long long>(bt.count) * W; i += nthreads)
-    a.F[0][ms_vi<ABL>(a, a.srcs[bt.offset + i / W], a.nsets, SIGMA) * W + i % W] = 0ULL;
+    a.F[0][ms_vi<ABL>(a, ms_srcs(a)[bt.offset + i / W], a.nsets, SIGMA) * W + i % W] = 0ULL;
   if (a.levels16 && !a.planes)
     fill_minus_one(a.levels16 + static_cast<long long>(bt.offset) * a.n, static_cast<long long>(bt.count) * a.n, gtid,
                    nthreads);
@@ -1644,7 +1659,7 @@ __device__ __attribute__((noinline)) void ms_batch_seed(args_ref<MsArgs> a_, int
   const uint32_t tau = static_cast<uint32_t>(a.tau);
   const gptr<unsigned long long> st = &a.ctl->ms_acc[0][xcc][0];
   for (long long c = gtid; c < bt.count; c += nthreads) {
-    const long long u = a.srcs[bt.offset + c];
+    const long long u = ms_srcs(a)[bt.offset + c];
     const long long i = ms_vi<ABL>(a, u, a.nsets, SIGMA) * bt.W + c / 64;
     const unsigned long long bit = 1ULL << (c % 64);
     __hip_atomic_fetch_or(a.V + i, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1836,6 +1851,7 @@ __global__ void __launch_bounds__(BLOCK) k_ms_persistent(MsArgs args) {
   const MsGatherLds glds = ms_gather_lds(lds);
   const bool count_sources = a.sums != nullptr || a.reach != nullptr || a.cc != nullptr;
   ms_lds_init(lds);
+  if (blockIdx.x == 0 && threadIdx.x == 0) host_status_begin(a.hstat);
   BarrierCtx bc;
   if (!barrier_register((Ctl*)a.ctl, &bc, a.timeout_ticks)) return;
   int total_levels = 0;
@@ -1901,8 +1917,11 @@ __global__ void __launch_bounds__(BLOCK) k_ms_persistent(MsArgs args) {
   if (blockIdx.x == 0) {
     if (threadIdx.x < 8) a.ctl->xcd_blocks[threadIdx.x][0] = 0u;
     if (threadIdx.x == 8) a.ctl->xcd_active[0] = 0u;
-    if (threadIdx.x == 0) a.ctl->nlevels[0] = total_levels;
-    if (threadIdx.x == 0) a.ctl->ms_nrec[0] = nrec;
+    if (threadIdx.x == 0) {
+      a.ctl->nlevels[0] = total_levels;
+      a.ctl->ms_nrec[0] = nrec;
+      host_status_end(a.hstat, a.ctl, total_levels);
+    }
   }
 }
 
@@ -2012,8 +2031,9 @@ __global__ void __launch_bounds__(BLOCK) k_ms_phase(MsArgs args, int parity) {
     for (int i = 0; i < 5; ++i) a.ctl->ms_state[parity ^ 1][i] = next[i];
 }
 
-__global__ void k_ms_start(Ctl* ctl) {
+__global__ void k_ms_start(Ctl* ctl, unsigned long long* hstat) {
   if (threadIdx.x == 0) {
+    host_status_begin(to_global(hstat));  // (stays 0: the host reads the control block after graph replays)
     for (int i = 0; i < 5; ++i) ctl->ms_state[0][i] = 0;  // MS_INIT, batch 0
     ctl->nlevels[0] = 0;
     ctl->ms_nrec[0] = 0;
@@ -2181,6 +2201,7 @@ MsArgs ms_args(const DevGraph& g, const MsDev* ms, const int32_t* srcs_dev, cons
   a.seed = seed;
   a.timeout_ticks = 3000000000ULL;  // 30 s
   a.ablation = g.ms_ablation;
+  a.hstat = to_global(g.hstat);
   return a;
 }
 
@@ -2233,14 +2254,20 @@ hipError_t ms_run(const DevGraph& g, MsDev* ms, const int32_t* srcs, int32_t k, 
   hipError_t e = ensure(g, ms, wmax, k, nplan);
   if (e != hipSuccess) return e;
   if (levels16 && (e = ensure_levels(g, ms, wmax, st)) != hipSuccess) return e;
-  if ((e = hipMemcpyAsync(ms->srcs, srcs, sizeof(int32_t) * k, hipMemcpyHostToDevice, st)) != hipSuccess) return e;
-  if ((e = hipMemcpyAsync(ms->batches, plan.data(), sizeof(MsBatch) * nplan, hipMemcpyHostToDevice, st)) !=
-      hipSuccess)
-    return e;
-  // the copies read pageable host memory; wait so `plan` may go out of scope
-  if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
   MsArgs a = ms_args(g, ms, ms->srcs, static_cast<const MsBatch*>(ms->batches), nplan, policy, eta, seed, levels16,
                      sums, reach, cc, far, probe);
+  if (k <= kMsInlineSrcs && nplan <= kMsInlineBatches) {
+    a.inlined = 1;
+    std::copy(srcs, srcs + k, a.srcs_in);
+    std::copy(plan.begin(), plan.end(), a.plan_in);
+  } else {
+    if ((e = hipMemcpyAsync(ms->srcs, srcs, sizeof(int32_t) * k, hipMemcpyHostToDevice, st)) != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(ms->batches, plan.data(), sizeof(MsBatch) * nplan, hipMemcpyHostToDevice, st)) !=
+        hipSuccess)
+      return e;
+    // the copies read pageable host memory; wait so `plan` may go out of scope
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+  }
   const unsigned shmem = policy == BLEST_POLICY_LEARNED ? kLdsMlpFloats * sizeof(float) : 0u;
   if (!graph || probe) {
     void* args[] = {static_cast<void*>(&a)};
@@ -2310,7 +2337,7 @@ hipError_t ms_run(const DevGraph& g, MsDev* ms, const int32_t* srcs, int32_t k, 
   }
   if ((e = hipEventRecord(ms->gev[0], st)) != hipSuccess) return e;
   if ((e = hipStreamWaitEvent(gs, ms->gev[0], 0)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_ms_start, dim3(1), dim3(64), 0, gs, g.ctl);
+  hipLaunchKernelGGL(k_ms_start, dim3(1), dim3(64), 0, gs, g.ctl, g.hstat);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // every batch has at most 3 + 3 * 32768 phases (levels are int16)
   const long long max_replays = static_cast<long long>(nplan) * (3LL * 32768 + 4) / kMsGraphKernels + 2;
