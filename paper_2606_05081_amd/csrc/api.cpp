@@ -312,6 +312,11 @@ blest_status blest_build(const blest_csr* csr, const blest_opts* opts_in, blest_
   d.nslices = b.nslices;
   d.block = o.block_size;
   d.num_cu = num_cu;
+  {
+    int lds = 0;
+    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && lds > 0)
+      d.max_lds = lds;
+  }
   d.persistent = o.persistent;
   d.prefilter = o.prefilter;
   d.single_block = o.single_block;

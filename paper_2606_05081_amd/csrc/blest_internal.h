@@ -234,6 +234,7 @@ struct DevGraph {
   LevelRec* log = nullptr;
   int log_cap = 0;
   MlpDev* mlp = nullptr;
+  int max_lds = 65536;        // LDS bytes a workgroup may have
   int* host_flags = nullptr;  // pinned: [0] done flag readback of the per-stage mode, [2..3] of the graph mode,
                               // [4..5] status word of the persistent launches
   unsigned long long* hstat = nullptr;  // device address of host_flags + 4

@@ -38,6 +38,7 @@ struct MsDev {
   void* batches = nullptr;           // batch descriptors
   int batches_cap = 0;
   int grid = 0, block = 512;
+  size_t static_lds = 0;             // of the persistent kernel
   MsLevelRec* log = nullptr;       // per-level records of the last call
   int log_cap = 0;
   hipStream_t gstream = nullptr;  // graph mode: capture/replay stream (non-blocking)

@@ -116,6 +116,7 @@ struct MsArgs {
   unsigned long long timeout_ticks;
   int32_t ablation;       // BLEST_MS_NO_GETVI | BLEST_MS_NO_DIRTY (the paper's ablation steps), else 0
   gptr<unsigned long long> hstat;  // pinned host word: how the launch went
+  int32_t fb_words;       // front-bit words the gather keeps in LDS (all of them), or 0: read from memory
   int32_t inlined;        // 1: the sources and the plan are these, not srcs and batches
   MsBatch plan_in[kMsInlineBatches];
   int32_t srcs_in[kMsInlineSrcs];
@@ -686,6 +687,10 @@ constexpr int kRowLanes = W <= 2 ? 1 : W / 2;
 template <int W>
 constexpr int kRowsPerWave = 64 / kRowLanes<W>;
 
+// N consecutive 32-bit entries from any entry on.
+template <int N>
+using i32_vec = int __attribute__((ext_vector_type(N), aligned(4)));
+
 // Words 2 sub, 2 sub + 1 of a row (W = 1: its only word and 0).
 template <int W>
 __device__ __forceinline__ u64x2 load_pair(gptr<const unsigned long long> base, long long vi, int sub) {
@@ -807,11 +812,13 @@ struct MsGatherLds {
   lptr<int> cnt;                  // 64 * kWMax per-traversal counts
   lptr<unsigned long long> stat;  // kMsStatWords statistics
   lptr<int> next;                 // the workgroup's next task
+  lptr<uint32_t> fbits;           // the level's front bits (FL)
 };
 
 // FUSED: also Stage 2 of the level; otherwise the marks go to N and the dirty
-// flags for ms_finalize. COUNT: per-traversal counts of the new pairs.
-template <int SIGMA, int W, int BLOCK, bool FUSED, bool COUNT, int ABL>
+// flags for ms_finalize. COUNT: per-traversal counts of the new pairs. FL: the
+// front bits are read from LDS, where every workgroup copies them first.
+template <int SIGMA, int W, int BLOCK, bool FUSED, bool COUNT, bool FL, int ABL>
 __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi, int level,
                                                     unsigned long long raw_stats, MsGatherLds lds) {
   args_ref<MsArgs> a = uniform_args(a_);
@@ -933,9 +940,15 @@ __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi,
       c[m] = i < E[m] ? col[i] : -1;
     }
   };
+  auto front_word = [&](int c) -> uint32_t {
+    if constexpr (FL)
+      return lds.fbits[c >> 5];
+    else
+      return fb[c >> 5];
+  };
   auto load_words = [&](Cols& k) {
 #pragma unroll
-    for (int m = 0; m < M; ++m) k.w[m] = k.c[m] >= 0 ? fb[k.c[m] >> 5] : 0u;
+    for (int m = 0; m < M; ++m) k.w[m] = k.c[m] >= 0 ? front_word(k.c[m]) : 0u;
   };
   auto scan = [&](const int (&P)[M], const int (&E)[M], int stride, Cols& k, u64x2 (&acc)[M]) {
     Cols nx;
@@ -1040,6 +1053,22 @@ __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi,
   for (int i = threadIdx.x; i < kMsWideSlots * kWMax; i += BLOCK) lds.wide[i] = 0ULL;
   if (threadIdx.x < kMsWideSlots) lds.done[threadIdx.x] = 0;
   if (threadIdx.x == 0) *lds.next = 0;
+  if constexpr (FL) {
+    // 16 bytes per thread and load, four loads in flight (the buffer and the
+    // LDS copy are padded to 16 bytes)
+    const gptr<const u32x4> src = (gptr<const u32x4>)fb;
+    const lptr<u32x4> dst = (lptr<u32x4>)lds.fbits;
+    const int nv = (a.fb_words + 3) / 4;
+    for (int i0 = threadIdx.x; i0 < nv; i0 += 4 * BLOCK) {
+      u32x4 q[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (i0 + j * BLOCK < nv) q[j] = src[i0 + j * BLOCK];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (i0 + j * BLOCK < nv) dst[i0 + j * BLOCK] = q[j];
+    }
+  }
   __syncthreads();
   int t = take();
   Head cur = head(t);
@@ -1144,16 +1173,21 @@ __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi,
       const int p1 = cur.p1 - cur.p0 > kMsLightDeg ? cur.p0 : cur.p1;  // longer rows are in the lists above
       bool run = group(is_open(op)) && p < p1;
       if (__ballot(run)) {
+        // a lane's G consecutive columns in one load (they may start at any
+        // entry; col is padded by 4): G loads of one column each, spread over
+        // R rows, kept the address unit busy for most of a sparse level
         auto columns = [&](int q, int (&c)[G]) {
+          const int i = q + G * sub;
+          i32_vec<G> x;
 #pragma unroll
-          for (int g = 0; g < G; ++g) {
-            const int i = q + g * L + sub;
-            c[g] = run && i < p1 ? col[i] : -1;
-          }
+          for (int g = 0; g < G; ++g) x[g] = -1;
+          if (run && i < p1) x = *(gptr<const i32_vec<G>>)(col + i);
+#pragma unroll
+          for (int g = 0; g < G; ++g) c[g] = i + g < p1 ? x[g] : -1;
         };
         auto words = [&](const int (&c)[G], uint32_t (&w)[G]) {
 #pragma unroll
-          for (int g = 0; g < G; ++g) w[g] = c[g] >= 0 ? fb[c[g] >> 5] : 0u;
+          for (int g = 0; g < G; ++g) w[g] = c[g] >= 0 ? front_word(c[g]) : 0u;
         };
         int c0[G], c1[G];
         uint32_t fw[G];
@@ -1241,12 +1275,17 @@ __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi,
 template <int SIGMA, int BLOCK, bool FUSED, int ABL>
 __device__ __forceinline__ void ms_gather_any(args_ref<MsArgs> a, int bi, int level, int W, const MsView& st,
                                               const MsGatherLds& lds, bool count) {
+  constexpr bool FL = SIGMA == 8 && FUSED && ABL == 0;  // kernels that may hold the front bits in LDS
   auto go = [&](auto width) {
     constexpr int WW = decltype(width)::value;
-    if (FUSED && count)
-      ms_gather<SIGMA, WW, BLOCK, FUSED, FUSED, ABL>(a, bi, level, st.raw, lds);
+    if (FL && a.fb_words && count)
+      ms_gather<SIGMA, WW, BLOCK, FUSED, FUSED, FL, ABL>(a, bi, level, st.raw, lds);
+    else if (FL && a.fb_words)
+      ms_gather<SIGMA, WW, BLOCK, FUSED, false, FL, ABL>(a, bi, level, st.raw, lds);
+    else if (FUSED && count)
+      ms_gather<SIGMA, WW, BLOCK, FUSED, FUSED, false, ABL>(a, bi, level, st.raw, lds);
     else
-      ms_gather<SIGMA, WW, BLOCK, FUSED, false, ABL>(a, bi, level, st.raw, lds);
+      ms_gather<SIGMA, WW, BLOCK, FUSED, false, false, ABL>(a, bi, level, st.raw, lds);
   };
   switch (W) {
     case 1:
@@ -1592,10 +1631,14 @@ __device__ __attribute__((noinline)) void ms_finalize(args_ref<MsArgs> a_, int b
 
 // ------------------------------------------------------------- batches
 
-// LDS every multi-source kernel needs.
-template <int SIGMA, int BLOCK>
+// LDS every multi-source kernel needs: the queue engine's tables (f), in whose
+// place the gather step has 256 ints per wave of compacted neighbours and then
+// the front bits. DYN: that region is dynamic LDS, sized by the host
+// (ms_dynamic_lds).
+constexpr int kMsRowWords = 128;  // 64-bit words of a wave's compacted neighbours
+template <int SIGMA, int BLOCK, bool DYN>
 struct MsLds {
-  unsigned long long f[(BLOCK / 64) * ms_lds_words<SIGMA>()];  // the queue engine's tables; the gather's compaction
+  unsigned long long f[DYN ? 1 : (BLOCK / 64) * ms_lds_words<SIGMA>()];
   unsigned long long wide[kMsWideSlots * kWMax];
   int done[kMsWideSlots];
   unsigned long long stat[kMsStatWords];
@@ -1603,18 +1646,20 @@ struct MsLds {
   int next;
 };
 
-template <int SIGMA, int BLOCK>
-__device__ __forceinline__ void ms_lds_init(MsLds<SIGMA, BLOCK>& s) {
+template <int SIGMA, int BLOCK, bool DYN>
+__device__ __forceinline__ void ms_lds_init(MsLds<SIGMA, BLOCK, DYN>& s) {
   for (int c = threadIdx.x; c < 64 * kWMax; c += BLOCK) s.cnt[c] = 0;
   if (threadIdx.x < kMsStatWords) s.stat[threadIdx.x] = 0ULL;
   __syncthreads();
 }
 
-template <int SIGMA, int BLOCK>
-__device__ __forceinline__ MsGatherLds ms_gather_lds(MsLds<SIGMA, BLOCK>& s) {
-  static_assert(ms_lds_words<SIGMA>() * 2 >= 256, "the gather compacts up to 256 columns per wave");
-  return MsGatherLds{to_lds(reinterpret_cast<int*>(s.f + wave_in_block() * ms_lds_words<SIGMA>())), to_lds(s.wide),
-                     to_lds(s.done), to_lds(s.cnt), to_lds(s.stat), to_lds(&s.next)};
+// region: the LDS of the queue engine's tables.
+template <int SIGMA, int BLOCK, bool DYN>
+__device__ __forceinline__ MsGatherLds ms_gather_lds(MsLds<SIGMA, BLOCK, DYN>& s, lptr<unsigned long long> region) {
+  static_assert(ms_lds_words<SIGMA>() >= kMsRowWords, "the gather compacts up to 256 columns per wave");
+  return MsGatherLds{(lptr<int>)(region + wave_in_block() * kMsRowWords), to_lds(s.wide), to_lds(s.done),
+                     to_lds(s.cnt), to_lds(s.stat), to_lds(&s.next),
+                     (lptr<uint32_t>)(region + (BLOCK / 64) * kMsRowWords)};
 }
 
 // Clears what a batch starts from: visited and next words, the front bits,
@@ -1749,10 +1794,21 @@ __device__ __attribute__((noinline)) void ms_reduce_batch(args_ref<MsArgs> a_, i
   }
 }
 
-// A level whose queue holds fewer than 1 / kMsDenseDenom of the graph's arcs
-// as slices takes the queue form of a BVSS step, any other the gather step,
-// which reads at most the arcs of the vertices still open.
+// A level whose queue holds at least 1 / kMsDenseDenom of the graph's arcs as
+// slices takes the gather step, which reads at most the arcs of the vertices
+// still open; one with fewer the queue form of a BVSS step, unless even so the
+// gather step is the quicker. That is judged by what both measured: a gather
+// step takes 14 us (16 K vertices) and up to 18 more with the vertices (256 K
+// and beyond), and 1 us per 250,000 arcs of open vertices; the queue form, with
+// its two more passes and barriers, 28 us for a few slices and 50 to 90 from
+// about 2,000. (Last levels of 64 traversals on 16 K vertices: 42 and 27 us by
+// the queue, 13 by the gather; first level of 256 on 300 K vertices: 92 and 50.)
 constexpr long long kMsDenseDenom = 128;
+__device__ __forceinline__ bool ms_gather_quicker(long long n, long long m, long long slices, float open_part) {
+  const float gather = 14.0f + fminf(static_cast<float>(n) * (1.0f / 13000.0f), 18.0f) +
+                       static_cast<float>(m) * (1.0f / 250000.0f) * open_part;
+  return gather <= (slices >= 2048 ? 53.0f : 28.0f);
+}
 
 // What a level does, from its statistics alone (the same in every wave).
 struct MsChoice {
@@ -1796,7 +1852,10 @@ __device__ __attribute__((noinline)) int ms_decide_level(args_ref<MsArgs> a_, un
   const MsBatch bt = ms_batch(a, bi);
   const long long fresh = st.get(MS_FRESH), qlen = st.get(MS_QUEUE), qslices = st.get(MS_QSLICES);
   const long long unv = static_cast<long long>(bt.count) * a.n - st.get(MS_CUMIN) - fresh;
-  MsChoice ch{!MF && ms_abl<ABL>(a) == 0 && qslices * kMsDenseDenom >= a.m, BLEST_ENGINE_BVSS, 0};
+  const float open_part = static_cast<float>(unv) / (static_cast<float>(bt.count) * static_cast<float>(a.n));
+  MsChoice ch{!MF && ms_abl<ABL>(a) == 0 &&
+                  (qslices * kMsDenseDenom >= a.m || ms_gather_quicker(a.n, a.m, qslices, open_part)),
+              BLEST_ENGINE_BVSS, 0};
   const bool writer = blockIdx.x == 0 && wave_in_block() == 0;
   if (!ch.dense || writer) {
     float feat[kMaxSwitchFeatures];
@@ -1842,13 +1901,19 @@ __global__ void __launch_bounds__(BLOCK) k_ms_persistent(MsArgs args) {
   constexpr bool MF = MODE == 1;
   constexpr int ABL = MODE >= 10 ? MODE - 10 : 0;
   constexpr int GABL = MODE >= 10 ? -1 : 0;  // the gather's: one body for all ablation kernels
-  extern __shared__ float s_mlp[];
-  __shared__ MsLds<SIGMA, BLOCK> lds;
+  extern __shared__ __attribute__((aligned(16))) float s_mlp[];
+  // dynamic LDS: the switch network (learned policy), then the tables or front bits
+  constexpr bool DYN = SIGMA == 8 && MODE == 0;
+  __shared__ MsLds<SIGMA, BLOCK, DYN> lds;
+  const lptr<unsigned long long> region =
+      DYN ? (lptr<unsigned long long>)to_lds(s_mlp + (a.policy == BLEST_POLICY_LEARNED ? kLdsMlpFloats : 0))
+          : to_lds(lds.f);
+  static_assert(kLdsMlpFloats % 4 == 0, "the region is 16-byte aligned");
   const bool learned = a.policy == BLEST_POLICY_LEARNED && a.mlp != nullptr && a.mlp->valid;
   if (learned) mlp_to_lds((const MlpDev*)a.mlp, s_mlp);
   const int wave = wave_in_block();
-  const lptr<unsigned long long> my_f = to_lds(lds.f) + wave * ms_lds_words<SIGMA>();
-  const MsGatherLds glds = ms_gather_lds(lds);
+  const lptr<unsigned long long> my_f = region + wave * ms_lds_words<SIGMA>();
+  const MsGatherLds glds = ms_gather_lds(lds, region);
   const bool count_sources = a.sums != nullptr || a.reach != nullptr || a.cc != nullptr;
   ms_lds_init(lds);
   if (blockIdx.x == 0 && threadIdx.x == 0) host_status_begin(a.hstat);
@@ -1944,7 +2009,7 @@ __global__ void __launch_bounds__(BLOCK) k_ms_phase(MsArgs args, int parity) {
   args_ref<MsArgs> a = kernel_args(args);
   constexpr int ABL = -1;
   extern __shared__ float s_mlp[];
-  __shared__ MsLds<SIGMA, BLOCK> lds;
+  __shared__ MsLds<SIGMA, BLOCK, false> lds;
   const int phase = a.ctl->ms_state[parity][0];
   const int bi = uniform(a.ctl->ms_state[parity][1]);
   const int level = uniform(a.ctl->ms_state[parity][2]);
@@ -1954,7 +2019,7 @@ __global__ void __launch_bounds__(BLOCK) k_ms_phase(MsArgs args, int parity) {
   if (phase != MS_DONE) {
     const int wave = wave_in_block();
     const lptr<unsigned long long> my_f = to_lds(lds.f) + wave * ms_lds_words<SIGMA>();
-    const MsGatherLds glds = ms_gather_lds(lds);
+    const MsGatherLds glds = ms_gather_lds(lds, to_lds(lds.f));
     const unsigned xcc = xcc_id();
     const bool count_sources = a.sums != nullptr || a.reach != nullptr || a.cc != nullptr;
     ms_lds_init(lds);
@@ -2087,6 +2152,27 @@ void ms_graph_destroy(MsDev* ms) {
   for (auto& nd : ms->gnode) nd = nullptr;
 }
 
+// Dynamic LDS of the persistent kernel, and whether its gather steps read the
+// front bits from there (a.fb_words): when they fit beside the compaction rows,
+// up to 1.1 M vertices (0.95 M with the switch network's weights). The test of an
+// arc is then one LDS read instead of one of the up to 64 cache lines of a
+// wave's load. First gather level of 64 to 512 traversals on a 1 M vertex R-MAT
+// (30 M arcs): 236, 238, 285 and 381 us with the bits in memory, 153, 152, 199
+// and 286 in LDS; on 256 K vertices (32 KB of bits, as much as the vector L1)
+// 90 and 80. A level pays the copy, 2 to 3 us for 128 KB.
+unsigned ms_dynamic_lds(const DevGraph& g, const MsDev& ms, int policy, MsArgs* a) {
+  const unsigned mlp = policy == BLEST_POLICY_LEARNED ? kLdsMlpFloats * sizeof(float) : 0u;
+  a->fb_words = 0;
+  if (g.sigma != 8 || g.ms_mfma || g.ms_ablation) return mlp;  // these kernels' tables are static
+  constexpr unsigned waves = kMsBlock / 64;
+  const unsigned tables = mlp + waves * ms_lds_words<8>() * 8u;
+  const int64_t words = (g.nsets * g.sigma + 31) / 32;
+  const int64_t front = mlp + waves * kMsRowWords * 8u + 16 * ((words + 3) / 4);
+  if (a->probe || front + static_cast<int64_t>(ms.static_lds) > g.max_lds) return tables;
+  a->fb_words = static_cast<int32_t>(words);
+  return std::max(tables, static_cast<unsigned>(front));
+}
+
 hipError_t ensure(const DevGraph& g, MsDev* ms, int wmax, int32_t k, int nbatches) {
   const int64_t nhat = g.nsets * g.sigma;
   if (ms->wmax < wmax || ms->nhat != nhat) {
@@ -2127,8 +2213,13 @@ hipError_t ensure(const DevGraph& g, MsDev* ms, int wmax, int32_t k, int nbatche
   }
   if (ms->grid == 0) {
     int nb = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, ms_kernel(g), kMsBlock,
-                                                                 kLdsMlpFloats * sizeof(float));
+    hipFuncAttributes attr;
+    hipError_t e = hipFuncGetAttributes(&attr, ms_kernel(g));
+    if (e != hipSuccess) return e;
+    ms->static_lds = attr.sharedSizeBytes;
+    MsArgs any{};
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, ms_kernel(g), kMsBlock,
+                                                     ms_dynamic_lds(g, *ms, BLEST_POLICY_LEARNED, &any));
     if (e != hipSuccess) return e;
     if (nb < 1) return hipErrorInvalidConfiguration;
     ms->grid = g.num_cu;
@@ -2271,7 +2362,8 @@ hipError_t ms_run(const DevGraph& g, MsDev* ms, const int32_t* srcs, int32_t k, 
   const unsigned shmem = policy == BLEST_POLICY_LEARNED ? kLdsMlpFloats * sizeof(float) : 0u;
   if (!graph || probe) {
     void* args[] = {static_cast<void*>(&a)};
-    return hipLaunchCooperativeKernel(ms_kernel(g), dim3(ms->grid), dim3(ms->block), args, shmem, st);
+    const unsigned dyn = ms_dynamic_lds(g, *ms, policy, &a);
+    return hipLaunchCooperativeKernel(ms_kernel(g), dim3(ms->grid), dim3(ms->block), args, dyn, st);
   }
   // Graph mode: kMsGraphKernels phase kernels, then copies of the state and
   // error words to pinned host memory, built once as a hipGraph for a stream
@@ -2477,9 +2569,9 @@ hipError_t ms_run_noalloc(const DevGraph& g, MsDev* ms, const int32_t* srcs, con
   // no level planes here (the entry point allocates nothing): the caller's
   // rows are written directly
   a.planes = nullptr;
-  const unsigned shmem = policy == BLEST_POLICY_LEARNED ? kLdsMlpFloats * sizeof(float) : 0u;
   void* args[] = {static_cast<void*>(&a)};
-  return hipLaunchCooperativeKernel(ms_kernel(g), dim3(ms->grid), dim3(ms->block), args, shmem, st);
+  const unsigned dyn = ms_dynamic_lds(g, *ms, policy, &a);
+  return hipLaunchCooperativeKernel(ms_kernel(g), dim3(ms->grid), dim3(ms->block), args, dyn, st);
 }
 
 }  // namespace blest
