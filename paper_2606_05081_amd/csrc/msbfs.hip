@@ -117,6 +117,7 @@ struct MsArgs {
   int32_t ablation;       // BLEST_MS_NO_GETVI | BLEST_MS_NO_DIRTY (the paper's ablation steps), else 0
   gptr<unsigned long long> hstat;  // pinned host word: how the launch went
   int32_t fb_words;       // front-bit words the gather keeps in LDS (all of them), or 0: read from memory
+  int32_t mlp_shared;     // 1: the switch network's weights lie in the gather's LDS and are reloaded for each level
   int32_t inlined;        // 1: the sources and the plan are these, not srcs and batches
   MsBatch plan_in[kMsInlineBatches];
   int32_t srcs_in[kMsInlineSrcs];
@@ -1837,9 +1838,18 @@ __device__ __forceinline__ void ms_log(args_ref<MsArgs> a, int nrec, int bi, int
   for (int k = 0; k < kMaxSwitchFeatures; ++k) rec->feat[k] = feat[k];
 }
 
+// Whether a level takes the gather step whatever its engine.
+__device__ __forceinline__ bool ms_dense(args_ref<MsArgs> a, const MsView& st, int count) {
+  const long long slices = st.get(MS_QSLICES), all = static_cast<long long>(count) * a.n;
+  const long long unv = all - st.get(MS_CUMIN) - st.get(MS_FRESH);
+  return slices * kMsDenseDenom >= a.m ||
+         ms_gather_quicker(a.n, a.m, slices, static_cast<float>(unv) / static_cast<float>(all));
+}
+
 // Decides level `level` and logs it. The engine of a dense level changes
 // nothing but its record (both engines take the gather form), so there only
-// workgroup 0's first wave, which writes the record, evaluates it.
+// the last workgroup's first wave, which writes the record, evaluates it (the
+// last has the fewest tasks, and workgroup 0 clears the next counters).
 template <int ABL, bool MF>
 __device__ __attribute__((noinline)) int ms_decide_level(args_ref<MsArgs> a_, unsigned long long raw_stats, int bi,
                                                          int level, int nrec, lptr<const float> s_mlp,
@@ -1852,11 +1862,8 @@ __device__ __attribute__((noinline)) int ms_decide_level(args_ref<MsArgs> a_, un
   const MsBatch bt = ms_batch(a, bi);
   const long long fresh = st.get(MS_FRESH), qlen = st.get(MS_QUEUE), qslices = st.get(MS_QSLICES);
   const long long unv = static_cast<long long>(bt.count) * a.n - st.get(MS_CUMIN) - fresh;
-  const float open_part = static_cast<float>(unv) / (static_cast<float>(bt.count) * static_cast<float>(a.n));
-  MsChoice ch{!MF && ms_abl<ABL>(a) == 0 &&
-                  (qslices * kMsDenseDenom >= a.m || ms_gather_quicker(a.n, a.m, qslices, open_part)),
-              BLEST_ENGINE_BVSS, 0};
-  const bool writer = blockIdx.x == 0 && wave_in_block() == 0;
+  MsChoice ch{!MF && ms_abl<ABL>(a) == 0 && ms_dense(a, st, bt.count), BLEST_ENGINE_BVSS, 0};
+  const bool writer = blockIdx.x == gridDim.x - 1 && wave_in_block() == 0;
   if (!ch.dense || writer) {
     float feat[kMaxSwitchFeatures];
     const int live = st.live();
@@ -1906,7 +1913,7 @@ __global__ void __launch_bounds__(BLOCK) k_ms_persistent(MsArgs args) {
   constexpr bool DYN = SIGMA == 8 && MODE == 0;
   __shared__ MsLds<SIGMA, BLOCK, DYN> lds;
   const lptr<unsigned long long> region =
-      DYN ? (lptr<unsigned long long>)to_lds(s_mlp + (a.policy == BLEST_POLICY_LEARNED ? kLdsMlpFloats : 0))
+      DYN ? (lptr<unsigned long long>)to_lds(s_mlp + (a.policy == BLEST_POLICY_LEARNED && !a.mlp_shared ? kLdsMlpFloats : 0))
           : to_lds(lds.f);
   static_assert(kLdsMlpFloats % 4 == 0, "the region is 16-byte aligned");
   const bool learned = a.policy == BLEST_POLICY_LEARNED && a.mlp != nullptr && a.mlp->valid;
@@ -1932,8 +1939,15 @@ __global__ void __launch_bounds__(BLOCK) k_ms_persistent(MsArgs args) {
     for (;; ++level) {
       const MsView st = ms_stats(a.ctl, level % kStatSlots);
       if (st.get(MS_FRESH) == 0) break;
+      // (only the last workgroup evaluates the network at a dense level)
+      const bool reload = DYN && learned && a.mlp_shared && (blockIdx.x == gridDim.x - 1 || !ms_dense(a, st, bt.count));
+      if (reload) {
+        mlp_to_lds((const MlpDev*)a.mlp, s_mlp);
+        __syncthreads();
+      }
       const MsChoice ch =
           ms_decide<ABL, MF>(a, st, bi, level, nrec, to_lds((const float*)s_mlp), learned);
+      if (reload) __syncthreads();  // every wave has read the weights
       const gptr<MsLevelRec> rec = (a.log && nrec < a.log_cap) ? a.log + nrec : nullptr;
       ++nrec;
       ms_prepare_next<SIGMA>(a, bt.W, level + 1);
@@ -2154,7 +2168,8 @@ void ms_graph_destroy(MsDev* ms) {
 
 // Dynamic LDS of the persistent kernel, and whether its gather steps read the
 // front bits from there (a.fb_words): when they fit beside the compaction rows,
-// up to 1.1 M vertices (0.95 M with the switch network's weights). The test of an
+// up to 1.07 M vertices. (From 0.91 M on the switch network's weights lie in the
+// same place and are loaded again before each decision, 2 us.) The test of an
 // arc is then one LDS read instead of one of the up to 64 cache lines of a
 // wave's load. First gather level of 64 to 512 traversals on a 1 M vertex R-MAT
 // (30 M arcs): 236, 238, 285 and 381 us with the bits in memory, 153, 152, 199
@@ -2163,14 +2178,17 @@ void ms_graph_destroy(MsDev* ms) {
 unsigned ms_dynamic_lds(const DevGraph& g, const MsDev& ms, int policy, MsArgs* a) {
   const unsigned mlp = policy == BLEST_POLICY_LEARNED ? kLdsMlpFloats * sizeof(float) : 0u;
   a->fb_words = 0;
+  a->mlp_shared = 0;
   if (g.sigma != 8 || g.ms_mfma || g.ms_ablation) return mlp;  // these kernels' tables are static
   constexpr unsigned waves = kMsBlock / 64;
   const unsigned tables = mlp + waves * ms_lds_words<8>() * 8u;
   const int64_t words = (g.nsets * g.sigma + 31) / 32;
-  const int64_t front = mlp + waves * kMsRowWords * 8u + 16 * ((words + 3) / 4);
-  if (a->probe || front + static_cast<int64_t>(ms.static_lds) > g.max_lds) return tables;
+  const int64_t front = waves * kMsRowWords * 8u + 16 * ((words + 3) / 4);
+  const int64_t room = g.max_lds - static_cast<int64_t>(ms.static_lds);
+  if (a->probe || front > room) return tables;
   a->fb_words = static_cast<int32_t>(words);
-  return std::max(tables, static_cast<unsigned>(front));
+  a->mlp_shared = mlp + front > room;
+  return std::max(a->mlp_shared ? tables - mlp : tables, static_cast<unsigned>(a->mlp_shared ? front : mlp + front));
 }
 
 hipError_t ensure(const DevGraph& g, MsDev* ms, int wmax, int32_t k, int nbatches) {
@@ -2348,6 +2366,10 @@ hipError_t ms_run(const DevGraph& g, MsDev* ms, const int32_t* srcs, int32_t k, 
   MsArgs a = ms_args(g, ms, ms->srcs, static_cast<const MsBatch*>(ms->batches), nplan, policy, eta, seed, levels16,
                      sums, reach, cc, far, probe);
   if (k <= kMsInlineSrcs && nplan <= kMsInlineBatches) {
+    // (a capturing stream is refused, as the synchronisation below would refuse it)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
+      return hipErrorStreamCaptureUnsupported;
     a.inlined = 1;
     std::copy(srcs, srcs + k, a.srcs_in);
     std::copy(plan.begin(), plan.end(), a.plan_in);

@@ -1,6 +1,7 @@
 """Multi-source calls on both sides of two lines: front bits in LDS or read
-from memory (1,074,560 vertices, 907,776 with the switch network's weights,
-are the last that fit beside the kernel's other LDS), and source lists in the
+from memory (1,074,560 vertices are the last that fit beside the kernel's other
+LDS, 907,776 the last beside the switch network's weights too, which share the
+place beyond), and source lists in the
 kernel arguments (512 sources, 8 batches) or copied. Levels, sums and
 distances are integers: array equality with the oracle."""
 import numpy as np
