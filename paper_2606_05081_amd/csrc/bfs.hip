@@ -683,21 +683,87 @@ __device__ __attribute__((noinline)) long long engine_push(args_ref<BfsArgs> a_,
   return work;
 }
 
-// E2: bottom-up (Alg. 4). A lane owns one vertex; an unvisited vertex of
-// degree <= kPullLight scans its row alone and stops at the first frontier
-// neighbour. Longer rows are scanned by the whole wave, 64 neighbours per
-// step, stopping at the first step that finds one.
+// E2: bottom-up (Alg. 4). A lane owns a vertex of each of kPullChunks chunks
+// of 64 and scans its row four neighbours per step, all chunks together, to
+// its first frontier neighbour; a row longer than kPullLight goes over to the
+// whole wave, 64 neighbours per step, after kPullTry of them. What bounds it is
+// the chain of loads of a step (four columns, their front words) times the
+// steps of the longest row in flight, with two waves per SIMD: with a chunk at
+// a time, and every long row scanned by the wave from its start, the step at
+// which a 1 M vertex R-MAT (30 M arcs) is first searched bottom-up took 87 us,
+// with two chunks and the lanes' tries 23 (four chunks: 23, and 2 us more at
+// the steps of a 256 K R-MAT and of an Erdos-Renyi graph, whose rows end soon).
 constexpr int kPullLight = 32;
+constexpr int kPullTry = 16;
+constexpr int kPullChunks = 2;
+
+// Scans columns q[k] .. lim[k] of U rows of this lane, four at a time, each to
+// its first neighbour in front; bit k of the result: found, q[k] past the
+// columns read. (One 16-byte load of four neighbours: col is padded by 4
+// entries, so the load stays in bounds at the end of the array.)
+template <int SIGMA, int U>
+__device__ __forceinline__ uint32_t pull_scan(gptr<const int32_t> col, gptr<const typename MaskOf<SIGMA>::T> front,
+                                              int (&q)[U], const int (&lim)[U]) {
+  using M = typename MaskOf<SIGMA>::T;
+  uint32_t found = 0;
+  for (;;) {
+    bool on[U];
+    bool more = false;
+    int c[U][4];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      on[k] = q[k] < lim[k] && !((found >> k) & 1u);
+      more |= on[k];
+    }
+    if (!__ballot(more)) return found;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) c[k][t] = 0;
+      if (on[k]) __builtin_memcpy(c[k], reinterpret_cast<const int32_t*>(col + q[k]), sizeof(c[k]));
+    }
+    M w[U][4];
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        w[k][t] = on[k] && q[k] + t < lim[k] ? front[static_cast<uint32_t>(c[k][t]) / SIGMA] : M(0);
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      bool hit = false;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) hit |= (w[k][t] >> (static_cast<uint32_t>(c[k][t]) % SIGMA)) & 1u;
+      if (hit) found |= 1u << k;
+      if (on[k]) q[k] += 4;
+    }
+  }
+}
+
+// The whole wave scans columns p .. e of one row; whether one is in front.
+template <int SIGMA>
+__device__ __forceinline__ bool pull_scan_wave(gptr<const int32_t> col, gptr<const typename MaskOf<SIGMA>::T> front,
+                                               int p, int e, uint32_t& work) {
+  for (; p < e; p += 64) {
+    const int i = p + lane_id();
+    bool f = false;
+    if (i < e) {
+      const uint32_t v = static_cast<uint32_t>(col[i]);
+      f = (front[v / SIGMA] >> (v % SIGMA)) & 1u;
+      ++work;
+    }
+    if (__ballot(f)) return true;
+  }
+  return false;
+}
 
 template <int SIGMA>
 __device__ __attribute__((noinline)) long long engine_pull(args_ref<BfsArgs> a_, int sel, long long gw,
                                                            long long nw) {
   args_ref<BfsArgs> a = uniform_args(a_);
   sel = uniform(sel);
-  gw = uniform(gw);
-  nw = uniform(nw);
-  long long work = 0;
+  uint32_t work = 0;
   using M = typename MaskOf<SIGMA>::T;
+  constexpr int U = kPullChunks;
   gptr<const M> __restrict__ vis = (gptr<const M>)a.vis;
   gptr<const M> __restrict__ front = (gptr<const M>)front_buf(a, sel);
   gptr<const M> __restrict__ degm = (gptr<const M>)a.degmask_in;
@@ -709,60 +775,50 @@ __device__ __attribute__((noinline)) long long engine_pull(args_ref<BfsArgs> a_,
   // 64-vertex chunks: round k gives the waves chunks k*nw .. k*nw + nw - 1,
   // rotated by k, so chunks with heavy rows that recur with a fixed stride
   // (a relabelling that puts each window's hubs first) spread over all waves
-  const long long nchunks = (nv + 63) / 64;
-  for (long long k = 0; k * nw < nchunks; ++k) {
-    const long long chunk = k * nw + (gw + k) % nw;
-    if (chunk >= nchunks) continue;
-    const long long ubase = chunk * 64;
-    const long long u = ubase + lane;
-    bool cand = false;
-    int p = 0, e = 0;
-    if (u < nv) {
-      const long long s = u / SIGMA;
-      const M unv = static_cast<M>(~vis[s] & degm[s]);
-      cand = (unv >> (u % SIGMA)) & 1u;
-    }
-    if (cand) {
-      p = rp[u];
-      e = rp[u + 1];
-    }
-    const bool heavy = cand && (e - p > kPullLight);
-    if (cand && !heavy) {
-      // four independent neighbour loads per step shorten the dependent chain
-      const int p0 = p;
-      bool found = false;
-      for (; p < e && !found; p += 4) {
-        // one 16-byte load of 4 neighbours (col is padded by 4 entries, so
-        // the load stays in bounds at the end of the array)
-        int q[4];
-        __builtin_memcpy(q, reinterpret_cast<const int32_t*>(col + p), sizeof(q));
-        const int v0 = q[0];
-        const int v1 = p + 1 < e ? q[1] : v0;
-        const int v2 = p + 2 < e ? q[2] : v0;
-        const int v3 = p + 3 < e ? q[3] : v0;
-        found = ((front[v0 / SIGMA] >> (v0 % SIGMA)) & 1u) | ((front[v1 / SIGMA] >> (v1 % SIGMA)) & 1u) |
-                ((front[v2 / SIGMA] >> (v2 % SIGMA)) & 1u) | ((front[v3 / SIGMA] >> (v3 % SIGMA)) & 1u);
+  const int nchunks = static_cast<int>((nv + 63) / 64), waves = uniform(static_cast<int>(nw));
+  int turn = uniform(static_cast<int>(gw));
+  for (int round0 = 0; round0 < nchunks; round0 += U * waves) {
+    uint32_t u[U];
+    int p[U], e[U], q[U], lim[U];
+    bool cand[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int chunk = round0 + k * waves + turn;
+      turn = turn + 1 == waves ? 0 : turn + 1;
+      u[k] = static_cast<uint32_t>(chunk) * 64u + static_cast<uint32_t>(lane);
+      cand[k] = false;
+      if (chunk < nchunks && u[k] < nv) {
+        const M unv = static_cast<M>(~vis[u[k] / SIGMA] & degm[u[k] / SIGMA]);
+        cand[k] = (unv >> (u[k] % SIGMA)) & 1u;
       }
-      if (found) mark[u] = 1;
-      work += min(p, e) - p0;
     }
-    unsigned long long hb = __ballot(heavy);
-    while (hb) {
-      const int l = __builtin_ctzll(hb);
-      hb &= hb - 1;
-      const int hp = __builtin_amdgcn_readlane(p, l), he = __builtin_amdgcn_readlane(e, l);
-      for (int qq = hp; qq < he; qq += 64) {
-        const int i = qq + lane;
-        bool f = false;
-        if (i < he) {
-          const int v = col[i];
-          f = (front[v / SIGMA] >> (v % SIGMA)) & 1u;
-          ++work;
-        }
-        if (__ballot(f)) {
-          if (lane == 0) mark[ubase + l] = 1;
-          break;
-        }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      p[k] = e[k] = 0;
+      if (cand[k]) {
+        p[k] = rp[u[k]];
+        e[k] = rp[u[k] + 1];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      q[k] = p[k];
+      lim[k] = e[k] - p[k] > kPullLight ? p[k] + kPullTry : e[k];
+    }
+    const uint32_t found = pull_scan<SIGMA, U>(col, front, q, lim);
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const bool f = (found >> k) & 1u;
+      work += static_cast<uint32_t>(min(q[k], lim[k]) - p[k]);
+      if (f) mark[u[k]] = 1;
+      unsigned long long hb = __ballot(!f && lim[k] < e[k]);
+      while (hb) {
+        const int l = __builtin_ctzll(hb);
+        hb &= hb - 1;
+        if (pull_scan_wave<SIGMA>(col, front, __builtin_amdgcn_readlane(lim[k], l),
+                                  __builtin_amdgcn_readlane(e[k], l), work) &&
+            lane == l)
+          mark[u[k]] = 1;
       }
     }
   }
@@ -1850,12 +1906,14 @@ __device__ __attribute__((noinline)) void eager_bu(args_ref<BfsArgs> a_, int lev
   gptr<const int32_t> col = a.col_in;
   const long long nv = a.nsets * SIGMA;
   const int lane = lane_id();
-  const long long nchunks = (nv + 63) / 64;
+  const int nchunks = static_cast<int>((nv + 63) / 64), waves = static_cast<int>(nwaves);
   // 64-vertex chunks, round k rotated by k (as in the lazy bottom-up engine)
-  for (long long k = 0; k * nwaves < nchunks; ++k) {
-    const long long chunk = k * nwaves + (gwave + k) % nwaves;
+  int turn = static_cast<int>(gwave);
+  for (int round0 = 0; round0 < nchunks; round0 += waves) {
+    const int chunk = round0 + turn;
+    turn = turn + 1 == waves ? 0 : turn + 1;
     if (chunk >= nchunks) continue;
-    const long long u = chunk * 64 + lane;
+    const long long u = chunk * 64LL + lane;
     bool cand = false;
     int p = 0, e = 0;
     if (u < nv) {
@@ -1868,33 +1926,18 @@ __device__ __attribute__((noinline)) void eager_bu(args_ref<BfsArgs> a_, int lev
       p = rp[u];
       e = rp[u + 1];
     }
-    const bool heavy = cand && e - p > kPullLight;
-    bool found = false;
-    if (cand && !heavy) {
-      for (int q = p; q < e && !found; ++q) {
-        const int v = col[q];
-        found = (fc[v / SIGMA] >> (v % SIGMA)) & 1u;
-        ++st.work;
-      }
-    }
-    unsigned long long hb = __ballot(heavy);
+    int q[1] = {p};
+    const int lim[1] = {e - p > kPullLight ? p + kPullTry : e};
+    bool found = pull_scan<SIGMA, 1>(col, fc, q, lim) != 0;
+    st.work += static_cast<uint32_t>(min(q[0], lim[0]) - p);
+    unsigned long long hb = __ballot(!found && lim[0] < e);
     while (hb) {
       const int l = __builtin_ctzll(hb);
       hb &= hb - 1;
-      const int hp = __builtin_amdgcn_readlane(p, l), he = __builtin_amdgcn_readlane(e, l);
-      for (int q = hp; q < he; q += 64) {
-        const int i = q + lane;
-        bool f = false;
-        if (i < he) {
-          const int v = col[i];
-          f = (fc[v / SIGMA] >> (v % SIGMA)) & 1u;
-          ++st.work;
-        }
-        if (__ballot(f)) {
-          if (lane == l) found = true;
-          break;
-        }
-      }
+      if (pull_scan_wave<SIGMA>(col, fc, __builtin_amdgcn_readlane(lim[0], l), __builtin_amdgcn_readlane(e, l),
+                                st.work) &&
+          lane == l)
+        found = true;
     }
     const unsigned long long got = __ballot(found);
     if (!got) continue;

@@ -62,3 +62,35 @@ def test_lazy_options(blest, opt):
             run_all_policies(blest, g, src, ref, seeds=(2,))
             assert [r["frontier"] for r in g.level_stats()] == oracle.level_counts(ref).tolist()
         g.close()
+
+
+@pytest.mark.parametrize("scheme", ["LAZY", "EAGER"])
+@pytest.mark.parametrize("sigma", [8, 16, 32])
+def test_bottom_up_row_lengths(blest, scheme, sigma):
+    """Rows one below, at and one above every bound of the bottom-up scan (four
+    columns a step, 16 by a lane, 32, 64 a wave step), whose only neighbour in
+    the frontier is the first, the last, or one before the last."""
+    lens = [1, 2, 3, 4, 5, 15, 16, 17, 31, 32, 33, 34, 47, 48, 79, 80, 81, 144, 145, 400]
+    nrow = 3 * len(lens)
+    leaves = max(lens)
+    # ids: gate first, leaves, rows, gate last; every leaf belongs to a row only
+    us, vs = [], []
+    last = 1 + leaves + nrow
+    for i in range(nrow):
+        row, d, kind = 1 + leaves + i, lens[i // 3], i % 3
+        gate = 0 if kind == 0 else last
+        others = 1 + (np.arange(d - 1) * 7 + i) % leaves if d > 1 else np.zeros(0, np.int64)
+        if kind == 2:
+            others = np.concatenate([others[:-1], [last + 1]]) if d > 1 else others  # beyond the gate
+        us.append(np.full(others.size + 1, row))
+        vs.append(np.concatenate([others, [gate]]))
+    src = last + 2
+    us.append(np.array([src, src]))
+    vs.append(np.array([0, last]))
+    rp, col = inputs.from_pairs(src + 1, np.concatenate(us).astype(np.int32), np.concatenate(vs).astype(np.int32))
+    g = blest.Graph(rp, col, sigma=sigma, reorder=0, update_scheme=getattr(blest.Update, scheme))
+    for s in (src, 0, last, 1, 1 + leaves):
+        ref = oracle.bfs(rp, col, s)
+        run_all_policies(blest, g, s, ref, seeds=(1,))
+        assert [r["frontier"] for r in g.level_stats()] == oracle.level_counts(ref).tolist()
+    g.close()
