@@ -1653,7 +1653,10 @@ __global__ void __launch_bounds__(BLOCK) k_bfs_persistent(BfsArgs args) {
 // the queue Q_l (buffers l mod 3), builds F_{l+1} and Q_{l+1} (buffers
 // (l + 1) mod 3, all-zero words when the level starts), ORs F_l into the
 // visited words walking Q_l, and zeroes the words of F_{l-1} walking Q_{l-1},
-// which makes that buffer clean for level l + 1. Visited words therefore hold
+// which makes that buffer clean for level l + 1. (A slice set without slices,
+// of vertices without out-arcs in a directed graph, is in no queue: its vertices
+// enter the visited words when they are found, and the bits they leave in the
+// frontier words are read by nothing, as no row has them as in-neighbours.) Visited words therefore hold
 // every vertex of levels < l and possibly some of level l, so a vertex was
 // reached before level l + 1 iff its bit is set in visited | F_l, whichever
 // of the two copies a wave reads. The statistics of level l + 1 (the inputs
@@ -1707,9 +1710,15 @@ struct EagerStats {
 // A vertex reached at this level, by the lane that reached it first: into the
 // workgroup's list (its levels, statistics and queue entries follow at the end
 // of the step, for all of them together).
+// A vertex without an out-arc (directed graphs only) goes into the visited words
+// here: where its whole set has none, the set has no slice, so no queue brings
+// its word there at the next level.
 __device__ __forceinline__ void eager_write(args_ref<BfsArgs> a, uint32_t u, int new_level, EagerStats& st) {
   const int32_t deg = a.rp[u + 1] - a.rp[u];
   a.levels[a.orig_id ? a.orig_id[u] : static_cast<int32_t>(u)] = new_level;
+  if (deg == 0)
+    __hip_atomic_fetch_or((gptr<uint32_t>)a.vis + (u >> 5), 1u << (u & 31u), __ATOMIC_RELAXED,
+                          __HIP_MEMORY_SCOPE_AGENT);
   st.frontier += 1;
   st.fedges += static_cast<uint32_t>(deg);
   st.deg32 += deg >= 32;
@@ -2292,7 +2301,10 @@ __device__ __forceinline__ void eager_level(args_ref<BfsArgs> a, int level, cons
       __hip_atomic_store(&a.ctl->acc[zslot][t][0], 0ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   {
-    // F_l into the visited words (walking Q_l); F_{l-1} cleared (walking Q_{l-1})
+    // F_l into the visited words (walking Q_l); F_{l-1} cleared (walking Q_{l-1}).
+    // In a directed graph eager_write ORs vertices into the same 32-bit words
+    // meanwhile, so both do it by atomics.
+    const bool atomic = a.rp_in != a.rp;
     const gptr<const uint4> qc = a.queue[level % 3];
     const gptr<const uint4> qp = a.queue[(level + 2) % 3];
     gptr<M> vis = (gptr<M>)a.vis;
@@ -2300,7 +2312,11 @@ __device__ __forceinline__ void eager_level(args_ref<BfsArgs> a, int level, cons
     gptr<M> fp = (gptr<M>)eager_front(a, (level + 2) % 3);
     for (long long i = gtid; i < v.queue; i += nthreads) {
       const uint32_t s = qc[i].w;
-      vis[s] = static_cast<M>(vis[s] | fc[s]);
+      const M old = vis[s], bits = fc[s];
+      if (!atomic)
+        vis[s] = static_cast<M>(old | bits);
+      else if (bits & ~old)
+        atomic_or_word<SIGMA>(vis + s, bits);
     }
     for (long long i = gtid; i < prev_queue; i += nthreads) fp[qp[i].w] = 0;
   }
