@@ -23,6 +23,7 @@
 // kept for comparison.
 #include "device_common.h"
 #include "mlp_infer.h"
+#include "row_pos.h"
 
 namespace blest {
 
@@ -635,9 +636,9 @@ __device__ __attribute__((noinline)) long long engine_push(args_ref<BfsArgs> a_,
   for (long long i = gwave; i < nheavy; i += nwaves) {
     const unsigned long long e = heavy[i];
     const int u = static_cast<int>(e >> 32);
-    const int b = rp[u] + static_cast<int>(e & 0xffffffffULL);
-    const int end = min(rp[u + 1], b + kHeavyChunk);
-    for (int p = b + lane; p < end; p += 64) {
+    const row_pos b = rp[u] + static_cast<uint32_t>(e);
+    const row_pos end = row_part_end(b, kHeavyChunk, rp[u + 1]);
+    for (row_pos p = b + lane; p < end; p += 64) {
       const int v = col[p];
       ++work;
       if (!((vis[v / SIGMA] >> (v % SIGMA)) & 1u)) {
@@ -703,7 +704,7 @@ constexpr int kPullChunks = 2;
 // entries, so the load stays in bounds at the end of the array.)
 template <int SIGMA, int U>
 __device__ __forceinline__ uint32_t pull_scan(gptr<const int32_t> col, gptr<const typename MaskOf<SIGMA>::T> front,
-                                              int (&q)[U], const int (&lim)[U]) {
+                                              row_pos (&q)[U], const row_pos (&lim)[U]) {
   using M = typename MaskOf<SIGMA>::T;
   uint32_t found = 0;
   for (;;) {
@@ -727,7 +728,7 @@ __device__ __forceinline__ uint32_t pull_scan(gptr<const int32_t> col, gptr<cons
     for (int k = 0; k < U; ++k)
 #pragma unroll
       for (int t = 0; t < 4; ++t)
-        w[k][t] = on[k] && q[k] + t < lim[k] ? front[static_cast<uint32_t>(c[k][t]) / SIGMA] : M(0);
+        w[k][t] = on[k] && row_has(q[k], t, lim[k]) ? front[static_cast<uint32_t>(c[k][t]) / SIGMA] : M(0);
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       bool hit = false;
@@ -742,9 +743,9 @@ __device__ __forceinline__ uint32_t pull_scan(gptr<const int32_t> col, gptr<cons
 // The whole wave scans columns p .. e of one row; whether one is in front.
 template <int SIGMA>
 __device__ __forceinline__ bool pull_scan_wave(gptr<const int32_t> col, gptr<const typename MaskOf<SIGMA>::T> front,
-                                               int p, int e, uint32_t& work) {
+                                               row_pos p, row_pos e, uint32_t& work) {
   for (; p < e; p += 64) {
-    const int i = p + lane_id();
+    const row_pos i = p + lane_id();
     bool f = false;
     if (i < e) {
       const uint32_t v = static_cast<uint32_t>(col[i]);
@@ -779,7 +780,7 @@ __device__ __attribute__((noinline)) long long engine_pull(args_ref<BfsArgs> a_,
   int turn = uniform(static_cast<int>(gw));
   for (int round0 = 0; round0 < nchunks; round0 += U * waves) {
     uint32_t u[U];
-    int p[U], e[U], q[U], lim[U];
+    row_pos p[U], e[U], q[U], lim[U];
     bool cand[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
@@ -809,7 +810,7 @@ __device__ __attribute__((noinline)) long long engine_pull(args_ref<BfsArgs> a_,
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       const bool f = (found >> k) & 1u;
-      work += static_cast<uint32_t>(min(q[k], lim[k]) - p[k]);
+      work += min(q[k], lim[k]) - p[k];
       if (f) mark[u[k]] = 1;
       unsigned long long hb = __ballot(!f && lim[k] < e[k]);
       while (hb) {
@@ -1924,7 +1925,7 @@ __device__ __attribute__((noinline)) void eager_bu(args_ref<BfsArgs> a_, int lev
     if (chunk >= nchunks) continue;
     const long long u = chunk * 64LL + lane;
     bool cand = false;
-    int p = 0, e = 0;
+    row_pos p = 0, e = 0;
     if (u < nv) {
       const long long s = u / SIGMA;
       const M unv = static_cast<M>(~(vis[s] | fc[s]) & degm[s]);
@@ -1935,10 +1936,10 @@ __device__ __attribute__((noinline)) void eager_bu(args_ref<BfsArgs> a_, int lev
       p = rp[u];
       e = rp[u + 1];
     }
-    int q[1] = {p};
-    const int lim[1] = {e - p > kPullLight ? p + kPullTry : e};
+    row_pos q[1] = {p};
+    const row_pos lim[1] = {e - p > kPullLight ? p + kPullTry : e};
     bool found = pull_scan<SIGMA, 1>(col, fc, q, lim) != 0;
-    st.work += static_cast<uint32_t>(min(q[0], lim[0]) - p);
+    st.work += min(q[0], lim[0]) - p;
     unsigned long long hb = __ballot(!found && lim[0] < e);
     while (hb) {
       const int l = __builtin_ctzll(hb);

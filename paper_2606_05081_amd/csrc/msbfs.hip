@@ -34,6 +34,7 @@
 #include "device_common.h"
 #include "mlp_infer.h"
 #include "msbfs.h"
+#include "row_pos.h"
 
 namespace blest {
 
@@ -934,12 +935,10 @@ __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi,
     int c[M];
     uint32_t w[M];
   };
-  auto load_cols = [&](const int (&P)[M], const int (&E)[M], int ahead, int (&c)[M]) {
+  auto load_cols = [&](const row_pos (&P)[M], const row_pos (&E)[M], uint32_t ahead, int (&c)[M]) {
 #pragma unroll
-    for (int m = 0; m < M; ++m) {
-      const int i = P[m] + ahead + lane;
-      c[m] = i < E[m] ? col[i] : -1;
-    }
+    for (int m = 0; m < M; ++m)
+      c[m] = row_has(P[m], ahead + lane, E[m]) ? col[P[m] + (ahead + lane)] : -1;
   };
   auto front_word = [&](int c) -> uint32_t {
     if constexpr (FL)
@@ -951,7 +950,7 @@ __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi,
 #pragma unroll
     for (int m = 0; m < M; ++m) k.w[m] = k.c[m] >= 0 ? front_word(k.c[m]) : 0u;
   };
-  auto scan = [&](const int (&P)[M], const int (&E)[M], int stride, Cols& k, u64x2 (&acc)[M]) {
+  auto scan = [&](const row_pos (&P)[M], const row_pos (&E)[M], uint32_t stride, Cols& k, u64x2 (&acc)[M]) {
     Cols nx;
     load_cols(P, E, stride, nx.c);
     int na[M];
@@ -1027,7 +1026,8 @@ __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi,
   // and its visited words. The next task's are loaded before the current one
   // is worked on.
   struct Head {
-    int u, p0, p1;
+    int u;
+    row_pos p0, p1;
   };
   auto head = [&](int t) {
     Head h{-1, 0, 0};
@@ -1084,15 +1084,15 @@ __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi,
       // holds the row, slot 0 writes it. The pieces of a wide row meet in
       // LDS; the wave that adds the last one goes on with the whole row.
       const bool open = __ballot(is_open(op)) != 0ULL;
-      int p = __builtin_amdgcn_readlane(cur.p0, 0), pe = __builtin_amdgcn_readlane(cur.p1, 0);
+      row_pos p = __builtin_amdgcn_readlane(cur.p0, 0), pe = __builtin_amdgcn_readlane(cur.p1, 0);
       const int slot = t / kMsWidePieces;
       if (t < twide) {
-        const int len = ((pe - p + kMsWidePieces - 1) / kMsWidePieces + 63) & ~63;
+        const uint32_t len = row_piece_len(p, pe, kMsWidePieces);
         p += (t % kMsWidePieces) * len;
-        pe = min(pe, p + len);
+        pe = row_part_end(p, len, pe);
       }
       if (open) {
-        int P[M], E[M];
+        row_pos P[M], E[M];
 #pragma unroll
         for (int m = 0; m < M; ++m) {
           P[m] = p + 64 * m;
@@ -1135,7 +1135,7 @@ __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi,
       // M rows (neighbours in the list, so of about the same degree), 64
       // columns of each per step; slot m writes row m
       const bool open = group(is_open(op));
-      int P[M], E[M];
+      row_pos P[M], E[M];
       u64x2 acc[M];
       bool more = false;
 #pragma unroll
@@ -1170,21 +1170,21 @@ __device__ __attribute__((noinline)) void ms_gather(args_ref<MsArgs> a_, int bi,
       // ahead and their front bits one, so a step waits for one round of
       // frontier rows.
       constexpr int G = L == 1 ? 4 : 8 / L, STEP = G * L;
-      int p = cur.p0;
-      const int p1 = cur.p1 - cur.p0 > kMsLightDeg ? cur.p0 : cur.p1;  // longer rows are in the lists above
+      row_pos p = cur.p0;
+      const row_pos p1 = cur.p1 - cur.p0 > kMsLightDeg ? cur.p0 : cur.p1;  // longer rows are in the lists above
       bool run = group(is_open(op)) && p < p1;
       if (__ballot(run)) {
         // a lane's G consecutive columns in one load (they may start at any
         // entry; col is padded by 4): G loads of one column each, spread over
         // R rows, kept the address unit busy for most of a sparse level
-        auto columns = [&](int q, int (&c)[G]) {
-          const int i = q + G * sub;
+        auto columns = [&](row_pos q, int (&c)[G]) {
+          const row_pos i = q + G * sub;
           i32_vec<G> x;
 #pragma unroll
           for (int g = 0; g < G; ++g) x[g] = -1;
           if (run && i < p1) x = *(gptr<const i32_vec<G>>)(col + i);
 #pragma unroll
-          for (int g = 0; g < G; ++g) c[g] = i + g < p1 ? x[g] : -1;
+          for (int g = 0; g < G; ++g) c[g] = row_has(i, g, p1) ? x[g] : -1;
         };
         auto words = [&](const int (&c)[G], uint32_t (&w)[G]) {
 #pragma unroll
