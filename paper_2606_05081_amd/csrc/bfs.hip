@@ -685,57 +685,78 @@ __device__ __attribute__((noinline)) long long engine_push(args_ref<BfsArgs> a_,
 }
 
 // E2: bottom-up (Alg. 4). A lane owns a vertex of each of kPullChunks chunks
-// of 64 and scans its row four neighbours per step, all chunks together, to
-// its first frontier neighbour; a row longer than kPullLight goes over to the
-// whole wave, 64 neighbours per step, after kPullTry of them. What bounds it is
-// the chain of loads of a step (four columns, their front words) times the
-// steps of the longest row in flight, with two waves per SIMD: with a chunk at
-// a time, and every long row scanned by the wave from its start, the step at
-// which a 1 M vertex R-MAT (30 M arcs) is first searched bottom-up took 87 us,
-// with two chunks and the lanes' tries 23 (four chunks: 23, and 2 us more at
-// the steps of a 256 K R-MAT and of an Erdos-Renyi graph, whose rows end soon).
+// of 64 and scans its row to its first frontier neighbour, all chunks together:
+// kPullBlocks blocks of four columns are loaded at a time, then their front
+// words block by block; a row longer than kPullLight goes over to the whole
+// wave, 64 neighbours per step, after kPullTry of them. On small and medium
+// graphs the chain of loads of a step (columns, their front words) bounds it,
+// times the steps of the longest row in flight, with two waves per SIMD: with a
+// chunk at a time, and every long row scanned by the wave from its start, the
+// step at which a 1 M vertex R-MAT (30 M arcs) is first searched bottom-up took
+// 87 us, with two chunks and the lanes' tries 23. Where most rows are read to
+// their end it is the rate of L2 requests (270 G/s: a front word each, and a
+// block of columns), and on large graphs the rows in flight, a 128-byte line
+// each, push the front words out of the L2. A line is then fetched again for
+// every block: a first step on a 2^24-vertex uniform graph (268 M arcs) took
+// 1,435 us a block at a time and 1,260 with two; on 2^22 vertices 295 and 275.
+// Four blocks: 1,125 and 265, but 46 instead of 43 us at the dense levels of a
+// 4 M vertex R-MAT, whose rows end in the first one.
 constexpr int kPullLight = 32;
 constexpr int kPullTry = 16;
 constexpr int kPullChunks = 2;
+constexpr int kPullBlocks = 2;
 
-// Scans columns q[k] .. lim[k] of U rows of this lane, four at a time, each to
-// its first neighbour in front; bit k of the result: found, q[k] past the
-// columns read. (One 16-byte load of four neighbours: col is padded by 4
+// Scans columns q[k] .. lim[k] of U rows of this lane, each to its first
+// neighbour in front; bit k of the result: found, q[k] past the columns
+// tested. (One 16-byte load per block of four neighbours: col is padded by 4
 // entries, so the load stays in bounds at the end of the array.)
 template <int SIGMA, int U>
 __device__ __forceinline__ uint32_t pull_scan(gptr<const int32_t> col, gptr<const typename MaskOf<SIGMA>::T> front,
                                               row_pos (&q)[U], const row_pos (&lim)[U]) {
   using M = typename MaskOf<SIGMA>::T;
+  constexpr int B = kPullBlocks;
   uint32_t found = 0;
   for (;;) {
-    bool on[U];
     bool more = false;
-    int c[U][4];
+    int c[U][B][4];
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      on[k] = q[k] < lim[k] && !((found >> k) & 1u);
-      more |= on[k];
-    }
+    for (int k = 0; k < U; ++k) more |= q[k] < lim[k] && !((found >> k) & 1u);
     if (!__ballot(more)) return found;
 #pragma unroll
     for (int k = 0; k < U; ++k) {
+      const bool open = !((found >> k) & 1u);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) c[k][t] = 0;
-      if (on[k]) __builtin_memcpy(c[k], reinterpret_cast<const int32_t*>(col + q[k]), sizeof(c[k]));
+      for (int b = 0; b < B; ++b) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) c[k][b][t] = 0;
+        if (open && row_has(q[k], 4 * b, lim[k]))
+          __builtin_memcpy(c[k][b], reinterpret_cast<const int32_t*>(col + (q[k] + 4 * b)), sizeof(c[k][b]));
+      }
     }
-    M w[U][4];
 #pragma unroll
-    for (int k = 0; k < U; ++k)
+    for (int b = 0; b < B; ++b) {
+      bool on[U];
+      more = false;
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
-        w[k][t] = on[k] && row_has(q[k], t, lim[k]) ? front[static_cast<uint32_t>(c[k][t]) / SIGMA] : M(0);
+      for (int k = 0; k < U; ++k) {
+        on[k] = q[k] < lim[k] && !((found >> k) & 1u);
+        more |= on[k];
+      }
+      if (b > 0 && !__ballot(more)) return found;
+      M w[U][4];
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      bool hit = false;
+      for (int k = 0; k < U; ++k)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) hit |= (w[k][t] >> (static_cast<uint32_t>(c[k][t]) % SIGMA)) & 1u;
-      if (hit) found |= 1u << k;
-      if (on[k]) q[k] += 4;
+        for (int t = 0; t < 4; ++t)
+          w[k][t] = on[k] && row_has(q[k], t, lim[k]) ? front[static_cast<uint32_t>(c[k][b][t]) / SIGMA] : M(0);
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        bool hit = false;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) hit |= (w[k][t] >> (static_cast<uint32_t>(c[k][b][t]) % SIGMA)) & 1u;
+        if (hit) found |= 1u << k;
+        if (on[k]) q[k] += 4;
+      }
     }
   }
 }
