@@ -334,6 +334,13 @@ __device__ __forceinline__ MsStep ms_step(args_ref<MsArgs> a, int bi, int level)
 
 // ---------------------------------------------------------------- Stage 1
 
+// The calling wave's place among the queue's takers: neighbouring VSSs go to
+// different workgroups, so that a queue shorter than the grid's waves keeps
+// every compute unit busy instead of 16 waves of a few.
+__device__ __forceinline__ long long ms_queue_wave() {
+  return static_cast<long long>(wave_in_block()) * gridDim.x + blockIdx.x;
+}
+
 template <int SIGMA, class SliceT, int K, int ABL>
 __device__ __attribute__((noinline)) void ms_engine_bvss_k(args_ref<MsArgs> a_, int bi, int level, long long qlen,
                                  lptr<unsigned long long> lds_f) {
@@ -344,7 +351,7 @@ __device__ __attribute__((noinline)) void ms_engine_bvss_k(args_ref<MsArgs> a_, 
   qlen = uniform(qlen);
   const gptr<const uint4> q = a.queue[level & 1];
   const long long nw = blockDim.x / 64, nwaves = gridDim.x * nw;
-  const long long gwave = blockIdx.x * nw + wave_in_block();
+  const long long gwave = ms_queue_wave();
   const int W = sp.W;
   const gptr<const SliceT> sl = (gptr<const SliceT>)a.slices;
   const long long rho = a.nsets;
@@ -427,7 +434,7 @@ __device__ __attribute__((noinline)) void ms_engine_bvss8(args_ref<MsArgs> a_, i
   qlen = uniform(qlen);
   const gptr<const uint4> q = a.queue[level & 1];
   const long long nw = blockDim.x / 64, nwaves = gridDim.x * nw;
-  const long long gwave = blockIdx.x * nw + wave_in_block();
+  const long long gwave = ms_queue_wave();
   constexpr int SIGMA = 8;
   const int W = sp.W;
   const gptr<const SliceT> sl = (gptr<const SliceT>)a.slices;
@@ -545,7 +552,7 @@ __device__ __attribute__((noinline)) void ms_engine_mfma(args_ref<MsArgs> a_, in
   qlen = uniform(qlen);
   const gptr<const uint4> q = a.queue[level & 1];
   const long long nw = blockDim.x / 64, nwaves = gridDim.x * nw;
-  const long long gwave = blockIdx.x * nw + wave_in_block();
+  const long long gwave = ms_queue_wave();
   constexpr int SIGMA = 8;
   const int W = sp.W;
   const gptr<const SliceT> sl = (gptr<const SliceT>)a.slices;
@@ -1456,6 +1463,14 @@ __device__ __forceinline__ void ms_append(gptr<uint4> queue, gptr<unsigned long 
   __syncthreads();
 }
 
+// Slice sets that a workgroup takes at a time in a sweep over all of them: one
+// a thread, or fewer (whole waves) where that leaves workgroups without any.
+template <int BLOCK>
+__device__ __forceinline__ int ms_sweep_sets(long long nsets) {
+  const long long share = (nsets + gridDim.x - 1) / gridDim.x;
+  return static_cast<int>(min((share + 63) / 64 * 64, static_cast<long long>(BLOCK)));
+}
+
 // The queue and the activity words of a level whose frontier a gather step
 // (or the seeding) wrote, for a level that the queue form takes.
 template <int SIGMA, int BLOCK, int ABL>
@@ -1470,11 +1485,13 @@ __device__ __attribute__((noinline)) void ms_emit(args_ref<MsArgs> a_, int W, in
   const gptr<const uint32_t> fb = a.fb[level % 3];
   const uint32_t tau = static_cast<uint32_t>(a.tau);
   const long long rho = a.nsets;
-  for (long long base = static_cast<long long>(blockIdx.x) * BLOCK; base < rho;
-       base += static_cast<long long>(gridDim.x) * BLOCK) {
+  const int per = ms_sweep_sets<BLOCK>(rho);
+  for (long long base = static_cast<long long>(blockIdx.x) * per; base < rho;
+       base += static_cast<long long>(gridDim.x) * per) {
     const long long s = base + threadIdx.x;
-    const uint32_t bits = s < rho ? set_bits<SIGMA>(fb, s) : 0u;
-    const bool mine = s < rho && (bits || !track);
+    const bool in = static_cast<int>(threadIdx.x) < per && s < rho;
+    const uint32_t bits = in ? set_bits<SIGMA>(fb, s) : 0u;
+    const bool mine = in && (bits || !track);
     if (!__syncthreads_or(mine)) continue;
     uint32_t s0 = 0, ns = 0;
     int nq = 0;
@@ -1515,10 +1532,11 @@ __device__ __attribute__((noinline)) void ms_finalize(args_ref<MsArgs> a_, int b
   // finalised at every level, all its words count as active and all its
   // VSSs are queued.
   const bool track = !(ms_abl<ABL>(a) & BLEST_MS_NO_DIRTY);
-  for (long long base = static_cast<long long>(blockIdx.x) * BLOCK; base < a.nsets;
-       base += static_cast<long long>(gridDim.x) * BLOCK) {
+  const int per = ms_sweep_sets<BLOCK>(a.nsets);
+  for (long long base = static_cast<long long>(blockIdx.x) * per; base < a.nsets;
+       base += static_cast<long long>(gridDim.x) * per) {
     const long long s = base + threadIdx.x;
-    const bool mine = s < a.nsets && (!track || a.dirty[s]);
+    const bool mine = static_cast<int>(threadIdx.x) < per && s < a.nsets && (!track || a.dirty[s]);
     if (!__syncthreads_or(mine)) continue;
     int nq = 0;
     uint32_t s0 = 0, ns = 0, fbits = 0;
