@@ -2363,21 +2363,29 @@ hipError_t ensure_levels(const DevGraph& g, MsDev* ms, int wmax, hipStream_t st)
   return hipSuccess;
 }
 
+// Words per vertex of a batch of `count` sources of a width. A level costs bytes
+// per word, also those no source uses: one source in a 512-wide batch on scale-20
+// R-MAT took 942 us with 8 words, 486 with one; 100 sources 1,602 with 8, 930
+// with two. (Four words instead of eight gain on large graphs, 1,754 -> 1,349 us
+// for 200 sources, but their gather steps take longer where rows are short: 12.0
+// -> 13.1 ms on a 256 x 256 grid. So more than 128 sources keep the width's.)
+int ms_batch_words(int count, int width) { return count <= 64 ? 1 : count <= 128 ? 2 : width / 64; }
+
 hipError_t ms_run(const DevGraph& g, MsDev* ms, const int32_t* srcs, int32_t k, const int32_t* widths, int nwidths,
                   int policy, float eta, uint64_t seed, int16_t* levels16, int64_t* sums, int64_t* reach, double* cc,
                   hipStream_t st, int graph, int64_t* far, int probe) {
   if (k <= 0) return hipSuccess;
   std::vector<MsBatch> plan;
   int32_t off = 0;
+  int wmax = 1;  // the buffers hold the widths asked for
   for (int i = 0; off < k; ++i) {
     const int width = widths[nwidths > 0 ? std::min(i, nwidths - 1) : 0];
-    const int W = width / 64;
-    plan.push_back(MsBatch{off, std::min(64 * W, k - off), W, 0});
-    off += 64 * W;
+    const int count = std::min(width, k - off);
+    plan.push_back(MsBatch{off, count, ms_batch_words(count, width), 0});
+    wmax = std::max(wmax, width / 64);
+    off += count;
   }
   const int nplan = static_cast<int>(plan.size());
-  int wmax = 1;
-  for (int i = 0; i < nplan; ++i) wmax = std::max(wmax, plan[i].W);
   hipError_t e = ensure(g, ms, wmax, k, nplan);
   if (e != hipSuccess) return e;
   if (levels16 && (e = ensure_levels(g, ms, wmax, st)) != hipSuccess) return e;
@@ -2602,7 +2610,10 @@ hipError_t ms_run_noalloc(const DevGraph& g, MsDev* ms, const int32_t* srcs, con
   const int per = 64 * W;
   const int nplan = (k + per - 1) / per;
   MsBatch plan[kNoAllocMaxBatches];
-  for (int i = 0; i < nplan; ++i) plan[i] = MsBatch{i * per, std::min(per, k - i * per), W, 0};
+  for (int i = 0; i < nplan; ++i) {
+    const int count = std::min(per, k - i * per);
+    plan[i] = MsBatch{i * per, count, ms_batch_words(count, width), 0};
+  }
   if ((e = hipMemcpyAsync(dplan, plan, sizeof(MsBatch) * nplan, hipMemcpyHostToDevice, st)) != hipSuccess) return e;
   if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
   MsArgs a = ms_args(g, ms, dsrcs, dplan, nplan, policy, eta, seed, levels16, nullptr, nullptr, nullptr, nullptr, 0);
