@@ -405,6 +405,11 @@ blest_status blest_set_ms_switch_model(blest_graph* g, const float* params, int3
  * Errors: INVALID_ARG (min_prob outside (0, 1]). */
 blest_status blest_set_switch_confidence(blest_graph* g, float min_prob);
 
+/* The same for one network of g alone: the single-source one
+ * (multi_source = 0) or the multi-source one (1). g must not be NULL.
+ * Errors: INVALID_ARG, HIP. */
+blest_status blest_set_network_confidence(blest_graph* g, int32_t multi_source, float min_prob);
+
 /* Per-level features (12 floats, the network's inputs before standardising)
  * of the last BFS's levels, to host: feat[nlev][12]. With F the frontier, Q its
  * VSSs, S their slices, m_f its edges, U the unvisited vertices, m_u their

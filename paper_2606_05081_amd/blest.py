@@ -152,6 +152,7 @@ SIGNATURES = {
     "blest_export_bvss": (_i32, [_vp, _p64, _p64, _p64, _p32, _pu64, _p32]),
     "blest_set_switch_model": (_i32, [_vp, _pf32, _i32, _pf32, _pf32]),
     "blest_set_switch_confidence": (_i32, [_vp, _f32]),
+    "blest_set_network_confidence": (_i32, [_vp, _i32, _f32]),
     "blest_set_log_work": (_i32, [_vp, _i32]),
     "blest_mlp_forward": (_i32, [_vp, _vp, _i32, _vp, _vp]),
     "blest_mlp_loss_grad": (_i32, [_vp, _vp, _vp, _vp, _i32, _vp, _vp, _vp]),
@@ -329,6 +330,10 @@ def blest_set_switch_confidence(h, min_prob: float):
     _check(lib().blest_set_switch_confidence(h, float(min_prob)))
 
 
+def blest_set_network_confidence(h, multi_source: bool, min_prob: float):
+    _check(lib().blest_set_network_confidence(h, int(bool(multi_source)), float(min_prob)))
+
+
 def blest_set_log_work(h, on: bool):
     _check(lib().blest_set_log_work(h, int(bool(on))))
 
@@ -481,10 +486,10 @@ class Graph:
         return out
 
     def set_ms_switch_model(self, params, mean, std, min_confidence: float | None = None):
-        """Multi-source network; min_confidence (if given) applies to both networks."""
+        """Multi-source network; min_confidence (if given) is its confidence floor alone."""
         blest_set_ms_switch_model(self._h, params, mean, std)
         if min_confidence is not None:
-            blest_set_switch_confidence(self._h, min_confidence)
+            blest_set_network_confidence(self._h, True, min_confidence)
 
     def closeness(self, srcs, stream=None):
         k = len(srcs)
@@ -549,9 +554,10 @@ class Graph:
                 "slice_mask": masks[:nsl], "perm": perm}
 
     def set_switch_model(self, params, mean, std, min_confidence: float | None = None):
+        """Single-source network; min_confidence (if given) is its confidence floor alone."""
         blest_set_switch_model(self._h, params, mean, std)
         if min_confidence is not None:
-            blest_set_switch_confidence(self._h, min_confidence)
+            blest_set_network_confidence(self._h, False, min_confidence)
 
     def set_log_work(self, on: bool = True):
         blest_set_log_work(self._h, on)

@@ -760,6 +760,17 @@ blest_status blest_set_switch_confidence(blest_graph* g, float min_prob) {
   return BLEST_OK;
 }
 
+blest_status blest_set_network_confidence(blest_graph* g, int32_t multi_source, float min_prob) {
+  if (!g) return fail(BLEST_ERR_INVALID_ARG, "NULL graph");
+  if (multi_source != 0 && multi_source != 1) return fail(BLEST_ERR_INVALID_ARG, "multi_source must be 0 or 1");
+  if (!(min_prob > 0.0f && min_prob <= 1.0f)) return fail(BLEST_ERR_INVALID_ARG, "min_prob must be in (0, 1]");
+  const float r = 1.0f / min_prob;
+  CK(hipSetDevice(g->d.device));
+  CK(hipMemcpy(reinterpret_cast<char*>(multi_source ? g->d.ms_mlp : g->d.mlp) + offsetof(blest::MlpDev, max_ratio), &r,
+               sizeof(float), hipMemcpyHostToDevice));
+  return BLEST_OK;
+}
+
 blest_status blest_set_log_work(blest_graph* g, int32_t on) {
   if (!g) return fail(BLEST_ERR_INVALID_ARG, "NULL graph");
   g->d.count_work = on ? 1 : 0;
