@@ -65,7 +65,8 @@ typedef struct {
 
 /* Engine choice per BFS level (Section "Switching Mechanism"). */
 #define BLEST_POLICY_HEURISTIC 0  /* Eq. 3: bottom-up iff #unvisited < eta*|Q|, else BVSS top-down */
-#define BLEST_POLICY_BVSS 1       /* plain method: BVSS top-down every level */
+#define BLEST_POLICY_BVSS 1       /* plain method: BVSS top-down every level (its dense multi-source
+                                     levels in the gather form, see blest_ms_level_stat.gather) */
 #define BLEST_POLICY_PUSH 2       /* scalar top-down (push over CSR) every level */
 #define BLEST_POLICY_BOTTOM_UP 3  /* bottom-up (Alg. 4) every level */
 #define BLEST_POLICY_LEARNED 4    /* switch MLP (blest_set_switch_model); Eq. 3 fallback */
@@ -126,7 +127,9 @@ typedef struct {
   int32_t ms_mfma;        /* 1: the multi-source top-down neighbour check as an int8 matrix product on
                              the matrix cores (sigma = 8; an experiment against the bitwise check,
                              same results). 0 (default): bitwise */
-  int32_t reserved;
+  int32_t ms_queue_form;  /* 1: the multi-source levels that a BVSS step explores always take its queue
+                             form; 0 (default): the gather form where that is the quicker (see
+                             blest_ms_level_stat.gather). Results are unchanged */
 } blest_opts;
 
 /* Multi-source ablation flags (Section "Ablation Studies", MS-BFS: (A) drops
@@ -251,14 +254,16 @@ blest_status blest_far(blest_graph* g, const int32_t* srcs_host, int64_t k, int6
 /* Same result as blest_msbfs_batched, but every level runs both multi-source
  * engines (BVSS and bottom-up) from the same state and times each (device
  * clock), for switch training data (persistent launch; returns after the
- * stream syncs). Records via blest_msbfs_last_levels. */
+ * stream syncs); a level that both take in the gather form (see
+ * blest_ms_level_stat.gather) runs once. Records via blest_msbfs_last_levels. */
 blest_status blest_msbfs_probe(blest_graph* g, const int32_t* srcs_host, int32_t k, const int32_t* widths_host,
                                int32_t nwidths, int16_t* levels_dev, void* stream);
 
 /* Per-level record of the last multi-source call (all batches in order). */
 typedef struct {
   int32_t batch, level;
-  int32_t engine;          /* BLEST_ENGINE_BVSS or _BOTTOM_UP (-1 in probe mode) */
+  int32_t engine;          /* BLEST_ENGINE_BVSS or _BOTTOM_UP as the policy chose it (-1 in probe
+                              mode); what ran is told by `gather` */
   int32_t mlp_fallback;    /* learned policy: 1 if the pairs rule decided */
   int32_t width;           /* sources in the batch */
   int32_t live;            /* traversals whose frontier is non-empty at this level */
@@ -266,8 +271,14 @@ typedef struct {
   int64_t queue;           /* VSSs queued */
   int64_t queue_slices;
   int64_t unvisited_pairs;
-  double t_engine_us[2];   /* probe mode: BVSS, bottom-up; else -1 */
+  double t_engine_us[2];   /* probe mode: BVSS, bottom-up; else -1. Where both take the gather form
+                              (gather = 1) it runs once and its time stands in both */
   float feat[12];          /* the multi-source switch network's inputs */
+  int32_t gather;          /* the form the level took: 1 = gather, the rows of A one by one (bottom-up
+                              levels, and BVSS levels whose queue holds at least 1/128 of the arcs as
+                              slices or is estimated the slower); 0 = the queued slices (in probe mode:
+                              the queue form for BVSS, the gather form for bottom-up) */
+  int32_t reserved;
 } blest_ms_level_stat;
 
 /* Copies up to cap records of the last multi-source call to buf (host);
@@ -356,7 +367,9 @@ typedef struct {
   int32_t mlp_fallback; /* learned policy: 1 if Eq. 3 was used (input out of range) */
   int32_t bvss_panel;   /* 1 if the BVSS step read the panel-blocked copy (all slices, LDS marks) */
   int64_t work;         /* adjacency entries read by the step's engine: slices (BVSS),
-                           CSR edges (push, bottom-up); probe mode: all three engines */
+                           CSR edges (push, bottom-up; a small BVSS level of the eager scheme,
+                           which one workgroup runs over its frontier's rows); probe mode: all
+                           three engines */
   double t_count_us;    /* grid levels: time from the step's start until Stage 2's statistics
                            were known (before any list emission); 0 for one-workgroup levels */
 } blest_level_stat;

@@ -87,7 +87,7 @@ class Opts(ctypes.Structure):
                 ("stage2_count_first", ctypes.c_int32), ("msbfs_graph", ctypes.c_int32),
                 ("jaccard_window", ctypes.c_int32), ("update_scheme", ctypes.c_int32),
                 ("directed", ctypes.c_int32), ("ms_ablation", ctypes.c_int32), ("ms_mfma", ctypes.c_int32),
-                ("reserved", ctypes.c_int32)]
+                ("ms_queue_form", ctypes.c_int32)]
 
 
 class GraphStats(ctypes.Structure):
@@ -116,7 +116,7 @@ class MsLevelStat(ctypes.Structure):
                 ("mlp_fallback", ctypes.c_int32), ("width", ctypes.c_int32), ("live", ctypes.c_int32),
                 ("new_pairs", ctypes.c_int64), ("queue", ctypes.c_int64), ("queue_slices", ctypes.c_int64),
                 ("unvisited_pairs", ctypes.c_int64), ("t_engine_us", ctypes.c_double * 2),
-                ("feat", ctypes.c_float * 12)]
+                ("feat", ctypes.c_float * 12), ("gather", ctypes.c_int32), ("reserved", ctypes.c_int32)]
 
 
 # Every exported symbol of the C ABI: name -> (restype, argtypes).

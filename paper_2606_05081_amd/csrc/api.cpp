@@ -377,6 +377,7 @@ blest_status blest_build(const blest_csr* csr, const blest_opts* opts_in, blest_
   d.directed = o.directed;
   d.ms_ablation = o.ms_ablation;
   d.ms_mfma = o.ms_mfma;
+  d.ms_queue_form = o.ms_queue_form != 0;
   if (o.directed) {
     int32_t* rpi = nullptr;
     int32_t* coli = nullptr;
@@ -893,6 +894,7 @@ blest_status blest_msbfs_last_levels(const blest_graph* g, blest_ms_level_stat* 
     o.unvisited_pairs = r.unvisited;
     for (int e = 0; e < 2; ++e) o.t_engine_us[e] = r.t_engine[e] ? r.t_engine[e] * g->d.tick_us : -1.0;
     std::memcpy(o.feat, r.feat, sizeof(o.feat));
+    o.gather = r.gather;
   }
   return BLEST_OK;
 }

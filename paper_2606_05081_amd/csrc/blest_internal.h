@@ -130,6 +130,7 @@ struct MsLevelRec {
   long long fresh, queue, qslices, unvisited;  // new pairs, VSSs, slices, unvisited pairs
   unsigned long long t_engine[2];              // probe mode: device ticks of BVSS and bottom-up
   float feat[kMaxSwitchFeatures];
+  int gather;                                  // the level took the gather form
 };
 
 // One record per frontier level, written by workgroup 0 of the persistent kernel.
@@ -252,6 +253,7 @@ struct DevGraph {
   int ms_nrows = 0, ms_nwide = 0, ms_nlong = 0;  // their number; those above kMsWideDeg, kMsLongDeg
   int ms_ablation = 0;        // multi-source ablation flags (BLEST_MS_NO_*)
   int ms_mfma = 0;            // multi-source top-down check on MFMA (experiment)
+  int ms_queue_form = 0;      // multi-source BVSS levels never take the gather form
   int grid_eager = 0;         // co-resident grid of the eager kernel
   double u_div = 0.0;         // update divergence of the BVSS
 };

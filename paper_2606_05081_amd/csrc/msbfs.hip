@@ -76,8 +76,6 @@ struct MsBatch {
 constexpr int kMsInlineSrcs = 512, kMsInlineBatches = 8;
 
 struct MsArgs {
-  gptr<const int32_t> rp;
-  gptr<const int32_t> col;
   gptr<const int32_t> rp_in;   // in-arcs (the gather step); rp/col for an undirected graph
   gptr<const int32_t> col_in;
   gptr<const int32_t> rows;    // vertices of in-degree > kMsLightDeg, by descending in-degree
@@ -115,6 +113,7 @@ struct MsArgs {
   gptr<MsLevelRec> log;        // one record per level of the call, or NULL
   int32_t log_cap;
   unsigned long long timeout_ticks;
+  int32_t queue_form;     // 1: BVSS levels never take the gather form
   int32_t ablation;       // BLEST_MS_NO_GETVI | BLEST_MS_NO_DIRTY (the paper's ablation steps), else 0
   gptr<unsigned long long> hstat;  // pinned host word: how the launch went
   int32_t fb_words;       // front-bit words the gather keeps in LDS (all of them), or 0: read from memory
@@ -1845,6 +1844,7 @@ __device__ __forceinline__ void ms_log(args_ref<MsArgs> a, int nrec, int bi, int
   rec->batch = bi;
   rec->level = level;
   rec->engine = a.probe ? -1 : ch.engine;
+  rec->gather = a.probe ? ch.dense : ch.gather();
   rec->fallback = ch.fallback;
   rec->width = width;
   rec->live = live;
@@ -1858,6 +1858,7 @@ __device__ __forceinline__ void ms_log(args_ref<MsArgs> a, int nrec, int bi, int
 
 // Whether a level takes the gather step whatever its engine.
 __device__ __forceinline__ bool ms_dense(args_ref<MsArgs> a, const MsView& st, int count) {
+  if (a.queue_form) return false;
   const long long slices = st.get(MS_QSLICES), all = static_cast<long long>(count) * a.n;
   const long long unv = all - st.get(MS_CUMIN) - st.get(MS_FRESH);
   return slices * kMsDenseDenom >= a.m ||
@@ -1985,12 +1986,12 @@ __global__ void __launch_bounds__(BLOCK) k_ms_persistent(MsArgs args) {
           ms_engine_bvss<SIGMA, SliceT, MF, ABL>(a, bi, level, qlen, my_f);
           if (!grid_barrier((Ctl*)a.ctl, bc)) return;
         }
-        const unsigned long long t1 = dev_ticks();
+        const unsigned long long t1 = queued ? dev_ticks() : t0;
         ms_gather_any<SIGMA, BLOCK, false, GABL>(a, bi, level, bt.W, st, glds, false);
         if (!grid_barrier((Ctl*)a.ctl, bc)) return;
         if (blockIdx.x == 0 && threadIdx.x == 0 && rec) {
           const unsigned long long t2 = dev_ticks();
-          rec->t_engine[0] = (queued ? t1 : t2) - t0;
+          rec->t_engine[0] = (queued ? t1 : t2) - t0;  // (the same run where not queued)
           rec->t_engine[1] = t2 - t1;
         }
       } else if (gather) {
@@ -2282,8 +2283,6 @@ MsArgs ms_args(const DevGraph& g, const MsDev* ms, const int32_t* srcs_dev, cons
                int policy, float eta, uint64_t seed, int16_t* levels16, int64_t* sums, int64_t* reach, double* cc,
                int64_t* far, int probe) {
   MsArgs a{};
-  a.rp = to_global(g.rp);
-  a.col = to_global(g.col);
   a.rp_in = to_global(g.rp_in);
   a.col_in = to_global(g.col_in);
   a.slice_ptr = to_global(g.slice_ptr);
@@ -2327,6 +2326,7 @@ MsArgs ms_args(const DevGraph& g, const MsDev* ms, const int32_t* srcs_dev, cons
   a.eta = eta;
   a.seed = seed;
   a.timeout_ticks = 3000000000ULL;  // 30 s
+  a.queue_form = g.ms_queue_form;
   a.ablation = g.ms_ablation;
   a.hstat = to_global(g.hstat);
   return a;
