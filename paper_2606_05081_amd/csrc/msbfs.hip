@@ -1815,17 +1815,23 @@ __device__ __attribute__((noinline)) void ms_reduce_batch(args_ref<MsArgs> a_, i
 // A level whose queue holds at least 1 / kMsDenseDenom of the graph's arcs as
 // slices takes the gather step, which reads at most the arcs of the vertices
 // still open; one with fewer the queue form of a BVSS step, unless even so the
-// gather step is the quicker. That is judged by what both measured: a gather
-// step takes 14 us (16 K vertices) and up to 18 more with the vertices (256 K
-// and beyond), and 1 us per 250,000 arcs of open vertices; the queue form, with
-// its two more passes and barriers, 28 us for a few slices and 50 to 90 from
-// about 2,000. (Last levels of 64 traversals on 16 K vertices: 42 and 27 us by
-// the queue, 13 by the gather; first level of 256 on 300 K vertices: 92 and 50.)
+// gather step is the quicker. A gather step takes 14 us (16 K vertices) and up
+// to 18 more with the vertices (256 K and beyond), and 1 us per 250,000 arcs of
+// open vertices; a level by the queue about 65 with what it adds to its
+// neighbours (a list of its own, a second pass, two more barriers). The batch
+// width moves both sides alike: closeness of 64, 128, 256 and 512 sources, plain
+// method, on uniform graphs of mean degree 4 and 16 (30 K to 4 M vertices), grids
+// (29 K to 1 M) and R-MAT of scale 15 to 22 takes by this rule at most 4% longer
+// than with every level gathered or every level queued, and up to 18% less. (64
+// sources, us by the rule, all gathered, all queued: 250 K vertices of degree 4
+// 503, 504, 1,184; 490 K grid 35,640, 35,910, 75,800; scale 22 3,080, 3,740, 4,240.
+// With 28 in the place of 65, and 53 from 2,048 slices on, 569, 38,550 and 3,080.)
 constexpr long long kMsDenseDenom = 128;
-__device__ __forceinline__ bool ms_gather_quicker(long long n, long long m, long long slices, float open_part) {
-  const float gather = 14.0f + fminf(static_cast<float>(n) * (1.0f / 13000.0f), 18.0f) +
-                       static_cast<float>(m) * (1.0f / 250000.0f) * open_part;
-  return gather <= (slices >= 2048 ? 53.0f : 28.0f);
+constexpr float kMsQueueLevelUs = 65.0f;
+__device__ __forceinline__ bool ms_gather_quicker(long long n, long long m, float open_part) {
+  return 14.0f + fminf(static_cast<float>(n) * (1.0f / 13000.0f), 18.0f) +
+             static_cast<float>(m) * (1.0f / 250000.0f) * open_part <=
+         kMsQueueLevelUs;
 }
 
 // What a level does, from its statistics alone (the same in every wave).
@@ -1862,7 +1868,7 @@ __device__ __forceinline__ bool ms_dense(args_ref<MsArgs> a, const MsView& st, i
   const long long slices = st.get(MS_QSLICES), all = static_cast<long long>(count) * a.n;
   const long long unv = all - st.get(MS_CUMIN) - st.get(MS_FRESH);
   return slices * kMsDenseDenom >= a.m ||
-         ms_gather_quicker(a.n, a.m, slices, static_cast<float>(unv) / static_cast<float>(all));
+         ms_gather_quicker(a.n, a.m, static_cast<float>(unv) / static_cast<float>(all));
 }
 
 // Decides level `level` and logs it. The engine of a dense level changes
