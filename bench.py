@@ -357,16 +357,25 @@ def c3_leg(kind, scale, gseed, sseed, model, eta_tuned, torch, blest, inputs, ns
 
 def ms_algorithmic_bytes(recs, n, nsets, sigma, slice_bytes, k):
     """Lower bound of the bytes a multi-source call must move, from its level
-    records: per level, (slice word + sigma/8) B per slice of a queued VSS and
-    the sigma * kappa / 8 frontier bytes each queued VSS stages; kappa/8 B per
-    hit row (the next-word flush) and 3 kappa/8 B per dirty vertex (next,
-    visited and frontier words), bounded below by the new (vertex, traversal)
-    pairs, since a vertex has at most kappa of them: new_pairs / 8 and
-    3 new_pairs / 8; and the int16 levels: 2 B per (source, vertex) filled,
-    and 2 B per visited pair written."""
+    records. A level that took the queue form: (slice word + sigma/8) B per
+    slice of a queued VSS and the sigma * kappa / 8 frontier bytes each queued
+    VSS stages; kappa/8 B per hit row (the next-word flush) and 3 kappa/8 B per
+    dirty vertex (next, visited and frontier words), bounded below by the new
+    (vertex, traversal) pairs, since a vertex has at most kappa of them:
+    new_pairs / 8 and 3 new_pairs / 8; and 2 B per visited pair. A level that
+    took the gather form (record field `gather`): the front bits, n / 8 B; the
+    visited words of every vertex, kappa / 8 B each; and per new pair, as above,
+    a bit of a frontier word read, of the visited, next and frontier words
+    written and of a level plane, and a column per kappa of them (how many
+    columns a row reads before it is covered is not recorded, so this is far
+    below what such a level moves). And the int16 levels: 2 B per (source,
+    vertex)."""
     total = 2 * k * n
     for r in recs:
         kappa = r["width"]
+        if r.get("gather"):
+            total += n // 8 + n * kappa // 8 + 5 * r["new_pairs"] // 8 + 4 * r["new_pairs"] // kappa
+            continue
         total += (slice_bytes + sigma // 8) * r["queue_slices"] + sigma * kappa // 8 * r["queue"]
         total += r["new_pairs"] // 2 + 2 * r["new_pairs"]
     return int(total)
@@ -599,7 +608,9 @@ def main():
         # the paper's multi-source ablation ladder on the same 960 sources
         # (Section "Ablation Studies"): naive = one single-source traversal per
         # source; (A) no getVI remap and no dynamic slice-set tracking; (AB) no
-        # tracking; (Full) = the msbfs leg above
+        # tracking; (Full) = both, with every BVSS level in the queue form as in
+        # the rungs below it; full_with_gather = the msbfs leg above, whose dense
+        # levels take the gather form
         sout1 = torch.empty(mg.n, dtype=torch.int32, device=dev)
         mg.set_policy(blest.Policy.HEURISTIC)
         naive_ms = timed_call(lambda: [mg.bfs(int(x), sout1) for x in msrcs], torch)
@@ -611,9 +622,14 @@ def main():
             ladder[tag] = round(960 / timed_call(lambda: ag.msbfs_batched(msrcs, [64, 128, 256, 512], mout),
                                                  torch) * 1e3, 1)
             ag.close()
-        ladder["full"] = extras["msbfs_sources_per_s"]
+        qg = blest.Graph(mrp, mcol, device=0, ms_queue_form=1, autotune=True, **{"async": 1})
+        qg.msbfs_batched(msrcs, [64, 128, 256, 512], mout)
+        ladder["full"] = round(960 / timed_call(lambda: qg.msbfs_batched(msrcs, [64, 128, 256, 512], mout), torch) * 1e3, 1)
+        qg.close()
+        ladder["full_with_gather"] = extras["msbfs_sources_per_s"]
         extras["msbfs_ablation_sources_per_s"] = ladder
-        # the neighbour check on the matrix cores (int8 MFMA) instead of bitwise, same sources
+        # the neighbour check on the matrix cores (int8 MFMA) instead of bitwise, same sources (to be
+        # compared with the ladder's "full", the bitwise check with the same levels in the queue form)
         xg = blest.Graph(mrp, mcol, device=0, ms_mfma=1, autotune=True, **{"async": 1})
         xg.msbfs_batched(msrcs, [64, 128, 256, 512], mout)
         extras["msbfs_mfma_sources_per_s"] = round(
