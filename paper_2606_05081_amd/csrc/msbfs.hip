@@ -2381,6 +2381,11 @@ hipError_t ms_run(const DevGraph& g, MsDev* ms, const int32_t* srcs, int32_t k, 
                   int policy, float eta, uint64_t seed, int16_t* levels16, int64_t* sums, int64_t* reach, double* cc,
                   hipStream_t st, int graph, int64_t* far, int probe) {
   if (k <= 0) return hipSuccess;
+  // A capturing stream is refused before anything is allocated or launched: a
+  // recorded launch of k_ms_perm would leave an id map that no kernel has written.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
+    return hipErrorStreamCaptureUnsupported;
   std::vector<MsBatch> plan;
   int32_t off = 0;
   int wmax = 1;  // the buffers hold the widths asked for
@@ -2398,10 +2403,6 @@ hipError_t ms_run(const DevGraph& g, MsDev* ms, const int32_t* srcs, int32_t k, 
   MsArgs a = ms_args(g, ms, ms->srcs, static_cast<const MsBatch*>(ms->batches), nplan, policy, eta, seed, levels16,
                      sums, reach, cc, far, probe);
   if (k <= kMsInlineSrcs && nplan <= kMsInlineBatches) {
-    // (a capturing stream is refused, as the synchronisation below would refuse it)
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
-      return hipErrorStreamCaptureUnsupported;
     a.inlined = 1;
     std::copy(srcs, srcs + k, a.srcs_in);
     std::copy(plan.begin(), plan.end(), a.plan_in);
