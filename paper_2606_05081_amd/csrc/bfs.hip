@@ -1707,8 +1707,9 @@ __device__ __forceinline__ typename MaskOf<SIGMA>::T atomic_or_word(gptr<typenam
   }
 }
 
-constexpr int kEpList = 1024;       // vertices a frontier may have: a level of one workgroup costs 11 ns a vertex,
-                                    // one of the grid about 11 us (2048 x 2048 grid: 512 38.3 ms, 1024 36.4 ms)
+constexpr int kEpList = 1024;       // vertices a frontier may have: a level of one workgroup costs 12 ns a vertex,
+                                    // one of the grid 13 us (2048 x 2048 grid, 2,492 levels, kernel time of one
+                                    // run: 38.3 ms with 512, 36.4 with 1024)
 constexpr int kEpLog2Slots = 11, kEpSlots = 1 << kEpLog2Slots;  // table slots: at most half full
 constexpr uint32_t kEpEdges = 4096;  // a level's frontier edges (so the new vertices fit the list)
 
@@ -1997,9 +1998,10 @@ __device__ __attribute__((noinline)) void eager_bu(args_ref<BfsArgs> a_, int lev
 // for; a queued set of a grid graph has 18 slices for 1 to 3 frontier
 // vertices).
 // Measured on a 2048 x 2048 grid graph (2,492 levels of up to 3,312 vertices):
-// 59.2 ms when one workgroup ran levels of up to 256 queued slices through the
-// grid's own functions and arguments were read from the stack, 36.4 ms now;
-// 11 ns a frontier vertex here, about 11 us a level on the grid.
+// 51.5 ms a call when one workgroup ran levels of up to 256 queued slices
+// through the grid's own functions and arguments were read from the stack, 34.3
+// now (one box); 773 levels here, 6.2 us each and 12 ns a frontier vertex, 1,719
+// on the grid, 13.2 us each.
 // Phase A walks the rows and collects the new vertices in LDS, phase B loads
 // their row and slice pointers, writes levels and sums the statistics; a hash
 // table of the new vertices' slice sets tells the first vertex of a set.
